@@ -20,7 +20,6 @@ Keys of a case:
 """
 import math
 
-import numpy as np
 import torch
 
 from paper_2604_26334_amd import binding as B
