@@ -97,39 +97,34 @@ struct AttnArgs {
                                // the launch covers every chunk the cache can hold (a captured graph is
                                // replayed at any context); workgroups past the context leave at once
 };
-// Attention of a chunk of `ntok` new tokens (rows of q, q_stride elements apart) over one kind of rows:
-//  causal == 0: the cache shards of kv heads head0 .. head0 + nheads - 1 (k_base = first shard; shards
-//   head_stride bytes apart, K rows [cap][128] then V rows; row_stride = 128); every token sees the ctx
-//   cached positions;
-//  causal == 1: the chunk's own K / V rows, read in place from the tokens' QKV rows (k_base / v_base =
-//   kv head 0 of token 0, row_stride = the QKV row width; head0 .. as above): token t sees rows 0 .. t.
-// Partials go to part[((t * n_q + q_head) * chunk_cap + chunk0 + chunk) * 130] (maximum, weight sum, 128 sums).
+// Attention of a chunk of `ntok` new tokens (rows of q, q_stride elements apart): every token sees the ctx cached
+// positions of its kv head (cache shards of kv heads head0 .. head0 + nheads - 1, k_base = the first one, head_stride
+// bytes apart, K rows [cap][128] then V rows) and, causally, the chunk's own K / V rows, read in place from the
+// tokens' QKV rows (k_own / v_own = kv head 0 of token 0, own_stride elements between tokens).  One launch per run of
+// cache shards.  nsplit == 1: finished rows out[t][q_head * 128 ..]; > 1: records
+// part[((t * n_q + q_head) * nsplit + split) * 130] (maximum, weight sum, 128 sums) for launch_attn_combine_chunk.
+// nsplit and rounds_per_split come from attn_chunk_deal.
 struct AttnChunkArgs {
-    const __half *k_base, *v_base;
+    const __half *k_base;
     uint64_t head_stride;
     uint32_t cap, ctx, head0, nheads, group, n_q;
-    uint32_t row_stride, causal, ntok, q_stride, chunk0, chunk_cap;
-    uint32_t tok_per_wg;   // set by the launch: tokens one workgroup serves
-    // the one-pass form only (launch_attn_chunk_onepass): it walks the cache shards at k_base (row_stride 128,
-    // ctx positions) AND the chunk's own rows in one launch, and writes finished attention rows
-    const __half *k_own, *v_own;   // kv head 0 of token 0 in the QKV rows
-    uint32_t own_stride;           // elements between two tokens' QKV rows
-    __half *out;                   // attention rows [ntok][n_q * 128], out_stride elements apart
+    uint32_t ntok, q_stride, nsplit, rounds_per_split;
+    const __half *k_own, *v_own;
+    uint32_t own_stride;
+    __half *out;
     uint32_t out_stride;
     const __half *q;
     float *part;
 };
+// ctx and the plan's token count, query heads per kv head and kv heads of the model -> the deal of the positions
+void attn_chunk_deal(uint32_t ctx, uint32_t plan_tokens, uint32_t group, uint32_t n_kv, uint32_t *nsplit, uint32_t *rounds_per_split);
 hipError_t launch_attn_chunk(const AttnChunkArgs &a, hipStream_t st);
-// Chunks of many tokens: one launch per run of cache shards walks the cached positions and then the chunk's own
-// rows with running softmax statistics and writes out[t][q_head * 128 ..] directly (no partial records)
-hipError_t launch_attn_chunk_onepass(const AttnChunkArgs &a, hipStream_t st);
 // appends ntok tokens' K / V rows (from their QKV rows) at positions ctx .. of every kv head's cache home
 hipError_t launch_kv_append_rows(uint32_t ctx, uint32_t cap, const __half *qkv, uint32_t qkv_w, uint32_t n_q, uint32_t n_kv, uint32_t ntok,
                                  const uint64_t *home, hipStream_t st);
-// merges every token's chunks (cache chunks below ctx, then the chunk's own) in ascending order, writes the
-// attention rows out[t][n_q * 128] (out_stride elements apart) and appends the tokens' K / V rows at
-// positions ctx .. ctx + ntok - 1 of each kv head's cache home
-hipError_t launch_attn_combine_chunk(const float *part, uint32_t chunk_cap, uint32_t ctx, uint32_t cap, const __half *qkv,
+// merges every token's records in split order, writes the attention rows out[t][n_q * 128] (out_stride
+// elements apart) and appends the tokens' K / V rows at positions ctx .. ctx + ntok - 1 of each kv head's cache home
+hipError_t launch_attn_combine_chunk(const float *part, uint32_t nsplit, uint32_t ctx, uint32_t cap, const __half *qkv,
                                      uint32_t qkv_w, uint32_t n_q, uint32_t n_kv, uint32_t ntok, const uint64_t *home, __half *out,
                                      uint32_t out_stride, hipStream_t st);
 // *dst = v (device word), in stream order

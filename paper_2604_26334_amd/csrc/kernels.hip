@@ -4,10 +4,9 @@
 //   matmuls by token count:  1 -> gemv_w4_kernel,  2..4 -> gemv_mt_kernel (whole scale groups),
 //                            otherwise gemm_w4_kernel (+ splitk_epilogue* when K is split)
 //   attention:  one query token -> attn_decode_kernel + attn_combine_kernel,
-//               a long chunk of query tokens -> attn_chunk_onepass_kernel (one walk over the cache and
-//               the chunk's own rows);  a short chunk -> attn_chunk_mfma_kernel over 256-position
-//               pieces of the cache (attn_chunk_kernel when there are fewer than 16 score rows), the
-//               pieces merged by attn_combine_chunk_kernel
+//               a chunk of query tokens -> attn_chunk_kernel, one walk over the cache and the chunk's own
+//               rows; for a short chunk the walk is dealt out to several workgroups, whose records
+//               attn_combine_chunk_kernel merges
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -749,29 +748,24 @@ constexpr int kAttnWaves = 8;             // waves per workgroup (measured at a 
 constexpr int kAttnIts = 8;               // steps of 4 positions per wave
 constexpr int kAttnPos = kAttnWaves * kAttnIts * 4;   // positions per workgroup (a multiple of kAttnChunk, which sizes the partials)
 static_assert(kAttnPos % kAttnChunk == 0, "the workspace is sized for one partial per kAttnChunk positions");
-constexpr uint32_t kKRowBytes = 272;   // LDS pitch of a staged K row: the 16 rows of an operand read lie 4 banks apart
-constexpr uint32_t kVRowBytes = 288;   // LDS pitch of a staged V row: 256 + 32, so that the four rows of a transpose read lie 8 banks apart
-// A operand of O^T += V^T P^T for MFMA step s of a staged chunk and dim tile dt: lane (i, c) needs dim
-// 16 dt + i of the 8 positions 32 s + 8 c .. + 7, i.e. a COLUMN of the staged rows.  The LDS transpose read
-// of gfx950 (ds_read_b64_tr_b16) does that within each group of 16 lanes: lane L of a group names 8 bytes
-// (4 numbers), lane m receives number m % 4 of lanes m / 4, m / 4 + 4, m / 4 + 8, m / 4 + 12 (checked on the
-// hardware with index numbers as data).  With lane L naming row L / 4, dims 4 (L % 4) .. + 3 of the tile,
-// lane i receives dim i of four consecutive positions; two reads make the operand.
-// lane_base = staged rows + (8 c + i / 4) * kVRowBytes + (i % 4) * 8.
-__device__ __forceinline__ h8_t v_operand(const unsigned char *lane_base, int s, int dt) {
+// A operand of O^T += V^T P^T for a 32-position tile of staged V rows and a tile of 16 dims: lane (i, c) needs dim i
+// of the 8 positions 8 c .. 8 c + 7, i.e. a COLUMN of the staged rows.  The LDS transpose read of gfx950
+// (ds_read_b64_tr_b16) does that within each group of 16 lanes: lane L of a group names 8 bytes (4 numbers), lane m
+// receives number m % 4 of lanes m / 4, m / 4 + 4, m / 4 + 8, m / 4 + 12 (checked on the hardware with index numbers
+// as data).  With lane L naming row L / 4, dims 4 (L % 4) .. + 3 of the tile, lane i receives dim i of four
+// consecutive positions; two reads, four rows apart, make the operand.
+__device__ __forceinline__ h8_t v_operand(const unsigned char *p) {
 #if defined(__HIP_DEVICE_COMPILE__)
     typedef __attribute__((__vector_size__(4 * sizeof(__fp16)))) __fp16 fp16x4_t;
     typedef __attribute__((address_space(3))) fp16x4_t lds_fp16x4_t;
-    const unsigned char *p = lane_base + (32 * s) * kVRowBytes + dt * 32;
     const fp16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_fp16x4_t *)(p));
-    const fp16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_fp16x4_t *)(p + 4 * kVRowBytes));
+    const fp16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_fp16x4_t *)(p + 4 * 256));
     const uint2 a = __builtin_bit_cast(uint2, lo), b = __builtin_bit_cast(uint2, hi);
     return __builtin_bit_cast(h8_t, make_uint4(a.x, a.y, b.x, b.y));
 #else
     return h8_t{};
 #endif
 }
-static_assert(kAttnPos == kAttnPosPerWg, "the executor numbers the chunk's own partials behind ceil(ctx / kAttnPosPerWg) cache chunks");
 
 // sum over each row of 16 lanes, result in every lane of the row (DPP: no LDS traffic)
 __device__ __forceinline__ float row16_sum(float v) {
@@ -911,447 +905,279 @@ __global__ __launch_bounds__(kAttnWaves * 64, 16 / kAttnWaves) void attn_decode_
 }
 
 // ------------------------------------------------------------------------------------
-// Attention for a CHUNK of new tokens (chunked prefill over the cache): the same streaming scheme with
-// a loop over the chunk's tokens.  A workgroup holds 256 positions of one kv head in registers (cache
-// rows, or the chunk's own K / V rows read in place from the QKV buffer: row stride and base differ,
-// nothing else) and serves every token of the chunk in turn: token t sees positions below limit(t) =
-// ctx for cache rows, t + 1 for the chunk's rows (causal).  Per (token, query head, position chunk) it
-// writes the chunk maximum, weight sum and 128 weighted sums; attn_combine_chunk_kernel merges a
-// token's chunks in ascending order, so the result does not depend on where a cache shard lives.
+// Attention for a CHUNK of new tokens (chunked prefill over the cache), on the matrix cores.  Score rows are
+// (token, query head of the kv group) pairs; a workgroup of eight waves holds 64 rows of one kv head and walks
+// ROUNDS of kAttnRound = 128 positions: the cache's, then the chunk's own K / V rows read in place from the QKV
+// rows (base and row stride differ, nothing else), up to the last position any of its rows sees.  Wave
+// (r2, pg) works on rows 32 r2 .. + 31 and positions 32 pg .. + 31 of every round:
+//  scores, transposed: S^T = K Q^T, A = 16 positions x 32 dims of K, B = 16 query rows (registers, loaded once):
+//   the accumulator then holds, in lane (row j, c), four positions of row j;
+//  weights x values, transposed: O^T = V^T P^T, with B = the weights exactly as the score accumulators hold them
+//   (the two 16-position tiles are numbered so that lane group c owns 8 consecutive positions: 4 from each) and
+//   A = 16 dims x 32 positions of V by LDS transpose reads (v_operand);
+// with a running maximum, weight sum and O^T per row and wave, which the four position groups of a row merge in
+// LDS at the end, in order.
+// What bounds it, per round and CU (64 rows): 64 KB of rows from the L2 (1024 cycles at 64 bytes per clock),
+// 128 KB of operand reads from LDS (1024), 2 x 32 MFMAs per SIMD (1024), about 1300 cycles of softmax arithmetic
+// per SIMD.  So: rows go from memory straight into LDS, two rounds' worth of stages, the next round on its way
+// while one is multiplied (one barrier per round); two row tiles per wave share every operand read; two waves per
+// SIMD so that one's softmax meets the other's MFMAs.  Rows of one (kv head, round) are read by all row
+// blocks: the head is the fastest grid index, so with 8 heads a head's blocks share an XCD's L2.
+// SPLIT: the rounds are dealt out to `nsplit` workgroups per row block (short chunks leave most CUs idle
+// otherwise) and each writes, per row, a record (maximum, weight sum, 128 weighted sums) that
+// attn_combine_chunk_kernel merges in split order; without SPLIT the finished rows are written.  The deal goes by
+// context, the plan's token count and the whole model's heads, never by the launch's, so the result does not
+// depend on where a cache shard lives.
+// Measured, 32 query / 8 kv heads over 4096 cached positions: 512 tokens 108 -> 73 us (37 rounds of 1.9 us; the
+// row fills alone take 41, the rest without them 50); 64 tokens 24 + 10 us (cache and own rows in two launches of a
+// kernel that kept 256 positions per workgroup) -> 17 us.
 // ------------------------------------------------------------------------------------
-template <int G>
-__global__ __launch_bounds__(kAttnWaves * 64, 16 / kAttnWaves) void attn_chunk_kernel(AttnChunkArgs a) {
-    __shared__ float red[kAttnWaves][G][128];
-    __shared__ float redm[kAttnWaves][G], redl[kAttnWaves][G];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int dl = lane & 15, pg = lane >> 4;
-    const uint32_t chunk = blockIdx.x, hk = blockIdx.y;
-    const uint32_t kv_head = a.head0 + hk;
-    const __half *K = a.causal ? a.k_base + (size_t)kv_head * 128 : reinterpret_cast<const __half *>(reinterpret_cast<const char *>(a.k_base) + (size_t)hk * a.head_stride);
-    const __half *V = a.causal ? a.v_base + (size_t)kv_head * 128 : K + (size_t)a.cap * 128;
-    const uint32_t q0 = kv_head * G;
-    const float scale = 0.08838834764831845f;   // 1 / sqrt(128)
-    const uint32_t row_b = a.row_stride * 2u;   // bytes between two positions' rows
-    const uint32_t npos = a.causal ? a.ntok : a.ctx;                        // rows that exist
-    const uint32_t range = npos ? (npos - 1) * row_b + 256u : 0u;          // a row past the end reads as zeros
-    const uint32_t base = chunk * kAttnPos + wave * (kAttnPos / kAttnWaves);
-    const __amdgpu_buffer_rsrc_t kb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(K), 0, (int)range, 0x00020000);
-    const __amdgpu_buffer_rsrc_t vb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(V), 0, (int)range, 0x00020000);
-    const uint32_t voff = (uint32_t)pg * row_b + (uint32_t)dl * 16u;
-    const uint32_t soff = __builtin_amdgcn_readfirstlane(base * row_b);
-    uint4 kq[kAttnIts], vq[kAttnIts];
-#pragma unroll
-    for (int it = 0; it < kAttnIts; ++it)
-        kq[it] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(kb, voff, soff + it * 4 * row_b, 0));
-#pragma unroll
-    for (int it = 0; it < kAttnIts; ++it)
-        vq[it] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(vb, voff, soff + it * 4 * row_b, 0));
-    float vf[kAttnIts][8];
-#pragma unroll
-    for (int it = 0; it < kAttnIts; ++it) {
-        const uint32_t vd[4] = {vq[it].x, vq[it].y, vq[it].z, vq[it].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const h2_t pr = as_h2(vd[e]);
-            vf[it][2 * e] = (float)pr.x;
-            vf[it][2 * e + 1] = (float)pr.y;
-        }
-    }
-    // this workgroup's share of the tokens (blockIdx.z), from the first token that sees any position of
-    // this chunk (causal: token chunk * kAttnPos)
-    const uint32_t t_lo = blockIdx.z * a.tok_per_wg, t_hi = min(a.ntok, t_lo + a.tok_per_wg);
-    const uint32_t t_first = max(t_lo, a.causal ? chunk * kAttnPos : 0u);
-#pragma unroll 1
-    for (uint32_t t = t_first; t < t_hi; ++t) {
-        const uint32_t limit = a.causal ? t + 1 : a.ctx;
-        uint4 qv[G];
-#pragma unroll
-        for (int h = 0; h < G; ++h) qv[h] = *reinterpret_cast<const uint4 *>(a.q + (size_t)t * a.q_stride + (size_t)(q0 + h) * 128 + dl * 8);
-        float sc[kAttnIts][G], mx[G];
-#pragma unroll
-        for (int h = 0; h < G; ++h) mx[h] = -INFINITY;
-#pragma unroll
-        for (int it = 0; it < kAttnIts; ++it) {
-            const uint32_t j = base + it * 4 + pg;
-#pragma unroll
-            for (int h = 0; h < G; ++h) {
-                float d = 0.f;
-                d = __builtin_amdgcn_fdot2(as_h2(qv[h].x), as_h2(kq[it].x), d, false);
-                d = __builtin_amdgcn_fdot2(as_h2(qv[h].y), as_h2(kq[it].y), d, false);
-                d = __builtin_amdgcn_fdot2(as_h2(qv[h].z), as_h2(kq[it].z), d, false);
-                d = __builtin_amdgcn_fdot2(as_h2(qv[h].w), as_h2(kq[it].w), d, false);
-                const float r = row16_sum(d) * scale;
-                sc[it][h] = j < limit ? r : -INFINITY;
-                mx[h] = fmaxf(mx[h], sc[it][h]);
-            }
-        }
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-            mx[h] = fmaxf(mx[h], __shfl_xor(mx[h], 16, 64));
-            mx[h] = fmaxf(mx[h], __shfl_xor(mx[h], 32, 64));
-        }
-        float l[G], o[G][8];
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-            l[h] = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[h][e] = 0.f;
-        }
-#pragma unroll
-        for (int it = 0; it < kAttnIts; ++it) {
-#pragma unroll
-            for (int h = 0; h < G; ++h) {
-                const float p = sc[it][h] == -INFINITY ? 0.f : __expf(sc[it][h] - mx[h]);
-                l[h] += p;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[h][e] = fmaf(p, vf[it][e], o[h][e]);
-            }
-        }
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-            l[h] += __shfl_xor(l[h], 16, 64);
-            l[h] += __shfl_xor(l[h], 32, 64);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                o[h][e] += __shfl_xor(o[h][e], 16, 64);
-                o[h][e] += __shfl_xor(o[h][e], 32, 64);
-            }
-            if (pg == 0) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) red[wave][h][dl * 8 + e] = o[h][e];
-                if (dl == 0) { redl[wave][h] = l[h]; redm[wave][h] = mx[h]; }
-            }
-        }
-        __syncthreads();
-        for (int u = tid; u < G * 128; u += kAttnWaves * 64) {
-            const int h = u >> 7, d = u & 127;
-            // the chunk's first position is below the limit (t >= t_first), so wave 0's maximum is finite
-            float m = redm[0][h];
-#pragma unroll
-            for (int k = 1; k < kAttnWaves; ++k) m = fmaxf(m, redm[k][h]);
-            float od = 0.f, ld = 0.f;   // waves in ascending order
-#pragma unroll
-            for (int k = 0; k < kAttnWaves; ++k) {
-                const float w = redm[k][h] == -INFINITY ? 0.f : __expf(redm[k][h] - m);
-                od = fmaf(w, red[k][h][d], od);
-                ld = fmaf(w, redl[k][h], ld);
-            }
-            float *dst = a.part + (((size_t)t * a.n_q + q0 + h) * a.chunk_cap + a.chunk0 + chunk) * 130;
-            dst[2 + d] = od;
-            if (d == 0) {
-                dst[0] = m;
-                dst[1] = ld;
-            }
-        }
-        __syncthreads();   // the next token reuses the reduction buffers
-    }
-}
+constexpr uint32_t kAttnRound = 128;                           // positions per round
+constexpr uint32_t kAttnStageBytes = kAttnRound * 2 * 256;     // K rows, then V rows of a round
+constexpr uint32_t kAttnOPitch = 132;                          // floats per row when the position groups meet
+constexpr size_t kAttnRowsLds = 4 * 64 * kAttnOPitch * 4 + 2 * 4 * 64 * 4;   // the meeting's rows, maxima and sums (more than two stages)
+static_assert(2 * kAttnStageBytes <= 4 * 64 * kAttnOPitch * 4 && kAttnRowsLds <= 160 * 1024, "LDS of the chunk attention");
 
-// ------------------------------------------------------------------------------------
-// The same partials on the matrix cores.  Rows of the score matrix are (token, query head of the
-// kv group) pairs, 16 per wave, 64 per workgroup; a workgroup covers 256 positions of one kv head in
-// 8 steps of 32.
-//  scores, transposed: S^T = K Q^T by v_mfma_f32_16x16x32_f16 with A = 16 positions x 32 dims of K
-//   (lane (p, c) loads 16 bytes of a K row straight from memory) and B = the wave's 16 query rows
-//   (registers, loaded once): the accumulator then holds, in lane (row j, rg), four positions of row j;
-//  weights x values, transposed: O^T = V^T P^T with B = the weights exactly as the score
-//   accumulators hold them (the two 16-position tiles of a step are numbered so that lane group c
-//   owns 8 consecutive positions: 4 from each tile) and A = 16 dims x 32 positions of V, read
-//   column-wise (8 two-byte reads) from the chunk's V rows staged in LDS once per workgroup.
-// Two passes over the chunk's 8 steps: all scores (64 registers) and the row maximum, then weights,
-// weight sum and O^T; per (row, chunk) the same (maximum, weight sum, 128 weighted sums) record as
-// the vector-ALU kernel writes, merged by attn_combine_chunk_kernel in chunk order.
-// ------------------------------------------------------------------------------------
+// 16-byte piece u of a staged row lies in slot u ^ swizzle of the row.  K rows: an operand read takes, per lane
+// group, piece u of the 16 rows 8 (i / 4) + i % 4: their swizzles are the 16 numbers i.  V rows: a transpose read
+// takes 32 bytes (pieces 2 dt, 2 dt + 1) of the rows 8 c + i / 4: even swizzles keep the pair together, eight
+// different ones spread the rows over all banks.
+__device__ __forceinline__ uint32_t k_swz(uint32_t row) { return (row & 3u) | (((row >> 3) & 3u) << 2); }
+__device__ __forceinline__ uint32_t v_swz(uint32_t row) { return ((row & 3u) | (((row >> 3) & 1u) << 2)) << 1; }
 
-// Score pass of the chunk kernels: S^T = K Q^T for the 16 position tiles of a 256-position chunk (tile t: step
-// t / 2, tile t % 2 of the step: positions P0 + 32 (t / 2) + 8 (p / 4) + 4 (t % 2) + p % 4, p = 0 .. 15).  The K
-// rows are A operands straight from memory, so their loads have to be under way well before the MFMAs that
-// take them: kKAhead tiles (4 loads each) stay in flight, a tile's registers refilled as soon as its MFMAs have
-// read them.  (Left to the scheduler, every load sat right in front of its MFMA: 64 exposed round trips to
-// the L2 per chunk.)
-constexpr int kKAhead = 4;
-struct KTiles { h8_t k[kKAhead][4]; };
-__device__ __forceinline__ void k_tile_load(__amdgpu_buffer_rsrc_t kb, uint32_t P0, uint32_t row_b, int t, int i, int c, h8_t (&dst)[4]) {
-    const uint32_t pos = P0 + 32 * (t >> 1) + 8 * (i >> 2) + 4 * (t & 1) + (i & 3);        // the K row this lane supplies
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-        dst[kk] = __builtin_bit_cast(h8_t, __builtin_amdgcn_raw_buffer_load_b128(kb, pos * row_b + kk * 64 + c * 16, 0, 0));
-}
-__device__ __forceinline__ void k_tiles_open(__amdgpu_buffer_rsrc_t kb, uint32_t P0, uint32_t row_b, int i, int c, KTiles &kt) {
-#pragma unroll
-    for (int t = 0; t < kKAhead; ++t) k_tile_load(kb, P0, row_b, t, i, c, kt.k[t]);
-}
-// scores (scaled, -inf where the lane's row does not see the position) and their maximum over the lane's registers
-__device__ __forceinline__ void attn_scores(__amdgpu_buffer_rsrc_t kb, uint32_t P0, uint32_t row_b, int i, int c, KTiles &kt,
-                                            const h8_t (&qreg)[4], float scale, uint32_t limit, f4_t (&S)[8][2], float &mx) {
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        __builtin_amdgcn_sched_barrier(0);
-        f4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(kt.k[t % kKAhead][kk], qreg[kk], acc, 0, 0, 0);
-        if (t + kKAhead < 16) k_tile_load(kb, P0, row_b, t + kKAhead, i, c, kt.k[t % kKAhead]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const uint32_t pj = P0 + 32 * (t >> 1) + 8 * c + 4 * (t & 1) + r;
-            acc[r] = pj < limit ? acc[r] * scale : -INFINITY;
-            mx = fmaxf(mx, acc[r]);
-        }
-        S[t >> 1][t & 1] = acc;
-    }
-}
-
-__global__ __launch_bounds__(256, 2) void attn_chunk_mfma_kernel(AttnChunkArgs a) {
-    extern __shared__ uint4 lds_v4[];
-    unsigned char *ldsv = reinterpret_cast<unsigned char *>(lds_v4);   // [256 positions][kVRowBytes]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int i = lane & 15, c = lane >> 4;
-    const uint32_t chunk = blockIdx.x, hk = blockIdx.y, G = a.group;
-    const uint32_t kv_head = a.head0 + hk;
-    const __half *K = a.causal ? a.k_base + (size_t)kv_head * 128 : reinterpret_cast<const __half *>(reinterpret_cast<const char *>(a.k_base) + (size_t)hk * a.head_stride);
-    const __half *V = a.causal ? a.v_base + (size_t)kv_head * 128 : K + (size_t)a.cap * 128;
-    const uint32_t q0 = kv_head * G;
-    const uint32_t row_b = a.row_stride * 2u;
-    const uint32_t npos = a.causal ? a.ntok : a.ctx;
-    const uint32_t range = npos ? (npos - 1) * row_b + 256u : 0u;   // a row past the end reads as zeros
-    const uint32_t P0 = chunk * kAttnPos;
-    const uint32_t R = a.ntok * G;                                   // score rows of this kv head
-    const uint32_t row0 = blockIdx.z * 64;
+template <bool SPLIT>
+__global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
+    extern __shared__ uint4 at_lds[];
+    unsigned char *lds = reinterpret_cast<unsigned char *>(at_lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t i = lane & 15, c = lane >> 4;
+    const uint32_t r2 = wave & 1, pg = wave >> 1;
+    const uint32_t hk = blockIdx.x, G = a.group;
+    const uint32_t kv_head = a.head0 + hk, q0 = kv_head * G;
+    const uint32_t R = a.ntok * G, row0 = blockIdx.y * 64;
     if (row0 >= R) return;
-    // causal: the workgroup's last token sees nothing of this chunk -> nothing to write (uniform)
-    if (a.causal && min(a.ntok - 1, (row0 + 63) / G) < P0) return;
-    const __amdgpu_buffer_rsrc_t kb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(K), 0, (int)range, 0x00020000);
-    const __amdgpu_buffer_rsrc_t vb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(V), 0, (int)range, 0x00020000);
+    // rounds of this workgroup: cache rounds first, then the chunk's own up to its rows' last token
+    const uint32_t nr_cache = (a.ctx + kAttnRound - 1) / kAttnRound;
+    const uint32_t last_tok = min(a.ntok - 1, (row0 + 63) / G);
+    const uint32_t nr = nr_cache + last_tok / kAttnRound + 1;
+    const uint32_t rd0 = SPLIT ? blockIdx.z * a.rounds_per_split : 0u;
+    const uint32_t rd1 = SPLIT ? min(nr, rd0 + a.rounds_per_split) : nr;
 
-    KTiles kt;
-    k_tiles_open(kb, P0, row_b, i, c, kt);      // the first K tiles set out ahead of everything else
-    __builtin_amdgcn_sched_barrier(0);
-    // V rows of the chunk -> LDS (all 256 threads; 16 bytes each, 16 rounds): every piece is requested before
-    // the first is written (written one by one, each load was waited for before the next was issued)
-    {
-        uint4 vq[16];
+    const __half *kc = reinterpret_cast<const __half *>(reinterpret_cast<const char *>(a.k_base) + (size_t)hk * a.head_stride);
+    const __half *vc = kc + (size_t)a.cap * 128;
+    const __half *ko = a.k_own + (size_t)kv_head * 128, *vo = a.v_own + (size_t)kv_head * 128;
+    // a round's rows straight into LDS: wave w moves rows 16 w .. + 15 of K and of V, four rows per instruction;
+    // positions past the end re-read the last row (their weights are zero)
+    auto stage = [&](uint32_t rd, uint32_t buf) {
+        const bool own = rd >= nr_cache;
+        const uint32_t row_b = own ? a.own_stride * 2u : 256u, npos = own ? a.ntok : a.ctx;
+        const uint32_t P0 = (own ? rd - nr_cache : rd) * kAttnRound;
+        const int range = (int)((npos - 1) * row_b + 256u);
+        const __amdgpu_buffer_rsrc_t kb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(own ? ko : kc), 0, range, 0x00020000);
+        const __amdgpu_buffer_rsrc_t vb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(own ? vo : vc), 0, range, 0x00020000);
+        unsigned char *dk = lds + buf * kAttnStageBytes + wave * (16 * 256), *dv = dk + kAttnRound * 256;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const uint32_t idx = r * 256 + tid, pos = idx >> 4, seg = idx & 15;
-            vq[r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(vb, (P0 + pos) * row_b + seg * 16, 0, 0));
+        for (uint32_t t = 0; t < 4; ++t) {
+            const uint32_t row = wave * 16 + t * 4 + c;
+            const uint32_t off = min(P0 + row, npos - 1) * row_b;
+            load_to_lds16(kb, (lds_void *)(dk + t * 1024), off + ((i ^ k_swz(row)) << 4), 0);
+            load_to_lds16(vb, (lds_void *)(dv + t * 1024), off + ((i ^ v_swz(row)) << 4), 0);
         }
-        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (rd0 < rd1) stage(rd0, 0);
+
+    // the wave's 32 query rows (B operands of the score MFMAs)
+    uint32_t tok[2], hq[2];
+    h8_t q[2][4];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const uint32_t idx = r * 256 + tid, pos = idx >> 4, seg = idx & 15;
-            uint2 *dst = reinterpret_cast<uint2 *>(ldsv + pos * kVRowBytes + seg * 16);
-            dst[0] = make_uint2(vq[r].x, vq[r].y);
-            dst[1] = make_uint2(vq[r].z, vq[r].w);
-        }
+    for (int t = 0; t < 2; ++t) {
+        const uint32_t rho = min(row0 + r2 * 32 + t * 16 + i, R - 1);
+        tok[t] = rho / G; hq[t] = rho % G;
+        const __half *qr = a.q + (size_t)tok[t] * a.q_stride + (size_t)(q0 + hq[t]) * 128 + c * 8;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) q[t][kk] = __builtin_bit_cast(h8_t, *reinterpret_cast<const uint4 *>(qr + kk * 32));
     }
-    // this wave's 16 query rows (B operand of the score MFMAs): row rho = (token, head of the group)
-    const uint32_t rho = min(row0 + wave * 16 + i, R - 1);
-    const uint32_t tok = rho / G, hq = rho % G;
-    const bool row_ok = row0 + wave * 16 + i < R;
-    const uint32_t limit = a.causal ? tok + 1 : a.ctx;               // positions below it are visible to this lane's row
-    h8_t qreg[4];
+    // weights are 2^(c2 s - c2 m) of the raw scores s = q.k: 1 / sqrt(128) and log2(e) in one factor
+    const float c2 = 0.08838834764831845f * 1.4426950408889634f;
+    float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};   // l_run: this lane's positions only
+    f4_t O[2][8];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-        qreg[kk] = __builtin_bit_cast(h8_t, *reinterpret_cast<const uint4 *>(a.q + (size_t)tok * a.q_stride + (size_t)(q0 + hq) * 128 + kk * 32 + c * 8));
-
-    const float scale = 0.08838834764831845f;   // 1 / sqrt(128)
-    // pass 1: scores of the 8 steps.  Tile T of a step holds positions base + 8 (p >> 2) + 4 T + (p & 3), p = 0..15
-    f4_t S[8][2];
-    float mx = -INFINITY;
-    attn_scores(kb, P0, row_b, i, c, kt, qreg, scale, limit, S, mx);
-    mx = rows4_meet<true>(mx);      // the row's four lanes (one per lane group) meet
-    __syncthreads();                // the staged V rows are complete
-
-    // pass 2: weights, their sum, and O^T += V^T P^T
-    f4_t O[8];
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) O[dt] = f4_t{0.f, 0.f, 0.f, 0.f};
-    float l = 0.f;
+        for (int dt = 0; dt < 8; ++dt) O[t][dt] = f4_t{0.f, 0.f, 0.f, 0.f};
+    // LDS byte offsets of this lane's operand pieces in a stage
+    uint32_t koff[4], voff[8];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        float pv[8];
+    for (uint32_t kk = 0; kk < 4; ++kk) koff[kk] = (32 * pg + 8 * (i >> 2) + (i & 3)) * 256 + (((4 * kk + c) ^ i) << 4);
+    {
+        const uint32_t vrow = 32 * pg + 8 * c + (i >> 2);
+#pragma unroll
+        for (uint32_t dt = 0; dt < 8; ++dt)
+            voff[dt] = kAttnRound * 256 + vrow * 256 + (((2 * dt + ((i & 3) >> 1)) ^ v_swz(vrow)) << 4) + (i & 1) * 8;
+    }
+    for (uint32_t rd = rd0; rd < rd1; ++rd) {
+        const uint32_t buf = (rd - rd0) & 1;
+        // this wave's rows of the round have landed; behind the barrier everyone's have, and everyone has left
+        // the other stage
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (rd + 1 < rd1) stage(rd + 1, buf ^ 1);
+        __builtin_amdgcn_sched_barrier(0);
+        const bool own = rd >= nr_cache;
+        const uint32_t P0 = (own ? rd - nr_cache : rd) * kAttnRound + 32 * pg;    // the wave's first position
+        // (uniform) the wave's positions all lie past what its rows see
+        const uint32_t last_seen = own ? min(a.ntok - 1, (row0 + r2 * 32 + 31) / G) : a.ctx - 1;
+        if (P0 > last_seen) continue;
+        const unsigned char *st = lds + buf * kAttnStageBytes;
+        f4_t S[2][2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int T = 0; T < 2; ++T) S[t][T] = f4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int T = 0; T < 2; ++T)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float sc = S[s][T][r];
-                pv[4 * T + r] = sc == -INFINITY ? 0.f : __expf(sc - mx);
-                l += pv[4 * T + r];
+            for (int kk = 0; kk < 4; ++kk) {
+                const h8_t kr = __builtin_bit_cast(h8_t, *reinterpret_cast<const uint4 *>(st + koff[kk] + T * 1024));
+#pragma unroll
+                for (int t = 0; t < 2; ++t) S[t][T] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kr, q[t][kk], S[t][T], 0, 0, 0);
             }
-        const h8_t Bp = {(_Float16)pv[0], (_Float16)pv[1], (_Float16)pv[2], (_Float16)pv[3],
-                         (_Float16)pv[4], (_Float16)pv[5], (_Float16)pv[6], (_Float16)pv[7]};
-        // A operand: dim 16 dt + i of the 8 positions 32 s + 8 c .. + 7 (a column of the staged rows)
-        const unsigned char *vbase = ldsv + (8 * c + (i >> 2)) * kVRowBytes + (i & 3) * 8;
+        // positions a row does not see: only the cache's last round and the own rounds can hold any
+        if (own || P0 + 32 > a.ctx) {
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v_operand(vbase, s, dt), Bp, O[dt], 0, 0, 0);
-    }
-    l = rows4_meet<false>(l);
-    // lane (row i, group c) holds dims 16 dt + 4 c + r of its row
-    if (!row_ok || mx == -INFINITY) return;      // no such row, or a row that sees nothing of this chunk
-    float *dst = a.part + (((size_t)tok * a.n_q + q0 + hq) * a.chunk_cap + a.chunk0 + chunk) * 130;
+            for (int t = 0; t < 2; ++t) {
+                const uint32_t limit = own ? tok[t] + 1 : a.ctx;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) {
-        float2 *d2 = reinterpret_cast<float2 *>(dst + 2 + 16 * dt + 4 * c);
-        d2[0] = make_float2(O[dt][0], O[dt][1]);
-        d2[1] = make_float2(O[dt][2], O[dt][3]);
-    }
-    if (c == 0) {
-        dst[0] = mx;
-        dst[1] = l;
-    }
-}
-
-// ------------------------------------------------------------------------------------
-// Many-token chunks (plans of kAttnOnePassTokens tokens and more): the same two products, but one
-// workgroup walks ALL positions of its 64 score rows -- the cache's chunks, then the chunk's own rows up
-// to its last token -- keeping a running maximum, weight sum and O^T per row and rescaling them when a
-// chunk raises the maximum, and writes the finished attention rows.  No partial records: their size
-// (tokens x heads x chunks) is what makes the record form unusable for long chunks over long contexts.
-// The order of the chunks is fixed, so the result does not depend on where a cache shard lives.
-// ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256, 1) void attn_chunk_onepass_kernel(AttnChunkArgs a) {
-    extern __shared__ uint4 lds_v4[];
-    unsigned char *ldsv = reinterpret_cast<unsigned char *>(lds_v4);   // V rows [256 positions][kVRowBytes]
-    unsigned char *ldsk = ldsv + kAttnPos * kVRowBytes;                 // K rows [256 positions][kKRowBytes]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int i = lane & 15, c = lane >> 4;
-    const uint32_t hk = blockIdx.x, G = a.group;
-    const uint32_t kv_head = a.head0 + hk;
-    const uint32_t q0 = kv_head * G;
-    const uint32_t R = a.ntok * G;
-    const uint32_t row0 = blockIdx.y * 64;
-    if (row0 >= R) return;
-    const uint32_t rho = min(row0 + wave * 16 + i, R - 1);
-    const uint32_t tok = rho / G, hq = rho % G;
-    const bool row_ok = row0 + wave * 16 + i < R;
-    const uint32_t last_tok = min(a.ntok - 1, (row0 + 63) / G);      // the workgroup's last token
-    h8_t qreg[4];
+                for (int T = 0; T < 2; ++T)
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-        qreg[kk] = __builtin_bit_cast(h8_t, *reinterpret_cast<const uint4 *>(a.q + (size_t)tok * a.q_stride + (size_t)(q0 + hq) * 128 + kk * 32 + c * 8));
-    const float scale = 0.08838834764831845f;   // 1 / sqrt(128)
-    float m_run = -INFINITY, l_run = 0.f;
-    f4_t O[8];
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) O[dt] = f4_t{0.f, 0.f, 0.f, 0.f};
-
-    const uint32_t nc_cache = (a.ctx + kAttnPos - 1) / kAttnPos, nc_own = last_tok / kAttnPos + 1;
-#pragma unroll 1
-    for (uint32_t cc = 0; cc < nc_cache + nc_own; ++cc) {
-        const bool own = cc >= nc_cache;                  // the same for the whole workgroup
-        const uint32_t chunk = own ? cc - nc_cache : cc;
-        const __half *K = own ? a.k_own + (size_t)kv_head * 128 : reinterpret_cast<const __half *>(reinterpret_cast<const char *>(a.k_base) + (size_t)hk * a.head_stride);
-        const __half *V = own ? a.v_own + (size_t)kv_head * 128 : K + (size_t)a.cap * 128;
-        const uint32_t row_b = (own ? a.own_stride : 128u) * 2u;
-        const uint32_t npos = own ? a.ntok : a.ctx;
-        const uint32_t range = (npos - 1) * row_b + 256u;
-        const uint32_t limit = own ? tok + 1 : a.ctx;
-        const uint32_t P0 = chunk * kAttnPos;
-        const __amdgpu_buffer_rsrc_t kb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(K), 0, (int)range, 0x00020000);
-        const __amdgpu_buffer_rsrc_t vb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(V), 0, (int)range, 0x00020000);
-        // the chunk's K and V rows -> LDS: every thread requests its 32 pieces (16 bytes each) at once, so the
-        // whole 128 KB is under way together (the four waves share the K rows instead of each reading them all)
-        {
-            uint4 kq[16], vq[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t idx = r * 256 + tid, pos = idx >> 4, seg = idx & 15;
-                kq[r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(kb, (P0 + pos) * row_b + seg * 16, 0, 0));
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t idx = r * 256 + tid, pos = idx >> 4, seg = idx & 15;
-                vq[r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(vb, (P0 + pos) * row_b + seg * 16, 0, 0));
-            }
-            __syncthreads();     // every wave has left the previous chunk's staged rows
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t idx = r * 256 + tid, pos = idx >> 4, seg = idx & 15;
-                *reinterpret_cast<uint4 *>(ldsk + pos * kKRowBytes + seg * 16) = kq[r];
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t idx = r * 256 + tid, pos = idx >> 4, seg = idx & 15;
-                uint2 *dst = reinterpret_cast<uint2 *>(ldsv + pos * kVRowBytes + seg * 16);
-                dst[0] = make_uint2(vq[r].x, vq[r].y);
-                dst[1] = make_uint2(vq[r].z, vq[r].w);
+                    for (int r = 0; r < 4; ++r) S[t][T][r] = P0 + 8 * c + 4 * T + r < limit ? S[t][T][r] : -INFINITY;
             }
         }
-        __syncthreads();     // the staged rows are complete
-        f4_t S[8][2];
-        float mx = -INFINITY;
-        {
-            // S^T = K Q^T, the K rows as A operands from LDS: lane (i, c) supplies row 8 (i / 4) + i % 4 (+ 4 for
-            // the second tile of a step), bytes 64 kk + 16 c
-            const unsigned char *kbase = ldsk + (8 * (i >> 2) + (i & 3)) * kKRowBytes + c * 16;
+        float mx[2];
 #pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                f4_t acc = {0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < 2; ++t) {
+            mx[t] = fmaxf(fmaxf(fmaxf(S[t][0][0], S[t][0][1]), fmaxf(S[t][0][2], S[t][0][3])),
+                          fmaxf(fmaxf(S[t][1][0], S[t][1][1]), fmaxf(S[t][1][2], S[t][1][3])));
+            mx[t] = fmaxf(m_run[t], rows4_meet<true>(mx[t]));
+        }
+        // some row's maximum rose: rescale (a row that has seen nothing holds zeros, and the difference of two
+        // -inf is not a number)
+        if (__any(mx[0] > m_run[0] || mx[1] > m_run[1])) {
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    const h8_t kreg = __builtin_bit_cast(h8_t, *reinterpret_cast<const uint4 *>(kbase + (32 * (t >> 1) + 4 * (t & 1)) * kKRowBytes + kk * 64));
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(kreg, qreg[kk], acc, 0, 0, 0);
-                }
+            for (int t = 0; t < 2; ++t) {
+                const float resc = m_run[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run[t] - mx[t]) * c2);
+                m_run[t] = mx[t];
+                l_run[t] *= resc;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const uint32_t pj = P0 + 32 * (t >> 1) + 8 * c + 4 * (t & 1) + r;
-                    acc[r] = pj < limit ? acc[r] * scale : -INFINITY;
-                    mx = fmaxf(mx, acc[r]);
-                }
-                S[t >> 1][t & 1] = acc;
+                for (int dt = 0; dt < 8; ++dt) O[t][dt] = O[t][dt] * resc;
             }
         }
-        mx = rows4_meet<true>(mx);
-        const float m_new = fmaxf(m_run, mx);
-        // a row that has seen nothing yet keeps zeros (the difference of two -inf is not a number)
-        const float resc = m_run == -INFINITY ? 0.f : __expf(m_run - m_new);
-        m_run = m_new;
-        l_run *= resc;
+        h8_t P[2];
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) O[dt] = O[dt] * resc;
-        float l = 0.f;
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
+        for (int t = 0; t < 2; ++t) {
+            const float ms = m_run[t] == -INFINITY ? 0.f : m_run[t] * c2;
             float pv[8];
 #pragma unroll
             for (int T = 0; T < 2; ++T)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float sc = S[s][T][r];
-                    pv[4 * T + r] = sc == -INFINITY ? 0.f : __expf(sc - m_new);
-                    l += pv[4 * T + r];
+                    pv[4 * T + r] = __builtin_amdgcn_exp2f(fmaf(S[t][T][r], c2, -ms));
+                    l_run[t] += pv[4 * T + r];
                 }
-            const h8_t Bp = {(_Float16)pv[0], (_Float16)pv[1], (_Float16)pv[2], (_Float16)pv[3],
-                             (_Float16)pv[4], (_Float16)pv[5], (_Float16)pv[6], (_Float16)pv[7]};
-            const unsigned char *vbase = ldsv + (8 * c + (i >> 2)) * kVRowBytes + (i & 3) * 8;
-#pragma unroll
-            for (int dt = 0; dt < 8; ++dt) O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v_operand(vbase, s, dt), Bp, O[dt], 0, 0, 0);
+            P[t] = h8_t{(_Float16)pv[0], (_Float16)pv[1], (_Float16)pv[2], (_Float16)pv[3],
+                        (_Float16)pv[4], (_Float16)pv[5], (_Float16)pv[6], (_Float16)pv[7]};
         }
-        l_run += rows4_meet<false>(l);
-    }
-    if (!row_ok) return;
-    // every row sees at least its own token, so l_run > 0; lane (row i, group c) holds dims 16 dt + 4 c + r
-    const float inv = 1.0f / l_run;
-    __half *dst = a.out + (size_t)tok * a.out_stride + (size_t)(q0 + hq) * 128;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) {
-        __half2 *d2 = reinterpret_cast<__half2 *>(dst + 16 * dt + 4 * c);
-        d2[0] = __half2{to_half(O[dt][0] * inv), to_half(O[dt][1] * inv)};
-        d2[1] = __half2{to_half(O[dt][2] * inv), to_half(O[dt][3] * inv)};
+        for (int dt = 0; dt < 8; ++dt) {
+            const h8_t vr = v_operand(st + voff[dt]);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) O[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vr, P[t], O[t][dt], 0, 0, 0);
+        }
+    }
+    // the four position groups of a row meet: every wave leaves its rows, maxima and sums in LDS
+    __syncthreads();     // the last stage's reads are behind everyone
+    float *ob = reinterpret_cast<float *>(lds), *om = ob + 4 * 64 * kAttnOPitch, *ol = om + 4 * 64;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const float l = rows4_meet<false>(l_run[t]);
+        const uint32_t row = r2 * 32 + t * 16 + i;
+        float *dst = ob + (pg * 64 + row) * kAttnOPitch + 4 * c;   // lane (row i, group c) holds dims 16 dt + 4 c + r
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<float4 *>(dst + 16 * dt) = make_float4(O[t][dt][0], O[t][dt][1], O[t][dt][2], O[t][dt][3]);
+        if (c == 0) { om[pg * 64 + row] = m_run[t]; ol[pg * 64 + row] = l; }
+    }
+    __syncthreads();
+    const uint32_t row = tid >> 3, d0 = (tid & 7) * 16, rho = row0 + row;
+    if (rho >= R) return;
+    float m = om[row];
+#pragma unroll
+    for (int g = 1; g < 4; ++g) m = fmaxf(m, om[g * 64 + row]);
+    float l = 0.f, o[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[e] = 0.f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const float mg = om[g * 64 + row], w = mg == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mg - m) * c2);
+        const float4 *src = reinterpret_cast<const float4 *>(ob + (g * 64 + row) * kAttnOPitch + d0);
+        l = fmaf(w, ol[g * 64 + row], l);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float4 v = src[e];
+            o[4 * e] = fmaf(w, v.x, o[4 * e]); o[4 * e + 1] = fmaf(w, v.y, o[4 * e + 1]);
+            o[4 * e + 2] = fmaf(w, v.z, o[4 * e + 2]); o[4 * e + 3] = fmaf(w, v.w, o[4 * e + 3]);
+        }
+    }
+    const uint32_t t = rho / G, h = q0 + rho % G;
+    if (SPLIT) {
+        float *dst = a.part + (((size_t)t * a.n_q + h) * a.nsplit + blockIdx.z) * 130;
+        if (d0 == 0) *reinterpret_cast<float2 *>(dst) = make_float2(m * 0.08838834764831845f, l);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) reinterpret_cast<float2 *>(dst + 2 + d0)[e] = make_float2(o[2 * e], o[2 * e + 1]);
+    } else {
+        const float inv = 1.0f / l;      // every row sees at least its own token
+        uint32_t d[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            d[e] = (uint32_t)__builtin_bit_cast(uint16_t, to_half(o[2 * e] * inv)) | ((uint32_t)__builtin_bit_cast(uint16_t, to_half(o[2 * e + 1] * inv)) << 16);
+        uint4 *dst = reinterpret_cast<uint4 *>(a.out + (size_t)t * a.out_stride + (size_t)h * 128 + d0);
+        dst[0] = uint4{d[0], d[1], d[2], d[3]};
+        dst[1] = uint4{d[4], d[5], d[6], d[7]};
     }
 }
 
-hipError_t launch_attn_chunk_onepass(const AttnChunkArgs &a, hipStream_t st) {
+// How the positions of a chunk's attention are dealt out: plans of kAttnOnePassTokens tokens and more fill the
+// CUs with row blocks (and their workspace holds no records); below, as many splits as bring the launch to
+// about one workgroup per CU, in whole rounds.  One split means finished rows and no merge.
+void attn_chunk_deal(uint32_t ctx, uint32_t plan_tokens, uint32_t group, uint32_t n_kv, uint32_t *nsplit, uint32_t *rounds_per_split) {
+    const uint32_t rounds = (ctx + kAttnRound - 1) / kAttnRound + (plan_tokens + kAttnRound - 1) / kAttnRound;
+    const uint32_t blocks = (plan_tokens * group + 63) / 64 * n_kv;
+    uint32_t per = rounds;
+    if (plan_tokens < kAttnOnePassTokens) {
+        const uint32_t want = std::max(1u, std::min(rounds, 256u / std::max(1u, blocks)));
+        per = (rounds + want - 1) / want;
+    }
+    *rounds_per_split = per;
+    *nsplit = (rounds + per - 1) / per;
+}
+
+hipError_t launch_attn_chunk(const AttnChunkArgs &a, hipStream_t st) {
     if (a.nheads == 0 || a.ntok == 0) return hipSuccess;
-    if (a.group == 0 || a.group > 16 || !a.out || !a.k_own || !a.v_own) return hipErrorInvalidValue;
-    if (((uint64_t)a.ctx + kAttnPos) * 256u > 0x7FFFFFFFull || ((uint64_t)a.ntok + kAttnPos) * a.own_stride * 2u > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    dim3 grid(a.nheads, (a.ntok * a.group + 63) / 64);
-    const size_t ldsb = (size_t)kAttnPos * (kVRowBytes + kKRowBytes);
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_chunk_onepass_kernel),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsb);
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(attn_chunk_onepass_kernel, grid, dim3(256), ldsb, st, a);
+    if (a.group == 0 || a.group > 16 || !a.k_own || !a.v_own || a.nsplit == 0) return hipErrorInvalidValue;
+    const uint32_t rounds = (a.ctx + kAttnRound - 1) / kAttnRound + (a.ntok + kAttnRound - 1) / kAttnRound;
+    if ((uint64_t)a.nsplit * a.rounds_per_split < rounds || (a.nsplit > 1 ? !a.part : !a.out)) return hipErrorInvalidValue;
+    // 32-bit buffer offsets
+    if (((uint64_t)a.ctx + kAttnRound) * 256u > 0x7FFFFFFFull || ((uint64_t)a.ntok + kAttnRound) * a.own_stride * 2u > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    dim3 grid(a.nheads, (a.ntok * a.group + 63) / 64, a.nsplit);
+    static const hipError_t attr_s = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_chunk_kernel<true>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAttnRowsLds);
+    static const hipError_t attr_f = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_chunk_kernel<false>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAttnRowsLds);
+    if (attr_s != hipSuccess) return attr_s;
+    if (attr_f != hipSuccess) return attr_f;
+    if (a.nsplit > 1) hipLaunchKernelGGL(attn_chunk_kernel<true>, grid, dim3(512), kAttnRowsLds, st, a);
+    else hipLaunchKernelGGL(attn_chunk_kernel<false>, grid, dim3(512), kAttnRowsLds, st, a);
     return hipGetLastError();
 }
 
@@ -1372,76 +1198,38 @@ hipError_t launch_kv_append_rows(uint32_t ctx, uint32_t cap, const __half *qkv, 
     return hipGetLastError();
 }
 
-hipError_t launch_attn_chunk(const AttnChunkArgs &a_in, hipStream_t st) {
-    AttnChunkArgs a = a_in;
-    const uint32_t npos = a.causal ? a.ntok : a.ctx;
-    if (npos == 0 || a.nheads == 0 || a.ntok == 0) return hipSuccess;
-    if (a.group == 0 || a.group > 16) return hipErrorInvalidValue;
-    if (a.ntok * a.group < 16) {
-        // fewer score rows than one MFMA tile (a last chunk of one or two tokens): the vector-ALU form,
-        // the tokens shared out over blockIdx.z.  Same records; which form runs depends on the token
-        // count only, never on the placement.
-        const uint32_t wg_xy = (npos + kAttnPos - 1) / kAttnPos * a.nheads;
-        a.tok_per_wg = std::max(1u, (a.ntok + std::max(1u, 1024u / wg_xy) - 1) / std::max(1u, 1024u / wg_xy));
-        dim3 gv((npos + kAttnPos - 1) / kAttnPos, a.nheads, (a.ntok + a.tok_per_wg - 1) / a.tok_per_wg);
-        if (a.chunk0 + gv.x > a.chunk_cap || (uint64_t)npos * a.row_stride * 2u > 0x7FFFFFFFull) return hipErrorInvalidValue;
-        switch (a.group) {
-            case 1: hipLaunchKernelGGL(attn_chunk_kernel<1>, gv, dim3(kAttnWaves * 64), 0, st, a); break;
-            case 2: hipLaunchKernelGGL(attn_chunk_kernel<2>, gv, dim3(kAttnWaves * 64), 0, st, a); break;
-            case 4: hipLaunchKernelGGL(attn_chunk_kernel<4>, gv, dim3(kAttnWaves * 64), 0, st, a); break;
-            case 8: hipLaunchKernelGGL(attn_chunk_kernel<8>, gv, dim3(kAttnWaves * 64), 0, st, a); break;
-            default: return hipErrorInvalidValue;
-        }
-        return hipGetLastError();
-    }
-    dim3 grid((npos + kAttnPos - 1) / kAttnPos, a.nheads, (a.ntok * a.group + 63) / 64);
-    if (a.chunk0 + grid.x > a.chunk_cap) return hipErrorInvalidValue;
-    if (((uint64_t)npos + kAttnPos) * a.row_stride * 2u > 0x7FFFFFFFull) return hipErrorInvalidValue;   // 32-bit buffer offsets
-    const size_t ldsb = (size_t)kAttnPos * kVRowBytes;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_chunk_mfma_kernel),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsb);
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(attn_chunk_mfma_kernel, grid, dim3(256), ldsb, st, a);
-    return hipGetLastError();
-}
-
-// One workgroup of 128 threads per (query head, token): thread d merges dimension d over the token's
-// chunks in ascending order -- the cache's chunks below ctx, then the chunk's own rows up to the token
-// itself -- writes the attention output row (the O projection's input) and, for the first query head
-// of each kv group, appends the token's K and V rows at position ctx + t of that head's cache home.
-__global__ __launch_bounds__(128) void attn_combine_chunk_kernel(const float *part, uint32_t chunk_cap, uint32_t ctx, uint32_t cap,
+// One workgroup of 128 threads per (query head, token): thread d merges dimension d over the token's records
+// in split order (a record of a split the token sees nothing of has maximum -inf), writes the attention output
+// row (the O projection's input) and, for the first query head of each kv group, appends the token's K and V
+// rows at position ctx + t of that head's cache home.
+__global__ __launch_bounds__(128) void attn_combine_chunk_kernel(const float *part, uint32_t nsplit, uint32_t ctx, uint32_t cap,
                                                                  const __half *qkv, uint32_t qkv_w, uint32_t n_q, uint32_t n_kv,
                                                                  const uint64_t *home, __half *out, uint32_t out_stride) {
     const uint32_t h = blockIdx.x, t = blockIdx.y, d = threadIdx.x;
     const uint32_t group = n_q / n_kv, g = h / group;
-    const uint32_t nc_cache = (ctx + kAttnPos - 1) / kAttnPos, nc_own = t / kAttnPos + 1;
-    const float *ph = part + ((size_t)t * n_q + h) * chunk_cap * 130;
-    // the records are read eight (then four) chunks at a time, every load of a round requested before the first
-    // is used (a chunk past the last re-reads the last one and is left out); the sums stay in chunk order
-    const uint32_t nct = nc_cache + nc_own;
-    float mx = -INFINITY;
-    for (uint32_t c0 = 0; c0 < nct; c0 += 8) {
-        float mv[8];
+    const float *ph = part + ((size_t)t * n_q + h) * nsplit * 130;
+    // eight records at a time, every load of a round requested before the first is used (a record past the last
+    // re-reads the last one and is left out); one walk with a running maximum, the sums in split order
+    float mx = -INFINITY, L = 0.f, o = 0.f;
+    for (uint32_t c0 = 0; c0 < nsplit; c0 += 8) {
+        float mv[8], lv[8], ov[8], m8 = mx;
 #pragma unroll
-        for (uint32_t u = 0; u < 8; ++u) mv[u] = ph[(size_t)min(c0 + u, nct - 1) * 130];
-#pragma unroll
-        for (uint32_t u = 0; u < 8; ++u) mx = fmaxf(mx, mv[u]);
-    }
-    float L = 0.f, o = 0.f;
-    for (uint32_t c0 = 0; c0 < nct; c0 += 4) {
-        float mv[4], lv[4], ov[4];
-#pragma unroll
-        for (uint32_t u = 0; u < 4; ++u) {
-            const float *pc = ph + (size_t)min(c0 + u, nct - 1) * 130;
+        for (uint32_t u = 0; u < 8; ++u) {
+            const float *pc = ph + (size_t)min(c0 + u, nsplit - 1) * 130;
             mv[u] = pc[0]; lv[u] = pc[1]; ov[u] = pc[2 + d];
         }
 #pragma unroll
-        for (uint32_t u = 0; u < 4; ++u) {
-            if (c0 + u < nct) {
-                const float w = __expf(mv[u] - mx);
-                L = fmaf(w, lv[u], L);
-                o = fmaf(w, ov[u], o);
-            }
+        for (uint32_t u = 0; u < 8; ++u) m8 = fmaxf(m8, mv[u]);
+        // (no branch on a record's maximum: the loads would sink into it one by one)
+        const float ms = m8 == -INFINITY ? 0.f : m8, resc = __expf(mx - ms);
+        L *= resc;
+        o *= resc;
+        mx = m8;
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) {
+            const float w = c0 + u < nsplit ? __expf(mv[u] - ms) : 0.f;
+            L = fmaf(w, lv[u], L);
+            o = fmaf(w, ov[u], o);
         }
     }
     out[(size_t)t * out_stride + (size_t)h * 128 + d] = to_half(o / L);
@@ -1452,13 +1240,12 @@ __global__ __launch_bounds__(128) void attn_combine_chunk_kernel(const float *pa
     }
 }
 
-hipError_t launch_attn_combine_chunk(const float *part, uint32_t chunk_cap, uint32_t ctx, uint32_t cap, const __half *qkv,
+hipError_t launch_attn_combine_chunk(const float *part, uint32_t nsplit, uint32_t ctx, uint32_t cap, const __half *qkv,
                                      uint32_t qkv_w, uint32_t n_q, uint32_t n_kv, uint32_t ntok, const uint64_t *home, __half *out,
                                      uint32_t out_stride, hipStream_t st) {
     if (ntok == 0) return hipSuccess;
-    if (n_kv == 0 || n_q % n_kv || (uint64_t)ctx + ntok > cap || ntok > 65535) return hipErrorInvalidValue;
-    if ((ctx + kAttnPos - 1) / kAttnPos + (ntok + kAttnPos - 1) / kAttnPos > chunk_cap) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(attn_combine_chunk_kernel, dim3(n_q, ntok), dim3(128), 0, st, part, chunk_cap, ctx, cap, qkv, qkv_w, n_q, n_kv, home,
+    if (n_kv == 0 || n_q % n_kv || nsplit == 0 || (uint64_t)ctx + ntok > cap || ntok > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(attn_combine_chunk_kernel, dim3(n_q, ntok), dim3(128), 0, st, part, nsplit, ctx, cap, qkv, qkv_w, n_q, n_kv, home,
                        out, out_stride);
     return hipGetLastError();
 }

@@ -358,25 +358,19 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         }
         case PS_K_ATTN: {
             const Shard &s = p.shards[op.info.shard0];
-            const uint32_t ccap = (m.kv_context + kAttnChunk - 1) / kAttnChunk + (MP > 1 ? (MP + kAttnChunk - 1) / kAttnChunk : 0);
-            if (MP >= kAttnOnePassTokens) {   // many tokens: cache and own rows in one walk, finished rows out
+            if (MP > 1) {   // a chunk of tokens: the cached positions of this run of kv heads and the chunk's own rows
                 AttnChunkArgs c{};
                 c.k_base = reinterpret_cast<const __half *>(wptr(op)); c.head_stride = g.kv_shard_bytes;
                 c.cap = m.kv_context; c.ctx = st->ctx; c.head0 = s.expert; c.nheads = op.info.nshards;
-                c.group = m.n_q_heads / m.n_kv_heads; c.n_q = m.n_q_heads; c.row_stride = m.head_dim;
+                c.group = m.n_q_heads / m.n_kv_heads; c.n_q = m.n_q_heads;
                 c.ntok = M; c.q_stride = g.qkv_w; c.q = qkv;
                 c.k_own = qkv + (size_t)m.n_q_heads * m.head_dim; c.v_own = qkv + (size_t)(m.n_q_heads + m.n_kv_heads) * m.head_dim;
                 c.own_stride = g.qkv_w; c.out = reinterpret_cast<__half *>(WS + p.ws.attn); c.out_stride = g.attn_w;
-                PS_HIP(launch_attn_chunk_onepass(c, cs));
-                return PS_OK;
-            }
-            if (MP > 1) {   // a chunk of tokens over the cached positions of this run of kv heads
-                AttnChunkArgs c{};
-                c.k_base = reinterpret_cast<const __half *>(wptr(op)); c.head_stride = g.kv_shard_bytes;
-                c.cap = m.kv_context; c.ctx = st->ctx; c.head0 = s.expert; c.nheads = op.info.nshards;
-                c.group = m.n_q_heads / m.n_kv_heads; c.n_q = m.n_q_heads; c.row_stride = m.head_dim; c.causal = 0;
-                c.ntok = M; c.q_stride = g.qkv_w; c.chunk0 = 0; c.chunk_cap = ccap; c.q = qkv;
                 c.part = reinterpret_cast<float *>(WS + p.ws.apart);
+                attn_chunk_deal(c.ctx, MP, c.group, m.n_kv_heads, &c.nsplit, &c.rounds_per_split);
+                // (plans below kAttnOnePassTokens: groups of 1, 2, 4 or 8 query heads when there are fewer than 16 score rows)
+                if (MP < kAttnOnePassTokens && M * c.group < 16 && c.group != 1 && c.group != 2 && c.group != 4 && c.group != 8)
+                    PS_HIP(hipErrorInvalidValue);
                 PS_HIP(launch_attn_chunk(c, cs));
                 return PS_OK;
             }
@@ -391,23 +385,15 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             return PS_OK;
         }
         case PS_K_ATTN_COMBINE:
-            if (MP >= kAttnOnePassTokens) {   // the attention rows are finished: only the chunk's rows remain to be appended
-                PS_HIP(launch_kv_append_rows(st->ctx, m.kv_context, qkv, g.qkv_w, m.n_q_heads, m.n_kv_heads, M,
-                                             reinterpret_cast<const uint64_t *>(WS + p.ws.kvhome) + (size_t)l * m.n_kv_heads, cs));
-                return PS_OK;
-            }
-            if (MP > 1) {   // the chunk's own rows (causal), then every token's chunks merged and its rows appended
-                const uint32_t ccap = (m.kv_context + kAttnChunk - 1) / kAttnChunk + (MP + kAttnChunk - 1) / kAttnChunk;
-                AttnChunkArgs c{};
-                c.k_base = qkv + (size_t)m.n_q_heads * m.head_dim; c.v_base = qkv + (size_t)(m.n_q_heads + m.n_kv_heads) * m.head_dim;
-                c.cap = m.kv_context; c.ctx = st->ctx; c.head0 = 0; c.nheads = m.n_kv_heads;
-                c.group = m.n_q_heads / m.n_kv_heads; c.n_q = m.n_q_heads; c.row_stride = g.qkv_w; c.causal = 1;
-                c.ntok = M; c.q_stride = g.qkv_w; c.chunk0 = (st->ctx + kAttnPosPerWg - 1) / kAttnPosPerWg; c.chunk_cap = ccap; c.q = qkv;
-                c.part = reinterpret_cast<float *>(WS + p.ws.apart);
-                PS_HIP(launch_attn_chunk(c, cs));
-                PS_HIP(launch_attn_combine_chunk(c.part, ccap, st->ctx, m.kv_context, qkv, g.qkv_w, m.n_q_heads, m.n_kv_heads, M,
-                                                 reinterpret_cast<const uint64_t *>(WS + p.ws.kvhome) + (size_t)l * m.n_kv_heads,
-                                                 reinterpret_cast<__half *>(WS + p.ws.attn), g.attn_w, cs));
+            if (MP > 1) {
+                const uint64_t *home = reinterpret_cast<const uint64_t *>(WS + p.ws.kvhome) + (size_t)l * m.n_kv_heads;
+                uint32_t nsplit, per;
+                attn_chunk_deal(st->ctx, MP, m.n_q_heads / m.n_kv_heads, m.n_kv_heads, &nsplit, &per);
+                if (nsplit == 1)   // the attention rows are finished: only the chunk's rows remain to be appended
+                    PS_HIP(launch_kv_append_rows(st->ctx, m.kv_context, qkv, g.qkv_w, m.n_q_heads, m.n_kv_heads, M, home, cs));
+                else               // every token's records merged, and the chunk's rows appended
+                    PS_HIP(launch_attn_combine_chunk(reinterpret_cast<const float *>(WS + p.ws.apart), nsplit, st->ctx, m.kv_context, qkv, g.qkv_w,
+                                                     m.n_q_heads, m.n_kv_heads, M, home, reinterpret_cast<__half *>(WS + p.ws.attn), g.attn_w, cs));
                 return PS_OK;
             }
             PS_HIP(launch_attn_combine(reinterpret_cast<const float *>(WS + p.ws.apart),

@@ -626,6 +626,36 @@ def test_chunk_of_new_tokens_attends_over_the_kv_cache(ctx0, M):
         plan.close()
 
 
+@pytest.mark.parametrize("n_q,n_kv,ctx0,M", [(4, 4, 127, 2), (8, 2, 128, 16), (8, 1, 129, 17), (6, 2, 383, 33), (4, 2, 1000, 65),
+                                             (8, 2, 256, 127), (4, 1, 60, 129), (8, 2, 31, 255), (8, 2, 97, 257)])
+def test_chunk_attention_at_the_edges_of_its_rounds_and_row_blocks(n_q, n_kv, ctx0, M):
+    """Chunk attention walks rounds of 128 positions with 64 (token, head) rows per workgroup and 32 per wave:
+    contexts and chunk lengths around those sizes, one to eight query heads per kv head, against the oracle."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(_kv_cfg(1, ctx0 + M + 3), n_q_heads=n_q, n_kv_heads=n_kv)
+    W = Hn.WeightCache(cfg, 53)
+    K, V = S.kv_cache(53, 0, n_kv, ctx0, 128)
+    oK = np.zeros((n_kv, cfg["kv_context"], 128), np.float16)
+    oV = np.zeros_like(oK)
+    oK[:, :ctx0], oV[:, :ctx0] = K, V
+    x = S.activations(53, 0, M, cfg["hidden"])
+    refs = [O.stack_forward(x, cfg, W, mirror=mirror, kv=lambda _l: (oK, oV), ctx=ctx0) for mirror in (True, False)]
+    st = B.Stack(B.Plan(cfg, 1 << 30, M))
+    for k, ex, N, Kd in S.matrix_shapes(cfg):
+        st.load_matrix(0, k, ex, *W(0, k, ex))
+    for g in range(n_kv):
+        st.load_kv(0, g, K[g], V[g])
+    xin = torch.from_numpy(x).to(st.device)
+    xout = torch.zeros_like(xin)
+    st.set_context(ctx0)
+    st.forward(xin, xout)
+    st.synchronize()
+    got = xout.cpu().numpy()
+    st.close()
+    assert np.isfinite(got).all() and all(Hn.rel_err(got, r) <= TOL for r in refs)
+
+
 def test_chunked_prefill_fills_the_cache_it_then_decodes_over():
     """150 prompt tokens through a 64-token tier of a stack with a KV cache (three trips, each attending
     over the cache and the rows the earlier trips appended), then decode steps over the filled cache.
