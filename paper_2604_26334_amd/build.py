@@ -85,11 +85,12 @@ def check_resource_usage(remarks):
         raise RuntimeError("build check: h2d_gather_kernel allocates %s B of LDS, not the CU's 163840" % gather_lds)
 
 
-def gemm_wait_counts(mt, nw, at=2):
-    """(loads per prefetch, LDS fills among them, counted wait of a steady step) of gemm_w4_kernel<.., at, mt, .., nw>."""
-    nfill = mt // (4 * nw)
+def gemm_wait_counts(mt, nw, at=2, ks=1):
+    """(loads per prefetch, LDS fills among them, counted wait of a steady step) of gemm_w4_kernel<.., at, mt, .., nw, ks>."""
+    nwr = nw // ks
+    nfill = mt // (4 * nwr)
     lpi = nfill + at
-    depth = 3 if nw == 8 else (2 if mt <= 64 else 1)
+    depth = (3 if mt <= 128 else 2 if mt <= 160 else 1) if nwr == 8 else (2 if mt <= 64 else 1)
     early = depth >= 3
     land = depth - 2 if early else depth - 1
     return lpi, nfill, land * lpi + (at if early else 0)
@@ -103,12 +104,12 @@ def check_gemm_isa(path):
         raise RuntimeError("build check: no gemm_w4_kernel in " + path)
     bad = []
     for mangled, body in funcs:
-        m = re.match(r"_ZN2ps14gemm_w4_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)EEE", mangled)
+        m = re.match(r"_ZN2ps14gemm_w4_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)ELi(\d+)EEE", mangled)
         if not m:
             bad.append(mangled + ": unexpected template arguments")
             continue
-        at, mt, nw = int(m.group(2)), int(m.group(3)), int(m.group(5))
-        lpi, nfill, in_flight = gemm_wait_counts(mt, nw, at)
+        at, mt, nw, ks = int(m.group(2)), int(m.group(3)), int(m.group(5)), int(m.group(6))
+        lpi, nfill, in_flight = gemm_wait_counts(mt, nw, at, ks)
         segs, cur = [], []
         for ln in body.splitlines():
             f = ln.split()

@@ -1426,18 +1426,26 @@ __device__ __forceinline__ uint32_t lds_col(uint32_t u) { return ((u & 3) << 2) 
 
 // super-blocks of lookahead of the GEMM's prefetch ring (see the kernel): 2 for the few-token tiles;
 // the 8-wave workgroup (one per CU, its activation stages shared by twice the row-tiles) has the
-// LDS for 3
-constexpr int gemm_depth(int MT, int NW = 4) { return NW == 8 ? 3 : MT <= 64 ? 2 : 1; }
-// LDS of a workgroup: the activation stages, then per wave two scale buffers of 1 KB per row-tile
-constexpr size_t gemm_lds_bytes(int MT, int AT, int NW) { return (size_t)MT * 256 * (gemm_depth(MT, NW) + 1) + (size_t)NW * 2 * AT * 1024; }
+// LDS for 3, at 160 tokens for 2
+constexpr int gemm_depth(int MT, int NW = 4, int KS = 1) { return NW / KS == 8 ? (MT <= 128 ? 3 : MT <= 160 ? 2 : 1) : MT <= 64 ? 2 : 1; }
+// LDS of a workgroup: the activation stages (of each K part), then per wave two scale buffers of 1 KB per row-tile
+constexpr size_t gemm_lds_bytes(int MT, int AT, int NW, int KS = 1) {
+    return (size_t)KS * MT * 256 * (gemm_depth(MT, NW, KS) + 1) + (size_t)NW * 2 * AT * 1024;
+}
 
-template <int MODE, int AT, int MT, bool GROUPED, int NW = 4>
+// KS: K parts inside the workgroup.  With 2, waves 0 .. NW / 2 - 1 multiply the first half of the super-blocks and
+// the others, on the same rows and tokens, the second half, each half with activation stages of its own; the
+// second half's accumulators then pass through LDS and are added to the first's.
+template <int MODE, int AT, int MT, bool GROUPED, int NW = 4, int KS = 1>
 __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmArgs a) {
-    extern __shared__ uint4 lds[];                 // gemm_depth(MT, NW) + 1 stages of MT x 16 chunks, then 2 AT KB of scales per wave
+    extern __shared__ uint4 lds[];                 // KS x (gemm_depth + 1) stages of MT x 16 chunks, then 2 AT KB of scales per wave
     constexpr int NMT = MT / 16;
-    constexpr int NFILL = MT / (4 * NW);           // 16-byte chunks each thread moves per stage
-    static_assert(MT % (4 * NW) == 0, "a fill round covers 4 * NW tokens");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int NWR = NW / KS;                   // waves of one K part: each owns AT row-tiles
+    constexpr int NFILL = MT / (4 * NWR);          // 16-byte chunks each thread moves per stage
+    static_assert(MT % (4 * NWR) == 0, "a fill round covers 4 * NWR tokens");
+    static_assert(KS == 1 || (KS == 2 && !GROUPED && NW == 8), "two K parts: one workgroup of eight waves");
+    const int kpart = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / (NWR * 64));
+    const int tid = KS == 1 ? threadIdx.x : threadIdx.x % (NWR * 64), lane = tid & 63, wave = tid >> 6;   // within the K part
     const int i = lane & 15, c = lane >> 4;
 
     const uint4 *W = a.W;
@@ -1451,21 +1459,25 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     }
     const uint32_t m0 = blockIdx.y * MT;
     if (m0 >= ntok) return;
-    const uint32_t tile_base = (blockIdx.x * NW + wave) * AT;
 
     // activation fill, global memory straight into LDS (buffer_load ... lds): round r of a wave
     // writes 64 consecutive 16-byte slots, i.e. thread tid fills slot tid & 15 of token
-    // tok0 + 4 NW r, tok0 = tid >> 4, and therefore fetches the chunk that belongs there,
+    // tok0 + 4 NWR r, tok0 = tid >> 4, and therefore fetches the chunk that belongs there,
     // u = lds_col(slot ^ (tok0 & 15)) (lds_col is its own inverse).
     // xoff: byte offset of that chunk in the token's row (grouped launches look the row up);
     // tokens past the end re-read the last valid row: their MFMA columns are never stored, and the
     // fill needs neither a branch nor zeros.  Addresses are a uniform base plus these 32-bit
     // offsets, so the loop does no 64-bit vector arithmetic.
     const uint32_t tok0 = tid >> 4, u = lds_col((tid & 15) ^ (tok0 & 15));
-    uint32_t xoff[NFILL];
+    // (the many-token tiles work the offsets out again at every fill, from the first round's and the last row's: their
+    // accumulators leave no registers for one offset per round)
+    constexpr bool XCALC = !GROUPED && MT > 160;
+    uint32_t xoff[XCALC ? 1 : NFILL];
+    const uint32_t xstep = 4 * NWR * a.x_stride * (uint32_t)sizeof(__half);
+    const uint32_t xlast = ((ntok - 1) * a.x_stride + u * 8) * (uint32_t)sizeof(__half);
 #pragma unroll
-    for (int r = 0; r < NFILL; ++r) {
-        const uint32_t tok = min(m0 + tok0 + r * (4 * NW), ntok - 1);
+    for (int r = 0; r < (XCALC ? 1 : NFILL); ++r) {
+        const uint32_t tok = min(m0 + tok0 + r * (4 * NWR), ntok - 1);
         size_t rowi = tok;
         if (GROUPED) rowi = (MODE == GEMM_GATE_UP) ? (size_t)(pairs[tok] / (int32_t)a.top_k) : (size_t)pairs[tok];
         xoff[r] = (uint32_t)((rowi * a.x_stride + u * 8) * sizeof(__half));
@@ -1476,8 +1488,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     uint32_t woff[AT];
 #pragma unroll
     for (int t = 0; t < AT; ++t) {
-        const uint32_t tile = tile_base + t < a.ntiles ? tile_base + t : 0;
-        woff[t] = (tile * a.tile_u4 + lane) * 16u;
+        const uint32_t tile = (blockIdx.x * NWR + wave_u) * AT + t;
+        woff[t] = ((tile < a.ntiles ? tile : 0) * a.tile_u4 + lane) * 16u;
     }
     // buffer addressing: uniform part of an address in a scalar offset, lane part in xoff / woff
     const __amdgpu_buffer_rsrc_t xbuf = make_rsrc(a.x), wbuf = make_rsrc(W);
@@ -1491,7 +1503,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     // Prefetch ring: DEPTH super-blocks are in flight ahead of the one being multiplied, in R =
     // DEPTH + 1 weight register sets and LDS stages.  With few tokens an iteration is shorter than
     // the memory latency, so one super-block of lookahead leaves the loop waiting on its loads.
-    constexpr int DEPTH = gemm_depth(MT, NW), R = DEPTH + 1;
+    constexpr int DEPTH = gemm_depth(MT, NW, KS), R = DEPTH + 1;
     static_assert(AT <= 2, "the dequantisation is pipelined one MFMA step ahead; more tiles per wave do not fit the registers");
     constexpr int LPI = NFILL + AT;              // loads every prefetch issues per lane (scale fills, when it has them: AT more)
     // one super-block of weights of the wave's tiles: the lane's 16 code bytes
@@ -1505,13 +1517,14 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     // activation fills had pushed them out of the vector cache: a timing probe without scale loads
     // ran the 64-token gate/up launch 14 % faster.)  Like the activation fills these loads are not
     // register writes the compiler could wait for; the counted waits below cover them.
-    uint4 *const sc_lds = lds + R * (MT * 16) + __builtin_amdgcn_readfirstlane(wave) * (2 * AT * 64);
+    uint4 *const xs_lds = lds + kpart * (R * MT * 16);      // this K part's activation stages
+    uint4 *const sc_lds = lds + KS * (R * MT * 16) + (kpart * NWR + wave_u) * (2 * AT * 64);
     auto fill_x = [&](uint32_t sb, uint32_t stage) {
         // (wave-uniform; said so explicitly, or the fill's scalar offset is taken in a lane loop)
         const uint32_t xs = __builtin_amdgcn_readfirstlane(gather_col(sb * 128, a.x_off, a.x_group) * (uint32_t)sizeof(__half));
 #pragma unroll
         for (int r = 0; r < NFILL; ++r)
-            load_to_lds16(xbuf, (lds_void *)(lds + stage * (MT * 16) + r * (NW * 64) + wave_u * 64), xoff[r], xs);
+            load_to_lds16(xbuf, (lds_void *)(xs_lds + stage * (MT * 16) + r * (NWR * 64) + wave_u * 64), XCALC ? min(xoff[0] + r * xstep, xlast) : xoff[XCALC ? 0 : r], xs);
     };
 
     // scale group / slot of super-block sb, clamped to the last one (a prefetch past the end
@@ -1548,17 +1561,18 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
         }
     };
     // A operands of MFMA step kk from raw dwords + scale: (q - 8) * d rounded to fp16
+    auto dequant_t = [&](const Wset &ws, int kk, int t) -> h8_t {
+        const uint32_t q = kk == 0 ? ws.q[t].x : kk == 1 ? ws.q[t].y : kk == 2 ? ws.q[t].z : ws.q[t].w;
+        const _Float16 d = __builtin_bit_cast(_Float16, (uint16_t)dsc[t]);
+        const h2_t dd = {d, d};
+        h2_t w[4];
+        dequant8(q, w);
+        w[0] *= dd; w[1] *= dd; w[2] *= dd; w[3] *= dd;
+        return h8_t{w[0].x, w[0].y, w[1].x, w[1].y, w[2].x, w[2].y, w[3].x, w[3].y};
+    };
     auto dequant_a = [&](h8_t (&A)[AT], const Wset &ws, int kk) {
 #pragma unroll
-        for (int t = 0; t < AT; ++t) {
-            const uint32_t q = kk == 0 ? ws.q[t].x : kk == 1 ? ws.q[t].y : kk == 2 ? ws.q[t].z : ws.q[t].w;
-            const _Float16 d = __builtin_bit_cast(_Float16, (uint16_t)dsc[t]);
-            const h2_t dd = {d, d};
-            h2_t w[4];
-            dequant8(q, w);
-            w[0] *= dd; w[1] *= dd; w[2] *= dd; w[3] *= dd;
-            A[t] = h8_t{w[0].x, w[0].y, w[1].x, w[1].y, w[2].x, w[2].y, w[3].x, w[3].y};
-        }
+        for (int t = 0; t < AT; ++t) A[t] = dequant_t(ws, kk, t);
     };
 
     // One prefetch = the stage's NFILL LDS fills, THEN the 2 AT weight loads, in that order in the
@@ -1587,6 +1601,10 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
         sb_begin = blockIdx.z * a.sb_per_part;
         sb_end = min(a.nsb, sb_begin + a.sb_per_part);
     }
+    if (KS == 2) {   // (an even number of super-blocks: both halves take the same number of steps and barriers)
+        sb_begin = kpart * (a.nsb / 2);
+        sb_end = sb_begin + a.nsb / 2;
+    }
     prefetch(sb_begin, 0, sb_begin, wr[0], std::true_type{});
 #pragma unroll
     for (int d = 1; d < DEPTH; ++d) prefetch(min(sb_begin + d, sb_end - 1), d, sb_begin + d, wr[d], std::false_type{});
@@ -1614,10 +1632,12 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     __builtin_amdgcn_s_barrier();
     scales_of(sb_begin);
     dequant_a(Acur, wr[0], 0);
+    // RING: tiles whose operands of a whole MFMA step do not fit the registers twice beside the accumulators
+    constexpr bool RING = MT > 160;
     h8_t Bc[NMT], Bn[NMT];
     if (EARLY) {
 #pragma unroll
-        for (int n = 0; n < NMT; ++n) Bc[n] = __builtin_bit_cast(h8_t, lds[i * 16 + n * 256 + (c ^ i)]);
+        for (int n = 0; n < NMT; ++n) Bc[n] = __builtin_bit_cast(h8_t, xs_lds[i * 16 + n * 256 + (c ^ i)]);
     }
 
     // one super-block: U = its position in the ring (compile-time, so every register set and LDS
@@ -1632,8 +1652,40 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
         // barrier that ended the previous step, weights into the register set used then
         if (!tail) prefetch(min(sb + DEPTH, sb_end - 1), up, sb + DEPTH, wr[up], std::false_type{});
         __builtin_amdgcn_sched_barrier(0);   // keep the prefetch up here: its latency hides behind the MFMAs
-        const uint4 *ls = lds + u * (MT * 16) + i * 16;   // + n * 256: token n*16 + i
-        const uint4 *lsn = lds + un * (MT * 16) + i * 16;  // the next super-block's stage
+        const uint4 *ls = xs_lds + u * (MT * 16) + i * 16;   // + n * 256: token n*16 + i
+        const uint4 *lsn = xs_lds + un * (MT * 16) + i * 16;  // the next super-block's stage
+        if constexpr (RING) {
+            // the step's 4 NMT B operands in order (kk, token tile), in blocks of two through a ring of six: a block is
+            // read while the two before it are multiplied.  The A operands of kk + 1 are dequantised, one row-tile
+            // per block, in the first blocks of kk.
+            constexpr int NF = 4 * NMT, NR = 6;
+            h8_t Bb[NR], Ab[2][AT];
+            auto read_b = [&](int f) { Bb[f % NR] = __builtin_bit_cast(h8_t, ls[(f % NMT) * 256 + ((c + (f / NMT) * 4) ^ i)]); };
+#pragma unroll
+            for (int t = 0; t < AT; ++t) Ab[0][t] = Acur[t];
+#pragma unroll
+            for (int f = 0; f < NR - 2; ++f) read_b(f);
+#pragma unroll
+            for (int f0 = 0; f0 < NF; f0 += 2) {
+                if (f0 + NR - 2 < NF) { read_b(f0 + NR - 2); read_b(f0 + NR - 1); }
+                __builtin_amdgcn_sched_barrier(0);
+                const int kk = f0 / NMT, t = (f0 % NMT) / 2;     // NMT is even: a block lies in one MFMA step
+                if (t < AT) {
+                    if (kk < 3) Ab[(kk + 1) & 1][t] = dequant_t(wr[u], kk + 1, t);
+                    else {
+                        if (t == 0) { arrive_w(wr[un]); scales_of(sb + 1); }
+                        Ab[(kk + 1) & 1][t] = dequant_t(wr[un], 0, t);
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int t2 = 0; t2 < AT; ++t2)
+                        acc[t2][f0 % NMT + e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ab[kk & 1][t2], Bb[(f0 + e) % NR], acc[t2][f0 % NMT + e], 0, 0, 0);
+            }
+#pragma unroll
+            for (int t = 0; t < AT; ++t) Acur[t] = Ab[0][t];
+        } else {
         // B operands are read one MFMA step ahead, so the LDS latency hides behind a step's MFMAs
         if (!EARLY) {
 #pragma unroll
@@ -1669,6 +1721,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
                 for (int n = 0; n < NMT; ++n) Bc[n] = Bn[n];
             }
         }
+        }
         // super-block sb + 1's activations have landed once all but the later prefetches are done.
         // A bare barrier: __syncthreads() carries a fence that makes the compiler wait for EVERY
         // LDS-direct load in flight, i.e. also for the deeper prefetches.  What must be ordered
@@ -1695,8 +1748,27 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
         if (sb + 2 < sb_end) step(sb + 2, std::integral_constant<int, 2>{}, std::true_type{});
     }
 
+    if constexpr (KS == 2) {   // first half + second half (the last step's barrier is behind every wave: the stages are free)
+        f4_t *const xch = reinterpret_cast<f4_t *>(lds) + (size_t)wave_u * (AT * NMT * 64) + lane;
+        if (kpart == 1) {
+#pragma unroll
+            for (int t = 0; t < AT; ++t)
+#pragma unroll
+                for (int n = 0; n < NMT; ++n) xch[(t * NMT + n) * 64] = acc[t][n];
+        }
+        __syncthreads();
+        if (kpart == 1) return;
+#pragma unroll
+        for (int t = 0; t < AT; ++t)
+#pragma unroll
+            for (int n = 0; n < NMT; ++n) acc[t][n] += xch[(t * NMT + n) * 64];
+    }
+
     // epilogue: lane holds token j = lane & 15 of each token tile and rows 4*(lane >> 4) + r
-    const int j = lane & 15, rg = lane >> 4;
+    // (the lane and the wave's tiles are taken from scratch: nothing of them need live through the ring)
+    const int elane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const int j = elane & 15, rg = elane >> 4;
+    const uint32_t tile_base = (blockIdx.x * NWR + wave_u) * AT;
 #pragma unroll
     for (int n = 0; n < NMT; ++n) {
         const uint32_t tok = m0 + n * 16 + j;
@@ -1750,59 +1822,91 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     }
 }
 
-template <int MODE, int AT, int MT>
-static hipError_t launch_gemm_t(const GemmArgs &a, uint32_t ntasks, uint32_t max_tok, hipStream_t st) {
-    const uint32_t parts = (!ntasks && a.sb_per_part) ? (a.nsb + a.sb_per_part - 1) / a.sb_per_part : 1;
-    if constexpr (MT == 128) {
-        // Many-token launches of a whole matrix or slab: 8 waves per workgroup, one workgroup per CU.
-        // Its activation stages serve twice the row-tiles, which leaves LDS for three super-blocks of
-        // lookahead instead of one (measured: gate/up and down +10 %, O +6 %).  Both shapes multiply
-        // in the same order, so the choice never changes a result; it goes by how evenly each
-        // shape's workgroups fill the 256 CUs (a 6144-row QKV fills 1.5 rounds either way and runs
-        // 8 % slower in the wide shape).
-        const uint32_t ty = (max_tok + MT - 1) / MT;
-        const uint32_t wg8 = (a.ntiles + 8 * AT - 1) / (8 * AT) * ty, wg4 = (a.ntiles + 4 * AT - 1) / (4 * AT) * ty;
-        const double eff8 = (double)wg8 / ((wg8 + 255) / 256 * 256), eff4 = (double)wg4 / ((wg4 + 511) / 512 * 512);
-        if (!ntasks && parts == 1 && (eff8 >= 0.9 || eff8 > eff4 + 0.05)) {
-            dim3 grid8((a.ntiles + 8 * AT - 1) / (8 * AT), ty, 1);
-            const size_t lds8 = gemm_lds_bytes(MT, AT, 8);
-            static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_w4_kernel<MODE, AT, MT, false, 8>),
-                                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds8);
-            if (attr != hipSuccess) return attr;
-            hipLaunchKernelGGL((gemm_w4_kernel<MODE, AT, MT, false, 8>), grid8, dim3(512), lds8, st, a);
-            return hipGetLastError();
-        }
+template <int MODE, int AT, int MT, bool GROUPED, int NW, int KS>
+static hipError_t launch_gemm_k(const GemmArgs &a, uint32_t ntok, uint32_t gz, hipStream_t st) {
+    constexpr size_t ldsb = gemm_lds_bytes(MT, AT, NW, KS);
+    static_assert(ldsb <= 160 * 1024, "LDS of a CU");
+    if (ldsb > 64 * 1024) {
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_w4_kernel<MODE, AT, MT, GROUPED, NW, KS>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsb);
+        if (attr != hipSuccess) return attr;
     }
-    dim3 grid((a.ntiles + 4 * AT - 1) / (4 * AT), (max_tok + MT - 1) / MT, ntasks ? ntasks : parts);
-    const size_t lds = gemm_lds_bytes(MT, AT, 4);
-    if (lds > 64 * 1024) {
-        static const hipError_t attr_g = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_w4_kernel<MODE, AT, MT, true>),
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        static const hipError_t attr_u = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_w4_kernel<MODE, AT, MT, false>),
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (attr_g != hipSuccess) return attr_g;
-        if (attr_u != hipSuccess) return attr_u;
-    }
-    if (ntasks) hipLaunchKernelGGL((gemm_w4_kernel<MODE, AT, MT, true>), grid, dim3(256), lds, st, a);
-    else hipLaunchKernelGGL((gemm_w4_kernel<MODE, AT, MT, false>), grid, dim3(256), lds, st, a);
+    constexpr uint32_t rows = NW / KS * AT;   // row-tiles of a workgroup
+    dim3 grid((a.ntiles + rows - 1) / rows, (ntok + MT - 1) / MT, gz);
+    hipLaunchKernelGGL((gemm_w4_kernel<MODE, AT, MT, GROUPED, NW, KS>), grid, dim3(NW * 64), ldsb, st, a);
     return hipGetLastError();
+}
+
+// Two K parts inside the workgroup: for matrices whose 128-row x 64-token workgroups at the plan's token count leave at
+// most one per CU.  Four waves of them are one wave per SIMD, which waits for its own operand reads and
+// dequantisation; the second half of K on four more waves halves the steps (in one round of workgroups, 128 tokens: QKV
+// 25.6 -> 17.7 us, O 25.7 -> 17.1, down 73.6 -> 45.5; 512 tokens: O 28.8 -> 25.5, down 85.8 -> 71.9, but QKV, 1.5
+// workgroups per CU, 39.4 -> 44.7).
+static bool gemm_two_k_parts(const GemmArgs &a, uint32_t plan_tokens) {
+    return a.nsb % 2 == 0 && (a.total_tiles + 7) / 8 * ((plan_tokens + 63) / 64) <= 256;
+}
+
+// Token tile of an unsplit launch of a.M rows: the one with the smallest product of rounds of workgroups (one
+// eight-wave workgroup of 256 rows per CU, two four-wave ones of 128) and time per round.  A round costs a fixed
+// part (a barrier, the first operand reads and the fills of every step) plus a part per token, so a large tile is
+// cheap per token and few, full rounds matter most.  Measured on 4096-wide rows, us per round: 8 waves x 96 tokens 43,
+// 128: 54, 160: 62, 192: 69, 224: 78, 256: 89; 4 waves x 64 tokens 26 alone on a CU, 43 with two.
+// Gate/up, 28672 rows, against the former 128-token tile: 300 tokens 111 -> 74 us (160), 512: 122 -> 105 (256),
+// 1024: 242 -> 209 (256), 1536: 380 -> 318 (256), 2048: 517 -> 417 (192); QKV, 6144 rows, 2048: 142 -> 99 (224).
+static uint32_t gemm_pick_tile(const GemmArgs &a, uint32_t widest) {
+    const uint32_t g4 = (a.ntiles + 7) / 8, g8 = (a.ntiles + 15) / 16;
+    uint32_t best = 0, best_cost = 0xFFFFFFFFu;
+    for (uint32_t mt : {16u, 32u, 64u}) {
+        if (mt < 64 && a.M > mt) continue;
+        const uint32_t wg = g4 * ((a.M + mt - 1) / mt), one = mt == 64 ? 260 : mt == 32 ? 200 : 180, rest = wg % 512;
+        const uint32_t cost = wg / 512 * (one * 5 / 3) + (rest == 0 ? 0 : rest <= 256 ? one : one * 5 / 3);
+        if (cost < best_cost) { best_cost = cost; best = mt; }
+    }
+    for (uint32_t mt = 96; mt <= widest; mt += 32) {
+        const uint32_t wg = g8 * ((a.M + mt - 1) / mt);
+        const uint32_t cost = (wg + 255) / 256 * (185 + mt * 27 / 10);   // tenths of a microsecond
+        if (cost < best_cost) { best_cost = cost; best = mt; }
+    }
+    return best;
 }
 
 template <int MODE>
 static hipError_t launch_gemm_m(const GemmArgs &a, uint32_t ntasks, uint32_t max_tok, hipStream_t st) {
-    if (max_tok <= 16) return launch_gemm_t<MODE, 2, 16>(a, ntasks, max_tok, st);
-    if (max_tok <= 32) return launch_gemm_t<MODE, 2, 32>(a, ntasks, max_tok, st);
-    if (max_tok <= 64) return launch_gemm_t<MODE, 2, 64>(a, ntasks, max_tok, st);
-    // A few hundred tokens on a narrow matrix (O and down at 512 tokens: 32 eight-tile workgroups x 4 token
-    // tiles) leave half the CUs without a workgroup in 128-token tiles: 64-token tiles double the workgroups.
-    // The tile shape goes by the whole matrix and the plan's token count, never by the slab, and every shape
-    // adds a row's super-blocks in the same order, so the choice does not change a bit of the result.
-    // (measured on the 8B shapes over a 4K cache, per layer: 256 tokens 387 -> 296 us, 512 tokens 462 -> 409 us,
-    // 1024 tokens 714 -> 697 us; from 1.5 workgroups per CU on, the 128-token tile is the faster one)
-    if (!ntasks && (a.total_tiles + 7) / 8 * ((max_tok + 127) / 128) < 384) return launch_gemm_t<MODE, 2, 64>(a, ntasks, max_tok, st);
-    // 2 row-tiles per wave leave room for the pipelined dequant at two workgroups per CU; the
-    // 4-tile shape (half the LDS operand traffic) does not fit that register budget
-    return launch_gemm_t<MODE, 2, 128>(a, ntasks, max_tok, st);
+    if (ntasks) {   // grouped: one expert per blockIdx.z
+        if (max_tok <= 16) return launch_gemm_k<MODE, 2, 16, true, 4, 1>(a, max_tok, ntasks, st);
+        if (max_tok <= 32) return launch_gemm_k<MODE, 2, 32, true, 4, 1>(a, max_tok, ntasks, st);
+        if (max_tok <= 64) return launch_gemm_k<MODE, 2, 64, true, 4, 1>(a, max_tok, ntasks, st);
+        return launch_gemm_k<MODE, 2, 128, true, 4, 1>(a, max_tok, ntasks, st);
+    }
+    const uint32_t parts = a.sb_per_part ? (a.nsb + a.sb_per_part - 1) / a.sb_per_part : 1;
+    if (max_tok <= 16) return launch_gemm_k<MODE, 2, 16, false, 4, 1>(a, max_tok, parts, st);
+    if (max_tok <= 32) return launch_gemm_k<MODE, 2, 32, false, 4, 1>(a, max_tok, parts, st);
+    if (max_tok <= 64) return launch_gemm_k<MODE, 2, 64, false, 4, 1>(a, max_tok, parts, st);
+    if constexpr (MODE == GEMM_F32) return hipErrorInvalidValue;   // partial planes: at most 64 tokens
+    else {
+        // Plans of more than 64 tokens.  The tile goes by the rows that are there (a.M) and never changes a bit of the
+        // result; the K parts do, so they go by the whole matrix and the plan's token count.
+        if (gemm_two_k_parts(a, max_tok)) {
+            // the smallest tile that still leaves at most one workgroup per CU: 4096 x 4096 at 200 tokens 16.9 us in
+            // 32-token tiles, 19.1 in 48, 21.6 in 64; at 384 tokens (1.5 workgroups per CU in 32) 27.9 / 23.3 / 25.7
+            const uint32_t groups = (a.ntiles + 7) / 8;
+            if (groups * ((a.M + 31) / 32) <= 256) return launch_gemm_k<MODE, 2, 32, false, 8, 2>(a, a.M, 1, st);
+            if (groups * ((a.M + 47) / 48) <= 256) return launch_gemm_k<MODE, 2, 48, false, 8, 2>(a, a.M, 1, st);
+            return launch_gemm_k<MODE, 2, 64, false, 8, 2>(a, a.M, 1, st);
+        }
+        switch (gemm_pick_tile(a, MODE == GEMM_GATE_UP ? 256 : 224)) {   // (256 tokens spill in the other modes)
+            case 16: return launch_gemm_k<MODE, 2, 16, false, 4, 1>(a, a.M, 1, st);
+            case 32: return launch_gemm_k<MODE, 2, 32, false, 4, 1>(a, a.M, 1, st);
+            case 64: return launch_gemm_k<MODE, 2, 64, false, 4, 1>(a, a.M, 1, st);
+            case 96: return launch_gemm_k<MODE, 2, 96, false, 8, 1>(a, a.M, 1, st);
+            case 128: return launch_gemm_k<MODE, 2, 128, false, 8, 1>(a, a.M, 1, st);
+            case 160: return launch_gemm_k<MODE, 2, 160, false, 8, 1>(a, a.M, 1, st);
+            case 192: return launch_gemm_k<MODE, 2, 192, false, 8, 1>(a, a.M, 1, st);
+            case 224: return launch_gemm_k<MODE, 2, 224, false, 8, 1>(a, a.M, 1, st);
+        }
+        if constexpr (MODE == GEMM_GATE_UP) return launch_gemm_k<MODE, 2, 256, false, 8, 1>(a, a.M, 1, st);
+        return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_gemm(int mode, const GemmArgs &a, uint32_t ntasks, uint32_t max_tok, hipStream_t st) {

@@ -459,6 +459,38 @@ def test_one_stack_serves_the_prefill_tier_and_the_decode_tier(kind):
     st.close()
 
 
+@pytest.mark.parametrize("H,I,plan_tokens,counts", [(256, 7168, 1024, (1024, 770, 560, 400, 300, 161, 65, 20, 1)),
+                                                    (640, 7168, 512, (512, 257, 97)),
+                                                    (2048, 1280, 1024, (1024, 700, 500, 33)),
+                                                    (1152, 1408, 320, (320, 129))])
+def test_gemm_tiles_of_every_width_give_the_same_rows(H, I, plan_tokens, counts):
+    """Plans of more than 64 tokens: the token tile (16 to 256) goes by the rows of the trip, the K parts inside a
+    workgroup by the matrix and the plan.  The full trip against the oracle; every shorter one must give the same
+    bits for its rows.  K of 2, 5, 8, 9, 10, 11, 16 and 56 super-blocks (shorter and longer than the prefetch ring)."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(S.cfg_ffn_block(), hidden=H, ffn_inter=I)
+    W = Hn.WeightCache(cfg, 61)
+    x = S.activations(61, 0, plan_tokens, H)
+    st = B.Stack(B.Plan(cfg, 1 << 30, plan_tokens))
+    for k, ex, N, K in S.matrix_shapes(cfg):
+        st.load_matrix(0, k, ex, *W(0, k, ex))
+    xin = torch.from_numpy(x).to(st.device)
+    full = None
+    for n in counts:
+        xout = torch.full_like(xin, 7.0)
+        B.chunked_forward(st, xin[:n], xout[:n])
+        st.synchronize()
+        got = xout.cpu().numpy()
+        assert (got[n:] == 7.0).all()                # rows past the trip are not written
+        if full is None:
+            full = got
+            for mirror in (True, False):
+                assert Hn.rel_err(got, O.stack_forward(x, cfg, W, mirror=mirror)) <= TOL
+        np.testing.assert_array_equal(got[:n].view(np.uint16), full[:n].view(np.uint16))
+    st.close()
+
+
 def _kv_cfg(n_layers, cap):
     return dict(Hn.small_dense_cfg(n_layers), kv_context=cap)
 
