@@ -104,11 +104,11 @@ def check_gemm_isa(path):
         raise RuntimeError("build check: no gemm_w4_kernel in " + path)
     bad = []
     for mangled, body in funcs:
-        m = re.match(r"_ZN2ps14gemm_w4_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)ELi(\d+)EEE", mangled)
+        m = re.match(r"_ZN2ps14gemm_w4_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)(?:ELi(\d+))?EEE", mangled)
         if not m:
             bad.append(mangled + ": unexpected template arguments")
             continue
-        at, mt, nw, ks = int(m.group(2)), int(m.group(3)), int(m.group(5)), int(m.group(6))
+        at, mt, nw, ks = int(m.group(2)), int(m.group(3)), int(m.group(5)), int(m.group(6) or 1)
         lpi, nfill, in_flight = gemm_wait_counts(mt, nw, at, ks)
         segs, cur = [], []
         for ln in body.splitlines():
