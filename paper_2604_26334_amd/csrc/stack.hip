@@ -592,6 +592,10 @@ static bool graph_eligible(const ps_plan &p) {
     return !p.g.moe && p.n_slots == 0 && p.cpu_bytes == 0 && (p.M == 1 || (p.M <= 64 && !p.g.kv));
 }
 
+bool has_copies(const ps_schedule &sc) {
+    return std::any_of(sc.ops.begin(), sc.ops.end(), [](const Op &op) { return op.info.type == PS_OP_COPY; });
+}
+
 // True when the copy op at index i opens the only slot fill of its layer (the schedule lists a layer's
 // expert copies between its routing kernel and the next layer's ops; a fill ends at its ready record).
 bool only_fill_of_layer(const ps_schedule &sc, size_t i) {
@@ -664,6 +668,7 @@ int32_t run_schedule(ps_stack *st, const ps_schedule &sc, const __half *x_in, __
             if (!skip_head_op(st, op)) { ss.resident_bytes_step += op.info.bytes; ss.n_kernels++; }
         return PS_OK;
     }
+    const bool copies = has_copies(sc);   // nothing waits for a router event in a schedule without copies
     for (size_t i = 0; i < sc.ops.size(); ++i) {
         const Op &op = sc.ops[i];
         const ps_op_info &o = op.info;
@@ -747,7 +752,7 @@ int32_t run_schedule(ps_stack *st, const ps_schedule &sc, const __half *x_in, __
             if (rc) return rc;
             if (prof) PS_HIP(hipEventRecord(st->prof_ev[2 * i + 1], st->compute));
             if (o.flags & PS_OPF_RECORD_FREE) PS_HIP(hipEventRecord(st->ev_free[o.slot], st->compute));
-            if (o.flags & PS_OPF_RECORD_ROUTER) PS_HIP(hipEventRecord(st->ev_router[o.layer], st->compute));
+            if ((o.flags & PS_OPF_RECORD_ROUTER) && copies) PS_HIP(hipEventRecord(st->ev_router[o.layer], st->compute));
             if (o.type == PS_OP_KERNEL) {
                 if (o.slot < 0) ss.resident_bytes_step += o.bytes;
                 ss.n_kernels++;
@@ -801,6 +806,10 @@ uint64_t shard_tile_bytes(const ps::ModelGeom &g, uint32_t kind) {
     return 0;
 }
 
+// The MoE tables of one forward (logits | tasks | pairs) as they lie in the workspace; the pinned staging buffer has
+// the same layout, so whatever a forward fills goes up in one copy
+uint64_t moe_tables_bytes(const ps::Workspace &ws) { return ps::align_up(ws.pairs + ws.pairs_bytes - ws.logits, 256); }
+
 // Everything a stack derives from its current plan (Algorithm 1, SetupForSched): where the workspace
 // lies, where each shard's host copy is, which shards cover which matrix, the dense schedule.
 int32_t bind_plan(ps_stack *st) {
@@ -820,7 +829,7 @@ int32_t bind_plan(ps_stack *st) {
         }
     }
     if (p.g.moe) {
-        st->descs_off = ps::align_up(p.ws.logits_bytes + p.ws.tasks_bytes + p.ws.pairs_bytes, 256);
+        st->descs_off = moe_tables_bytes(p.ws);
     } else {
         st->dense_sched = ps_schedule();
         int32_t rc = ps::build_schedule(&st->plan, nullptr, &st->dense_sched);
@@ -975,7 +984,7 @@ int32_t stack_create_impl(const std::vector<const ps_plan *> &plans, bool multi,
             if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) { ps::set_error("hipEventCreate failed"); return fail(PS_E_HIP); }
         for (const ps_plan *q : plans) {   // room for the largest tier's tables
             if (!q) continue;
-            const uint64_t d = ps::align_up(q->ws.logits_bytes + q->ws.tasks_bytes + q->ws.pairs_bytes, 256);
+            const uint64_t d = moe_tables_bytes(q->ws);
             st->tables_bytes = std::max(st->tables_bytes, d + (q->ws.tasks_bytes / sizeof(ps::DeviceTask)) * sizeof(ps::CopyDesc));
         }
         for (int b = 0; b < 2; ++b) {
@@ -1346,7 +1355,8 @@ static int32_t forward_impl(ps_stack *st, const void *x_in, void *x_out, const f
     if (st->upload_pending[tb]) { PS_HIP(hipEventSynchronize(st->ev_upload[tb])); st->upload_pending[tb] = false; }
     st->n_descs = 0;
     uint8_t *th = static_cast<uint8_t *>(st->tables_host[tb]);
-    ps::DeviceTask *dt = reinterpret_cast<ps::DeviceTask *>(th + p.ws.logits_bytes);
+    const uint64_t tasks_at = p.ws.tasks - p.ws.logits, pairs_at = p.ws.pairs - p.ws.logits;   // in the staging buffer as in the workspace
+    ps::DeviceTask *dt = reinterpret_cast<ps::DeviceTask *>(th + tasks_at);
     if (sc.tasks.size() * sizeof(ps::DeviceTask) > p.ws.tasks_bytes || sc.pairs.size() * 4 > p.ws.pairs_bytes) {
         ps::set_error("internal: routing tables exceed the workspace"); return PS_E_STATE;
     }
@@ -1359,27 +1369,29 @@ static int32_t forward_impl(ps_stack *st, const void *x_in, void *x_out, const f
         dt[t].w_down = (uint64_t)(uintptr_t)(w + p.g.gate_up.bytes);
         dt[t].pair0 = h.pair0; dt[t].npairs = h.npairs; dt[t].expert = h.expert; dt[t].pad = 0;
     }
-    std::memcpy(th + p.ws.logits_bytes + p.ws.tasks_bytes, sc.pairs.data(), sc.pairs.size() * 4);
-    if (logits_dev) {   // the routing kernel reads the caller's device copy in place: nothing to upload
+    std::memcpy(th + pairs_at, sc.pairs.data(), sc.pairs.size() * 4);
+    // one upload (every copy is a launch of its own on the compute stream): from the logits, or from the
+    // task table where the routing kernel reads the caller's device copy of the logits in place
+    uint64_t from = tasks_at;
+    if (logits_dev) {
         st->route_logits = logits_dev;
         st->route_layer_stride = layer_stride;
     } else {            // the workspace copy: [layer][M][E], the first n_valid rows of each layer filled
         float *lh = reinterpret_cast<float *>(th);
         for (uint32_t l = 0; l < L; ++l)
             std::memcpy(lh + (size_t)l * p.M * E, router_logits + (size_t)l * layer_stride, (size_t)n_valid * E * 4);
-        PS_HIP(hipMemcpyAsync(st->ws_base + p.ws.logits, th, p.ws.logits_bytes, hipMemcpyHostToDevice, st->compute));
+        from = 0;
         st->route_logits = reinterpret_cast<const float *>(st->ws_base + p.ws.logits);
         st->route_layer_stride = (uint64_t)p.M * E;
     }
-    if (!sc.tasks.empty())
-        PS_HIP(hipMemcpyAsync(st->ws_base + p.ws.tasks, dt, sc.tasks.size() * sizeof(ps::DeviceTask), hipMemcpyHostToDevice, st->compute));
-    if (!sc.pairs.empty())
-        PS_HIP(hipMemcpyAsync(st->ws_base + p.ws.pairs, th + p.ws.logits_bytes + p.ws.tasks_bytes, sc.pairs.size() * 4,
-                              hipMemcpyHostToDevice, st->compute));
+    // (whole 16-byte units; the tables' areas are padded to 256 bytes, in the staging buffer as in the workspace)
+    PS_HIP(launch_upload_tables(th + from, st->ws_base + p.ws.logits + from, ps::align_up(pairs_at + sc.pairs.size() * 4, 16) - from, st->compute));
     rc = run_schedule(st, sc, static_cast<const __half *>(x_in), static_cast<__half *>(x_out));
     // the buffer is free again once the uploads (compute stream) and the gathers (copy stream) are done
-    PS_HIP(hipStreamWaitEvent(st->compute, st->ev_ready[0], 0));
-    PS_HIP(hipStreamWaitEvent(st->compute, st->ev_ready[1], 0));
+    if (has_copies(sc)) {
+        PS_HIP(hipStreamWaitEvent(st->compute, st->ev_ready[0], 0));
+        PS_HIP(hipStreamWaitEvent(st->compute, st->ev_ready[1], 0));
+    }
     PS_HIP(hipEventRecord(st->ev_upload[tb], st->compute));
     st->upload_pending[tb] = true;
     return rc;

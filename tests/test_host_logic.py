@@ -296,6 +296,27 @@ def test_moe_schedule_copies_only_selected_nonresident_experts_after_routing():
             assert o.flags & B.PS_OPF_WAIT_ROUTER and o.layer in seen_route
 
 
+@pytest.mark.parametrize("E,k", [(1, 1), (15, 3), (16, 16), (17, 4), (128, 8), (130, 64), (1000, 9)])
+def test_route_host_on_ties_infinities_zeros_and_nans(E, k):
+    """The rule, one scan per pick: the largest logit left, the lowest index among equals (-0 equals +0), and a NaN only
+    where nothing lies before it.  Widths around the vector length, rows with few distinct values and with NaNs."""
+    g = np.random.default_rng(E * 100 + k)
+    rows = [g.standard_normal(E), g.integers(-2, 3, E), np.zeros(E), np.full(E, -np.inf), np.full(E, np.inf),
+            g.choice([0.0, -0.0, 1e-42, -1e-42], E), g.choice([-np.inf, np.inf, 3.0, -3.4028235e38, 3.4028235e38], E),
+            np.where(g.random(E) < 0.2, np.nan, g.standard_normal(E)), np.full(E, np.nan)]
+    lg = np.asarray(rows, dtype=np.float32)
+    idx = B.route_host(lg, k)
+    for m in range(lg.shape[0]):
+        taken = np.zeros(E, bool)
+        for j in range(k):
+            best = -1
+            for e in range(E):
+                if not taken[e] and (best < 0 or lg[m, e] > lg[m, best]):
+                    best = e
+            taken[best] = True
+            assert idx[m, j] == best, (m, j)
+
+
 def test_route_host_matches_sort_rule():
     lg = S.router_logits(5, 0, 1, 9, 128)[0]
     lg[0, :] = 0.0
