@@ -175,6 +175,19 @@ def test_small_moe(M):
     _check(cfg, 3, M, _budgets(cfg, M, [1.0, 0.6, 0.35]), logits=lg)
 
 
+@pytest.mark.parametrize("busiest", [16, 17, 33, 48, 49, 65, 96, 97, 129])
+def test_expert_gemm_tile_by_the_busiest_experts_tokens(busiest):
+    """Grouped expert launches take the smallest token tile (16, 32, 48, 64, 96, else 128) that holds the busiest
+    expert's tokens; the other experts hold fewer, down to one."""
+    cfg = Hn.small_moe_cfg(1)
+    E, M = cfg["n_experts"], busiest + 6
+    g = np.random.default_rng(busiest)
+    lg = g.standard_normal((1, M, E)).astype(np.float32)
+    lg[0, :, 0] = np.where(np.arange(M) < busiest, 50.0, -50.0)      # expert 0: exactly `busiest` tokens
+    lg[0, :, 1] = np.where(np.arange(M) == M - 1, 60.0, -60.0)       # expert 1: one token
+    _check(cfg, 71, M, _budgets(cfg, M, [1.0, 0.5]), logits=lg)
+
+
 @pytest.mark.parametrize("kind,M", [("dense", 1), ("dense", 4), ("dense", 37), ("moe", 1), ("moe", 5)])
 def test_copy_modes_move_the_same_bytes(kind, M):
     """Streamed shards cross PCIe by hipMemcpyAsync (mode 0), by the gather kernel where the library's rule
