@@ -475,10 +475,12 @@ def test_one_stack_serves_the_prefill_tier_and_the_decode_tier(kind):
 @pytest.mark.parametrize("H,I,plan_tokens,counts", [(256, 7168, 1024, (1024, 770, 560, 400, 300, 161, 65, 20, 1)),
                                                     (640, 7168, 512, (512, 257, 97)),
                                                     (2048, 1280, 1024, (1024, 700, 500, 33)),
-                                                    (1152, 1408, 320, (320, 129))])
+                                                    (1152, 1408, 320, (320, 129)),
+                                                    (256, 14336, 64, (64, 48, 33, 32, 17, 16, 5)),
+                                                    (640, 14336, 48, (48, 31, 3)), (1024, 2816, 64, (64, 47, 9))])
 def test_gemm_tiles_of_every_width_give_the_same_rows(H, I, plan_tokens, counts):
-    """Plans of more than 64 tokens: the token tile (16 to 256) goes by the rows of the trip, the K parts inside a
-    workgroup by the matrix and the plan.  The full trip against the oracle; every shorter one must give the same
+    """The GEMM's token tile (16 to 256) goes by the rows of the trip, the K parts inside a workgroup and the partial
+    planes by the matrix and the plan.  The full trip against the oracle; every shorter one must give the same
     bits for its rows.  K of 2, 5, 8, 9, 10, 11, 16 and 56 super-blocks (shorter and longer than the prefetch ring)."""
     import torch
     from paper_2604_26334_amd import binding as B
