@@ -673,6 +673,33 @@ def test_chunk_of_new_tokens_attends_over_the_kv_cache(ctx0, M):
         plan.close()
 
 
+@pytest.mark.parametrize("n_q,n_kv,ctx0", [(2, 2, 256), (8, 1, 2048), (4, 1, 2049), (2, 1, 16384), (4, 2, 16641), (2, 1, 131400)])
+def test_decode_attention_merges_any_number_of_chunks(n_q, n_kv, ctx0):
+    """One token over 1 to 514 chunks of 256 positions: the merge sums eight chunks per wave at a time and takes
+    512 maxima per round; against the reference on the token's own QKV row."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(_kv_cfg(1, ctx0 + 2), n_q_heads=n_q, n_kv_heads=n_kv)
+    W = Hn.WeightCache(cfg, 59)
+    K, V = S.kv_cache(59, 0, n_kv, ctx0, 128)
+    x = S.activations(59, 0, 1, cfg["hidden"])
+    st = B.Stack(B.Plan(cfg, 1 << 30, 1))
+    for k, ex, N, Kd in S.matrix_shapes(cfg):
+        st.load_matrix(0, k, ex, *W(0, k, ex))
+    for g in range(n_kv):
+        st.load_kv(0, g, K[g], V[g])
+    xin = torch.from_numpy(x).to(st.device)
+    xout = torch.zeros_like(xin)
+    st.set_context(ctx0)
+    st.forward(xin, xout)
+    st.synchronize()
+    qkv = st.debug_buffer(0, np.float16, (1, (n_q + 2 * n_kv) * 128)).copy()
+    got = xout.cpu().numpy()
+    st.close()
+    ref = Hn.kv_token_reference_from_gpu_qkv(cfg, W, x, qkv, K, V, ctx0)
+    assert np.isfinite(got).all() and Hn.rel_err(got, ref) <= TOL
+
+
 @pytest.mark.parametrize("n_q,n_kv,ctx0,M", [(4, 4, 127, 2), (8, 2, 128, 16), (8, 1, 129, 17), (6, 2, 383, 33), (4, 2, 1000, 65),
                                              (8, 2, 256, 127), (4, 1, 60, 129), (8, 2, 31, 255), (8, 2, 97, 257)])
 def test_chunk_attention_at_the_edges_of_its_rounds_and_row_blocks(n_q, n_kv, ctx0, M):
