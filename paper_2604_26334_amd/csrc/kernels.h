@@ -74,15 +74,24 @@ hipError_t launch_gemv_mt(int mode, uint32_t ksplit, const GemvArgs &a, uint32_t
 hipError_t launch_splitk_epilogue(int mode, const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M,
                                   uint32_t ncols_phys, const float *rinv, const __half *res, __half *out,
                                   uint32_t out_stride, uint32_t out_row0, hipStream_t st);
-hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, hipStream_t st);
+// MoE routing of M tokens: the top_k largest fp32 logits (ties to the lower index, in descending order) and the
+// softmax over them.  As a launch of its own, or riding in the launch that produces the layer's RMS factors
+// (`route` of the two below; route_rides says whether the sizes allow it)
+struct RouteArgs {
+    const float *logits;   // [M][E]
+    uint32_t M, E, top_k;
+    int32_t *idx;          // [M][top_k]
+    float *w;
+};
+hipError_t launch_route(const RouteArgs &ra, hipStream_t st);
+bool route_rides(const RouteArgs &ra);
+hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, const RouteArgs *route, hipStream_t st);
 // residual epilogue over whole rows of the hidden state (ncols == out_stride == H, first column 0,
 // at most 8 planes) that also writes the RMS factor of each row it stores, bit-identical to
 // launch_splitk_epilogue(GEMM_RESID, ...) followed by launch_rinv(out, ...)
 hipError_t launch_splitk_epilogue_resid_rinv(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M,
                                              uint32_t H, const __half *res, __half *out, float eps, float *rinv,
-                                             hipStream_t st);
-hipError_t launch_route(const float *logits, uint32_t M, uint32_t E, uint32_t top_k, int32_t *idx, float *w,
-                        hipStream_t st);
+                                             const RouteArgs *route, hipStream_t st);
 // Decode attention over a KV cache, one new token.  A cache shard of one kv head is K rows
 // [cap][128] followed by V rows [cap][128], fp16; `nheads` shards lie head_stride bytes apart from
 // kv (kv heads head0 .. head0 + nheads - 1).  Each workgroup covers one kv head x one chunk of 256
@@ -140,8 +149,9 @@ hipError_t launch_attn_decode(const AttnArgs &a, hipStream_t st);
 // head's K row 0, device memory or device-visible pinned host memory).
 hipError_t launch_attn_combine(const float *part, uint32_t chunk_cap, uint32_t ctx, const uint32_t *ctx_dev, uint32_t cap,
                                const __half *qkv, uint32_t n_q, uint32_t n_kv, const uint64_t *home, __half *out, hipStream_t st);
+// out = h + the experts' rows weighted; rinv not null: also the RMS factor of every row stored, with launch_rinv's bits
 hipError_t launch_combine(const __half *h, const float *y, const float *w, uint32_t M, uint32_t H, uint32_t top_k,
-                          int residual, __half *out, hipStream_t st);
+                          int residual, __half *out, float eps, float *rinv, hipStream_t st);
 hipError_t launch_mfma_probe(int pi, int pk, int pj, float *out, hipStream_t st);
 hipError_t launch_lds_tr_probe(const uint32_t *addr, uint16_t *out, hipStream_t st);
 

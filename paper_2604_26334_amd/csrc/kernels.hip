@@ -623,42 +623,6 @@ hipError_t launch_gemv_mt(int mode, uint32_t ksplit, const GemvArgs &a, uint32_t
 }
 
 // ------------------------------------------------------------------------------------
-// rinv[m] = 1 / sqrt(mean(x[m]^2) + eps), one workgroup per token (used when M > 1): thread t adds
-// the 8-column chunks t, t + 256, ... in that order, the 64 lanes of a wave are summed by the
-// butterfly, the four waves in order.  All of a thread's loads (up to four per round) are issued
-// before the first is used; chunks past the row's end count as zeros.
-// ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void rinv_kernel(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv) {
-    __shared__ float part[4];
-    const uint32_t m = blockIdx.x;
-    const uint4 *row = reinterpret_cast<const uint4 *>(x + (size_t)m * H);
-    const uint32_t nq = H / 8;
-    float ss = 0.f;
-    for (uint32_t q0 = 0; q0 < nq; q0 += 1024) {
-        uint4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            // (a chunk past the row's end re-reads the last one and counts as zeros: no branch around the load,
-            // so the four requests go out together)
-            const uint32_t q = q0 + u * 256 + threadIdx.x;
-            const uint4 w = row[min(q, nq - 1)];
-            v[u] = q < nq ? w : uint4{0u, 0u, 0u, 0u};
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) ss += sumsq8(v[u]);
-    }
-    ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    if (threadIdx.x == 0) rinv[m] = rsqrtf((((part[0] + part[1]) + part[2]) + part[3]) / (float)H + eps);
-}
-
-hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, hipStream_t st) {
-    hipLaunchKernelGGL(rinv_kernel, dim3(M), dim3(256), 0, st, x, M, H, eps, rinv);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------
 // MoE routing: per token the top_k largest fp32 logits (ties to the lower index, listed
 // in descending order) and the softmax over the selected logits.  One wave per token.
 // ------------------------------------------------------------------------------------
@@ -689,9 +653,12 @@ __device__ __forceinline__ uint32_t wave_min_all(uint32_t v) {
 }
 
 template <int NR>   // 64 * NR >= E
-__global__ __launch_bounds__(256) void route_kernel(const float *logits, uint32_t M, uint32_t E, uint32_t top_k,
-                                                    int32_t *idx, float *w) {
-    const uint32_t m = blockIdx.x * 4 + (threadIdx.x >> 6);
+__device__ __forceinline__ void route_tokens(const RouteArgs &ra, uint32_t block) {   // four tokens, one per wave
+    const float *logits = ra.logits;
+    const uint32_t M = ra.M, E = ra.E, top_k = ra.top_k;
+    int32_t *idx = ra.idx;
+    float *w = ra.w;
+    const uint32_t m = block * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (m >= M) return;
     const float *l = logits + (size_t)m * E;
@@ -726,12 +693,62 @@ __global__ __launch_bounds__(256) void route_kernel(const float *logits, uint32_
     if ((uint32_t)lane < top_k) w[(size_t)m * top_k + lane] = ex / den;
 }
 
-hipError_t launch_route(const float *logits, uint32_t M, uint32_t E, uint32_t top_k, int32_t *idx, float *w,
-                        hipStream_t st) {
-    if (E > 1024 || top_k == 0 || top_k > 64 || top_k > E) return hipErrorInvalidValue;
-    if (E <= 128) hipLaunchKernelGGL(route_kernel<2>, dim3((M + 3) / 4), dim3(256), 0, st, logits, M, E, top_k, idx, w);
-    else if (E <= 256) hipLaunchKernelGGL(route_kernel<4>, dim3((M + 3) / 4), dim3(256), 0, st, logits, M, E, top_k, idx, w);
-    else hipLaunchKernelGGL(route_kernel<16>, dim3((M + 3) / 4), dim3(256), 0, st, logits, M, E, top_k, idx, w);
+template <int NR>
+__global__ __launch_bounds__(256) void route_kernel(RouteArgs ra) { route_tokens<NR>(ra, blockIdx.x); }
+
+hipError_t launch_route(const RouteArgs &ra, hipStream_t st) {
+    const uint32_t E = ra.E, blocks = (ra.M + 3) / 4;
+    if (E > 1024 || ra.top_k == 0 || ra.top_k > 64 || ra.top_k > E) return hipErrorInvalidValue;
+    if (E <= 128) hipLaunchKernelGGL(route_kernel<2>, dim3(blocks), dim3(256), 0, st, ra);
+    else if (E <= 256) hipLaunchKernelGGL(route_kernel<4>, dim3(blocks), dim3(256), 0, st, ra);
+    else hipLaunchKernelGGL(route_kernel<16>, dim3(blocks), dim3(256), 0, st, ra);
+    return hipGetLastError();
+}
+
+bool route_rides(const RouteArgs &ra) { return ra.M && ra.E <= 256 && ra.top_k && ra.top_k <= 64 && ra.top_k <= ra.E; }
+
+// ------------------------------------------------------------------------------------
+// rinv[m] = 1 / sqrt(mean(x[m]^2) + eps), one workgroup per token (used when M > 1): thread t adds
+// the 8-column chunks t, t + 256, ... in that order, the 64 lanes of a wave are summed by the
+// butterfly, the four waves in order.  All of a thread's loads (up to four per round) are issued
+// before the first is used; chunks past the row's end count as zeros.
+// ------------------------------------------------------------------------------------
+// NR > 0: the workgroups behind the first M route four tokens each (the MoE routing of a layer depends on nothing the
+// layer computes here, and as a launch of its own it costs 4 to 5 us).
+template <int NR>
+__global__ __launch_bounds__(256) void rinv_kernel(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, RouteArgs ra) {
+    if constexpr (NR > 0) {
+        if (blockIdx.x >= M) { route_tokens<NR>(ra, blockIdx.x - M); return; }
+    }
+    __shared__ float part[4];
+    const uint32_t m = blockIdx.x;
+    const uint4 *row = reinterpret_cast<const uint4 *>(x + (size_t)m * H);
+    const uint32_t nq = H / 8;
+    float ss = 0.f;
+    for (uint32_t q0 = 0; q0 < nq; q0 += 1024) {
+        uint4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            // (a chunk past the row's end re-reads the last one and counts as zeros: no branch around the load,
+            // so the four requests go out together)
+            const uint32_t q = q0 + u * 256 + threadIdx.x;
+            const uint4 w = row[min(q, nq - 1)];
+            v[u] = q < nq ? w : uint4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ss += sumsq8(v[u]);
+    }
+    ss = wave_sum(ss);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+    __syncthreads();
+    if (threadIdx.x == 0) rinv[m] = rsqrtf((((part[0] + part[1]) + part[2]) + part[3]) / (float)H + eps);
+}
+
+hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, const RouteArgs *route, hipStream_t st) {
+    if (!route) hipLaunchKernelGGL(rinv_kernel<0>, dim3(M), dim3(256), 0, st, x, M, H, eps, rinv, RouteArgs{});
+    else if (!route_rides(*route)) return hipErrorInvalidValue;
+    else if (route->E <= 128) hipLaunchKernelGGL(rinv_kernel<2>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, x, M, H, eps, rinv, *route);
+    else hipLaunchKernelGGL(rinv_kernel<4>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, x, M, H, eps, rinv, *route);
     return hipGetLastError();
 }
 
@@ -1378,38 +1395,65 @@ hipError_t launch_attn_combine(const float *part, uint32_t chunk_cap, uint32_t c
 }
 
 // ------------------------------------------------------------------------------------
-// MoE combine: out[m] = h[m] + sum_j w[m][j] * y[m*top_k + j], j in rank order
+// MoE combine: out[m] = h[m] + sum_j w[m][j] * y[m*top_k + j], j in rank order.  Eight columns per thread and round
+// (16-byte reads; four experts' rows requested before the first is added, a rank past the last re-reads the last one
+// and is left out).  RINV: one workgroup per token, whose threads own the same chunks as in rinv_kernel, square the
+// fp16 values they store and reduce in the same order, so rinv[m] has the bits of the separate launch (4 us), which is
+// then left out; otherwise the chunks of a token are spread over blockIdx.y.
 // ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void combine_kernel(const __half *h, const float *y, const float *w, uint32_t M,
-                                                      uint32_t H, uint32_t top_k, int residual, __half *out) {
-    const size_t n = (size_t)M * H;
-    for (size_t q = (size_t)blockIdx.x * 256 + threadIdx.x; q < n; q += (size_t)gridDim.x * 256) {
-        const uint32_t m = (uint32_t)(q / H), col = (uint32_t)(q % H);
-        float s = 0.f;
-        // eight experts' rows and weights are requested before the first is added (a rank past the last re-reads
-        // the last one and is left out); the sum stays in rank order
-        for (uint32_t j0 = 0; j0 < top_k; j0 += 8) {
-            float wv[8], yv[8];
+template <bool RINV>
+__global__ __launch_bounds__(256) void combine_kernel(const __half *h, const float *y, const float *w, uint32_t H,
+                                                      uint32_t top_k, int residual, __half *out, float eps, float *rinv) {
+    const uint32_t m = blockIdx.x, nq = H / 8;
+    float ss = 0.f;
+    for (uint32_t q = blockIdx.y * blockDim.x + threadIdx.x; q < nq; q += gridDim.y * blockDim.x) {
+        const uint4 hv = residual ? *reinterpret_cast<const uint4 *>(h + (size_t)m * H + q * 8) : uint4{0u, 0u, 0u, 0u};
+        float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (uint32_t j0 = 0; j0 < top_k; j0 += 4) {
+            float wv[4];
+            float4 yv[4][2];
 #pragma unroll
-            for (uint32_t u = 0; u < 8; ++u) {
+            for (uint32_t u = 0; u < 4; ++u) {
                 const size_t pr = (size_t)m * top_k + min(j0 + u, top_k - 1);
                 wv[u] = w[pr];
-                yv[u] = y[pr * H + col];
+                const float4 *src = reinterpret_cast<const float4 *>(y + pr * H + q * 8);
+                yv[u][0] = src[0];
+                yv[u][1] = src[1];
             }
 #pragma unroll
-            for (uint32_t u = 0; u < 8; ++u)
-                if (j0 + u < top_k) s += wv[u] * yv[u];
+            for (uint32_t u = 0; u < 4; ++u) {
+                if (j0 + u < top_k) {
+                    s[0] += wv[u] * yv[u][0].x; s[1] += wv[u] * yv[u][0].y; s[2] += wv[u] * yv[u][0].z; s[3] += wv[u] * yv[u][0].w;
+                    s[4] += wv[u] * yv[u][1].x; s[5] += wv[u] * yv[u][1].y; s[6] += wv[u] * yv[u][1].z; s[7] += wv[u] * yv[u][1].w;
+                }
+            }
         }
-        out[q] = __float2half((residual ? __half2float(h[q]) : 0.f) + s);
+        uint32_t d[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint16_t lo = __builtin_bit_cast(uint16_t, to_half((residual ? half_of(hv, 2 * e) : 0.f) + s[2 * e]));
+            const uint16_t hi = __builtin_bit_cast(uint16_t, to_half((residual ? half_of(hv, 2 * e + 1) : 0.f) + s[2 * e + 1]));
+            d[e] = (uint32_t)lo | ((uint32_t)hi << 16);
+        }
+        const uint4 o = uint4{d[0], d[1], d[2], d[3]};
+        *reinterpret_cast<uint4 *>(out + (size_t)m * H + q * 8) = o;
+        if (RINV) ss += sumsq8(o);
+    }
+    if constexpr (RINV) {
+        __shared__ float part[4];
+        ss = wave_sum(ss);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+        __syncthreads();
+        if (threadIdx.x == 0) rinv[m] = rsqrtf((((part[0] + part[1]) + part[2]) + part[3]) / (float)H + eps);
     }
 }
 
 hipError_t launch_combine(const __half *h, const float *y, const float *w, uint32_t M, uint32_t H, uint32_t top_k,
-                          int residual, __half *out, hipStream_t st) {
-    const size_t n = (size_t)M * H;
-    const size_t want = (n + 255) / 256;
-    const uint32_t blocks = (uint32_t)(want < 4096 ? want : 4096);
-    hipLaunchKernelGGL(combine_kernel, dim3(blocks), dim3(256), 0, st, h, y, w, M, H, top_k, residual, out);
+                          int residual, __half *out, float eps, float *rinv, hipStream_t st) {
+    if (M == 0) return hipSuccess;
+    if (H % 8 || top_k == 0) return hipErrorInvalidValue;
+    if (rinv) hipLaunchKernelGGL(combine_kernel<true>, dim3(M), dim3(256), 0, st, h, y, w, H, top_k, residual, out, eps, rinv);
+    else hipLaunchKernelGGL(combine_kernel<false>, dim3(M, (H / 8 + 63) / 64), dim3(64), 0, st, h, y, w, H, top_k, residual, out, eps, rinv);
     return hipGetLastError();
 }
 
@@ -2130,10 +2174,14 @@ hipError_t launch_splitk_epilogue(int mode, const float *partial, uint32_t parts
 // Planes past `parts` are not read (the load is redirected to the last plane and discarded by a
 // select, so the loads carry no branch).
 // ------------------------------------------------------------------------------------
+template <int NR>   // > 0: the workgroups behind the first M route four tokens each, as in rinv_kernel
 __global__ __launch_bounds__(256) void splitk_epilogue_resid_rinv_kernel(const float *partial, uint32_t parts,
-                                                                         uint32_t part_stride, uint32_t H,
+                                                                         uint32_t part_stride, uint32_t M, uint32_t H,
                                                                          const __half *res, __half *out, float eps,
-                                                                         float *rinv) {
+                                                                         float *rinv, RouteArgs ra) {
+    if constexpr (NR > 0) {
+        if (blockIdx.x >= M) { route_tokens<NR>(ra, blockIdx.x - M); return; }
+    }
     __shared__ float part[4];
     const uint32_t m = blockIdx.x, nq = H / 8;
     const float *prow = partial + (size_t)m * H;
@@ -2180,11 +2228,13 @@ __global__ __launch_bounds__(256) void splitk_epilogue_resid_rinv_kernel(const f
 
 hipError_t launch_splitk_epilogue_resid_rinv(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M,
                                              uint32_t H, const __half *res, __half *out, float eps, float *rinv,
-                                             hipStream_t st) {
+                                             const RouteArgs *route, hipStream_t st) {
     if (M == 0) return hipSuccess;
     if (parts == 0 || parts > 8 || H % 8 || part_stride % 4 || !partial || !out || !rinv) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(splitk_epilogue_resid_rinv_kernel, dim3(M), dim3(256), 0, st, partial, parts, part_stride, H, res,
-                       out, eps, rinv);
+    if (!route) hipLaunchKernelGGL(splitk_epilogue_resid_rinv_kernel<0>, dim3(M), dim3(256), 0, st, partial, parts, part_stride, M, H, res, out, eps, rinv, RouteArgs{});
+    else if (!route_rides(*route)) return hipErrorInvalidValue;
+    else if (route->E <= 128) hipLaunchKernelGGL(splitk_epilogue_resid_rinv_kernel<2>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, partial, parts, part_stride, M, H, res, out, eps, rinv, *route);
+    else hipLaunchKernelGGL(splitk_epilogue_resid_rinv_kernel<4>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, partial, parts, part_stride, M, H, res, out, eps, rinv, *route);
     return hipGetLastError();
 }
 

@@ -91,7 +91,9 @@ struct ps_stack {
     uint32_t kv_rows = 0;                     // cache positions written so far (loaded or appended): what a tier switch moves
     bool profiling = false;
     bool own_rinv_launch = false;             // decode mode 2: RMS factors always from rinv_kernel
-    const void *rinv_of = nullptr;            // rows whose RMS factors the last residual epilogue left in the workspace
+    const void *rinv_of = nullptr;            // rows whose RMS factors the last residual epilogue or combine left in the workspace
+    uint32_t routed_layer = kNotRouted;       // MoE layer whose routing rode in an earlier launch of this forward
+    static constexpr uint32_t kNotRouted = 0xFFFFFFFFu;
     std::vector<hipEvent_t> prof_ev;          // 2 per op of the last profiled forward
     std::vector<uint8_t> prof_is_copy;
     std::vector<double> prof_start, prof_dur;
@@ -281,6 +283,10 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         PS_HIP(launch_gemv_mt(mode, ks, a, M, cs));
         return PS_OK;
     }
+    // MoE: the layer's routing rides in the launch in front of the experts that leaves the RMS factors of their input
+    const RouteArgs ra{g.moe ? st->route_logits + (size_t)l * st->route_layer_stride : nullptr, M, m.n_experts, m.top_k,
+                       reinterpret_cast<int32_t *>(WS + p.ws.ridx), reinterpret_cast<float *>(WS + p.ws.rw)};
+    const RouteArgs *const riding = g.moe && route_rides(ra) ? &ra : nullptr;
     // batched decode (2..64 tokens) of a narrow matrix: split K over blockIdx.z into fp32 partial
     // planes, then one epilogue kernel sums them in order and applies the mode's epilogue
     auto run_gemm = [&](int mode, GemmArgs a, const MatGeom &mg) -> int32_t {
@@ -296,7 +302,8 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // the launch covers whole rows of the hidden state: its epilogue also leaves their RMS
             // factors (the bits rinv_kernel gives), and the PS_K_RINV op that follows is skipped
             PS_HIP(launch_splitk_epilogue_resid_rinv(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out,
-                                                     m.rms_eps, rinv, cs));
+                                                     m.rms_eps, rinv, riding, cs));
+            if (riding) st->routed_layer = l;
             st->rinv_of = a.out;
             return PS_OK;
         }
@@ -312,7 +319,10 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // the few-token kernels of QKV (factors of kind 0) and of a dense gate/up (kind 1) compute their own
             if (op.info.shard0 == 0 && few_token_gemv(p, g.qkv)) return PS_OK;
             if (op.info.shard0 == 1 && !g.moe && few_token_gemv(p, g.gate_up)) return PS_OK;
-            if (!have) PS_HIP(launch_rinv(rows, M, H, m.rms_eps, rinv, cs));
+            if (have) return PS_OK;
+            const bool ride = riding && op.info.shard0 == 1;
+            PS_HIP(launch_rinv(rows, M, H, m.rms_eps, rinv, ride ? riding : nullptr, cs));
+            if (ride) st->routed_layer = l;
             return PS_OK;
         }
         case PS_K_OUT: {   // every token's logits (head_rows == MP > 1)
@@ -404,9 +414,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                                        reinterpret_cast<__half *>(WS + p.ws.attn), cs));
             return PS_OK;
         case PS_K_ROUTE:
-            PS_HIP(launch_route(st->route_logits + (size_t)l * st->route_layer_stride, M,
-                                m.n_experts, m.top_k, reinterpret_cast<int32_t *>(WS + p.ws.ridx),
-                                reinterpret_cast<float *>(WS + p.ws.rw), cs));
+            if (st->routed_layer != l) PS_HIP(launch_route(ra, cs));
             return PS_OK;
         case PS_K_EXPERT_GATE_UP:
         case PS_K_EXPERT_DOWN: {
@@ -433,10 +441,16 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             }
             return PS_OK;
         }
-        case PS_K_COMBINE:
-            PS_HIP(launch_combine(hbuf, reinterpret_cast<const float *>(WS + p.ws.y),
-                                  reinterpret_cast<const float *>(WS + p.ws.rw), M, H, m.top_k, resid ? 1 : 0, xout, cs));
+        case PS_K_COMBINE: {
+            // the RMS factors of the rows it stores, where the next op takes any: the next layer's QKV (its few-token
+            // form computes its own) or the output head
+            const bool next = l + 1 < m.n_layers ? g.has_attn && !few_token_gemv(p, g.qkv) : st->head_rows > 1;
+            float *left = MP > 1 && next && !st->own_rinv_launch ? rinv : nullptr;
+            PS_HIP(launch_combine(hbuf, reinterpret_cast<const float *>(WS + p.ws.y), reinterpret_cast<const float *>(WS + p.ws.rw), M, H,
+                                  m.top_k, resid ? 1 : 0, xout, m.rms_eps, left, cs));
+            if (left) st->rinv_of = xout;
             return PS_OK;
+        }
     }
     set_error("unknown kernel id %u", op.info.kernel);
     return PS_E_STATE;
@@ -625,6 +639,7 @@ int32_t run_schedule(ps_stack *st, const ps_schedule &sc, const __half *x_in, __
     }
     st->prof_valid = false;
     st->rinv_of = nullptr;
+    st->routed_layer = ps_stack::kNotRouted;
     ps_stats &ss = st->stats;
     ss = ps_stats{};
     // graph mode with a KV cache: the context length travels in device memory, where the attention

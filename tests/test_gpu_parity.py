@@ -175,6 +175,16 @@ def test_small_moe(M):
     _check(cfg, 3, M, _budgets(cfg, M, [1.0, 0.6, 0.35]), logits=lg)
 
 
+@pytest.mark.parametrize("E,top_k,M", [(128, 2, 5), (130, 7, 9), (256, 3, 70), (264, 4, 6)])
+def test_routing_riding_in_the_rms_factor_launch(E, top_k, M):
+    """Up to 256 experts a layer's routing rides in the launch that leaves its RMS factors (the plane sum of O up to 64
+    tokens, the factor launch beyond), above that it has a launch of its own; the combine leaves the next layer's
+    factors.  Top-k not a multiple of four, token counts that are no multiple of the four tokens per workgroup."""
+    cfg = dict(Hn.small_moe_cfg(2), n_experts=E, top_k=top_k)
+    lg = S.router_logits(73, 0, cfg["n_layers"], M, E)
+    _check(cfg, 73, M, _budgets(cfg, M, [1.0, 0.6]), logits=lg)
+
+
 @pytest.mark.parametrize("busiest", [16, 17, 33, 48, 49, 65, 96, 97, 129])
 def test_expert_gemm_tile_by_the_busiest_experts_tokens(busiest):
     """Grouped expert launches take the smallest token tile (16, 32, 48, 64, 96, else 128) that holds the busiest
