@@ -1887,13 +1887,13 @@ static hipError_t launch_gemm_k(const GemmArgs &a, uint32_t ntok, uint32_t gz, h
     return hipGetLastError();
 }
 
-// Two K parts inside the workgroup: for matrices whose 128-row x 64-token workgroups at the plan's token count leave at
-// most one per CU.  Four waves of them are one wave per SIMD, which waits for its own operand reads and
-// dequantisation; the second half of K on four more waves halves the steps (in one round of workgroups, 128 tokens: QKV
-// 25.6 -> 17.7 us, O 25.7 -> 17.1, down 73.6 -> 45.5; 512 tokens: O 28.8 -> 25.5, down 85.8 -> 71.9, but QKV, 1.5
-// workgroups per CU, 39.4 -> 44.7).
+// Two K parts inside the workgroup: for matrices whose 128-row workgroups at the plan's token count leave at most one
+// per CU in tiles of up to 128 tokens.  Four waves of them are one wave per SIMD, which waits for its own operand reads
+// and dequantisation; the second half of K on four more waves halves the steps.  Against the best shape without the
+// parts: 128 tokens: QKV 25.6 -> 17.7 us, O 25.7 -> 17.1, down 73.6 -> 45.5; 512: QKV 39.2 -> 36.3, O 28.8 -> 25.5, down
+// 85.8 -> 71.9; 1024: O 43.6 -> 40.9, down 139 -> 120, but QKV, 1.5 workgroups per CU, 61.7 -> 74.9.
 static bool gemm_two_k_parts(const GemmArgs &a, uint32_t plan_tokens) {
-    return a.nsb % 2 == 0 && (a.total_tiles + 7) / 8 * ((plan_tokens + 63) / 64) <= 256;
+    return a.nsb % 2 == 0 && (a.total_tiles + 7) / 8 * ((plan_tokens + 127) / 128) <= 256;
 }
 
 // Token tile of an unsplit launch of a.M rows: the one with the smallest product of rounds of workgroups (one
@@ -1964,12 +1964,19 @@ static hipError_t launch_gemm_m(const GemmArgs &a, uint32_t ntasks, uint32_t max
         // Plans of more than 64 tokens.  The tile goes by the rows that are there (a.M) and never changes a bit of the
         // result; the K parts do, so they go by the whole matrix and the plan's token count.
         if (gemm_two_k_parts(a, max_tok)) {
-            // the smallest tile that still leaves at most one workgroup per CU: 4096 x 4096 at 200 tokens 16.9 us in
-            // 32-token tiles, 19.1 in 48, 21.6 in 64; at 384 tokens (1.5 workgroups per CU in 32) 27.9 / 23.3 / 25.7
+            // the smallest tile that still leaves at most one workgroup per CU (there is one: the rule saw to it): O at 200
+            // tokens 16.9 us in 32-token tiles, 19.1 in 48, 21.6 in 64; at 384 tokens (1.5 workgroups per CU in 32)
+            // 27.9 / 23.3 / 25.7; QKV at 512 tokens 39.2 without the parts, 36.3 in 112-token tiles; down at 768
+            // 122 without, 98.9 in 96
             const uint32_t groups = (a.ntiles + 7) / 8;
-            if (groups * ((a.M + 31) / 32) <= 256) return launch_gemm_k<MODE, 2, 32, false, 8, 2>(a, a.M, 1, st);
-            if (groups * ((a.M + 47) / 48) <= 256) return launch_gemm_k<MODE, 2, 48, false, 8, 2>(a, a.M, 1, st);
-            return launch_gemm_k<MODE, 2, 64, false, 8, 2>(a, a.M, 1, st);
+            auto one_round = [&](uint32_t mt) { return groups * ((a.M + mt - 1) / mt) <= 256; };
+            if (one_round(32)) return launch_gemm_k<MODE, 2, 32, false, 8, 2>(a, a.M, 1, st);
+            if (one_round(48)) return launch_gemm_k<MODE, 2, 48, false, 8, 2>(a, a.M, 1, st);
+            if (one_round(64)) return launch_gemm_k<MODE, 2, 64, false, 8, 2>(a, a.M, 1, st);
+            if (one_round(80)) return launch_gemm_k<MODE, 2, 80, false, 8, 2>(a, a.M, 1, st);
+            if (one_round(96)) return launch_gemm_k<MODE, 2, 96, false, 8, 2>(a, a.M, 1, st);
+            if (one_round(112)) return launch_gemm_k<MODE, 2, 112, false, 8, 2>(a, a.M, 1, st);
+            return launch_gemm_k<MODE, 2, 128, false, 8, 2>(a, a.M, 1, st);
         }
         switch (gemm_pick_tile(a, MODE == GEMM_GATE_UP ? 256 : 224)) {   // (256 tokens spill in the other modes)
             case 16: return launch_gemm_k<MODE, 2, 16, false, 4, 1>(a, a.M, 1, st);

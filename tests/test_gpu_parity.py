@@ -485,6 +485,7 @@ def test_one_stack_serves_the_prefill_tier_and_the_decode_tier(kind):
 @pytest.mark.parametrize("H,I,plan_tokens,counts", [(256, 7168, 1024, (1024, 770, 560, 400, 300, 161, 65, 20, 1)),
                                                     (640, 7168, 512, (512, 257, 97)),
                                                     (2048, 1280, 1024, (1024, 700, 500, 33)),
+                                                    (4096, 768, 1024, (1024, 870, 760, 630, 500, 380, 250)),
                                                     (1152, 1408, 320, (320, 129)),
                                                     (256, 14336, 64, (64, 48, 33, 32, 17, 16, 5)),
                                                     (640, 14336, 48, (48, 31, 3)), (1024, 2816, 64, (64, 47, 9))])
