@@ -23,11 +23,11 @@ extern "C" {
 int32_t ps_pack_matrix(const uint16_t *scales, const uint8_t *codes, uint32_t rows, uint32_t K,
                        uint8_t *out);
 
-/* ps_stack_set_decode_mode(st, PS_DECODE_MODE_OWN_RINV): mode 0, except that in a forward of 2..64
- * tokens the RMS factor of a hidden-state row always comes from a launch of its own; in modes 0 and
+/* ps_stack_set_decode_mode(st, PS_DECODE_MODE_OWN_RINV): mode 0, except that in a forward of 2 tokens
+ * or more the RMS factor of a hidden-state row always comes from a launch of its own; in modes 0 and
  * 1 the epilogue of an O or down matrix that one launch covers whole and that is summed from
- * split-K planes leaves the factor itself (same bits: the test of that claim is what this mode is
- * for). */
+ * split-K planes leaves the factor itself, and so do, in larger plans, the sums of squares that O and
+ * down leave (same bits: the test of that claim is what this mode is for). */
 #define PS_DECODE_MODE_OWN_RINV 2
 
 /* Time one kernel kind in isolation (measurement aid): every resident op of kind `kernel`

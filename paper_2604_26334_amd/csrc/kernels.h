@@ -47,6 +47,12 @@ struct GemmArgs {
     uint32_t out_stride, out_row0, top_k;
     uint32_t sb_per_part;  // split-K: super-blocks per blockIdx.z part (0 = whole K in one part)
     uint32_t part_stride;  // split-K: elements between the fp32 partial planes
+    // Sums of squares instead of a buffer of RMS factors (plans of more than 64 tokens): RESID leaves, per token and
+    // run of 128 output columns, the sum of squares of what it stored in ssq_out[run * M + token]; PLAIN and
+    // GATE_UP with ssq_in add a token's nsb runs (K columns), in pairs, and take their RMS factors from them
+    float *ssq_out;
+    const float *ssq_in;
+    float eps;
     const DeviceTask *tasks;
     const int32_t *pairs;
 };
@@ -85,6 +91,8 @@ struct RouteArgs {
 };
 hipError_t launch_route(const RouteArgs &ra, hipStream_t st);
 bool route_rides(const RouteArgs &ra);
+// the factors in the order of the GEMM's sums of squares (see GemmArgs), with their bits
+hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, hipStream_t st);
 hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, const RouteArgs *route, hipStream_t st);
 // residual epilogue over whole rows of the hidden state (ncols == out_stride == H, first column 0,
 // at most 8 planes) that also writes the RMS factor of each row it stores, bit-identical to

@@ -744,6 +744,59 @@ __global__ __launch_bounds__(256) void rinv_kernel(const __half *x, uint32_t M, 
     if (threadIdx.x == 0) rinv[m] = rsqrtf((((part[0] + part[1]) + part[2]) + part[3]) / (float)H + eps);
 }
 
+// up to 16 runs' sums of squares, in pairs (runs from n on count as zeros)
+__device__ __forceinline__ float sum_of_runs(const float *v, uint32_t n) {
+    auto four = [&](uint32_t k) {
+        return ((n > k ? v[k] : 0.f) + (n > k + 1 ? v[k + 1] : 0.f)) + ((n > k + 2 ? v[k + 2] : 0.f) + (n > k + 3 ? v[k + 3] : 0.f));
+    };
+    return (four(0) + four(4)) + (four(8) + four(12));
+}
+
+// The same factor with the sum taken the way the GEMM's residual epilogue and the matrices behind it take it (ssq_out /
+// ssq_in of GemmArgs), bit for bit: runs of 128 columns, in each the four 32-column shares of a wave, in each share the
+// four lanes of a token (4 columns of either row-tile).  H a multiple of 128.
+__global__ __launch_bounds__(256) void rinv_runs_kernel(const __half *x, uint32_t H, float eps, float *rinv) {
+    __shared__ float share[kMaxGroups * 8 * 4];      // K <= 16384: 128 runs
+    const uint32_t m = blockIdx.x, runs = H / 128, w = (threadIdx.x >> 2) & 3, rg = threadIdx.x & 3;
+    const __half *row = x + (size_t)m * H;
+    for (uint32_t run = threadIdx.x >> 4; run < runs; run += 16) {
+        uint2 v[2];
+        float part[2] = {0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 2; ++t) v[t] = *reinterpret_cast<const uint2 *>(row + run * 128 + w * 32 + t * 16 + rg * 4);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const h2_t a01 = as_h2(v[t].x), a23 = as_h2(v[t].y);
+            part[t] = fmaf((float)a01.x, (float)a01.x, part[t]); part[t] = fmaf((float)a01.y, (float)a01.y, part[t]);
+            part[t] = fmaf((float)a23.x, (float)a23.x, part[t]); part[t] = fmaf((float)a23.y, (float)a23.y, part[t]);
+        }
+        float sq = part[0] + part[1];
+        sq += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sq), 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
+        sq += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sq), 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
+        if (rg == 0) share[run * 4 + w] = sq;
+    }
+    __syncthreads();
+    float mine = 0.f;      // run threadIdx.x
+    if (threadIdx.x < runs) {
+        const float *r4 = share + threadIdx.x * 4;
+        mine = (r4[0] + r4[1]) + (r4[2] + r4[3]);
+    }
+    __syncthreads();
+    if (threadIdx.x < kMaxGroups * 8) share[threadIdx.x] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.;
+        for (uint32_t g = 0; g < runs; g += 16) s += sum_of_runs(share + g, runs - g);
+        rinv[m] = rsqrtf((float)s / (float)H + eps);
+    }
+}
+
+hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, hipStream_t st) {
+    if (H % 128 || H > kMaxGroups * 1024) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(rinv_runs_kernel, dim3(M), dim3(256), 0, st, x, H, eps, rinv);
+    return hipGetLastError();
+}
+
 hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, const RouteArgs *route, hipStream_t st) {
     if (!route) hipLaunchKernelGGL(rinv_kernel<0>, dim3(M), dim3(256), 0, st, x, M, H, eps, rinv, RouteArgs{});
     else if (!route_rides(*route)) return hipErrorInvalidValue;
@@ -1535,12 +1588,15 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
     // weights: 32-bit byte offset of the lane's 16 bytes in its tiles' first super-block; tiles past
     // the slab read tile 0 (discarded)
-    uint32_t woff[AT];
+    // (gate/up tiles come in pairs, so one offset serves both, the second tile a scalar offset further on)
+    constexpr bool PAIRED = MODE == GEMM_GATE_UP && AT == 2;
+    uint32_t woff[PAIRED ? 1 : AT];
 #pragma unroll
-    for (int t = 0; t < AT; ++t) {
+    for (int t = 0; t < (PAIRED ? 1 : AT); ++t) {
         const uint32_t tile = (blockIdx.x * NWR + wave_u) * AT + t;
         woff[t] = ((tile < a.ntiles ? tile : 0) * a.tile_u4 + lane) * 16u;
     }
+    const uint32_t tile_b = PAIRED ? a.tile_u4 * 16u : 0u;
     // buffer addressing: uniform part of an address in a scalar offset, lane part in xoff / woff
     const __amdgpu_buffer_rsrc_t xbuf = make_rsrc(a.x), wbuf = make_rsrc(W);
 
@@ -1585,13 +1641,13 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
         const uint32_t gb = gn * (9 * 1024);
 #pragma unroll
         for (int t = 0; t < AT; ++t)
-            w.q[t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wbuf, woff[t], gb + sn * 1024, kAuxNt));
+            w.q[t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wbuf, woff[PAIRED ? 0 : t], gb + sn * 1024 + t * tile_b, kAuxNt));
     };
     // scale area of group g of the wave's tiles -> the window's buffer of parity g & 1
     auto fill_scales = [&](uint32_t g) {
         const uint32_t so = g * (9 * 1024) + min(8u, a.nsb - g * 8u) * 1024;
 #pragma unroll
-        for (int t = 0; t < AT; ++t) load_to_lds16(wbuf, (lds_void *)(sc_lds + ((g & 1) * AT + t) * 64), woff[t], so);
+        for (int t = 0; t < AT; ++t) load_to_lds16(wbuf, (lds_void *)(sc_lds + ((g & 1) * AT + t) * 64), woff[PAIRED ? 0 : t], so + t * tile_b);
     };
     // the scales the next dequantisation uses (dsc): the lane's fp16 number sbx & 7 of its group
     uint32_t dsc[AT];
@@ -1658,6 +1714,32 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     prefetch(sb_begin, 0, sb_begin, wr[0], std::true_type{});
 #pragma unroll
     for (int d = 1; d < DEPTH; ++d) prefetch(min(sb_begin + d, sb_end - 1), d, sb_begin + d, wr[d], std::false_type{});
+    // (A launch of its own for the factors is 4 to 6 us and two dependent-launch gaps for a pass over data the matrix in
+    // front had in registers: two layers of 300 tokens at H = 4096 351 -> 339 us, two trips of 512 tokens 1222 -> 1203 us;
+    // at 2048 tokens, where the matrix kernels run at the card's power limit, no difference.  Runs of all tokens lie side by side; a token's runs in one row, 16 bytes of 64 rows
+    // to a request, cost the 256-token tiles 7 us a launch and were slower there than the launch they replace.)
+    // the RMS factor of token m0 + thread, from the buffer of factors or from the token's sums of squares (nsb of them: one
+    // per 128 columns of K): requested behind the opening prefetches, whose wait covers it, or, where the accumulators leave
+    // it no register, after the walk
+    constexpr bool FACTORS = !GROUPED && (MODE == GEMM_PLAIN || MODE == GEMM_GATE_UP), FACTORS_LATE = MT > 224;
+    static_assert(!FACTORS || MT <= NW * 64, "one token per thread");
+    float my_rinv = 0.f;
+    auto factor_of = [&](uint32_t t) {
+        const uint32_t tok = min(m0 + t, ntok - 1);
+        if (!a.ssq_in) { my_rinv = a.rinv[tok]; return; }
+        double s = 0.;
+        for (uint32_t g = 0; g < a.nsb; g += 16) {   // (the buffer goes on for 64 nsb floats per token)
+            const float *sq = a.ssq_in + (size_t)g * ntok + tok;
+            float v[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = sq[(size_t)e * ntok];
+            s += sum_of_runs(v, a.nsb - g);
+        }
+        my_rinv = rsqrtf((float)s / (float)(a.nsb * 128) + a.eps);
+    };
+    if constexpr (FACTORS && !FACTORS_LATE) {
+        if (threadIdx.x < MT) factor_of(threadIdx.x);
+    }
     // the A operands of the next MFMA step are dequantised while this step's MFMAs run
     h8_t Acur[AT], Anxt[AT];
     arrive_w(wr[0]);
@@ -1710,7 +1792,13 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
             // per block, in the first blocks of kk.
             constexpr int NF = 4 * NMT, NR = 6;
             h8_t Bb[NR], Ab[2][AT];
-            auto read_b = [&](int f) { Bb[f % NR] = __builtin_bit_cast(h8_t, ls[(f % NMT) * 256 + ((c + (f / NMT) * 4) ^ i)]); };
+            // (c + 4 kk) ^ i = (c ^ i) ^ 4 kk: the four addresses of a step are made from one where they are used
+            uint32_t lane_at = (uint32_t)(i * 16 + (c ^ i)) * 16u;
+            asm volatile("" : "+v"(lane_at));
+            const char *const stage_at = reinterpret_cast<const char *>(xs_lds + u * (MT * 16));
+            auto read_b = [&](int f) {
+                Bb[f % NR] = __builtin_bit_cast(h8_t, *reinterpret_cast<const uint4 *>(stage_at + (f % NMT) * 4096 + (lane_at ^ (uint32_t)(f / NMT) * 64u)));
+            };
 #pragma unroll
             for (int t = 0; t < AT; ++t) Ab[0][t] = Acur[t];
 #pragma unroll
@@ -1798,8 +1886,22 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
         if (sb + 2 < sb_end) step(sb + 2, std::integral_constant<int, 2>{}, std::true_type{});
     }
 
-    if constexpr (KS == 2) {   // first half + second half (the last step's barrier is behind every wave: the stages are free)
-        f4_t *const xch = reinterpret_cast<f4_t *>(lds) + (size_t)wave_u * (AT * NMT * 64) + lane;
+    // (the lane, the thread and the wave's tiles are taken from scratch: nothing of them need live through the ring)
+    uint32_t elane = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(elane));   // (volatile: computed here, not before the ring)
+#endif
+    const uint32_t etid = ((uint32_t)kpart * NWR + wave_u) * 64 + elane;
+    // (the last step's barrier is behind every wave: the stages are free)
+    float *const side = reinterpret_cast<float *>(lds) + (KS == 2 ? NWR * AT * NMT * 256 : 0);   // RMS factors of the tile's tokens / sums of squares
+    if constexpr (FACTORS) {
+        if (etid < MT) {
+            if (FACTORS_LATE) factor_of(etid);
+            side[etid] = my_rinv;
+        }
+    }
+    if constexpr (KS == 2) {   // first half + second half
+        f4_t *const xch = reinterpret_cast<f4_t *>(lds) + (size_t)wave_u * (AT * NMT * 64) + elane;
         if (kpart == 1) {
 #pragma unroll
             for (int t = 0; t < AT; ++t)
@@ -1807,27 +1909,32 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
                 for (int n = 0; n < NMT; ++n) xch[(t * NMT + n) * 64] = acc[t][n];
         }
         __syncthreads();
-        if (kpart == 1) return;
+        if (kpart == 0) {
 #pragma unroll
-        for (int t = 0; t < AT; ++t)
+            for (int t = 0; t < AT; ++t)
 #pragma unroll
-            for (int n = 0; n < NMT; ++n) acc[t][n] += xch[(t * NMT + n) * 64];
+                for (int n = 0; n < NMT; ++n) acc[t][n] += xch[(t * NMT + n) * 64];
+        }
+    } else if constexpr (FACTORS) {
+        __syncthreads();
     }
 
     // epilogue: lane holds token j = lane & 15 of each token tile and rows 4*(lane >> 4) + r
-    // (the lane and the wave's tiles are taken from scratch: nothing of them need live through the ring)
-    const int elane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     const int j = elane & 15, rg = elane >> 4;
     const uint32_t tile_base = (blockIdx.x * NWR + wave_u) * AT;
+    constexpr bool SSQ_OUT = !GROUPED && MODE == GEMM_RESID;
+    if (kpart == 0) {
 #pragma unroll
     for (int n = 0; n < NMT; ++n) {
         const uint32_t tok = m0 + n * 16 + j;
-        if (tok >= ntok) continue;
+        float sq[AT] = {};   // RESID: squares of what this lane stores for its token
+        if (MT > 224) asm volatile("" ::: "memory");   // (or every token's factor is read ahead, and there are no registers for them)
+        if (tok < ntok) {
         size_t orow = tok;           // output row
         size_t xrow = tok;           // row of rinv / residual
         if (pairs) { orow = (size_t)pairs[tok]; xrow = orow / a.top_k; }
         if (MODE == GEMM_GATE_UP) {
-            const float rinv = a.rinv[xrow];
+            const float rinv = FACTORS ? side[n * 16 + j] : a.rinv[xrow];
 #pragma unroll
             for (int t = 0; t < AT; t += 2) {
                 if (tile_base + t >= a.ntiles) continue;
@@ -1851,7 +1958,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
                 } else {
                     float v[4];
                     if (MODE == GEMM_PLAIN) {
-                        const float rinv = a.rinv[xrow];
+                        const float rinv = side[n * 16 + j];
 #pragma unroll
                         for (int r = 0; r < 4; ++r) v[r] = rinv * acc[t][n][r];
                     } else {
@@ -1864,9 +1971,34 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
                         }
                     }
                     __half2 *dst = reinterpret_cast<__half2 *>(a.out + orow * a.out_stride + col);
-                    dst[0] = __floats2half2_rn(v[0], v[1]);
-                    dst[1] = __floats2half2_rn(v[2], v[3]);
+                    const __half2 h01 = __floats2half2_rn(v[0], v[1]), h23 = __floats2half2_rn(v[2], v[3]);
+                    dst[0] = h01;
+                    dst[1] = h23;
+                    if (SSQ_OUT) {
+                        const float2 f01 = __half22float2(h01), f23 = __half22float2(h23);
+                        sq[t] = fmaf(f01.x, f01.x, sq[t]); sq[t] = fmaf(f01.y, f01.y, sq[t]);
+                        sq[t] = fmaf(f23.x, f23.x, sq[t]); sq[t] = fmaf(f23.y, f23.y, sq[t]);
+                    }
                 }
+            }
+        }
+        }
+        if constexpr (SSQ_OUT) {
+            if (a.ssq_out) {      // the token's four lanes meet: the wave's 32 columns
+                const float own = rows4_meet<false>(sq[0] + sq[AT - 1]);
+                if (rg == 0) side[wave_u * MT + n * 16 + j] = own;
+            }
+        }
+    }
+    }
+    if constexpr (SSQ_OUT) {
+        if (a.ssq_out) {      // four waves make a run of 128 columns
+            static_assert(AT == 2 && NWR % 4 == 0 && NWR / 4 * MT <= NW * 64, "runs of 128 columns, one sum per thread");
+            __syncthreads();
+            const uint32_t run = etid / MT, tk = etid % MT, wrun = blockIdx.x * (NWR / 4) + run;
+            if (run < NWR / 4 && m0 + tk < ntok && wrun * 8 < a.ntiles) {
+                const float *r4 = side + run * 4 * MT + tk;
+                a.ssq_out[(size_t)(a.out_row0 / 128 + wrun) * ntok + m0 + tk] = (r4[0] + r4[MT]) + (r4[2 * MT] + r4[3 * MT]);
             }
         }
     }

@@ -92,6 +92,9 @@ struct ps_stack {
     bool profiling = false;
     bool own_rinv_launch = false;             // decode mode 2: RMS factors always from rinv_kernel
     const void *rinv_of = nullptr;            // rows whose RMS factors the last residual epilogue or combine left in the workspace
+    const void *ssq_of = nullptr;             // rows whose sums of squares the last residual GEMM left in ssq_buf
+    float *ssq_buf = nullptr;
+    const float *ssq_use = nullptr;           // set by a PS_K_RINV op: what the matrices behind it take their RMS factors from
     uint32_t routed_layer = kNotRouted;       // MoE layer whose routing rode in an earlier launch of this forward
     static constexpr uint32_t kNotRouted = 0xFFFFFFFFu;
     std::vector<hipEvent_t> prof_ev;          // 2 per op of the last profiled forward
@@ -287,11 +290,30 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
     const RouteArgs ra{g.moe ? st->route_logits + (size_t)l * st->route_layer_stride : nullptr, M, m.n_experts, m.top_k,
                        reinterpret_cast<int32_t *>(WS + p.ws.ridx), reinterpret_cast<float *>(WS + p.ws.rw)};
     const RouteArgs *const riding = g.moe && route_rides(ra) ? &ra : nullptr;
+    // Many tokens, dense: O and down leave the sums of squares of the rows they store, per 128 columns, and the matrices
+    // behind them take their RMS factors from those (slabs of these matrices are cut at 256 rows); factors that need a
+    // launch of their own (the first layer's) are then summed in the same order
+    const bool factor_runs = MP > 64 && !g.moe && H % 256 == 0, sums_of_squares = factor_runs && !st->own_rinv_launch;
     // batched decode (2..64 tokens) of a narrow matrix: split K over blockIdx.z into fp32 partial
     // planes, then one epilogue kernel sums them in order and applies the mode's epilogue
     auto run_gemm = [&](int mode, GemmArgs a, const MatGeom &mg) -> int32_t {
         const uint32_t per = gemm_sb_per_part(mg, MP);
-        if (!per) { PS_HIP(launch_gemm(mode, a, 0, MP, cs)); return PS_OK; }
+        a.eps = m.rms_eps;
+        if (!per) {
+            if (mode != GEMM_RESID) a.ssq_in = st->ssq_use;
+            else if (sums_of_squares) {
+                // into an activation buffer that is dead until the next op but one has read them:
+                // behind O the rows that down will write, behind down those that were this layer's input (without
+                // attention that input is still down's residual, and the buffer of the attention half's output is free)
+                float *const x0 = reinterpret_cast<float *>(WS + p.ws.x0), *const x1 = reinterpret_cast<float *>(WS + p.ws.x1);
+                a.ssq_out = &mg == &g.o ? (l & 1 ? x1 : x0) : g.has_attn ? (l & 1 ? x0 : x1) : reinterpret_cast<float *>(WS + p.ws.h);
+                st->ssq_buf = a.ssq_out;
+                // (the slabs' launches together cover every column: the CPU takes parts of plans of up to 64 tokens only)
+                st->ssq_of = mg.ntiles * 16 == H ? a.out : nullptr;
+            }
+            PS_HIP(launch_gemm(mode, a, 0, MP, cs));
+            return PS_OK;
+        }
         GemmArgs pa = a;
         float *partial = reinterpret_cast<float *>(WS + p.ws.partial);
         const uint32_t ncols = a.ntiles * 16;
@@ -316,10 +338,14 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             const __half *rows = op.info.shard0 == 2 ? x_out : op.info.shard0 == 0 && g.has_attn ? xin : hbuf;   // 2: output head
             const bool have = st->rinv_of == rows;
             st->rinv_of = nullptr;
+            st->ssq_use = st->ssq_of == rows ? st->ssq_buf : nullptr;
+            st->ssq_of = nullptr;
+            if (st->ssq_use) return PS_OK;
             // the few-token kernels of QKV (factors of kind 0) and of a dense gate/up (kind 1) compute their own
             if (op.info.shard0 == 0 && few_token_gemv(p, g.qkv)) return PS_OK;
             if (op.info.shard0 == 1 && !g.moe && few_token_gemv(p, g.gate_up)) return PS_OK;
             if (have) return PS_OK;
+            if (factor_runs) { PS_HIP(launch_rinv_runs(rows, M, H, m.rms_eps, rinv, cs)); return PS_OK; }
             const bool ride = riding && op.info.shard0 == 1;
             PS_HIP(launch_rinv(rows, M, H, m.rms_eps, rinv, ride ? riding : nullptr, cs));
             if (ride) st->routed_layer = l;
@@ -639,6 +665,8 @@ int32_t run_schedule(ps_stack *st, const ps_schedule &sc, const __half *x_in, __
     }
     st->prof_valid = false;
     st->rinv_of = nullptr;
+    st->ssq_of = nullptr;
+    st->ssq_use = nullptr;
     st->routed_layer = ps_stack::kNotRouted;
     ps_stats &ss = st->stats;
     ss = ps_stats{};
@@ -1583,6 +1611,8 @@ int32_t ps_stack_time_kernel(ps_stack *st, uint32_t kernel, uint32_t reps, doubl
         for (const ps::Op &op : st->dense_sched.ops) {
             if (op.info.type != PS_OP_KERNEL || op.info.kernel != kernel || op.info.slot >= 0) continue;
             st->rinv_of = nullptr;   // timed in isolation: every launch is issued
+            st->ssq_of = nullptr;
+            st->ssq_use = nullptr;
             rc = issue_kernel(st, st->dense_sched, op, xin, xout);
             if (rc) break;
             ++n;

@@ -517,6 +517,23 @@ def test_gemm_tiles_of_every_width_give_the_same_rows(H, I, plan_tokens, counts)
     st.close()
 
 
+@pytest.mark.parametrize("H,attn,I,tokens", [(256, True, 512, 65), (768, True, 1280, 300), (2304, True, 768, 129),
+                                             (4352, False, 256, 200), (256, False, 7168, 1024), (640, True, 768, 100)])
+def test_rms_factors_from_the_sums_of_squares_of_o_and_down(H, attn, I, tokens):
+    """Plans of more than 64 tokens: O and down leave sums of squares and the matrices behind them take their RMS factors
+    from those; mode 2 gives every factor a launch of its own.  The same bits, and the oracle's rows.  Rows of 2, 6, 18 and
+    34 runs of 128 columns (16 are added at a time), with and without attention, a tile of 256 tokens, and H = 640, which
+    keeps the launch."""
+    cfg = dict(Hn.small_dense_cfg(3) if attn else S.cfg_ffn_block(), n_layers=3, hidden=H, ffn_inter=I)
+    if attn:
+        cfg.update(n_q_heads=4, n_kv_heads=2)
+    W = Hn.WeightCache(cfg, 67)
+    x = S.activations(67, 0, tokens, H)
+    outs = [Hn.run_gpu(cfg, W, 1 << 30, x, mode=mode)[0] for mode in (0, 2)]
+    np.testing.assert_array_equal(outs[0].view(np.uint16), outs[1].view(np.uint16))
+    assert Hn.rel_err(outs[0], O.stack_forward(x, cfg, W, mirror=True)) <= TOL
+
+
 def _kv_cfg(n_layers, cap):
     return dict(Hn.small_dense_cfg(n_layers), kv_context=cap)
 
