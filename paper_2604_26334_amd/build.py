@@ -7,7 +7,10 @@ compiler's own output for kernels.hip, and fails if it does not hold:
   - in every gemm_w4_kernel, a vmcnt(0) stands between the opening prefetches and the first barrier; every later stretch
     between two barriers that ends in a counted wait vmcnt(n > 0) issues exactly the loads of one
     prefetch, LDS fills first, and n is the count the kernel's ring depth implies; nothing else
-    touches vector memory inside the ring.
+    touches vector memory inside the ring;
+  - in every gemm_w4_kernel of two K parts, on every path to a write into LDS (the exchange of the parts' sums, which
+    lies over the ring's stages), a vmcnt(0) and then a barrier stand behind the last LDS fill: no wave's fill can
+    land on another wave's sums.
 """
 import os
 import re
@@ -96,6 +99,51 @@ def gemm_wait_counts(mt, nw, at=2, ks=1):
     return lpi, nfill, land * lpi + (at if early else 0)
 
 
+def lds_writes_behind_fills(body):
+    """LDS writes of a kernel's text that some path reaches while a fill (a load straight into LDS) may still be in flight
+    in this or another wave.  Per path: a fill leaves 2, vmcnt(0) turns 2 into 1 (this wave's have landed), a barrier
+    turns 1 into 0 (everyone's have: all waves run the same steps).  A counted wait changes nothing."""
+    blocks, order, cur = {"": []}, [""], ""
+    for ln in body.splitlines():
+        ln = ln.split(";")[0].strip()
+        m = re.match(r"(\.\w+):$", ln)
+        if m:
+            cur = m.group(1)
+            blocks[cur] = []
+            order.append(cur)
+        elif ln and not ln.startswith("."):
+            blocks[cur].append(ln)
+    bad, seen, todo = [], {}, [("", 0)]
+    while todo:
+        name, state = todo.pop()
+        if seen.get(name, -1) >= state:
+            continue
+        seen[name] = state
+        falls = True
+        for ln in blocks[name]:
+            ins = ln.split()[0]
+            if ins.startswith("buffer_load") and re.search(r"\blds\b", ln):
+                state = 2
+            elif ins == "s_waitcnt" and re.search(r"vmcnt\(0\)", ln):
+                state = min(state, 1)
+            elif ins == "s_barrier":
+                state = 0 if state == 1 else state
+            elif ins.startswith("ds_write") and state:
+                bad.append(ln)
+            elif ins.startswith("s_cbranch"):
+                todo.append((ln.split()[-1], state))
+            elif ins == "s_branch":
+                todo.append((ln.split()[-1], state))
+                falls = False
+                break
+            elif ins == "s_endpgm":
+                falls = False
+                break
+        if falls and order.index(name) + 1 < len(order):
+            todo.append((order[order.index(name) + 1], state))
+    return sorted(set(bad))
+
+
 def check_gemm_isa(path):
     """The invariant behind the GEMM's hand-counted waits, read off the generated code."""
     txt = open(path).read()
@@ -155,6 +203,10 @@ def check_gemm_isa(path):
                     bad.append(mangled + ": a ring step touches vector memory with something other than its prefetch")
         if steps == 0:
             bad.append(mangled + ": no ring step recognised")
+        if ks == 2:
+            over = lds_writes_behind_fills(body)
+            if over:
+                bad.append("%s: %d writes into LDS with a fill of the ring possibly in flight, e.g. %s" % (mangled, len(over), over[0]))
     if bad:
         raise RuntimeError("build check: the GEMM's counted waits do not match the generated code:\n  " + "\n  ".join(bad))
     return len(funcs)

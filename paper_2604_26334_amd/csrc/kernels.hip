@@ -1892,7 +1892,18 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(elane));   // (volatile: computed here, not before the ring)
 #endif
     const uint32_t etid = ((uint32_t)kpart * NWR + wave_u) * 64 + elane;
-    // (the last step's barrier is behind every wave: the stages are free)
+    // The last step's barrier is behind every wave, so no stage is read any more.  But where the walk ends in a whole turn
+    // of the ring, its last step has issued a fill past the walk's end, into stage R - 2, and passed the barrier with it
+    // in flight (up to one prefetch with DEPTH > 1).  Without K parts that harms nothing: what is written below lies in
+    // stage 0.  The exchange of two K parts covers stages 0 and 1, written by the waves of part 1 while the fill belongs
+    // to a wave of part 0: every wave lets its own land, then all meet.  (Gate/up of 28672
+    // rows, 64 tokens: K = 4096 24.6 us without and with the wait; K = 3072, whose halves end in a whole turn, 19.8 us
+    // with it.)
+    if constexpr (KS == 2 && DEPTH > 1) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
     float *const side = reinterpret_cast<float *>(lds) + (KS == 2 ? NWR * AT * NMT * 256 : 0);   // RMS factors of the tile's tokens / sums of squares
     if constexpr (FACTORS) {
         if (etid < MT) {

@@ -488,11 +488,16 @@ def test_one_stack_serves_the_prefill_tier_and_the_decode_tier(kind):
                                                     (4096, 768, 1024, (1024, 870, 760, 630, 500, 380, 250)),
                                                     (1152, 1408, 320, (320, 129)),
                                                     (256, 14336, 64, (64, 48, 33, 32, 17, 16, 5)),
-                                                    (640, 14336, 48, (48, 31, 3)), (1024, 2816, 64, (64, 47, 9))])
+                                                    (640, 14336, 48, (48, 31, 3)), (1024, 2816, 64, (64, 47, 9)),
+                                                    (1536, 14336, 64, (64, 48, 32, 16)), (3072, 14336, 48, (48, 32, 9)),
+                                                    (768, 14336, 64, (64, 33, 16)), (3072, 3584, 384, (384, 300, 200, 160, 128, 20)),
+                                                    (1536, 3584, 384, (384, 300, 200, 160, 128))])
 def test_gemm_tiles_of_every_width_give_the_same_rows(H, I, plan_tokens, counts):
     """The GEMM's token tile (16 to 256) goes by the rows of the trip, the K parts inside a workgroup and the partial
     planes by the matrix and the plan.  The full trip against the oracle; every shorter one must give the same
-    bits for its rows.  K of 2, 5, 8, 9, 10, 11, 16 and 56 super-blocks (shorter and longer than the prefetch ring)."""
+    bits for its rows.  K of 2, 5, 8, 9, 10, 11, 16 and 56 super-blocks (shorter and longer than the prefetch ring), and of
+    6, 12 and 24, whose halves end in a whole turn of the ring of three that the tiles of up to 64 tokens have (384 and
+    300 rows of the last two go in tiles of 96 and 80, whose ring has two: the same bits)."""
     import torch
     from paper_2604_26334_amd import binding as B
     cfg = dict(S.cfg_ffn_block(), hidden=H, ffn_inter=I)

@@ -885,3 +885,32 @@ def test_build_check_of_the_gemm_wait_counts(tmp_path):
             Bd.check_resource_usage(clean + gather % lds)
     with pytest.raises(RuntimeError):
         Bd.check_resource_usage(clean)
+
+
+@pytest.mark.parametrize("behind,ok", [
+    ([], False),                                                    # the ring may end in a whole turn: its last fill is in flight
+    (["drain"], False),                                             # this wave's fills have landed, another wave's need not have
+    (["barrier"], False),
+    (["barrier", "drain"], False),
+    (["drain", "barrier"], True),
+    (["skip", "drain", "barrier", "label"], False),                 # (as behind the steps that follow the last whole turn)
+    (["skip", "label", "drain", "barrier"], True),
+    (["drain", "barrier", "fill"], False),
+])
+def test_build_check_of_the_exchange_between_two_k_parts(tmp_path, behind, ok):
+    """A GEMM of two K parts passes one part's sums through LDS that the ring's stages lie in: the build refuses code in
+    which any path reaches those writes without a vmcnt(0) and then a barrier behind the last fill."""
+    from paper_2604_26334_amd import build as Bd
+    assert Bd.gemm_wait_counts(64, 8, ks=2) == (6, 4, 6) and Bd.gemm_wait_counts(96, 8, ks=2) == (8, 6, 0)
+    lds, w4 = "\tbuffer_load_dwordx4 v1, s[4:7], 0 offen lds\n", "\tbuffer_load_dwordx4 v[2:5], v1, s[4:7], 0 offen\n"
+    text = {"drain": "\ts_waitcnt vmcnt(0)\n", "barrier": "\ts_barrier\n", "fill": lds, "skip": "\ts_cbranch_scc1 .LBB0_3\n", "label": ".LBB0_3:\n"}
+    step = lds + w4 + w4 + "\ts_waitcnt vmcnt(3) lgkmcnt(0)\n\ts_barrier\n"
+    p = tmp_path / "k.s"
+    p.write_text("_ZN2ps14gemm_w4_kernelILi1ELi2ELi16ELb0ELi8ELi2EEEvNS_8GemmArgsE: ; @x\n" + lds + w4 + w4 + "\ts_waitcnt vmcnt(0)\n\ts_barrier\n"
+                 ".LBB0_1: ; the ring\n" + step + step + "\ts_cbranch_scc0 .LBB0_1\n" + "".join(text[b] for b in behind) +
+                 "\tds_write_b128 v1, v[2:5]\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier\n\tglobal_store_dword v[8:9], v7, off\n\ts_endpgm\n.Lfunc_end0:\n")
+    if ok:
+        assert Bd.check_gemm_isa(str(p)) == 1
+    else:
+        with pytest.raises(RuntimeError, match="possibly in flight"):
+            Bd.check_gemm_isa(str(p))
