@@ -122,12 +122,12 @@ struct AttnArgs {
 // tokens' QKV rows (k_own / v_own = kv head 0 of token 0, own_stride elements between tokens).  One launch per run of
 // cache shards.  nsplit == 1: finished rows out[t][q_head * 128 ..]; > 1: records
 // part[((t * n_q + q_head) * nsplit + split) * 130] (maximum, weight sum, 128 sums) for launch_attn_combine_chunk.
-// nsplit and rounds_per_split come from attn_chunk_deal.
+// nsplit and rounds_per_split come from attn_chunk_deal.  few: the weights in fp32's precision (fewer than 16 score rows).
 struct AttnChunkArgs {
     const __half *k_base;
     uint64_t head_stride;
     uint32_t cap, ctx, head0, nheads, group, n_q;
-    uint32_t ntok, q_stride, nsplit, rounds_per_split;
+    uint32_t ntok, q_stride, nsplit, rounds_per_split, few;
     const __half *k_own, *v_own;
     uint32_t own_stride;
     __half *out;

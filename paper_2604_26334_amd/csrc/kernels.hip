@@ -998,6 +998,12 @@ __global__ __launch_bounds__(kAttnWaves * 64, 16 / kAttnWaves) void attn_decode_
 // attn_combine_chunk_kernel merges in split order; without SPLIT the finished rows are written.  The deal goes by
 // context, the plan's token count and the whole model's heads, never by the launch's, so the result does not
 // depend on where a cache shard lives.
+// FEW: fewer than 16 score rows, i.e. one row tile of the two.  Its softmax weights keep fp32's precision, as the
+// one-token kernel's do: a weight (times 2^15, which leaves the remainders room and drops out in o / l) goes into the value
+// product as three fp16 numbers, its rounding and what is left of it twice.  The remainders' sums are kept apart and
+// added at the end.  One wave of each pair has rows, so the MFMAs are fewer than with full tiles, and the time is
+// the fills' and the latencies'.  2 tokens over 4000 positions 8.3 us with the weights in fp16, 8.3 with three parts;
+// 3 tokens over 1000 7.9 / 7.9.
 // Measured, 32 query / 8 kv heads over 4096 cached positions: 512 tokens 108 -> 73 us (37 rounds of 1.9 us; the
 // row fills alone take 41, the rest without them 50); 64 tokens 24 + 10 us (cache and own rows in two launches of a
 // kernel that kept 256 positions per workgroup) -> 17 us.
@@ -1015,8 +1021,9 @@ static_assert(2 * kAttnStageBytes <= 4 * 64 * kAttnOPitch * 4 && kAttnRowsLds <=
 __device__ __forceinline__ uint32_t k_swz(uint32_t row) { return (row & 3u) | (((row >> 3) & 3u) << 2); }
 __device__ __forceinline__ uint32_t v_swz(uint32_t row) { return ((row & 3u) | (((row >> 3) & 1u) << 2)) << 1; }
 
-template <bool SPLIT>
+template <bool SPLIT, bool FEW>
 __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
+    constexpr int NT = FEW ? 1 : 2;      // row tiles of a wave that hold rows
     extern __shared__ uint4 at_lds[];
     unsigned char *lds = reinterpret_cast<unsigned char *>(at_lds);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1058,10 +1065,10 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
     if (rd0 < rd1) stage(rd0, 0);
 
     // the wave's 32 query rows (B operands of the score MFMAs)
-    uint32_t tok[2], hq[2];
-    h8_t q[2][4];
+    uint32_t tok[NT], hq[NT];
+    h8_t q[NT][4];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < NT; ++t) {
         const uint32_t rho = min(row0 + r2 * 32 + t * 16 + i, R - 1);
         tok[t] = rho / G; hq[t] = rho % G;
         const __half *qr = a.q + (size_t)tok[t] * a.q_stride + (size_t)(q0 + hq[t]) * 128 + c * 8;
@@ -1070,7 +1077,10 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
     }
     // weights are 2^(c2 s - c2 m) of the raw scores s = q.k: 1 / sqrt(128) and log2(e) in one factor
     const float c2 = 0.08838834764831845f * 1.4426950408889634f;
-    float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};   // l_run: this lane's positions only
+    constexpr float up = FEW ? 32768.f : 1.f;  // weights are held as `up` times what they are
+    float m_run[NT], l_run[NT];                // l_run: this lane's positions only
+#pragma unroll
+    for (int t = 0; t < NT; ++t) { m_run[t] = -INFINITY; l_run[t] = 0.f; }
     f4_t O[2][8];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -1099,11 +1109,11 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
         const uint32_t P0 = (own ? rd - nr_cache : rd) * kAttnRound + 32 * pg;    // the wave's first position
         // (uniform) the wave's positions all lie past what its rows see
         const uint32_t last_seen = own ? min(a.ntok - 1, (row0 + r2 * 32 + 31) / G) : a.ctx - 1;
-        if (P0 > last_seen) continue;
+        if (P0 > last_seen || (FEW && r2)) continue;
         const unsigned char *st = lds + buf * kAttnStageBytes;
-        f4_t S[2][2];
+        f4_t S[NT][2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int T = 0; T < 2; ++T) S[t][T] = f4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1112,12 +1122,12 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
             for (int kk = 0; kk < 4; ++kk) {
                 const h8_t kr = __builtin_bit_cast(h8_t, *reinterpret_cast<const uint4 *>(st + koff[kk] + T * 1024));
 #pragma unroll
-                for (int t = 0; t < 2; ++t) S[t][T] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kr, q[t][kk], S[t][T], 0, 0, 0);
+                for (int t = 0; t < NT; ++t) S[t][T] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kr, q[t][kk], S[t][T], 0, 0, 0);
             }
         // positions a row does not see: only the cache's last round and the own rounds can hold any
         if (own || P0 + 32 > a.ctx) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < NT; ++t) {
                 const uint32_t limit = own ? tok[t] + 1 : a.ctx;
 #pragma unroll
                 for (int T = 0; T < 2; ++T)
@@ -1125,52 +1135,70 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
                     for (int r = 0; r < 4; ++r) S[t][T][r] = P0 + 8 * c + 4 * T + r < limit ? S[t][T][r] : -INFINITY;
             }
         }
-        float mx[2];
+        float mx[NT];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int t = 0; t < NT; ++t) {
             mx[t] = fmaxf(fmaxf(fmaxf(S[t][0][0], S[t][0][1]), fmaxf(S[t][0][2], S[t][0][3])),
                           fmaxf(fmaxf(S[t][1][0], S[t][1][1]), fmaxf(S[t][1][2], S[t][1][3])));
             mx[t] = fmaxf(m_run[t], rows4_meet<true>(mx[t]));
         }
         // some row's maximum rose: rescale (a row that has seen nothing holds zeros, and the difference of two
         // -inf is not a number)
-        if (__any(mx[0] > m_run[0] || mx[1] > m_run[1])) {
+        if (__any(mx[0] > m_run[0] || mx[NT - 1] > m_run[NT - 1])) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < NT; ++t) {
                 const float resc = m_run[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run[t] - mx[t]) * c2);
                 m_run[t] = mx[t];
                 l_run[t] *= resc;
 #pragma unroll
-                for (int dt = 0; dt < 8; ++dt) O[t][dt] = O[t][dt] * resc;
+                for (int dt = 0; dt < 8; ++dt) {
+                    O[t][dt] = O[t][dt] * resc;
+                    if (FEW) O[1][dt] = O[1][dt] * resc;
+                }
             }
         }
-        h8_t P[2];
+        h8_t P[FEW ? 3 : 2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int t = 0; t < NT; ++t) {
             const float ms = m_run[t] == -INFINITY ? 0.f : m_run[t] * c2;
             float pv[8];
 #pragma unroll
             for (int T = 0; T < 2; ++T)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    pv[4 * T + r] = __builtin_amdgcn_exp2f(fmaf(S[t][T][r], c2, -ms));
+                    pv[4 * T + r] = __builtin_amdgcn_exp2f(fmaf(S[t][T][r], c2, -ms)) * up;
                     l_run[t] += pv[4 * T + r];
                 }
             P[t] = h8_t{(_Float16)pv[0], (_Float16)pv[1], (_Float16)pv[2], (_Float16)pv[3],
                         (_Float16)pv[4], (_Float16)pv[5], (_Float16)pv[6], (_Float16)pv[7]};
+            if (FEW) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float rest = pv[e] - (float)P[0][e];
+                    P[1][e] = (_Float16)rest;
+                    P[FEW ? 2 : 1][e] = (_Float16)(rest - (float)P[1][e]);
+                }
+            }
         }
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) {
             const h8_t vr = v_operand(st + voff[dt]);
 #pragma unroll
             for (int t = 0; t < 2; ++t) O[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vr, P[t], O[t][dt], 0, 0, 0);
+            if (FEW) O[1][dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vr, P[FEW ? 2 : 1], O[1][dt], 0, 0, 0);
         }
     }
     // the four position groups of a row meet: every wave leaves its rows, maxima and sums in LDS
     __syncthreads();     // the last stage's reads are behind everyone
     float *ob = reinterpret_cast<float *>(lds), *om = ob + 4 * 64 * kAttnOPitch, *ol = om + 4 * 64;
+    if (FEW) {   // (an infinite value makes the remainders' sum NaN, where the weights' own has the infinity)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+        for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) O[0][dt][r] = fabsf(O[0][dt][r]) < INFINITY ? O[0][dt][r] + O[1][dt][r] : O[0][dt][r];
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
         const float l = rows4_meet<false>(l_run[t]);
         const uint32_t row = r2 * 32 + t * 16 + i;
         float *dst = ob + (pg * 64 + row) * kAttnOPitch + 4 * c;   // lane (row i, group c) holds dims 16 dt + 4 c + r
@@ -1232,23 +1260,26 @@ void attn_chunk_deal(uint32_t ctx, uint32_t plan_tokens, uint32_t group, uint32_
     *nsplit = (rounds + per - 1) / per;
 }
 
+template <bool SPLIT, bool FEW>
+static hipError_t launch_attn_chunk_k(const AttnChunkArgs &a, dim3 grid, hipStream_t st) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_chunk_kernel<SPLIT, FEW>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAttnRowsLds);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL((attn_chunk_kernel<SPLIT, FEW>), grid, dim3(512), kAttnRowsLds, st, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_attn_chunk(const AttnChunkArgs &a, hipStream_t st) {
     if (a.nheads == 0 || a.ntok == 0) return hipSuccess;
     if (a.group == 0 || a.group > 16 || !a.k_own || !a.v_own || a.nsplit == 0) return hipErrorInvalidValue;
+    if (a.few && a.ntok * a.group >= 16) return hipErrorInvalidValue;
     const uint32_t rounds = (a.ctx + kAttnRound - 1) / kAttnRound + (a.ntok + kAttnRound - 1) / kAttnRound;
     if ((uint64_t)a.nsplit * a.rounds_per_split < rounds || (a.nsplit > 1 ? !a.part : !a.out)) return hipErrorInvalidValue;
     // 32-bit buffer offsets
     if (((uint64_t)a.ctx + kAttnRound) * 256u > 0x7FFFFFFFull || ((uint64_t)a.ntok + kAttnRound) * a.own_stride * 2u > 0x7FFFFFFFull) return hipErrorInvalidValue;
     dim3 grid(a.nheads, (a.ntok * a.group + 63) / 64, a.nsplit);
-    static const hipError_t attr_s = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_chunk_kernel<true>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAttnRowsLds);
-    static const hipError_t attr_f = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_chunk_kernel<false>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAttnRowsLds);
-    if (attr_s != hipSuccess) return attr_s;
-    if (attr_f != hipSuccess) return attr_f;
-    if (a.nsplit > 1) hipLaunchKernelGGL(attn_chunk_kernel<true>, grid, dim3(512), kAttnRowsLds, st, a);
-    else hipLaunchKernelGGL(attn_chunk_kernel<false>, grid, dim3(512), kAttnRowsLds, st, a);
-    return hipGetLastError();
+    return a.few ? a.nsplit > 1 ? launch_attn_chunk_k<true, true>(a, grid, st) : launch_attn_chunk_k<false, true>(a, grid, st)
+                 : a.nsplit > 1 ? launch_attn_chunk_k<true, false>(a, grid, st) : launch_attn_chunk_k<false, false>(a, grid, st);
 }
 
 // the tokens' K and V rows go to positions ctx .. ctx + ntok - 1 of each kv head's cache home

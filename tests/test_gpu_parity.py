@@ -763,6 +763,63 @@ def test_chunk_attention_at_the_edges_of_its_rounds_and_row_blocks(n_q, n_kv, ct
     assert np.isfinite(got).all() and all(Hn.rel_err(got, r) <= TOL for r in refs)
 
 
+@pytest.mark.parametrize("n_q,n_kv,M", [(8, 2, 2), (8, 2, 3), (2, 2, 15), (8, 1, 1)])
+@pytest.mark.parametrize("ctx0", [60, 500, 4096])
+def test_short_chunks_weigh_their_values_in_fp32_precision(n_q, n_kv, M, ctx0):
+    """Chunks of fewer than 16 score rows: the softmax weights are not rounded to fp16.  The cached values are made so
+    that every row's weighted sum of them all but cancels (large random rows, less their projection on the rows' own
+    weights): what remains shows the weights' error, next to which the fp16 stores of the attention row and of h are
+    small.  Against float64 on the rows' own QKV; the yardstick is the error that weights rounded to fp16 (relative to the
+    row's largest) make.  Ragged: M rows through a plan of 20."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(_kv_cfg(1, ctx0 + 24), n_q_heads=n_q, n_kv_heads=n_kv)
+    W = Hn.WeightCache(cfg, 83)
+    K, V = S.kv_cache(83, 0, n_kv, ctx0, 128)
+    K = (K * np.float16(0.15)).astype(np.float16)         # weights of many positions matter
+    x = S.activations(83, 0, M, cfg["hidden"])
+    st = B.Stack(B.Plan(cfg, 1 << 30, 20))
+    for k, ex, N, Kd in S.matrix_shapes(cfg):
+        st.load_matrix(0, k, ex, *W(0, k, ex))
+    xin = torch.from_numpy(x).to(st.device)
+
+    def forward():
+        for g in range(n_kv):
+            st.load_kv(0, g, K[g], V[g])
+        xout = torch.zeros_like(xin)
+        st.set_context(ctx0)
+        B.chunked_forward(st, xin, xout)
+        st.synchronize()
+
+    forward()
+    G = n_q // n_kv
+    qkv = st.debug_buffer(0, np.float16, (M, (n_q + 2 * n_kv) * 128)).astype(np.float64).reshape(M, -1, 128)
+    weights = []                                              # per kv head: unnormalised [M * G][ctx0 + M]
+    for g in range(n_kv):
+        keys = np.concatenate([K[g].astype(np.float64), qkv[:, n_q + g]])
+        sc = np.einsum("thd,pd->thp", qkv[:, g * G:(g + 1) * G], keys) / np.sqrt(128.0)
+        sc = np.where(np.arange(ctx0 + M) <= ctx0 + np.arange(M)[:, None, None], sc, -np.inf).reshape(M * G, -1)
+        weights.append(np.exp(sc - sc.max(axis=1, keepdims=True)))
+        P = weights[g][:, :ctx0]
+        v = 8000.0 * np.random.default_rng(ctx0 + g).standard_normal((ctx0, 128))
+        V[g] = (v - P.T @ np.linalg.solve(P @ P.T, P @ v)).astype(np.float16)
+    forward()
+    h = st.debug_buffer(1, np.float16, (M, cfg["hidden"])).astype(np.float64)
+    st.close()
+
+    def h_of(rounded):
+        A = np.empty((M, n_q, 128))
+        for g in range(n_kv):
+            vals = np.concatenate([V[g].astype(np.float64), qkv[:, n_q + n_kv + g]])
+            w = weights[g].astype(np.float16).astype(np.float64) if rounded else weights[g]
+            A[:, g * G:(g + 1) * G] = (w @ vals / weights[g].sum(axis=1, keepdims=True)).reshape(M, G, 128)
+        return x.astype(np.float64) + O.linear(A.reshape(M, -1), *W(0, S.MAT_O, None))
+
+    err, err16 = np.linalg.norm(h - h_of(False)), np.linalg.norm(h_of(True) - h_of(False))
+    _say("rows", M * G, "ctx", ctx0, "error %.3e, of weights in fp16 %.3e" % (err, err16))
+    assert np.isfinite(h).all() and err <= 0.1 * err16
+
+
 def test_chunked_prefill_fills_the_cache_it_then_decodes_over():
     """150 prompt tokens through a 64-token tier of a stack with a KV cache (three trips, each attending
     over the cache and the rows the earlier trips appended), then decode steps over the filled cache.
