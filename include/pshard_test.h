@@ -38,7 +38,8 @@ int32_t ps_stack_time_kernel(ps_stack *st, uint32_t kernel, uint32_t reps, doubl
                              uint32_t *launches);
 /* device pointers into the workspace for inspection by tests (fp16 unless noted):
  * which = 0: QKV [M][qkv_w], 1: h [M][H], 2: s [M][I] or [M*top_k][I_e],
- * 3: route idx int32 [M][top_k], 4: route weights fp32 [M][top_k] */
+ * 3: route idx int32 [M][top_k], 4: route weights fp32 [M][top_k],
+ * 5: attention rows [M][n_q_heads * head_dim] (stacks with a KV cache) */
 int32_t ps_stack_debug_buffer(ps_stack *st, uint32_t which, void **dev_ptr, uint64_t *bytes);
 /* Diagnostic: one v_mfma_f32_16x16x32_f16 with A = unit at (row pi, k pk) and B = unit at
  * (k pk, column pj); out_dev: device fp32 [64 lanes][4 registers] receives the accumulator.

@@ -1045,7 +1045,8 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
     const __half *vc = kc + (size_t)a.cap * 128;
     const __half *ko = a.k_own + (size_t)kv_head * 128, *vo = a.v_own + (size_t)kv_head * 128;
     // a round's rows straight into LDS: wave w moves rows 16 w .. + 15 of K and of V, four rows per instruction;
-    // positions past the end re-read the last row (their weights are zero)
+    // positions past the end lie past the buffer's range, whose check returns zeros (their weights are zero, and an
+    // infinite value in a row read in their place would make NaN of that)
     auto stage = [&](uint32_t rd, uint32_t buf) {
         const bool own = rd >= nr_cache;
         const uint32_t row_b = own ? a.own_stride * 2u : 256u, npos = own ? a.ntok : a.ctx;
@@ -1057,7 +1058,7 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
 #pragma unroll
         for (uint32_t t = 0; t < 4; ++t) {
             const uint32_t row = wave * 16 + t * 4 + c;
-            const uint32_t off = min(P0 + row, npos - 1) * row_b;
+            const uint32_t off = (P0 + row) * row_b;
             load_to_lds16(kb, (lds_void *)(dk + t * 1024), off + ((i ^ k_swz(row)) << 4), 0);
             load_to_lds16(vb, (lds_void *)(dv + t * 1024), off + ((i ^ v_swz(row)) << 4), 0);
         }
@@ -1328,9 +1329,9 @@ __global__ __launch_bounds__(128) void attn_combine_chunk_kernel(const float *pa
         mx = m8;
 #pragma unroll
         for (uint32_t u = 0; u < 8; ++u) {
-            const float w = c0 + u < nsplit ? __expf(mv[u] - ms) : 0.f;
-            L = fmaf(w, lv[u], L);
-            o = fmaf(w, ov[u], o);
+            const float w = __expf(mv[u] - ms);
+            L = c0 + u < nsplit ? fmaf(w, lv[u], L) : L;   // (left out, not weighed with zero: a sum may be infinite)
+            o = c0 + u < nsplit ? fmaf(w, ov[u], o) : o;
         }
     }
     out[(size_t)t * out_stride + (size_t)h * 128 + d] = to_half(o / L);
@@ -1379,7 +1380,7 @@ hipError_t launch_attn_decode(const AttnArgs &a, hipStream_t st) {
 // wave w sums chunks [w per, (w + 1) per) of the weighted values, two dimensions per lane, and the eight sums meet in
 // order.  It is a chain of latencies, nothing else (1 MB of records at a 16K context): everything that does not depend
 // on a reduction -- the token's rows, the first maxima and sums, the first eight records of every wave -- is
-// requested at once and without a branch (a chunk past the end re-reads the last one and weighs nothing), the token's own
+// requested at once and without a branch (a chunk past the end re-reads the last one and is left out), the token's own
 // score is worked out by every wave for itself, and three barriers remain.  At 63 chunks 7.4 -> 4.7 us (the former
 // version's last, shorter quarter of the chunks was read one record at a time).
 constexpr uint32_t kAttnMaxChunks = 8192;   // 1M positions
@@ -1435,9 +1436,9 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(const float *part, ui
     if (c0 < c1) {
 #pragma unroll
         for (uint32_t u = 0; u < 8; ++u) {
-            const float w = c0 + u < c1 ? wbuf[min(c0 + u, last)] : 0.f;
-            o.x = fmaf(w, v0[u].x, o.x);
-            o.y = fmaf(w, v0[u].y, o.y);
+            const float w = wbuf[min(c0 + u, last)];
+            o.x = c0 + u < c1 ? fmaf(w, v0[u].x, o.x) : o.x;
+            o.y = c0 + u < c1 ? fmaf(w, v0[u].y, o.y) : o.y;
         }
         for (uint32_t c = c0 + 8; c < c1; c += 8) {
             float2 v[8];
@@ -1445,9 +1446,9 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(const float *part, ui
             for (uint32_t u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float2 *>(ph + (size_t)min(c + u, last) * 130 + 2 + 2 * lane);
 #pragma unroll
             for (uint32_t u = 0; u < 8; ++u) {
-                const float w = c + u < c1 ? wbuf[min(c + u, last)] : 0.f;
-                o.x = fmaf(w, v[u].x, o.x);
-                o.y = fmaf(w, v[u].y, o.y);
+                const float w = wbuf[min(c + u, last)];
+                o.x = c + u < c1 ? fmaf(w, v[u].x, o.x) : o.x;
+                o.y = c + u < c1 ? fmaf(w, v[u].y, o.y) : o.y;
             }
         }
     }

@@ -1646,6 +1646,7 @@ int32_t ps_stack_debug_buffer(ps_stack *st, uint32_t which, void **dev_ptr, uint
         case 2: *dev_ptr = st->ws_base + p.ws.s; *bytes = p.ws.s_bytes; return PS_OK;
         case 3: if (!p.g.moe) break; *dev_ptr = st->ws_base + p.ws.ridx; *bytes = P * 4; return PS_OK;
         case 4: if (!p.g.moe) break; *dev_ptr = st->ws_base + p.ws.rw; *bytes = P * 4; return PS_OK;
+        case 5: if (!p.g.kv) break; *dev_ptr = st->ws_base + p.ws.attn; *bytes = (uint64_t)p.M * p.g.attn_w * 2; return PS_OK;
     }
     ps::set_error("no such debug buffer");
     return PS_E_ARG;

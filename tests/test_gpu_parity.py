@@ -820,6 +820,38 @@ def test_short_chunks_weigh_their_values_in_fp32_precision(n_q, n_kv, M, ctx0):
     assert np.isfinite(h).all() and err <= 0.1 * err16
 
 
+@pytest.mark.parametrize("n_q,n_kv,plan_tokens,M,ctx0,at", [(2, 2, 1, 1, 2304, 1283), (2, 2, 1, 1, 2304, 2303), (2, 2, 1, 1, 4352, 300),
+                                                           (2, 2, 1, 1, 61, 60), (2, 2, 2, 2, 61, 60), (4, 2, 20, 1, 300, 299),
+                                                           (4, 2, 20, 20, 300, 299), (4, 2, 20, 20, 130, 5), (8, 8, 255, 20, 4096, 3973),
+                                                           (8, 8, 255, 255, 4090, 4089), (4, 2, 300, 300, 200, 199), (4, 2, 300, 300, 300, 100)])
+def test_an_infinite_value_in_the_cache_reaches_the_rows_that_see_it(n_q, n_kv, plan_tokens, M, ctx0, at):
+    """One infinite V entry: every token sees its position with a weight above zero, so its attention rows of that kv head
+    are infinite in that dimension and finite elsewhere.  At the end of the cached rows, where a round is partly empty, in
+    the row whose place in LDS is part of a later round's empty rows, and in records whose neighbours' merge reads them
+    without using them."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(_kv_cfg(1, ctx0 + M + 3), n_q_heads=n_q, n_kv_heads=n_kv)
+    W = Hn.WeightCache(cfg, 89)
+    K, V = S.kv_cache(89, 0, n_kv, ctx0, 128)
+    K = (K * np.float16(0.1)).astype(np.float16)          # no weight underflows
+    V[0, at, 7] = np.inf
+    x = S.activations(89, 0, M, cfg["hidden"])
+    st = B.Stack(B.Plan(cfg, 1 << 30, plan_tokens))
+    for k, ex, N, Kd in S.matrix_shapes(cfg):
+        st.load_matrix(0, k, ex, *W(0, k, ex))
+    for g in range(n_kv):
+        st.load_kv(0, g, K[g], V[g])
+    xin = torch.from_numpy(x).to(st.device)
+    st.set_context(ctx0)
+    B.chunked_forward(st, xin, torch.zeros_like(xin))
+    a = st.debug_buffer(5, np.float16, (M, n_q, 128)).copy()
+    st.close()
+    where = np.zeros(a.shape, bool)
+    where[:, :n_q // n_kv, 7] = True
+    assert (a[where] == np.inf).all() and np.isfinite(a[~where]).all()
+
+
 def test_chunked_prefill_fills_the_cache_it_then_decodes_over():
     """150 prompt tokens through a 64-token tier of a stack with a KV cache (three trips, each attending
     over the cache and the rows the earlier trips appended), then decode steps over the filled cache.
