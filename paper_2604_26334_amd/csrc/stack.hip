@@ -406,9 +406,6 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                 attn_chunk_deal(c.ctx, MP, c.group, m.n_kv_heads, &c.nsplit, &c.rounds_per_split);
                 // the last rows of a chunk, or a chunk of a few (a longer plan's stay as they are whatever comes with them)
                 c.few = MP < kAttnOnePassTokens && M * c.group < 16;
-                // (plans below kAttnOnePassTokens: groups of 1, 2, 4 or 8 query heads when there are fewer than 16 score rows)
-                if (MP < kAttnOnePassTokens && M * c.group < 16 && c.group != 1 && c.group != 2 && c.group != 4 && c.group != 8)
-                    PS_HIP(hipErrorInvalidValue);
                 PS_HIP(launch_attn_chunk(c, cs));
                 return PS_OK;
             }

@@ -820,6 +820,36 @@ def test_short_chunks_weigh_their_values_in_fp32_precision(n_q, n_kv, M, ctx0):
     assert np.isfinite(h).all() and err <= 0.1 * err16
 
 
+@pytest.mark.parametrize("n_q,n_kv,plan_tokens,M", [(6, 2, 20, 22), (7, 1, 16, 17), (5, 1, 3, 5), (12, 1, 16, 33), (3, 1, 300, 301)])
+def test_a_ragged_last_trip_runs_with_any_number_of_heads_per_kv_head(n_q, n_kv, plan_tokens, M):
+    """Trips of plan_tokens over a cache of 130 positions, the last of one or two tokens (3 to 14 score rows per kv head,
+    of 3, 5, 7 and 12 query heads): every trip runs, and the rows are the oracle's."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    ctx0 = 130
+    cfg = dict(_kv_cfg(1, ctx0 + M + 3), n_q_heads=n_q, n_kv_heads=n_kv)
+    W = Hn.WeightCache(cfg, 97)
+    K, V = S.kv_cache(97, 0, n_kv, ctx0, 128)
+    oK = np.zeros((n_kv, cfg["kv_context"], 128), np.float16)
+    oV = np.zeros_like(oK)
+    oK[:, :ctx0], oV[:, :ctx0] = K, V
+    x = S.activations(97, 0, M, cfg["hidden"])
+    ref = O.stack_forward(x, cfg, W, mirror=True, kv=lambda _l: (oK, oV), ctx=ctx0)
+    st = B.Stack(B.Plan(cfg, 1 << 30, plan_tokens))
+    for k, ex, N, Kd in S.matrix_shapes(cfg):
+        st.load_matrix(0, k, ex, *W(0, k, ex))
+    for g in range(n_kv):
+        st.load_kv(0, g, K[g], V[g])
+    xin = torch.from_numpy(x).to(st.device)
+    xout = torch.zeros_like(xin)
+    st.set_context(ctx0)
+    B.chunked_forward(st, xin, xout)
+    st.synchronize()
+    got = xout.cpu().numpy()
+    st.close()
+    assert np.isfinite(got).all() and Hn.rel_err(got, ref) <= TOL
+
+
 @pytest.mark.parametrize("n_q,n_kv,plan_tokens,M,ctx0,at", [(2, 2, 1, 1, 2304, 1283), (2, 2, 1, 1, 2304, 2303), (2, 2, 1, 1, 4352, 300),
                                                            (2, 2, 1, 1, 61, 60), (2, 2, 2, 2, 61, 60), (4, 2, 20, 1, 300, 299),
                                                            (4, 2, 20, 20, 300, 299), (4, 2, 20, 20, 130, 5), (8, 8, 255, 20, 4096, 3973),
