@@ -65,8 +65,9 @@ struct CopyDesc {
 // one launch copies `n` shards (descs may live in pinned host memory): the GPU pulls them over
 // PCIe itself, which avoids the per-call cost of many small hipMemcpyAsync
 hipError_t launch_h2d_gather(const CopyDesc *descs, uint32_t n, hipStream_t st);
-// a small block of pinned host memory -> device (both 16-byte aligned, bytes a multiple of 16)
-hipError_t launch_upload_tables(const void *src, void *dst, uint64_t bytes, hipStream_t st);
+// small blocks of pinned host memory -> device, at the same places: bytes 0 .. first - 1 and second_at .. second_at + second - 1
+// (everything a multiple of 16)
+hipError_t launch_upload_tables(const void *src, void *dst, uint64_t first, uint64_t second_at, uint64_t second, hipStream_t st);
 
 uint32_t gemv_ksplit(uint32_t ngroups, uint32_t total_units);
 hipError_t launch_gemv(int mode, uint32_t ksplit, const GemvArgs &a, uint32_t ntasks, hipStream_t st);

@@ -2236,16 +2236,21 @@ hipError_t launch_h2d_gather(const CopyDesc *descs, uint32_t n, hipStream_t st) 
 // trip over PCIe (3 to 4 us for up to 30 KB, 8 us for 282 KB), and a kernel in the stream needs no hand-over to a copy
 // engine and back (a 16-token step of two MoE layers 186 us by hipMemcpyAsync, 177 us this way).
 // ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void upload_tables_kernel(const u4_t *src, u4_t *dst, uint32_t n16) {
-    const uint32_t idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx < n16) dst[idx] = __builtin_nontemporal_load(src + idx);
+// Two runs in one launch: the tables' areas have room for every expert, and what is not in use stays where it is.
+__global__ __launch_bounds__(256) void upload_tables_kernel(const u4_t *src, u4_t *dst, uint32_t first16, uint32_t skip16, uint32_t n16) {
+    uint32_t idx = blockIdx.x * 256 + threadIdx.x;
+    if (idx >= n16) return;
+    if (idx >= first16) idx += skip16;
+    dst[idx] = __builtin_nontemporal_load(src + idx);
 }
 
-hipError_t launch_upload_tables(const void *src, void *dst, uint64_t bytes, hipStream_t st) {
-    if (bytes == 0) return hipSuccess;
-    if ((uintptr_t)src % 16 || (uintptr_t)dst % 16 || bytes % 16 || bytes / 16 > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    const uint32_t n16 = (uint32_t)(bytes / 16);
-    hipLaunchKernelGGL(upload_tables_kernel, dim3((n16 + 255) / 256), dim3(256), 0, st, static_cast<const u4_t *>(src), static_cast<u4_t *>(dst), n16);
+hipError_t launch_upload_tables(const void *src, void *dst, uint64_t first, uint64_t second_at, uint64_t second, hipStream_t st) {
+    if (first + second == 0) return hipSuccess;
+    if ((uintptr_t)src % 16 || (uintptr_t)dst % 16 || first % 16 || second_at % 16 || second % 16 || second_at < first || (second_at + second) / 16 > 0x7FFFFFFFull)
+        return hipErrorInvalidValue;
+    const uint32_t n16 = (uint32_t)((first + second) / 16);
+    hipLaunchKernelGGL(upload_tables_kernel, dim3((n16 + 255) / 256), dim3(256), 0, st, static_cast<const u4_t *>(src), static_cast<u4_t *>(dst),
+                       (uint32_t)(first / 16), (uint32_t)((second_at - first) / 16), n16);
     return hipGetLastError();
 }
 

@@ -1426,8 +1426,10 @@ static int32_t forward_impl(ps_stack *st, const void *x_in, void *x_out, const f
         st->route_logits = reinterpret_cast<const float *>(st->ws_base + p.ws.logits);
         st->route_layer_stride = (uint64_t)p.M * E;
     }
-    // (whole 16-byte units; the tables' areas are padded to 256 bytes, in the staging buffer as in the workspace)
-    PS_HIP(launch_upload_tables(th + from, st->ws_base + p.ws.logits + from, ps::align_up(pairs_at + sc.pairs.size() * 4, 16) - from, st->compute));
+    // (whole 16-byte units; the tables' areas are padded to 256 bytes, in the staging buffer as in the workspace.  Of the
+    // task and pair areas only what is in use: they have room for min(experts, pairs) tasks a layer)
+    PS_HIP(launch_upload_tables(th + from, st->ws_base + p.ws.logits + from, tasks_at + sc.tasks.size() * sizeof(ps::DeviceTask) - from,
+                                pairs_at - from, ps::align_up(sc.pairs.size() * 4, 16), st->compute));
     rc = run_schedule(st, sc, static_cast<const __half *>(x_in), static_cast<__half *>(x_out));
     // the buffer is free again once the uploads (compute stream) and the gathers (copy stream) are done
     if (has_copies(sc)) {

@@ -198,6 +198,38 @@ def test_expert_gemm_tile_by_the_busiest_experts_tokens(busiest):
     _check(cfg, 71, M, _budgets(cfg, M, [1.0, 0.5]), logits=lg)
 
 
+@pytest.mark.parametrize("device_logits", [False, True])
+def test_only_the_routing_tables_in_use_are_uploaded(device_logits):
+    """A trip of 40 tokens, then one of a single token through the same plan: the single token's two tasks replace the first
+    two of the device's table, and the other entries stay the 40 tokens' (the staging buffers alternate, so an upload of
+    the whole area would bring bytes that no forward put there)."""
+    import ctypes as C
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = Hn.small_moe_cfg(1)
+    E, k, M = cfg["n_experts"], cfg["top_k"], 40
+    W = Hn.WeightCache(cfg, 101)
+    st = B.Stack(B.Plan(cfg, 1 << 30, M))
+    for kind, ex, N, K in S.matrix_shapes(cfg):
+        st.load_matrix(0, kind, ex, *W(0, kind, ex))
+    p, n = C.c_void_p(), C.c_uint64()
+    assert B.lib().ps_stack_debug_buffer(st.h, 4, C.byref(p), C.byref(n)) == 0      # route weights; logits and tasks lie behind them
+    up = lambda v: (v + 255) // 256 * 256
+    at = up(up(p.value - st.arena.data_ptr() + n.value) + M * E * 4)
+    tables = []
+    for rows in (M, 1):
+        x = torch.from_numpy(S.activations(101, rows, rows, cfg["hidden"])).to(st.device)
+        lg = S.router_logits(101, rows, 1, rows, E)
+        B.chunked_forward(st, x, torch.empty_like(x), lg, router_logits_dev=torch.from_numpy(lg).to(st.device) if device_logits else None)
+        st.synchronize()
+        tables.append(st.arena[at:at + E * 32].cpu().numpy().view(np.uint32).reshape(E, 8).copy())   # .. pair0, npairs, expert, -
+    st.close()
+    assert sorted(tables[0][:, 6]) == list(range(E)) and tables[0][:, 5].sum() == M * k              # every expert has tokens
+    chosen = np.sort(np.argsort(-lg[0, 0], kind="stable")[:k])
+    assert list(tables[1][:k, 6]) == list(chosen) and (tables[1][:k, 5] == 1).all()
+    np.testing.assert_array_equal(tables[1][k:], tables[0][k:])
+
+
 @pytest.mark.parametrize("kind,M", [("dense", 1), ("dense", 4), ("dense", 37), ("moe", 1), ("moe", 5)])
 def test_copy_modes_move_the_same_bytes(kind, M):
     """Streamed shards cross PCIe by hipMemcpyAsync (mode 0), by the gather kernel where the library's rule
