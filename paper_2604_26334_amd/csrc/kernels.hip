@@ -1005,7 +1005,10 @@ __global__ __launch_bounds__(kAttnWaves * 64, 16 / kAttnWaves) void attn_decode_
 // the fills' and the latencies'.  2 tokens over 4000 positions 8.3 us with the weights in fp16, 8.3 with three parts;
 // 3 tokens over 1000 7.9 / 7.9.
 // Measured, 32 query / 8 kv heads over 4096 cached positions: 512 tokens 108 -> 73 us (37 rounds of 1.9 us; the
-// row fills alone take 41, the rest without them 50); 64 tokens 24 + 10 us (cache and own rows in two launches of a
+// row fills alone take 41, the rest without them 50).  A round takes about the sum of its parts, not their maximum: the
+// compiler, which cannot tell which fill a transpose read depends on, waits for all of them (vmcnt(0)) in front of the
+// first one, so the next round's fills overlap the score half of a round only, and softmax and MFMAs of the two waves of
+// a SIMD overlap little (forms without that wait, and waves half a round apart, were no faster).  64 tokens 24 + 10 us (cache and own rows in two launches of a
 // kernel that kept 256 positions per workgroup) -> 17 us.
 // ------------------------------------------------------------------------------------
 constexpr uint32_t kAttnRound = 128;                           // positions per round
@@ -2076,8 +2079,12 @@ static bool gemm_two_k_parts(const GemmArgs &a, uint32_t plan_tokens) {
 // part (a barrier, the first operand reads and the fills of every step) plus a part per token, so a large tile is
 // cheap per token and few, full rounds matter most.  Measured on 4096-wide rows, us per round: 8 waves x 96 tokens 43,
 // 128: 54, 160: 62, 192: 69, 224: 78, 256: 89; 4 waves x 64 tokens 26 alone on a CU, 43 with two.
-// Gate/up, 28672 rows, against the former 128-token tile: 300 tokens 111 -> 74 us (160), 512: 122 -> 105 (256),
-// 1024: 242 -> 209 (256), 1536: 380 -> 318 (256), 2048: 517 -> 417 (192); QKV, 6144 rows, 2048: 142 -> 99 (224).
+// Gate/up, 28672 rows, launched alone, against the former 128-token tile: 300 tokens 111 -> 74 us (160), 512: 122 -> 105
+// (256), 1024: 242 -> 209 (256), 1536: 380 -> 318 (256).  At 2048 tokens the rule says 256, by a hair over 192, and in the
+// pass of a two-layer prefill, at the clock that holds under its load, the tiles are all alike: 256 438-446 us, 192
+// 435-443, 160 434-444, 224 (a worse last round) 474; another time 256 466 on average and 441 at the least, the former tile
+// 472-490 and 447.  QKV, 6144 rows, in that pass: 224 102-109, 160 135, 192 157, the former tile 115-120; O and down stay
+// with 128: 69 and 207, 160 74 and 224, 192 86 and 267.
 static uint32_t gemm_pick_tile(const GemmArgs &a, uint32_t widest) {
     const uint32_t g4 = (a.ntiles + 7) / 8, g8 = (a.ntiles + 15) / 16;
     uint32_t best = 0, best_cost = 0xFFFFFFFFu;
@@ -2139,10 +2146,12 @@ static hipError_t launch_gemm_m(const GemmArgs &a, uint32_t ntasks, uint32_t max
         // Plans of more than 64 tokens.  The tile goes by the rows that are there (a.M) and never changes a bit of the
         // result; the K parts do, so they go by the whole matrix and the plan's token count.
         if (gemm_two_k_parts(a, max_tok)) {
-            // the smallest tile that still leaves at most one workgroup per CU (there is one: the rule saw to it): O at 200
-            // tokens 16.9 us in 32-token tiles, 19.1 in 48, 21.6 in 64; at 384 tokens (1.5 workgroups per CU in 32)
-            // 27.9 / 23.3 / 25.7; QKV at 512 tokens 39.2 without the parts, 36.3 in 112-token tiles; down at 768
-            // 122 without, 98.9 in 96
+            // the smallest tile that still leaves at most one workgroup per CU (there is one: the rule saw to it).  What each
+            // tile is worth where it is the one, against the next larger: O / down, us: 200 tokens 32: 19.1 / 52 against
+            // 22.7 / 61; 300: 48: 22.2 / 62 against 22.9 / 64; 450: 64: 25.8 / 72 against 28.6 / 81; 600: 80: 30.8 / 87
+            // against 32.7 / 93; 700: 96: 33.2 / 97 against 35.6 / 102; 850: 112: 37.4 / 107 against 40.5 / 115.  A tile
+            // that is too small pays a second round (450 tokens in 48: 40 / 110).  QKV at 512 tokens 39.2 without the parts,
+            // 36.3 in 112-token tiles; down at 768 122 without, 98.9 in 96
             const uint32_t groups = (a.ntiles + 7) / 8;
             auto one_round = [&](uint32_t mt) { return groups * ((a.M + mt - 1) / mt) <= 256; };
             if (one_round(32)) return launch_gemm_k<MODE, 2, 32, false, 8, 2>(a, a.M, 1, st);

@@ -228,8 +228,10 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
     const ModelGeom &g = p.g;
     const auto &m = g.m;
     // M: token rows that carry data in this forward (the last chunk of a chunked prefill has fewer
-    // than the plan's MP).  Launch shapes, tile sizes and the K split go by MP alone, so a row's bits
-    // do not depend on how many rows came with it; rows past M are neither read nor written.
+    // than the plan's MP).  What the order of a row's sums depends on (K parts, K planes, the deal of the
+    // attention's positions) goes by MP and the whole matrix or model alone, so a row's bits do not depend on
+    // how many rows came with it (but for the attention of fewer than 16 score rows, which keeps more bits);
+    // the GEMM's token tile goes by M and keeps that order.  Rows past M are neither read nor written.
     const uint32_t M = st->n_valid, MP = p.M, H = m.hidden, l = op.info.layer;
     uint8_t *A = st->arena;       // weights: pinned shards and scratch slots
     uint8_t *WS = st->ws_base;    // activations, RMS factors, partial sums, tables
