@@ -121,7 +121,8 @@ struct AttnArgs {
 // positions of its kv head (cache shards of kv heads head0 .. head0 + nheads - 1, k_base = the first one, head_stride
 // bytes apart, K rows [cap][128] then V rows) and, causally, the chunk's own K / V rows, read in place from the
 // tokens' QKV rows (k_own / v_own = kv head 0 of token 0, own_stride elements between tokens).  One launch per run of
-// cache shards.  nsplit == 1: finished rows out[t][q_head * 128 ..]; > 1: records
+// cache shards.  nsplit == 1: finished rows out[t][q_head * 128 ..], and the tokens' K / V rows appended at positions
+// ctx .. ctx + ntok - 1 of home[kv head] (address of its K row 0); > 1: records
 // part[((t * n_q + q_head) * nsplit + split) * 130] (maximum, weight sum, 128 sums) for launch_attn_combine_chunk.
 // nsplit and rounds_per_split come from attn_chunk_deal.  few: the weights in fp32's precision (fewer than 16 score rows).
 struct AttnChunkArgs {
@@ -135,13 +136,11 @@ struct AttnChunkArgs {
     uint32_t out_stride;
     const __half *q;
     float *part;
+    const uint64_t *home;
 };
 // ctx and the plan's token count, query heads per kv head and kv heads of the model -> the deal of the positions
 void attn_chunk_deal(uint32_t ctx, uint32_t plan_tokens, uint32_t group, uint32_t n_kv, uint32_t *nsplit, uint32_t *rounds_per_split);
 hipError_t launch_attn_chunk(const AttnChunkArgs &a, hipStream_t st);
-// appends ntok tokens' K / V rows (from their QKV rows) at positions ctx .. of every kv head's cache home
-hipError_t launch_kv_append_rows(uint32_t ctx, uint32_t cap, const __half *qkv, uint32_t qkv_w, uint32_t n_q, uint32_t n_kv, uint32_t ntok,
-                                 const uint64_t *home, hipStream_t st);
 // merges every token's records in split order, writes the attention rows out[t][n_q * 128] (out_stride
 // elements apart) and appends the tokens' K / V rows at positions ctx .. ctx + ntok - 1 of each kv head's cache home
 hipError_t launch_attn_combine_chunk(const float *part, uint32_t nsplit, uint32_t ctx, uint32_t cap, const __half *qkv,

@@ -114,9 +114,9 @@ __device__ __forceinline__ float rows4_meet(float v) {
     // hazard the compiler would otherwise pad
     float a = v, b = v;
     asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-    float y = MAX ? fmaxf(a, b) : a + b, z = y;
+    float y = MAX ? __builtin_elementwise_maximum(a, b) : a + b, z = y;
     asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(y), "+v"(z));
-    return MAX ? fmaxf(y, z) : y + z;
+    return MAX ? __builtin_elementwise_maximum(y, z) : y + z;
 #else
     return v;
 #endif
@@ -988,11 +988,14 @@ __global__ __launch_bounds__(kAttnWaves * 64, 16 / kAttnWaves) void attn_decode_
 // with a running maximum, weight sum and O^T per row and wave, which the four position groups of a row merge in
 // LDS at the end, in order.
 // What bounds it, per round and CU (64 rows): 64 KB of rows from the L2 (1024 cycles at 64 bytes per clock),
-// 128 KB of operand reads from LDS (1024), 2 x 32 MFMAs per SIMD (1024), about 1300 cycles of softmax arithmetic
-// per SIMD.  So: rows go from memory straight into LDS, two rounds' worth of stages, the next round on its way
-// while one is multiplied (one barrier per round); two row tiles per wave share every operand read; two waves per
-// SIMD so that one's softmax meets the other's MFMAs.  Rows of one (kv head, round) are read by all row
-// blocks: the head is the fastest grid index, so with 8 heads a head's blocks share an XCD's L2.
+// 128 KB of operand reads from LDS, 2 x 32 MFMAs per SIMD (1024), about 1100 cycles of softmax arithmetic
+// per SIMD (a third of them the exponentials).  So: rows go from memory straight into LDS, two rounds' worth of stages,
+// the next round on its way while one is multiplied (one barrier per round); two row tiles per wave share every operand
+// read; two waves per SIMD.  What the scores cost is kept to the least: a row is rescaled only when its maximum has risen
+// by more than 2^kAttnGrow since it last was (some row of 32 rises in almost every round, and a rescaling is 64
+// multiplications; weights of up to 2^8 are as exact in fp16 and leave fp32 sums all the room they need), a round's place in
+// memory goes into the fills' scalar base, and the stage is a compile-time number.  Rows of one (kv head, round) are read by
+// all row blocks: the head is the fastest grid index, so with 8 heads a head's blocks share an XCD's L2.
 // SPLIT: the rounds are dealt out to `nsplit` workgroups per row block (short chunks leave most CUs idle
 // otherwise) and each writes, per row, a record (maximum, weight sum, 128 weighted sums) that
 // attn_combine_chunk_kernel merges in split order; without SPLIT the finished rows are written.  The deal goes by
@@ -1004,18 +1007,19 @@ __global__ __launch_bounds__(kAttnWaves * 64, 16 / kAttnWaves) void attn_decode_
 // added at the end.  One wave of each pair has rows, so the MFMAs are fewer than with full tiles, and the time is
 // the fills' and the latencies'.  2 tokens over 4000 positions 8.3 us with the weights in fp16, 8.3 with three parts;
 // 3 tokens over 1000 7.9 / 7.9.
-// Measured, 32 query / 8 kv heads over 4096 cached positions: 512 tokens 108 -> 73 us (37 rounds of 1.9 us; the
-// row fills alone take 41, the rest without them 50).  A round takes about the sum of its parts, not their maximum: the
-// compiler, which cannot tell which fill a transpose read depends on, waits for all of them (vmcnt(0)) in front of the
-// first one, so the next round's fills overlap the score half of a round only, and softmax and MFMAs of the two waves of
-// a SIMD overlap little (forms without that wait, and waves half a round apart, were no faster).  64 tokens 24 + 10 us (cache and own rows in two launches of a
-// kernel that kept 256 positions per workgroup) -> 17 us.
+// Measured, 32 query / 8 kv heads over 4096 cached positions: 512 tokens 75 -> 64.5 us by the last three of these (250 ->
+// 110 vector instructions per wave and round; 37 rounds of 1.6 us; the row fills alone take 45, the rest without them 49),
+// and the launch that appended the rows, 5 us, is gone; 64 tokens 16.9 -> 15.6.  A round still takes more than its largest
+// part, and these did not change that: every operand requested in front of the next round's fills (64), the next round's
+// scores worked out beside this one's weights (68), steps of 64 positions with three on their way (70, twice the LDS reads),
+// fewer vector instructions still (64.5).
 // ------------------------------------------------------------------------------------
 constexpr uint32_t kAttnRound = 128;                           // positions per round
-constexpr uint32_t kAttnStageBytes = kAttnRound * 2 * 256;     // K rows, then V rows of a round
+constexpr uint32_t kAttnHalfStage = kAttnRound * 256;           // K or V rows of a round; in LDS: K of two rounds, V of two rounds
+constexpr float kAttnGrow = 8.f;                               // a row's weights may reach 2^8 before it is rescaled
 constexpr uint32_t kAttnOPitch = 132;                          // floats per row when the position groups meet
 constexpr size_t kAttnRowsLds = 4 * 64 * kAttnOPitch * 4 + 2 * 4 * 64 * 4;   // the meeting's rows, maxima and sums (more than two stages)
-static_assert(2 * kAttnStageBytes <= 4 * 64 * kAttnOPitch * 4 && kAttnRowsLds <= 160 * 1024, "LDS of the chunk attention");
+static_assert(4 * kAttnHalfStage <= 4 * 64 * kAttnOPitch * 4 && kAttnRowsLds <= 160 * 1024, "LDS of the chunk attention");
 
 // 16-byte piece u of a staged row lies in slot u ^ swizzle of the row.  K rows: an operand read takes, per lane
 // group, piece u of the 16 rows 8 (i / 4) + i % 4: their swizzles are the 16 numbers i.  V rows: a transpose read
@@ -1023,6 +1027,11 @@ static_assert(2 * kAttnStageBytes <= 4 * 64 * kAttnOPitch * 4 && kAttnRowsLds <=
 // different ones spread the rows over all banks.
 __device__ __forceinline__ uint32_t k_swz(uint32_t row) { return (row & 3u) | (((row >> 3) & 3u) << 2); }
 __device__ __forceinline__ uint32_t v_swz(uint32_t row) { return ((row & 3u) | (((row >> 3) & 1u) << 2)) << 1; }
+
+// largest of three numbers, without the quieting steps fmaxf puts around values the compiler did not compute itself
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
+}
 
 template <bool SPLIT, bool FEW>
 __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
@@ -1049,24 +1058,47 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
     const __half *ko = a.k_own + (size_t)kv_head * 128, *vo = a.v_own + (size_t)kv_head * 128;
     // a round's rows straight into LDS: wave w moves rows 16 w .. + 15 of K and of V, four rows per instruction;
     // positions past the end lie past the buffer's range, whose check returns zeros (their weights are zero, and an
-    // infinite value in a row read in their place would make NaN of that)
+    // infinite value in a row read in their place would make NaN of that).  The round's place in memory goes into the
+    // buffer's base (scalar), so a lane's offsets stay as they are from round to round.
+    uint32_t lk[2], lv[2];      // lane offsets of the first two instructions' rows and of the other two's (swizzles differ)
+    auto lanes_of = [&](uint32_t row_b) {
+#pragma unroll
+        for (uint32_t u = 0; u < 2; ++u) {
+            const uint32_t row = wave * 16 + u * 8 + c;
+            lk[u] = (wave * 16 + c) * row_b + ((i ^ k_swz(row)) << 4);
+            lv[u] = (wave * 16 + c) * row_b + ((i ^ v_swz(row)) << 4);
+        }
+    };
+    lanes_of(rd0 >= nr_cache ? a.own_stride * 2u : 256u);
     auto stage = [&](uint32_t rd, uint32_t buf) {
         const bool own = rd >= nr_cache;
+        if (rd == nr_cache) lanes_of(a.own_stride * 2u);
         const uint32_t row_b = own ? a.own_stride * 2u : 256u, npos = own ? a.ntok : a.ctx;
         const uint32_t P0 = (own ? rd - nr_cache : rd) * kAttnRound;
-        const int range = (int)((npos - 1) * row_b + 256u);
-        const __amdgpu_buffer_rsrc_t kb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(own ? ko : kc), 0, range, 0x00020000);
-        const __amdgpu_buffer_rsrc_t vb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(own ? vo : vc), 0, range, 0x00020000);
-        unsigned char *dk = lds + buf * kAttnStageBytes + wave * (16 * 256), *dv = dk + kAttnRound * 256;
+        const int range = (int)((npos - P0 - 1) * row_b + 256u);
+        const size_t at = (size_t)P0 * row_b;
+        const __amdgpu_buffer_rsrc_t kb = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(own ? ko : kc) + at), 0, range, 0x00020000);
+        const __amdgpu_buffer_rsrc_t vb = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(own ? vo : vc) + at), 0, range, 0x00020000);
+        unsigned char *dk = lds + buf * kAttnHalfStage + wave * (16 * 256), *dv = dk + 2 * kAttnHalfStage;
 #pragma unroll
         for (uint32_t t = 0; t < 4; ++t) {
-            const uint32_t row = wave * 16 + t * 4 + c;
-            const uint32_t off = (P0 + row) * row_b;
-            load_to_lds16(kb, (lds_void *)(dk + t * 1024), off + ((i ^ k_swz(row)) << 4), 0);
-            load_to_lds16(vb, (lds_void *)(dv + t * 1024), off + ((i ^ v_swz(row)) << 4), 0);
+            load_to_lds16(kb, (lds_void *)(dk + t * 1024), lk[t >> 1] + t * 4 * row_b, 0);
+            load_to_lds16(vb, (lds_void *)(dv + t * 1024), lv[t >> 1] + t * 4 * row_b, 0);
         }
     };
     if (rd0 < rd1) stage(rd0, 0);
+    if constexpr (!SPLIT) {
+        // The chunk's K and V rows go to the cache's home, positions ctx and up, which no row block reads: every block moves
+        // the tokens whose first row it holds (as a launch of its own 5 us a layer, here inside the wait for the first round)
+        const uint32_t t0 = (row0 + G - 1) / G, t1 = min(a.ntok, (row0 + 64 + G - 1) / G);
+        unsigned char *const kh = reinterpret_cast<unsigned char *>(a.home[kv_head]);
+        for (uint32_t u = tid; u < (t1 - t0) * 32; u += 512) {
+            const uint32_t t = t0 + u / 32, e = u & 15;
+            const bool v = u & 16;
+            const uint4 piece = *reinterpret_cast<const uint4 *>((v ? vo : ko) + (size_t)t * a.own_stride + e * 8);
+            *reinterpret_cast<uint4 *>(kh + ((size_t)(v ? a.cap : 0u) + a.ctx + t) * 256 + e * 16) = piece;
+        }
+    }
 
     // the wave's 32 query rows (B operands of the score MFMAs)
     uint32_t tok[NT], hq[NT];
@@ -1098,10 +1130,10 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
         const uint32_t vrow = 32 * pg + 8 * c + (i >> 2);
 #pragma unroll
         for (uint32_t dt = 0; dt < 8; ++dt)
-            voff[dt] = kAttnRound * 256 + vrow * 256 + (((2 * dt + ((i & 3) >> 1)) ^ v_swz(vrow)) << 4) + (i & 1) * 8;
+            voff[dt] = 2 * kAttnHalfStage + vrow * 256 + (((2 * dt + ((i & 3) >> 1)) ^ v_swz(vrow)) << 4) + (i & 1) * 8;
     }
-    for (uint32_t rd = rd0; rd < rd1; ++rd) {
-        const uint32_t buf = (rd - rd0) & 1;
+    auto round = [&](uint32_t rd, auto BUF) {      // (the stage is a compile-time number: LDS addresses are lane offset + constant)
+        constexpr uint32_t buf = decltype(BUF)::value;
         // this wave's rows of the round have landed; behind the barrier everyone's have, and everyone has left
         // the other stage
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -1113,8 +1145,8 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
         const uint32_t P0 = (own ? rd - nr_cache : rd) * kAttnRound + 32 * pg;    // the wave's first position
         // (uniform) the wave's positions all lie past what its rows see
         const uint32_t last_seen = own ? min(a.ntok - 1, (row0 + r2 * 32 + 31) / G) : a.ctx - 1;
-        if (P0 > last_seen || (FEW && r2)) continue;
-        const unsigned char *st = lds + buf * kAttnStageBytes;
+        if (P0 > last_seen || (FEW && r2)) return;
+        const unsigned char *st = lds + buf * kAttnHalfStage;
         f4_t S[NT][2];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -1128,8 +1160,10 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
 #pragma unroll
                 for (int t = 0; t < NT; ++t) S[t][T] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kr, q[t][kk], S[t][T], 0, 0, 0);
             }
-        // positions a row does not see: only the cache's last round and the own rounds can hold any
+        // positions a row does not see: only the cache's last round and the own rounds can hold any (the empty statement
+        // keeps this a branch: as selects it would be 32 vector instructions in every round)
         if (own || P0 + 32 > a.ctx) {
+            asm volatile("");
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const uint32_t limit = own ? tok[t] + 1 : a.ctx;
@@ -1142,15 +1176,16 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
         float mx[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            mx[t] = fmaxf(fmaxf(fmaxf(S[t][0][0], S[t][0][1]), fmaxf(S[t][0][2], S[t][0][3])),
-                          fmaxf(fmaxf(S[t][1][0], S[t][1][1]), fmaxf(S[t][1][2], S[t][1][3])));
-            mx[t] = fmaxf(m_run[t], rows4_meet<true>(mx[t]));
+            mx[t] = max3(max3(S[t][0][0], S[t][0][1], S[t][0][2]), max3(S[t][0][3], S[t][1][0], S[t][1][1]), max3(S[t][1][2], S[t][1][3], S[t][1][3]));
+            mx[t] = rows4_meet<true>(mx[t]);
         }
-        // some row's maximum rose: rescale (a row that has seen nothing holds zeros, and the difference of two
-        // -inf is not a number)
-        if (__any(mx[0] > m_run[0] || mx[NT - 1] > m_run[NT - 1])) {
+        // Some row's maximum rose by more than the weights may grow (2^kAttnGrow; fp16 holds 2^15 of them): rescale.  A row
+        // that has seen nothing holds zeros, and the difference of two -inf is not a number.
+        const float room = FEW ? 0.f : kAttnGrow / c2;
+        if (__any(mx[0] > m_run[0] + room || mx[NT - 1] > m_run[NT - 1] + room)) {
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
+                mx[t] = fmaxf(m_run[t], mx[t]);
                 const float resc = m_run[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run[t] - mx[t]) * c2);
                 m_run[t] = mx[t];
                 l_run[t] *= resc;
@@ -1191,6 +1226,10 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
             for (int t = 0; t < 2; ++t) O[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vr, P[t], O[t][dt], 0, 0, 0);
             if (FEW) O[1][dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vr, P[FEW ? 2 : 1], O[1][dt], 0, 0, 0);
         }
+    };
+    for (uint32_t rd = rd0; rd < rd1; rd += 2) {
+        round(rd, std::integral_constant<uint32_t, 0>{});
+        if (rd + 1 < rd1) round(rd + 1, std::integral_constant<uint32_t, 1>{});
     }
     // the four position groups of a row meet: every wave leaves its rows, maxima and sums in LDS
     __syncthreads();     // the last stage's reads are behind everyone
@@ -1278,29 +1317,13 @@ hipError_t launch_attn_chunk(const AttnChunkArgs &a, hipStream_t st) {
     if (a.group == 0 || a.group > 16 || !a.k_own || !a.v_own || a.nsplit == 0) return hipErrorInvalidValue;
     if (a.few && a.ntok * a.group >= 16) return hipErrorInvalidValue;
     const uint32_t rounds = (a.ctx + kAttnRound - 1) / kAttnRound + (a.ntok + kAttnRound - 1) / kAttnRound;
-    if ((uint64_t)a.nsplit * a.rounds_per_split < rounds || (a.nsplit > 1 ? !a.part : !a.out)) return hipErrorInvalidValue;
+    if ((uint64_t)a.nsplit * a.rounds_per_split < rounds || (a.nsplit > 1 ? !a.part : !a.out || !a.home)) return hipErrorInvalidValue;
+    if ((uint64_t)a.ctx + a.ntok > a.cap) return hipErrorInvalidValue;
     // 32-bit buffer offsets
     if (((uint64_t)a.ctx + kAttnRound) * 256u > 0x7FFFFFFFull || ((uint64_t)a.ntok + kAttnRound) * a.own_stride * 2u > 0x7FFFFFFFull) return hipErrorInvalidValue;
     dim3 grid(a.nheads, (a.ntok * a.group + 63) / 64, a.nsplit);
     return a.few ? a.nsplit > 1 ? launch_attn_chunk_k<true, true>(a, grid, st) : launch_attn_chunk_k<false, true>(a, grid, st)
                  : a.nsplit > 1 ? launch_attn_chunk_k<true, false>(a, grid, st) : launch_attn_chunk_k<false, false>(a, grid, st);
-}
-
-// the tokens' K and V rows go to positions ctx .. ctx + ntok - 1 of each kv head's cache home
-__global__ __launch_bounds__(128) void kv_append_rows_kernel(uint32_t ctx, uint32_t cap, const __half *qkv, uint32_t qkv_w, uint32_t n_q,
-                                                             uint32_t n_kv, const uint64_t *home) {
-    const uint32_t g = blockIdx.x, t = blockIdx.y, d = threadIdx.x;
-    __half *Kh = reinterpret_cast<__half *>(home[g]);
-    Kh[((size_t)ctx + t) * 128 + d] = qkv[(size_t)t * qkv_w + (size_t)(n_q + g) * 128 + d];
-    Kh[((size_t)cap + ctx + t) * 128 + d] = qkv[(size_t)t * qkv_w + (size_t)(n_q + n_kv + g) * 128 + d];
-}
-
-hipError_t launch_kv_append_rows(uint32_t ctx, uint32_t cap, const __half *qkv, uint32_t qkv_w, uint32_t n_q, uint32_t n_kv, uint32_t ntok,
-                                 const uint64_t *home, hipStream_t st) {
-    if (ntok == 0) return hipSuccess;
-    if (n_kv == 0 || (uint64_t)ctx + ntok > cap || ntok > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kv_append_rows_kernel, dim3(n_kv, ntok), dim3(128), 0, st, ctx, cap, qkv, qkv_w, n_q, n_kv, home);
-    return hipGetLastError();
 }
 
 // One workgroup of 128 threads per (query head, token): thread d merges dimension d over the token's records

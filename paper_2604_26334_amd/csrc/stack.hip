@@ -405,6 +405,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                 c.k_own = qkv + (size_t)m.n_q_heads * m.head_dim; c.v_own = qkv + (size_t)(m.n_q_heads + m.n_kv_heads) * m.head_dim;
                 c.own_stride = g.qkv_w; c.out = reinterpret_cast<__half *>(WS + p.ws.attn); c.out_stride = g.attn_w;
                 c.part = reinterpret_cast<float *>(WS + p.ws.apart);
+                c.home = reinterpret_cast<const uint64_t *>(WS + p.ws.kvhome) + (size_t)l * m.n_kv_heads;
                 attn_chunk_deal(c.ctx, MP, c.group, m.n_kv_heads, &c.nsplit, &c.rounds_per_split);
                 // the last rows of a chunk, or a chunk of a few (a longer plan's stay as they are whatever comes with them)
                 c.few = MP < kAttnOnePassTokens && M * c.group < 16;
@@ -426,9 +427,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                 const uint64_t *home = reinterpret_cast<const uint64_t *>(WS + p.ws.kvhome) + (size_t)l * m.n_kv_heads;
                 uint32_t nsplit, per;
                 attn_chunk_deal(st->ctx, MP, m.n_q_heads / m.n_kv_heads, m.n_kv_heads, &nsplit, &per);
-                if (nsplit == 1)   // the attention rows are finished: only the chunk's rows remain to be appended
-                    PS_HIP(launch_kv_append_rows(st->ctx, m.kv_context, qkv, g.qkv_w, m.n_q_heads, m.n_kv_heads, M, home, cs));
-                else               // every token's records merged, and the chunk's rows appended
+                if (nsplit > 1)    // every token's records merged, and the chunk's rows appended (one split: the attention did both)
                     PS_HIP(launch_attn_combine_chunk(reinterpret_cast<const float *>(WS + p.ws.apart), nsplit, st->ctx, m.kv_context, qkv, g.qkv_w,
                                                      m.n_q_heads, m.n_kv_heads, M, home, reinterpret_cast<__half *>(WS + p.ws.attn), g.attn_w, cs));
                 return PS_OK;

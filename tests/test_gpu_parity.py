@@ -914,6 +914,53 @@ def test_an_infinite_value_in_the_cache_reaches_the_rows_that_see_it(n_q, n_kv, 
     assert (a[where] == np.inf).all() and np.isfinite(a[~where]).all()
 
 
+@pytest.mark.parametrize("n_q,n_kv,plan_tokens,M,ctx0", [(8, 2, 300, 300, 1500), (2, 2, 256, 70, 700), (8, 8, 256, 256, 63), (4, 2, 64, 64, 2000),
+                                                       (8, 1, 64, 9, 900), (8, 2, 64, 3, 1300)])
+def test_chunk_attention_whose_scores_rise_along_the_cache(n_q, n_kv, plan_tokens, M, ctx0):
+    """Keys that grow along one direction: a row's scores rise (or fall) steadily, by more and by less per round than what a
+    row's weights may grow before it is rescaled, with one jump.  The attention rows against float64 on the rows' own QKV:
+    a weight is off by 2^-11 (fp16; far less for fewer than 16 score rows), its exponent by what fp32 makes of scores of up
+    to 800 (8 bits of 24: 2^-14), the stored row by 2^-11; and the appended rows are the QKV rows' bits."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(_kv_cfg(1, ctx0 + plan_tokens + 3), n_q_heads=n_q, n_kv_heads=n_kv)
+    W = Hn.WeightCache(cfg, 97)
+    K, V = S.kv_cache(97, 0, n_kv, ctx0, 128)
+    rng = np.random.default_rng(97)
+    u = rng.standard_normal(128)
+    ramp = np.linspace(0.0, 30.0, ctx0) + np.where(np.arange(ctx0) > ctx0 // 2, 12.0, 0.0)
+    K = (0.1 * K.astype(np.float64) + (ramp[:, None] * (u / np.linalg.norm(u)) * 11.3)).astype(np.float16)
+    plan = B.Plan(cfg, 1 << 30, plan_tokens)
+    st = B.Stack(plan)
+    for k, ex, N, Kd in S.matrix_shapes(cfg):
+        st.load_matrix(0, k, ex, *W(0, k, ex))
+    for g in range(n_kv):
+        st.load_kv(0, g, K[g], V[g])
+    xin = torch.from_numpy(S.activations(97, 0, M, cfg["hidden"])).to(st.device)
+    st.set_context(ctx0)
+    B.chunked_forward(st, xin, torch.zeros_like(xin))
+    qkv16 = st.debug_buffer(0, np.float16, (M, n_q + 2 * n_kv, 128)).copy()
+    got = st.debug_buffer(5, np.float16, (M, n_q, 128)).astype(np.float64)
+    homes = sorted((s for s in plan.shards() if s.kind == B.PS_SHARD_KV and s.resident == 1), key=lambda s: s.expert)
+    cache = [st.arena[s.offset:s.offset + 2 * cfg["kv_context"] * 256].cpu().numpy().view(np.float16).reshape(2, -1, 128) for s in homes]
+    st.close()
+    plan.close()
+    qkv = qkv16.astype(np.float64)
+    G = n_q // n_kv
+    for g in range(n_kv):
+        np.testing.assert_array_equal(cache[g][0, ctx0:ctx0 + M].view(np.uint16), qkv16[:, n_q + g].view(np.uint16))
+        np.testing.assert_array_equal(cache[g][1, ctx0:ctx0 + M].view(np.uint16), qkv16[:, n_q + n_kv + g].view(np.uint16))
+        keys = np.concatenate([K[g].astype(np.float64), qkv[:, n_q + g]])
+        vals = np.concatenate([V[g].astype(np.float64), qkv[:, n_q + n_kv + g]])
+        for h in range(g * G, (g + 1) * G):
+            sc = qkv[:, h] @ keys.T / np.sqrt(128.0)
+            sc = np.where(np.arange(ctx0 + M) <= ctx0 + np.arange(M)[:, None], sc, -np.inf)
+            P = np.exp(sc - sc.max(axis=1, keepdims=True))
+            P /= P.sum(axis=1, keepdims=True)
+            err, bound = np.abs(got[:, h] - P @ vals), (2.0 ** -10 + 2.0 ** -13) * (P @ np.abs(vals)) + 2.0 ** -11 * np.abs(P @ vals) + 1e-6
+            assert (err <= bound).all(), (h, float((err / bound).max()))
+
+
 def test_chunked_prefill_fills_the_cache_it_then_decodes_over():
     """150 prompt tokens through a 64-token tier of a stack with a KV cache (three trips, each attending
     over the cache and the rows the earlier trips appended), then decode steps over the filled cache.
