@@ -81,6 +81,9 @@ hipError_t launch_gemv_mt(int mode, uint32_t ksplit, const GemvArgs &a, uint32_t
 hipError_t launch_splitk_epilogue(int mode, const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M,
                                   uint32_t ncols_phys, const float *rinv, const __half *res, __half *out,
                                   uint32_t out_stride, uint32_t out_row0, hipStream_t st);
+// the PLAIN epilogue with the RMS factors worked out from the matrix's input rows x [M][H], with launch_rinv's bits
+hipError_t launch_splitk_epilogue_norm(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M, uint32_t ncols, const __half *x,
+                                       uint32_t H, float eps, __half *out, uint32_t out_stride, uint32_t out_row0, hipStream_t st);
 // MoE routing of M tokens: the top_k largest fp32 logits (ties to the lower index, in descending order) and the
 // softmax over them.  As a launch of its own, or riding in the launch that produces the layer's RMS factors
 // (`route` of the two below; route_rides says whether the sizes allow it)

@@ -713,16 +713,9 @@ bool route_rides(const RouteArgs &ra) { return ra.M && ra.E <= 256 && ra.top_k &
 // butterfly, the four waves in order.  All of a thread's loads (up to four per round) are issued
 // before the first is used; chunks past the row's end count as zeros.
 // ------------------------------------------------------------------------------------
-// NR > 0: the workgroups behind the first M route four tokens each (the MoE routing of a layer depends on nothing the
-// layer computes here, and as a launch of its own it costs 4 to 5 us).
-template <int NR>
-__global__ __launch_bounds__(256) void rinv_kernel(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, RouteArgs ra) {
-    if constexpr (NR > 0) {
-        if (blockIdx.x >= M) { route_tokens<NR>(ra, blockIdx.x - M); return; }
-    }
-    __shared__ float part[4];
-    const uint32_t m = blockIdx.x;
-    const uint4 *row = reinterpret_cast<const uint4 *>(x + (size_t)m * H);
+// The factor of one row, in thread 0 .. 255 alike (part: four floats of LDS)
+__device__ __forceinline__ float row_factor(const __half *x, uint32_t H, float eps, float *part) {
+    const uint4 *row = reinterpret_cast<const uint4 *>(x);
     const uint32_t nq = H / 8;
     float ss = 0.f;
     for (uint32_t q0 = 0; q0 < nq; q0 += 1024) {
@@ -741,7 +734,20 @@ __global__ __launch_bounds__(256) void rinv_kernel(const __half *x, uint32_t M, 
     ss = wave_sum(ss);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
     __syncthreads();
-    if (threadIdx.x == 0) rinv[m] = rsqrtf((((part[0] + part[1]) + part[2]) + part[3]) / (float)H + eps);
+    return rsqrtf((((part[0] + part[1]) + part[2]) + part[3]) / (float)H + eps);
+}
+
+// NR > 0: the workgroups behind the first M route four tokens each (the MoE routing of a layer depends on nothing the
+// layer computes here, and as a launch of its own it costs 4 to 5 us).
+template <int NR>
+__global__ __launch_bounds__(256) void rinv_kernel(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, RouteArgs ra) {
+    if constexpr (NR > 0) {
+        if (blockIdx.x >= M) { route_tokens<NR>(ra, blockIdx.x - M); return; }
+    }
+    __shared__ float part[4];
+    const uint32_t m = blockIdx.x;
+    const float f = row_factor(x + (size_t)m * H, H, eps, part);
+    if (threadIdx.x == 0) rinv[m] = f;
 }
 
 // up to 16 runs' sums of squares, in pairs (runs from n on count as zeros)
@@ -2381,6 +2387,42 @@ hipError_t launch_splitk_epilogue(int mode, const float *partial, uint32_t parts
             break;
         default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------
+// Split-K epilogue of a matrix behind a norm (PLAIN) whose input rows' RMS factors nobody has left: the first layer's QKV.
+// blockIdx.y is the token, blockIdx.x 1024 of its columns; every workgroup of a token works the factor out for itself, beside
+// its planes' loads: thread t adds the chunks t, t + 256, ... of the input row, reduced as in rinv_kernel, so the factor has
+// the bits of the launch (3 to 5 us, latency) that is left out.  64 tokens, 6144 columns of 4096: 4.5 us with or without.
+// ------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void splitk_epilogue_norm_kernel(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t ncols,
+                                                                   const __half *x, uint32_t H, float eps, __half *out,
+                                                                   uint32_t out_stride, uint32_t out_row0) {
+    __shared__ float part[4];
+    const uint32_t m = blockIdx.y, j = (blockIdx.x * 256 + threadIdx.x) * 4, jc = min(j, ncols - 4);
+    const float *p0 = partial + (size_t)m * ncols + jc;
+    float4 pa[8];
+#pragma unroll
+    for (uint32_t p = 0; p < 8; ++p) pa[p] = *reinterpret_cast<const float4 *>(p0 + (size_t)min(p, parts - 1) * part_stride);
+    const float ri = row_factor(x + (size_t)m * H, H, eps, part);
+    if (j >= ncols) return;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (uint32_t p = 0; p < 8; ++p) {
+        if (p < parts) { v.x += pa[p].x; v.y += pa[p].y; v.z += pa[p].z; v.w += pa[p].w; }
+    }
+    __half2 *d2 = reinterpret_cast<__half2 *>(out + (size_t)m * out_stride + out_row0 + j);
+    d2[0] = __half2{to_half(ri * v.x), to_half(ri * v.y)};
+    d2[1] = __half2{to_half(ri * v.z), to_half(ri * v.w)};
+}
+
+hipError_t launch_splitk_epilogue_norm(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M, uint32_t ncols, const __half *x,
+                                       uint32_t H, float eps, __half *out, uint32_t out_stride, uint32_t out_row0, hipStream_t st) {
+    if (M == 0) return hipSuccess;
+    if (ncols % 16 || out_row0 % 4 || out_stride % 4 || part_stride % 4 || parts < 1 || parts > 8 || H % 8 || M > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(splitk_epilogue_norm_kernel, dim3((ncols + 1023) / 1024, M), dim3(256), 0, st, partial, parts, part_stride, ncols, x, H, eps,
+                       out, out_stride, out_row0);
     return hipGetLastError();
 }
 

@@ -95,6 +95,7 @@ struct ps_stack {
     const void *ssq_of = nullptr;             // rows whose sums of squares the last residual GEMM left in ssq_buf
     float *ssq_buf = nullptr;
     const float *ssq_use = nullptr;           // set by a PS_K_RINV op: what the matrices behind it take their RMS factors from
+    const void *own_factors = nullptr;        // set by a PS_K_RINV op: rows whose factors the plane sum behind them works out itself
     uint32_t routed_layer = kNotRouted;       // MoE layer whose routing rode in an earlier launch of this forward
     static constexpr uint32_t kNotRouted = 0xFFFFFFFFu;
     std::vector<hipEvent_t> prof_ev;          // 2 per op of the last profiled forward
@@ -331,6 +332,11 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             st->rinv_of = a.out;
             return PS_OK;
         }
+        if (mode == GEMM_PLAIN && st->own_factors == a.x) {
+            PS_HIP(launch_splitk_epilogue_norm(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, ncols, a.x, H, m.rms_eps, a.out, a.out_stride,
+                                               a.out_row0, cs));
+            return PS_OK;
+        }
         PS_HIP(launch_splitk_epilogue(mode, partial, (mg.nsb + per - 1) / per, pa.part_stride, M, ncols, rinv, a.res,
                                       a.out, a.out_stride, a.out_row0, cs));
         return PS_OK;
@@ -342,11 +348,15 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             st->rinv_of = nullptr;
             st->ssq_use = st->ssq_of == rows ? st->ssq_buf : nullptr;
             st->ssq_of = nullptr;
+            st->own_factors = nullptr;
             if (st->ssq_use) return PS_OK;
             // the few-token kernels of QKV (factors of kind 0) and of a dense gate/up (kind 1) compute their own
             if (op.info.shard0 == 0 && few_token_gemv(p, g.qkv)) return PS_OK;
             if (op.info.shard0 == 1 && !g.moe && few_token_gemv(p, g.gate_up)) return PS_OK;
             if (have) return PS_OK;
+            // nobody has left the factors QKV wants, and its planes are summed by a launch of its own: that one works them out
+            // (a launch fewer; each of a token's workgroups reads the row again, which 64 tokens do not notice)
+            if (op.info.shard0 == 0 && g.has_attn && gemm_sb_per_part(g.qkv, MP) && !st->own_rinv_launch) { st->own_factors = rows; return PS_OK; }
             if (factor_runs) { PS_HIP(launch_rinv_runs(rows, M, H, m.rms_eps, rinv, cs)); return PS_OK; }
             const bool ride = riding && op.info.shard0 == 1;
             PS_HIP(launch_rinv(rows, M, H, m.rms_eps, rinv, ride ? riding : nullptr, cs));
@@ -667,6 +677,7 @@ int32_t run_schedule(ps_stack *st, const ps_schedule &sc, const __half *x_in, __
     st->rinv_of = nullptr;
     st->ssq_of = nullptr;
     st->ssq_use = nullptr;
+    st->own_factors = nullptr;
     st->routed_layer = ps_stack::kNotRouted;
     ps_stats &ss = st->stats;
     ss = ps_stats{};

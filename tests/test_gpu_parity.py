@@ -331,6 +331,34 @@ def test_rms_factor_left_by_the_residual_epilogue_matches_its_own_launch(M, moe)
     st.close()
 
 
+@pytest.mark.parametrize("n_q,n_kv,hidden,M,share", [(4, 2, 512, 5, 1.0), (7, 1, 1536, 64, 1.0), (2, 2, 2176, 33, 1.0), (32, 8, 512, 17, 1.0),
+                                                   (4, 2, 512, 16, 0.4)])
+def test_plane_sum_of_qkv_works_out_the_factors_nobody_left(n_q, n_kv, hidden, M, share):
+    """The first layer's RMS factors (and with streamed slabs every layer's) come from QKV's plane sum instead of a launch
+    (mode 2): the same bits, for widths that end inside a workgroup's 1024 columns, rows shorter and longer than its
+    256 chunks, and matrices in slabs."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(Hn.small_dense_cfg(2), n_q_heads=n_q, n_kv_heads=n_kv, hidden=hidden)
+    W = Hn.WeightCache(cfg, 13)
+    wb, _ = Hn.total_weight_bytes(cfg)
+    plan = B.Plan(cfg, int(wb * share) + B.Plan(cfg, 1 << 62, M).summary().workspace_bytes + (1 << 20), M)
+    st = B.Stack(plan)
+    for layer in range(cfg["n_layers"]):
+        for kind, expert, N, K in S.matrix_shapes(cfg):
+            st.load_matrix(layer, kind, expert, *W(layer, kind, expert))
+    x = torch.from_numpy(S.activations(13, 0, M, hidden)).cuda()
+    res = {}
+    for mode in (2, 0):
+        st.set_decode_mode(mode)
+        y = torch.empty_like(x)
+        st.forward(x, y)
+        st.synchronize()
+        res[mode] = y.cpu().numpy().view(np.uint16)
+    st.close()
+    np.testing.assert_array_equal(res[0], res[2])
+
+
 @pytest.mark.parametrize("M,hidden", [(1, 512), (4, 1024), (16, 512)])
 def test_graph_replay_matches_eager_on_every_replay(M, hidden):
     """HIP-graph decode mode (one token; batched-decode steps of a few tokens, in the few-token kernel and in
