@@ -69,8 +69,17 @@ hipError_t launch_h2d_gather(const CopyDesc *descs, uint32_t n, hipStream_t st);
 // (everything a multiple of 16)
 hipError_t launch_upload_tables(const void *src, void *dst, uint64_t first, uint64_t second_at, uint64_t second, hipStream_t st);
 
+// MoE routing of M tokens: the top_k largest fp32 logits (ties to the lower index, in descending order) and the
+// softmax over them.  As a launch of its own, or riding in the launch that produces the layer's RMS factors or,
+// for one token, in O's (`route` of these launches; route_rides says whether the sizes allow it)
+struct RouteArgs {
+    const float *logits;   // [M][E]
+    uint32_t M, E, top_k;
+    int32_t *idx;          // [M][top_k]
+    float *w;
+};
 uint32_t gemv_ksplit(uint32_t ngroups, uint32_t total_units);
-hipError_t launch_gemv(int mode, uint32_t ksplit, const GemvArgs &a, uint32_t ntasks, hipStream_t st);
+hipError_t launch_gemv(int mode, uint32_t ksplit, const GemvArgs &a, uint32_t ntasks, const RouteArgs *route, hipStream_t st);
 hipError_t launch_gemm(int mode, const GemmArgs &a, uint32_t ntasks, uint32_t max_tok, hipStream_t st);
 // Two to kGemvMtTokens tokens of a dense sub-layer whose K is a multiple of 1024 (rows of x x_stride
 // elements apart, rows of out and res out_stride apart): the one-token kernel's launch shape with the dot
@@ -84,15 +93,6 @@ hipError_t launch_splitk_epilogue(int mode, const float *partial, uint32_t parts
 // the PLAIN epilogue with the RMS factors worked out from the matrix's input rows x [M][H], with launch_rinv's bits
 hipError_t launch_splitk_epilogue_norm(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M, uint32_t ncols, const __half *x,
                                        uint32_t H, float eps, __half *out, uint32_t out_stride, uint32_t out_row0, hipStream_t st);
-// MoE routing of M tokens: the top_k largest fp32 logits (ties to the lower index, in descending order) and the
-// softmax over them.  As a launch of its own, or riding in the launch that produces the layer's RMS factors
-// (`route` of the two below; route_rides says whether the sizes allow it)
-struct RouteArgs {
-    const float *logits;   // [M][E]
-    uint32_t M, E, top_k;
-    int32_t *idx;          // [M][top_k]
-    float *w;
-};
 hipError_t launch_route(const RouteArgs &ra, hipStream_t st);
 bool route_rides(const RouteArgs &ra);
 // the factors in the order of the GEMM's sums of squares (see GemmArgs), with their bits

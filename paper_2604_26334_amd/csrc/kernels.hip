@@ -155,6 +155,77 @@ __device__ __forceinline__ uint32_t gather_col(uint32_t k, uint32_t x_off, uint3
 }
 
 // ------------------------------------------------------------------------------------
+// MoE routing: per token the top_k largest fp32 logits (ties to the lower index, listed
+// in descending order) and the softmax over the selected logits.  One wave per token.
+// ------------------------------------------------------------------------------------
+// Wave-wide maximum / minimum, the same value in every lane: the 16 lanes of a row meet through DPP
+// row operations (no LDS traffic), the four rows through four lane reads.
+__device__ __forceinline__ int dpp_i(int v, int ctrl) {
+    switch (ctrl) {
+        case 0: return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);    // quad_perm 1,0,3,2
+        case 1: return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);    // quad_perm 2,3,0,1
+        case 2: return __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false);   // row_half_mirror
+        default: return __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false);  // row_mirror
+    }
+}
+__device__ __forceinline__ float wave_max_all(float v) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v = fmaxf(v, __builtin_bit_cast(float, dpp_i(__builtin_bit_cast(int, v), c)));
+    const int b = __builtin_bit_cast(int, v);
+    const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 0)), r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 16));
+    const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 32)), r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 48));
+    return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
+}
+__device__ __forceinline__ uint32_t wave_min_all(uint32_t v) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v = min(v, (uint32_t)dpp_i((int)v, c));
+    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 0), r1 = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
+    const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 32), r3 = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+    return min(min(r0, r1), min(r2, r3));
+}
+
+template <int NR>   // 64 * NR >= E
+__device__ __forceinline__ void route_tokens(const RouteArgs &ra, uint32_t block) {   // four tokens, one per wave
+    const float *logits = ra.logits;
+    const uint32_t M = ra.M, E = ra.E, top_k = ra.top_k;
+    int32_t *idx = ra.idx;
+    float *w = ra.w;
+    const uint32_t m = block * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (m >= M) return;
+    const float *l = logits + (size_t)m * E;
+    float v[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const uint32_t e = r * 64 + lane;
+        v[r] = e < E ? l[e] : -INFINITY;
+    }
+    uint32_t taken = 0;  // bit r: this lane's entry r already selected
+    float sel = 0.f, lmax = 0.f;
+    for (uint32_t j = 0; j < top_k; ++j) {
+        float best = -INFINITY;
+        uint32_t be = 0xFFFFFFFFu;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const uint32_t e = r * 64 + lane;
+            if (e < E && !((taken >> r) & 1u) && (be == 0xFFFFFFFFu || v[r] > best)) { best = v[r]; be = e; }
+        }
+        // the largest value in the wave, then the lowest index among the lanes that hold it
+        // (a lane with nothing left holds -inf and the index 0xFFFFFFFF, which never wins)
+        const float top = wave_max_all(best);
+        be = wave_min_all(best == top ? be : 0xFFFFFFFFu);
+        best = top;
+        if ((be & 63u) == (uint32_t)lane) taken |= 1u << (be >> 6);
+        if (j == 0) lmax = best;
+        if ((uint32_t)lane == j) sel = best;
+        if (lane == 0) idx[(size_t)m * top_k + j] = (int32_t)be;
+    }
+    const float ex = (uint32_t)lane < top_k ? __expf(sel - lmax) : 0.f;
+    const float den = wave_sum(ex);
+    if ((uint32_t)lane < top_k) w[(size_t)m * top_k + lane] = ex / den;
+}
+
+// ------------------------------------------------------------------------------------
 // Decode kernel, one token: fused 4-bit dequant GEMV.  A "unit" is one row-tile (16 outputs)
 // or, for GATE_UP, a gate tile plus its up tile.  KSPLIT waves share a unit, wave kpart taking
 // scale groups kpart, kpart + KSPLIT, ... of K; a workgroup holds NW / KSPLIT units.
@@ -366,8 +437,13 @@ __device__ __forceinline__ void gemv_item(const GemvArgs &a, const uint4 *W, con
     out[row] = to_half(v);
 }
 
-template <int MODE, int NW, bool FULLG>
-__global__ __launch_bounds__(NW * 64, 4) void gemv_w4_kernel(GemvArgs a, uint32_t ks) {   // 4 waves per SIMD: at most 128 VGPRs
+// ROUTE: the workgroup behind the matrix's routes the token (a MoE layer's routing depends on nothing the layer computes, and
+// as a launch of its own it costs 4 to 5 us between O and the experts; here it runs beside O).
+template <int MODE, int NW, bool FULLG, bool ROUTE = false>
+__global__ __launch_bounds__(NW * 64, 4) void gemv_w4_kernel(GemvArgs a, uint32_t ks, RouteArgs ra) {   // 4 waves per SIMD: at most 128 VGPRs
+    if constexpr (ROUTE) {
+        if (blockIdx.x == gridDim.x - 1) { route_tokens<4>(ra, 0); return; }
+    }
     __shared__ GemvLds<NW> lds;
     const uint4 *W = a.W;
     const __half *x = a.x;
@@ -392,8 +468,8 @@ __global__ __launch_bounds__(NW * 64, 4) void gemv_w4_kernel(GemvArgs a, uint32_
     gemv_item<MODE, NW, DBUF, FULLG>(a, W, x, out, out_f32, blockIdx.x, ks, lds);
 }
 
-template <int MODE, bool FULLG>
-static hipError_t launch_gemv_f(const GemvArgs &a, uint32_t ks, uint32_t ntasks, hipStream_t st) {
+template <int MODE, bool FULLG, bool ROUTE = false>
+static hipError_t launch_gemv_f(const GemvArgs &a, uint32_t ks, uint32_t ntasks, const RouteArgs &ra, hipStream_t st) {
     // waves per workgroup: at least the K split; two units per workgroup (8 waves) when that still
     // leaves about one workgroup per CU -- fewer, larger workgroups start sooner (measured on the
     // 8B shapes: QKV 6.6 -> 5.4 us, gate/up 13.4 -> 13.0 us; O, with 256 units, is best left at one
@@ -401,16 +477,16 @@ static hipError_t launch_gemv_f(const GemvArgs &a, uint32_t ks, uint32_t ntasks,
     uint32_t nw = ks > 8 ? 16 : ks > 4 ? 8 : 4;
     if (ks == 4 && (a.nunits + 1) / 2 >= 192) nw = 8;   // (with one wave per unit, ks < 4, the larger workgroup measured slower)
     const uint32_t units = nw / ks;
-    dim3 grid((a.nunits + units - 1) / units, ntasks ? ntasks : 1);
-    if (nw == 16) hipLaunchKernelGGL((gemv_w4_kernel<MODE, 16, FULLG>), grid, dim3(1024), 0, st, a, ks);
-    else if (nw == 8) hipLaunchKernelGGL((gemv_w4_kernel<MODE, 8, FULLG>), grid, dim3(512), 0, st, a, ks);
-    else hipLaunchKernelGGL((gemv_w4_kernel<MODE, 4, FULLG>), grid, dim3(256), 0, st, a, ks);
+    dim3 grid((a.nunits + units - 1) / units + (ROUTE ? 1 : 0), ntasks ? ntasks : 1);
+    if (nw == 16) hipLaunchKernelGGL((gemv_w4_kernel<MODE, 16, FULLG, ROUTE>), grid, dim3(1024), 0, st, a, ks, ra);
+    else if (nw == 8) hipLaunchKernelGGL((gemv_w4_kernel<MODE, 8, FULLG, ROUTE>), grid, dim3(512), 0, st, a, ks, ra);
+    else hipLaunchKernelGGL((gemv_w4_kernel<MODE, 4, FULLG, ROUTE>), grid, dim3(256), 0, st, a, ks, ra);
     return hipGetLastError();
 }
 
 template <int MODE>
 static hipError_t launch_gemv_t(const GemvArgs &a, uint32_t ks, uint32_t ntasks, hipStream_t st) {
-    return (a.nsb % 8 == 0) ? launch_gemv_f<MODE, true>(a, ks, ntasks, st) : launch_gemv_f<MODE, false>(a, ks, ntasks, st);
+    return (a.nsb % 8 == 0) ? launch_gemv_f<MODE, true>(a, ks, ntasks, RouteArgs{}, st) : launch_gemv_f<MODE, false>(a, ks, ntasks, RouteArgs{}, st);
 }
 
 // The K split is a pure performance choice (results do not depend on it): it grows until the
@@ -421,10 +497,14 @@ uint32_t gemv_ksplit(uint32_t ngroups, uint32_t total_units) {
     return ks;
 }
 
-hipError_t launch_gemv(int mode, uint32_t ksplit, const GemvArgs &a, uint32_t ntasks, hipStream_t st) {
+hipError_t launch_gemv(int mode, uint32_t ksplit, const GemvArgs &a, uint32_t ntasks, const RouteArgs *route, hipStream_t st) {
     if (ksplit != 1 && ksplit != 2 && ksplit != 4 && ksplit != 8 && ksplit != 16) return hipErrorInvalidValue;
     // weights are addressed as a uniform base plus 32-bit byte offsets
     if ((uint64_t)a.nunits * (mode == GEMV_GATE_UP ? 2u : 1u) * a.tile_u4 * 16u > 0xFFFFFFFFull) return hipErrorInvalidValue;
+    if (route) {
+        if (mode != GEMV_RESID || ntasks || route->M != 1 || !route_rides(*route)) return hipErrorInvalidValue;
+        return (a.nsb % 8 == 0) ? launch_gemv_f<GEMV_RESID, true, true>(a, ksplit, 0, *route, st) : launch_gemv_f<GEMV_RESID, false, true>(a, ksplit, 0, *route, st);
+    }
     switch (mode) {
         case GEMV_PLAIN: return launch_gemv_t<GEMV_PLAIN>(a, ksplit, ntasks, st);
         case GEMV_RESID: return launch_gemv_t<GEMV_RESID>(a, ksplit, ntasks, st);
@@ -620,77 +700,6 @@ hipError_t launch_gemv_mt(int mode, uint32_t ksplit, const GemvArgs &a, uint32_t
         case GEMV_GATE_UP: return launch_gemv_mt_t<GEMV_GATE_UP>(a, ksplit, ntok, st);
     }
     return hipErrorInvalidValue;
-}
-
-// ------------------------------------------------------------------------------------
-// MoE routing: per token the top_k largest fp32 logits (ties to the lower index, listed
-// in descending order) and the softmax over the selected logits.  One wave per token.
-// ------------------------------------------------------------------------------------
-// Wave-wide maximum / minimum, the same value in every lane: the 16 lanes of a row meet through DPP
-// row operations (no LDS traffic), the four rows through four lane reads.
-__device__ __forceinline__ int dpp_i(int v, int ctrl) {
-    switch (ctrl) {
-        case 0: return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);    // quad_perm 1,0,3,2
-        case 1: return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);    // quad_perm 2,3,0,1
-        case 2: return __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false);   // row_half_mirror
-        default: return __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false);  // row_mirror
-    }
-}
-__device__ __forceinline__ float wave_max_all(float v) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) v = fmaxf(v, __builtin_bit_cast(float, dpp_i(__builtin_bit_cast(int, v), c)));
-    const int b = __builtin_bit_cast(int, v);
-    const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 0)), r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 16));
-    const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 32)), r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 48));
-    return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
-}
-__device__ __forceinline__ uint32_t wave_min_all(uint32_t v) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) v = min(v, (uint32_t)dpp_i((int)v, c));
-    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 0), r1 = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
-    const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 32), r3 = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
-    return min(min(r0, r1), min(r2, r3));
-}
-
-template <int NR>   // 64 * NR >= E
-__device__ __forceinline__ void route_tokens(const RouteArgs &ra, uint32_t block) {   // four tokens, one per wave
-    const float *logits = ra.logits;
-    const uint32_t M = ra.M, E = ra.E, top_k = ra.top_k;
-    int32_t *idx = ra.idx;
-    float *w = ra.w;
-    const uint32_t m = block * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (m >= M) return;
-    const float *l = logits + (size_t)m * E;
-    float v[NR];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        const uint32_t e = r * 64 + lane;
-        v[r] = e < E ? l[e] : -INFINITY;
-    }
-    uint32_t taken = 0;  // bit r: this lane's entry r already selected
-    float sel = 0.f, lmax = 0.f;
-    for (uint32_t j = 0; j < top_k; ++j) {
-        float best = -INFINITY;
-        uint32_t be = 0xFFFFFFFFu;
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const uint32_t e = r * 64 + lane;
-            if (e < E && !((taken >> r) & 1u) && (be == 0xFFFFFFFFu || v[r] > best)) { best = v[r]; be = e; }
-        }
-        // the largest value in the wave, then the lowest index among the lanes that hold it
-        // (a lane with nothing left holds -inf and the index 0xFFFFFFFF, which never wins)
-        const float top = wave_max_all(best);
-        be = wave_min_all(best == top ? be : 0xFFFFFFFFu);
-        best = top;
-        if ((be & 63u) == (uint32_t)lane) taken |= 1u << (be >> 6);
-        if (j == 0) lmax = best;
-        if ((uint32_t)lane == j) sel = best;
-        if (lane == 0) idx[(size_t)m * top_k + j] = (int32_t)be;
-    }
-    const float ex = (uint32_t)lane < top_k ? __expf(sel - lmax) : 0.f;
-    const float den = wave_sum(ex);
-    if ((uint32_t)lane < top_k) w[(size_t)m * top_k + lane] = ex / den;
 }
 
 template <int NR>

@@ -84,7 +84,7 @@ extern "C" int32_t ps_profile_measure(void *scratch_dev, uint64_t scratch_bytes,
             PS_HIP(hipEventRecord(e0, cs));
             for (int i = 0; i < kLaunches; ++i) {
                 a.W = reinterpret_cast<const uint4 *>(wts + (uint64_t)i * per * mg.tile_bytes);
-                PS_HIP(launch_gemv(GEMV_PLAIN, 1, a, 0, cs));
+                PS_HIP(launch_gemv(GEMV_PLAIN, 1, a, 0, nullptr, cs));
             }
             PS_HIP(hipEventRecord(e1, cs));
             PS_HIP(hipEventSynchronize(e1));
@@ -263,7 +263,7 @@ extern "C" int32_t ps_profile_db_measure(ps_profile_db *db, const ps_model_desc 
                 PS_HIP(hipEventRecord(e0, cs));
                 for (int i = 0; i < kLaunches; ++i) {
                     a.W = reinterpret_cast<const uint4 *>(wts + (uint64_t)(i % fit) * mg.bytes);
-                    PS_HIP(launch_gemv(GEMV_PLAIN, ks, a, 0, cs));
+                    PS_HIP(launch_gemv(GEMV_PLAIN, ks, a, 0, nullptr, cs));
                 }
                 PS_HIP(hipEventRecord(e1, cs));
                 PS_HIP(hipEventSynchronize(e1));

@@ -269,15 +269,22 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         GemvArgs a = gemv_base(g.head);
         a.top_k = 1; a.W = wptr(op); a.nunits = s.ntiles; a.x = x_out + (size_t)st->head_row0 * H;
         a.out = st->logits; a.out_row0 = s.tile0 * 16;
-        PS_HIP(launch_gemv(GEMV_PLAIN, gemv_ksplit(g.head.ngroups, g.head.ntiles), a, 0, cs));
+        PS_HIP(launch_gemv(GEMV_PLAIN, gemv_ksplit(g.head.ngroups, g.head.ntiles), a, 0, nullptr, cs));
         return PS_OK;
     }
+    // MoE: the layer's routing rides in the launch in front of the experts that leaves the RMS factors of their input
+    const RouteArgs ra{g.moe ? st->route_logits + (size_t)l * st->route_layer_stride : nullptr, M, m.n_experts, m.top_k,
+                       reinterpret_cast<int32_t *>(WS + p.ws.ridx), reinterpret_cast<float *>(WS + p.ws.rw)};
+    const RouteArgs *const riding = g.moe && route_rides(ra) ? &ra : nullptr;
     if (MP == 1 && op.info.kernel >= PS_K_QKV && op.info.kernel <= PS_K_DOWN) {
         GemvArgs a;
         int mode;
         uint32_t ks;
         dense_gemv_args(st, op, x_in, x_out, &a, &mode, &ks);
-        PS_HIP(launch_gemv(mode, ks, a, 0, cs));
+        // a MoE layer's routing rides in O's first launch
+        const bool ride = riding && op.info.kernel == PS_K_O && st->routed_layer != l;
+        PS_HIP(launch_gemv(mode, ks, a, 0, ride ? riding : nullptr, cs));
+        if (ride) st->routed_layer = l;
         return PS_OK;
     }
     if (op.info.kernel >= PS_K_QKV && op.info.kernel <= PS_K_DOWN &&
@@ -289,10 +296,6 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         PS_HIP(launch_gemv_mt(mode, ks, a, M, cs));
         return PS_OK;
     }
-    // MoE: the layer's routing rides in the launch in front of the experts that leaves the RMS factors of their input
-    const RouteArgs ra{g.moe ? st->route_logits + (size_t)l * st->route_layer_stride : nullptr, M, m.n_experts, m.top_k,
-                       reinterpret_cast<int32_t *>(WS + p.ws.ridx), reinterpret_cast<float *>(WS + p.ws.rw)};
-    const RouteArgs *const riding = g.moe && route_rides(ra) ? &ra : nullptr;
     // Many tokens, dense: O and down leave the sums of squares of the rows they store, per 128 columns, and the matrices
     // behind them take their RMS factors from those (slabs of these matrices are cut at 256 rows); factors that need a
     // launch of their own (the first layer's) are then summed in the same order
@@ -467,7 +470,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                 if (gu) { a.nunits = mg.ntiles / 2; a.x = hbuf; a.x_stride = H; a.out = sbuf; a.out_stride = g.ffn_i; }
                 else { a.nunits = mg.ntiles; a.x = sbuf; a.x_stride = g.ffn_i; a.out_f32 = y; a.out_stride = H; }
                 const uint32_t units = gu ? mg.ntiles / 2 : mg.ntiles;
-                PS_HIP(launch_gemv(gu ? GEMV_GATE_UP : GEMV_F32, gemv_ksplit(mg.ngroups, units * m.top_k), a, op.ntasks, cs));
+                PS_HIP(launch_gemv(gu ? GEMV_GATE_UP : GEMV_F32, gemv_ksplit(mg.ngroups, units * m.top_k), a, op.ntasks, nullptr, cs));
             } else {
                 GemmArgs a = gemm_base(mg);
                 a.tasks = tasks; a.pairs = pairs; a.ntiles = mg.ntiles;
@@ -1626,6 +1629,7 @@ int32_t ps_stack_time_kernel(ps_stack *st, uint32_t kernel, uint32_t reps, doubl
             st->rinv_of = nullptr;   // timed in isolation: every launch is issued
             st->ssq_of = nullptr;
             st->ssq_use = nullptr;
+            st->own_factors = nullptr;
             rc = issue_kernel(st, st->dense_sched, op, xin, xout);
             if (rc) break;
             ++n;

@@ -185,6 +185,16 @@ def test_routing_riding_in_the_rms_factor_launch(E, top_k, M):
     _check(cfg, 73, M, _budgets(cfg, M, [1.0, 0.6]), logits=lg)
 
 
+@pytest.mark.parametrize("E,top_k,n_kv,H", [(8, 2, 1, 256), (64, 8, 2, 1024), (130, 7, 4, 384), (256, 16, 1, 256), (264, 4, 1, 256)])
+def test_one_token_routing_rides_in_o_and_experts_share_a_launch(E, top_k, n_kv, H):
+    """One token: up to 256 experts the routing is a workgroup of O's first launch (O whole or in streamed slabs, K of whole
+    and of ragged scale groups), above that a launch of its own; where a layer's streamed experts come in one fill, they and
+    the resident ones go out in one launch of each kind.  The oracle, and the same bits at every budget."""
+    cfg = dict(Hn.small_moe_cfg(2), n_experts=E, top_k=top_k, n_kv_heads=n_kv, hidden=H)
+    lg = S.router_logits(79, 0, cfg["n_layers"], 1, E)
+    _check(cfg, 79, 1, _budgets(cfg, 1, [1.0, 0.8, 0.5, 0.3]), logits=lg)
+
+
 @pytest.mark.parametrize("busiest", [16, 17, 33, 48, 49, 65, 96, 97, 129])
 def test_expert_gemm_tile_by_the_busiest_experts_tokens(busiest):
     """Grouped expert launches take the smallest token tile (16, 32, 48, 64, 96, else 128) that holds the busiest
