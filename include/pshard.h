@@ -526,7 +526,8 @@ int32_t ps_stack_forward_chunked(ps_stack *st, const void *x_in, void *x_out, ui
                                  void *last_logits_dev, uint32_t *trips);
 /* Decode execution mode.  0 (default): one launch per shard.  1: applies when the plan is dense with
  * every shard (KV-cache shards included) resident and no CPU share, for one token or, without a KV
- * cache, for a batched-decode step of up to 64 tokens (otherwise mode 0 runs): the launch-per-shard
+ * cache, for a batched-decode step of up to 64 tokens, and a replay pays: at least 64 launches a step, or less than
+ * 4 MB of weights a launch (otherwise mode 0 runs, which is then the faster): the launch-per-shard
  * kernel sequence is captured once per (x_in, x_out, logits, valid rows) into a HIP graph (kernel
  * nodes only) and replayed; with a KV cache the context length then travels in a
  * device word set before each replay, and the attention launch covers every chunk the cache can

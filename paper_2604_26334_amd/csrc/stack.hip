@@ -70,7 +70,7 @@ struct ps_stack {
     void *tables_host[2] = {nullptr, nullptr};   // pinned: logits | tasks | pairs | copy descriptors of one forward (MoE)
     uint64_t tables_bytes = 0;
     int32_t decode_mode = 0;                  // as set by ps_stack_set_decode_mode (re-evaluated when a tier is installed)
-    bool use_graph = false;                   // all-resident one-token forward replayed from a HIP graph
+    bool use_graph = false;                   // all-resident decode step replayed from a HIP graph
     std::map<std::tuple<const void *, void *, void *, uint32_t>, hipGraphExec_t> graphs;   // per (x_in, x_out, logits, valid rows and head rows)
     // CPU back-end (plans with shards left in system memory): worker threads, pinned host copies of
     // the activations it reads (FFN input, SwiGLU output, final hidden state) and of what it writes
@@ -645,6 +645,21 @@ static bool graph_eligible(const ps_plan &p) {
     return !p.g.moe && p.n_slots == 0 && p.cpu_bytes == 0 && (p.M == 1 || (p.M <= 64 && !p.g.kv));
 }
 
+// Whether replaying an eligible plan's step beats issuing its launches one by one.  A replay costs the stream 4 to 11 us at its
+// two ends, whatever it holds (kernels inside one, and direct launches, follow each other without a gap), and saves a tenth
+// of a microsecond a launch and the host's 3.  Measured, us a step, replayed / direct, 8B-shaped layers: one token, 1 layer
+// 43.2 / 38.7, 4: 149.8 / 147.5, 8: 291.4 / 290.2, 16 (64 launches): 574.4 / 576.6, 32: 1138 / 1149; 4 tokens, 2 layers 93.8 /
+// 89.6, 8: 344 / 341; 64 tokens, 2 layers 168 / 161, 16: 1240 / 1231; 16000 cached positions, 2 layers 126 / 117, 4000, 16
+// layers 803 / 805.  So: from 64 launches on.  With less than 4 MB a launch the host is what a direct step waits for
+// (two layers of width 512: 39 us, all of it the host's, against 48 with 33 of the host's): there the mode keeps what it is
+// for, a host with time to spare.
+bool replay_pays(const ps_schedule &sc) {
+    uint64_t launches = 0, bytes = 0;
+    for (const Op &op : sc.ops)
+        if (op.info.type == PS_OP_KERNEL) { ++launches; bytes += op.info.bytes; }
+    return launches >= 64 || bytes < launches * (4ull << 20);
+}
+
 bool has_copies(const ps_schedule &sc) {
     return std::any_of(sc.ops.begin(), sc.ops.end(), [](const Op &op) { return op.info.type == PS_OP_COPY; });
 }
@@ -937,7 +952,7 @@ int32_t bind_plan(ps_stack *st) {
             st->dense_descs_cap = st->dense_sched.ops.size();
         }
     }
-    st->use_graph = st->decode_mode == 1 && graph_eligible(p) && st->have_dense_sched;
+    st->use_graph = st->decode_mode == 1 && graph_eligible(p) && st->have_dense_sched && replay_pays(st->dense_sched);
     if (p.g.kv) {
         // home of every kv head's cache: where its rows live between steps (arena or pinned pool)
         const auto &m = p.g.m;
@@ -1572,7 +1587,7 @@ int32_t ps_stack_set_decode_mode(ps_stack *st, int32_t mode) {
     const ps_plan &p = st->plan;
     // eligible: dense, one token, every shard resident (nothing to wait for but the previous kernel)
     st->decode_mode = mode;
-    st->use_graph = mode == 1 && graph_eligible(p) && st->have_dense_sched;
+    st->use_graph = mode == 1 && graph_eligible(p) && st->have_dense_sched && replay_pays(st->dense_sched);
     st->own_rinv_launch = mode == 2;
     return PS_OK;
 }
