@@ -52,9 +52,16 @@ struct GemmArgs {
     // GATE_UP with ssq_in add a token's nsb runs (K columns), in pairs, and take their RMS factors from them
     float *ssq_out;
     const float *ssq_in;
+    uint32_t quarters;    // not 0: ssq_in holds four sums per token instead (ssq_in[w * M + token], see RowQuarters) of this many columns
     float eps;
     const DeviceTask *tasks;
     const int32_t *pairs;
+};
+// RMS factors of M rows as what the four waves of launch_rinv would add up: sq[w * M + row], H columns (sq null: no such sums)
+struct RowQuarters {
+    const float *sq;
+    uint32_t M, H;
+    float eps;
 };
 
 // one host->device copy of a gathered batch: n16 16-byte units from pinned host memory to VRAM
@@ -88,7 +95,7 @@ constexpr int kGemvMtTokens = 4;
 hipError_t launch_gemv_mt(int mode, uint32_t ksplit, const GemvArgs &a, uint32_t ntok, hipStream_t st);
 // sums `parts` fp32 partial planes [M][ncols_phys] in ascending order and applies the mode's epilogue
 hipError_t launch_splitk_epilogue(int mode, const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M,
-                                  uint32_t ncols_phys, const float *rinv, const __half *res, __half *out,
+                                  uint32_t ncols_phys, const float *rinv, const RowQuarters &sums, const __half *res, __half *out,
                                   uint32_t out_stride, uint32_t out_row0, hipStream_t st);
 // the PLAIN epilogue with the RMS factors worked out from the matrix's input rows x [M][H], with launch_rinv's bits
 hipError_t launch_splitk_epilogue_norm(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M, uint32_t ncols, const __half *x,
@@ -104,6 +111,10 @@ hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float
 hipError_t launch_splitk_epilogue_resid_rinv(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M,
                                              uint32_t H, const __half *res, __half *out, float eps, float *rinv,
                                              const RouteArgs *route, hipStream_t st);
+// the same stores over four times the workgroups, with the sums of squares the factors come from instead of the factors
+// (quarters[w * M + row]; whoever wants a factor adds a row's four): their bits once added up
+hipError_t launch_splitk_epilogue_resid_quarters(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M, uint32_t H,
+                                                 const __half *res, __half *out, float *quarters, hipStream_t st);
 // Decode attention over a KV cache, one new token.  A cache shard of one kv head is K rows
 // [cap][128] followed by V rows [cap][128], fp16; `nheads` shards lie head_stride bytes apart from
 // kv (kv heads head0 .. head0 + nheads - 1).  Each workgroup covers one kv head x one chunk of 256

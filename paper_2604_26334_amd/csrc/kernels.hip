@@ -722,6 +722,11 @@ bool route_rides(const RouteArgs &ra) { return ra.M && ra.E <= 256 && ra.top_k &
 // butterfly, the four waves in order.  All of a thread's loads (up to four per round) are issued
 // before the first is used; chunks past the row's end count as zeros.
 // ------------------------------------------------------------------------------------
+__device__ __forceinline__ float factor_of_quarters(const RowQuarters &r, uint32_t m) {
+    const float p0 = r.sq[m], p1 = r.sq[r.M + m], p2 = r.sq[2 * r.M + m], p3 = r.sq[3 * r.M + m];
+    return rsqrtf((((p0 + p1) + p2) + p3) / (float)r.H + r.eps);
+}
+
 // The factor of one row, in thread 0 .. 255 alike (part: four floats of LDS)
 __device__ __forceinline__ float row_factor(const __half *x, uint32_t H, float eps, float *part) {
     const uint4 *row = reinterpret_cast<const uint4 *>(x);
@@ -1800,6 +1805,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     auto factor_of = [&](uint32_t t) {
         const uint32_t tok = min(m0 + t, ntok - 1);
         if (!a.ssq_in) { my_rinv = a.rinv[tok]; return; }
+        if (a.quarters) { my_rinv = factor_of_quarters(RowQuarters{a.ssq_in, ntok, a.quarters, a.eps}, tok); return; }
         double s = 0.;
         for (uint32_t g = 0; g < a.nsb; g += 16) {   // (the buffer goes on for 64 nsb floats per token)
             const float *sq = a.ssq_in + (size_t)g * ntok + tok;
@@ -2325,7 +2331,7 @@ hipError_t launch_scatter_rows(const float *src, const int32_t *idx, uint32_t n,
 // ------------------------------------------------------------------------------------
 template <int MODE>
 __global__ __launch_bounds__(256) void splitk_epilogue_kernel(const float *partial, uint32_t parts, uint32_t part_stride,
-                                                              uint32_t M, uint32_t ncols_phys, const float *rinv,
+                                                              uint32_t M, uint32_t ncols_phys, const float *rinv, RowQuarters sums,
                                                               const __half *res, __half *out, uint32_t out_stride,
                                                               uint32_t out_row0) {
     // one thread per four adjacent output columns (a 16-column tile is never straddled)
@@ -2355,7 +2361,7 @@ __global__ __launch_bounds__(256) void splitk_epilogue_kernel(const float *parti
         }
         float r[4] = {v.x, v.y, v.z, v.w};
         if (MODE == GEMM_PLAIN) {
-            const float ri = rinv[m];
+            const float ri = sums.sq ? factor_of_quarters(sums, m) : rinv[m];
 #pragma unroll
             for (int e = 0; e < 4; ++e) r[e] = ri * r[e];
         } else if (MODE == GEMM_RESID) {
@@ -2365,7 +2371,7 @@ __global__ __launch_bounds__(256) void splitk_epilogue_kernel(const float *parti
                 r[0] = r01.x + r[0]; r[1] = r01.y + r[1]; r[2] = r23.x + r[2]; r[3] = r23.y + r[3];
             }
         } else {
-            const float ri = rinv[m];
+            const float ri = sums.sq ? factor_of_quarters(sums, m) : rinv[m];
             const float g[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) r[e] = silu(ri * r[e]) * (ri * g[e]);
@@ -2377,7 +2383,7 @@ __global__ __launch_bounds__(256) void splitk_epilogue_kernel(const float *parti
 }
 
 hipError_t launch_splitk_epilogue(int mode, const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M,
-                                  uint32_t ncols_phys, const float *rinv, const __half *res, __half *out,
+                                  uint32_t ncols_phys, const float *rinv, const RowQuarters &sums, const __half *res, __half *out,
                                   uint32_t out_stride, uint32_t out_row0, hipStream_t st) {
     // four columns per thread: 16-byte plane reads, 8-byte stores (columns come in tiles of 16 and
     // out_row0 / out_stride are multiples of 16, so both stay aligned)
@@ -2386,13 +2392,13 @@ hipError_t launch_splitk_epilogue(int mode, const float *partial, uint32_t parts
     const uint32_t blocks = (uint32_t)std::min<size_t>((n + 255) / 256, 2048);
     switch (mode) {
         case GEMM_PLAIN:
-            hipLaunchKernelGGL(splitk_epilogue_kernel<GEMM_PLAIN>, dim3(blocks), dim3(256), 0, st, partial, parts, part_stride, M, ncols_phys, rinv, res, out, out_stride, out_row0);
+            hipLaunchKernelGGL(splitk_epilogue_kernel<GEMM_PLAIN>, dim3(blocks), dim3(256), 0, st, partial, parts, part_stride, M, ncols_phys, rinv, sums, res, out, out_stride, out_row0);
             break;
         case GEMM_RESID:
-            hipLaunchKernelGGL(splitk_epilogue_kernel<GEMM_RESID>, dim3(blocks), dim3(256), 0, st, partial, parts, part_stride, M, ncols_phys, rinv, res, out, out_stride, out_row0);
+            hipLaunchKernelGGL(splitk_epilogue_kernel<GEMM_RESID>, dim3(blocks), dim3(256), 0, st, partial, parts, part_stride, M, ncols_phys, rinv, sums, res, out, out_stride, out_row0);
             break;
         case GEMM_GATE_UP:
-            hipLaunchKernelGGL(splitk_epilogue_kernel<GEMM_GATE_UP>, dim3(blocks), dim3(256), 0, st, partial, parts, part_stride, M, ncols_phys, rinv, res, out, out_stride, out_row0);
+            hipLaunchKernelGGL(splitk_epilogue_kernel<GEMM_GATE_UP>, dim3(blocks), dim3(256), 0, st, partial, parts, part_stride, M, ncols_phys, rinv, sums, res, out, out_stride, out_row0);
             break;
         default: return hipErrorInvalidValue;
     }
@@ -2505,6 +2511,72 @@ hipError_t launch_splitk_epilogue_resid_rinv(const float *partial, uint32_t part
     else if (!route_rides(*route)) return hipErrorInvalidValue;
     else if (route->E <= 128) hipLaunchKernelGGL(splitk_epilogue_resid_rinv_kernel<2>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, partial, parts, part_stride, M, H, res, out, eps, rinv, *route);
     else hipLaunchKernelGGL(splitk_epilogue_resid_rinv_kernel<4>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, partial, parts, part_stride, M, H, res, out, eps, rinv, *route);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------
+// The same residual epilogue for dense layers, as four workgroups of one wave per token: wave w takes the chunks of the four-wave
+// kernel's wave w, two per lane and round with every load requested before the first is used, and leaves its sum of squares
+// for the readers to add up.  Bound by latency: a workgroup per token pulls 144 KB through each of 64 CUs in two rounds of
+// loads that wait for each other, this form 36 KB through each of 256 in one; 64 tokens of 4096 columns from eight planes
+// 4.8 -> 3.95 us (of which about 2.5 are a launch's own).
+// ------------------------------------------------------------------------------------
+__global__ __launch_bounds__(64) void splitk_epilogue_resid_quarters_kernel(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M,
+                                                                            uint32_t H, const __half *res, __half *out, float *quarters) {
+    const uint32_t w = blockIdx.x, m = blockIdx.y, nq = H / 8;
+    const float *prow = partial + (size_t)m * H;
+    float ss = 0.f;
+    for (uint32_t q0 = w * 64 + threadIdx.x; q0 < nq; q0 += 512) {
+        float4 a[2][8][2];
+        uint4 rv[2];
+#pragma unroll
+        for (uint32_t u = 0; u < 2; ++u) {
+            const uint32_t q = q0 + u * 256 < nq ? q0 + u * 256 : q0;      // (past the row's end the first chunk again, not stored)
+#pragma unroll
+            for (uint32_t p = 0; p < 8; ++p) {
+                const float *src = prow + (size_t)(p < parts ? p : parts - 1) * part_stride + q * 8;
+                a[u][p][0] = *reinterpret_cast<const float4 *>(src);
+                a[u][p][1] = *reinterpret_cast<const float4 *>(src + 4);
+            }
+            rv[u] = res ? *reinterpret_cast<const uint4 *>(res + (size_t)m * H + q * 8) : uint4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < 2; ++u) {
+            if (q0 + u * 256 >= nq) break;
+            float r[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (uint32_t p = 0; p < 8; ++p) {
+                const bool on = p < parts;   // adding +0 leaves a sum that started at +0 unchanged
+                r[0] += on ? a[u][p][0].x : 0.f; r[1] += on ? a[u][p][0].y : 0.f;
+                r[2] += on ? a[u][p][0].z : 0.f; r[3] += on ? a[u][p][0].w : 0.f;
+                r[4] += on ? a[u][p][1].x : 0.f; r[5] += on ? a[u][p][1].y : 0.f;
+                r[6] += on ? a[u][p][1].z : 0.f; r[7] += on ? a[u][p][1].w : 0.f;
+            }
+            if (res) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) r[e] = half_of(rv[u], e) + r[e];
+            }
+            uint32_t d[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint16_t lo = __builtin_bit_cast(uint16_t, to_half(r[2 * e]));
+                const uint16_t hi = __builtin_bit_cast(uint16_t, to_half(r[2 * e + 1]));
+                d[e] = (uint32_t)lo | ((uint32_t)hi << 16);
+            }
+            const uint4 o = uint4{d[0], d[1], d[2], d[3]};
+            *reinterpret_cast<uint4 *>(out + (size_t)m * H + (q0 + u * 256) * 8) = o;
+            ss += sumsq8(o);
+        }
+    }
+    ss = wave_sum(ss);
+    if (threadIdx.x == 0) quarters[w * M + m] = ss;
+}
+
+hipError_t launch_splitk_epilogue_resid_quarters(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M, uint32_t H,
+                                                 const __half *res, __half *out, float *quarters, hipStream_t st) {
+    if (M == 0) return hipSuccess;
+    if (parts == 0 || parts > 8 || H % 8 || part_stride % 4 || !partial || !out || !quarters || M > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(splitk_epilogue_resid_quarters_kernel, dim3(4, M), dim3(64), 0, st, partial, parts, part_stride, M, H, res, out, quarters);
     return hipGetLastError();
 }
 

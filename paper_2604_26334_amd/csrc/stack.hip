@@ -305,14 +305,15 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
     auto run_gemm = [&](int mode, GemmArgs a, const MatGeom &mg) -> int32_t {
         const uint32_t per = gemm_sb_per_part(mg, MP);
         a.eps = m.rms_eps;
+        // sums of squares go into an activation buffer that is dead until the next op but one has read them:
+        // behind O the rows that down will write, behind down those that were this layer's input (without
+        // attention that input is still down's residual, and the buffer of the attention half's output is free)
+        float *const x0 = reinterpret_cast<float *>(WS + p.ws.x0), *const x1 = reinterpret_cast<float *>(WS + p.ws.x1);
+        float *const dead = &mg == &g.o ? (l & 1 ? x1 : x0) : g.has_attn ? (l & 1 ? x0 : x1) : reinterpret_cast<float *>(WS + p.ws.h);
         if (!per) {
-            if (mode != GEMM_RESID) a.ssq_in = st->ssq_use;
+            if (mode != GEMM_RESID) { a.ssq_in = st->ssq_use; a.quarters = MP > 64 ? 0u : H; }
             else if (sums_of_squares) {
-                // into an activation buffer that is dead until the next op but one has read them:
-                // behind O the rows that down will write, behind down those that were this layer's input (without
-                // attention that input is still down's residual, and the buffer of the attention half's output is free)
-                float *const x0 = reinterpret_cast<float *>(WS + p.ws.x0), *const x1 = reinterpret_cast<float *>(WS + p.ws.x1);
-                a.ssq_out = &mg == &g.o ? (l & 1 ? x1 : x0) : g.has_attn ? (l & 1 ? x0 : x1) : reinterpret_cast<float *>(WS + p.ws.h);
+                a.ssq_out = dead;
                 st->ssq_buf = a.ssq_out;
                 // (the slabs' launches together cover every column: the CPU takes parts of plans of up to 64 tokens only)
                 st->ssq_of = mg.ntiles * 16 == H ? a.out : nullptr;
@@ -326,7 +327,17 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         pa.out_f32 = partial; pa.out = nullptr; pa.out_stride = ncols; pa.out_row0 = 0;
         pa.sb_per_part = per; pa.part_stride = MP * ncols;
         PS_HIP(launch_gemm(GEMM_F32, pa, 0, MP, cs));
-        if (mode == GEMM_RESID && ncols == H && a.out_row0 == 0 && a.out_stride == H && !st->own_rinv_launch) {
+        const bool whole_rows = mode == GEMM_RESID && ncols == H && a.out_row0 == 0 && a.out_stride == H && !st->own_rinv_launch;
+        if (whole_rows && !g.moe && p.cpu_bytes == 0) {
+            // four workgroups a token, whose sums of squares the dense matrices behind them add up as launch_rinv would (the
+            // experts' launches and the CPU's share read finished factors: below).  Four layers of 64 tokens at H = 4096, two
+            // steps: 634 -> 617 us
+            PS_HIP(launch_splitk_epilogue_resid_quarters(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out, dead, cs));
+            st->ssq_buf = dead;
+            st->ssq_of = a.out;
+            return PS_OK;
+        }
+        if (whole_rows) {
             // the launch covers whole rows of the hidden state: its epilogue also leaves their RMS
             // factors (the bits rinv_kernel gives), and the PS_K_RINV op that follows is skipped
             PS_HIP(launch_splitk_epilogue_resid_rinv(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out,
@@ -340,7 +351,8 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                                                a.out_row0, cs));
             return PS_OK;
         }
-        PS_HIP(launch_splitk_epilogue(mode, partial, (mg.nsb + per - 1) / per, pa.part_stride, M, ncols, rinv, a.res,
+        PS_HIP(launch_splitk_epilogue(mode, partial, (mg.nsb + per - 1) / per, pa.part_stride, M, ncols, rinv,
+                                      RowQuarters{mode == GEMM_RESID ? nullptr : st->ssq_use, M, H, m.rms_eps}, a.res,
                                       a.out, a.out_stride, a.out_row0, cs));
         return PS_OK;
     };

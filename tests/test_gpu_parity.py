@@ -369,6 +369,39 @@ def test_plane_sum_of_qkv_works_out_the_factors_nobody_left(n_q, n_kv, hidden, M
     np.testing.assert_array_equal(res[0], res[2])
 
 
+@pytest.mark.parametrize("hidden,inter,M,attn,resid", [(128, 1408, 64, True, True), (1536, 1408, 5, True, True), (2176, 1408, 33, True, True),
+                                                       (512, 14336, 64, True, True), (6272, 256, 16, True, True), (2176, 1408, 17, False, True),
+                                                       (512, 1408, 40, True, False)])
+def test_sums_of_squares_left_by_o_and_down_match_a_launch_of_their_own(hidden, inter, M, attn, resid):
+    """Dense layers, 2..64 tokens: O's and down's plane sums leave four sums of squares per row, and the matrix behind
+    them (split along K, or as wide as gate/up at 14336) adds them up: the same bits as a launch for the factors (mode 2),
+    for rows that end inside every wave's first, second and fourth chunk, without attention and without the residual."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(Hn.small_dense_cfg(3), hidden=hidden, ffn_inter=inter, no_attn=not attn, no_residual=not resid)
+    W = Hn.WeightCache(cfg, 17)
+    wb, _ = Hn.total_weight_bytes(cfg)
+    plan = B.Plan(cfg, wb + B.Plan(cfg, 1 << 62, M).summary().workspace_bytes + (1 << 20), M)
+    st = B.Stack(plan)
+    for layer in range(cfg["n_layers"]):
+        for kind, expert, N, K in S.matrix_shapes(cfg):
+            st.load_matrix(layer, kind, expert, *W(layer, kind, expert))
+    xs = [torch.from_numpy(S.activations(17, 0, M, hidden)).cuda()]
+    xs.append((xs[0] * 0.25).contiguous())
+    res = {}
+    for mode in (2, 0):
+        st.set_decode_mode(mode)
+        res[mode] = []
+        for x in xs:
+            y = torch.empty_like(x)
+            st.forward(x, y)
+            st.synchronize()
+            res[mode].append(y.cpu().numpy().view(np.uint16))
+    st.close()
+    for a, b in zip(res[0], res[2]):
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("M,hidden", [(1, 512), (4, 1024), (16, 512)])
 def test_graph_replay_matches_eager_on_every_replay(M, hidden):
     """HIP-graph decode mode (one token; batched-decode steps of a few tokens, in the few-token kernel and in
