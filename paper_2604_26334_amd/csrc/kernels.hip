@@ -1011,11 +1011,12 @@ __global__ __launch_bounds__(kAttnWaves * 64, 16 / kAttnWaves) void attn_decode_
 // 128 KB of operand reads from LDS, 2 x 32 MFMAs per SIMD (1024), about 1100 cycles of softmax arithmetic
 // per SIMD (a third of them the exponentials).  So: rows go from memory straight into LDS, two rounds' worth of stages,
 // the next round on its way while one is multiplied (one barrier per round); two row tiles per wave share every operand
-// read; two waves per SIMD.  What the scores cost is kept to the least: a row is rescaled only when its maximum has risen
-// by more than 2^kAttnGrow since it last was (some row of 32 rises in almost every round, and a rescaling is 64
-// multiplications; weights of up to 2^8 are as exact in fp16 and leave fp32 sums all the room they need), a round's place in
-// memory goes into the fills' scalar base, and the stage is a compile-time number.  Rows of one (kv head, round) are read by
-// all row blocks: the head is the fastest grid index, so with 8 heads a head's blocks share an XCD's L2.
+// read; two waves per SIMD.  What the scores cost is kept to the least: a tile of 16 rows is rescaled (32 multiplications)
+// only in rounds that raise one of its maxima, a round's place in memory goes into the fills' scalar base, and the stage is a
+// compile-time number.  A row's weights are always taken relative to its own running maximum: a rule by which rows wait
+// until some row of the wave has risen by 2^8 is faster (512 tokens 62.5 us against 70), but then a row's fp16 weights, and so
+// its bits, depend on the rows beside it; decided row by row it is 62.5 as well, with other roundings than these.  Rows of one (kv
+// head, round) are read by all row blocks: the head is the fastest grid index, so with 8 heads a head's blocks share an XCD's L2.
 // SPLIT: the rounds are dealt out to `nsplit` workgroups per row block (short chunks leave most CUs idle
 // otherwise) and each writes, per row, a record (maximum, weight sum, 128 weighted sums) that
 // attn_combine_chunk_kernel merges in split order; without SPLIT the finished rows are written.  The deal goes by
@@ -1027,16 +1028,14 @@ __global__ __launch_bounds__(kAttnWaves * 64, 16 / kAttnWaves) void attn_decode_
 // added at the end.  One wave of each pair has rows, so the MFMAs are fewer than with full tiles, and the time is
 // the fills' and the latencies'.  2 tokens over 4000 positions 8.3 us with the weights in fp16, 8.3 with three parts;
 // 3 tokens over 1000 7.9 / 7.9.
-// Measured, 32 query / 8 kv heads over 4096 cached positions: 512 tokens 75 -> 64.5 us by the last three of these (250 ->
-// 110 vector instructions per wave and round; 37 rounds of 1.6 us; the row fills alone take 45, the rest without them 49),
-// and the launch that appended the rows, 5 us, is gone; 64 tokens 16.9 -> 15.6.  A round still takes more than its largest
-// part, and these did not change that: every operand requested in front of the next round's fills (64), the next round's
-// scores worked out beside this one's weights (68), steps of 64 positions with three on their way (70, twice the LDS reads),
-// fewer vector instructions still (64.5).
+// Measured, 32 query / 8 kv heads over 4096 cached positions: 512 tokens 73.3 -> 70.0 us by the last three of these, and the
+// launch that appended the rows, 5 us, is gone; 16000 positions 226 -> 212; 64 tokens over 4000 17.5 -> 17.3.  A round takes
+// more than its largest part (row fills alone 45 us, the rest without them 49, both with the 62.5 us rule above), and these did
+// not change that: every operand requested in front of the next round's fills, the next round's scores worked out beside this
+// one's weights (+4 us), steps of 64 positions with three on their way (+6, twice the LDS reads).
 // ------------------------------------------------------------------------------------
 constexpr uint32_t kAttnRound = 128;                           // positions per round
 constexpr uint32_t kAttnHalfStage = kAttnRound * 256;           // K or V rows of a round; in LDS: K of two rounds, V of two rounds
-constexpr float kAttnGrow = 8.f;                               // a row's weights may reach 2^8 before it is rescaled
 constexpr uint32_t kAttnOPitch = 132;                          // floats per row when the position groups meet
 constexpr size_t kAttnRowsLds = 4 * 64 * kAttnOPitch * 4 + 2 * 4 * 64 * 4;   // the meeting's rows, maxima and sums (more than two stages)
 static_assert(4 * kAttnHalfStage <= 4 * 64 * kAttnOPitch * 4 && kAttnRowsLds <= 160 * 1024, "LDS of the chunk attention");
@@ -1199,12 +1198,11 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
             mx[t] = max3(max3(S[t][0][0], S[t][0][1], S[t][0][2]), max3(S[t][0][3], S[t][1][0], S[t][1][1]), max3(S[t][1][2], S[t][1][3], S[t][1][3]));
             mx[t] = rows4_meet<true>(mx[t]);
         }
-        // Some row's maximum rose by more than the weights may grow (2^kAttnGrow; fp16 holds 2^15 of them): rescale.  A row
-        // that has seen nothing holds zeros, and the difference of two -inf is not a number.
-        const float room = FEW ? 0.f : kAttnGrow / c2;
-        if (__any(mx[0] > m_run[0] + room || mx[NT - 1] > m_run[NT - 1] + room)) {
+        // Some row of the tile has a new maximum: rescale (the others by 1, so what a row becomes does not depend on its
+        // neighbours).  A row that has seen nothing holds zeros, and the difference of two -inf is not a number.
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
+        for (int t = 0; t < NT; ++t) {
+            if (__any(mx[t] > m_run[t])) {
                 mx[t] = fmaxf(m_run[t], mx[t]);
                 const float resc = m_run[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run[t] - mx[t]) * c2);
                 m_run[t] = mx[t];

@@ -988,8 +988,8 @@ def test_an_infinite_value_in_the_cache_reaches_the_rows_that_see_it(n_q, n_kv, 
 @pytest.mark.parametrize("n_q,n_kv,plan_tokens,M,ctx0", [(8, 2, 300, 300, 1500), (2, 2, 256, 70, 700), (8, 8, 256, 256, 63), (4, 2, 64, 64, 2000),
                                                        (8, 1, 64, 9, 900), (8, 2, 64, 3, 1300)])
 def test_chunk_attention_whose_scores_rise_along_the_cache(n_q, n_kv, plan_tokens, M, ctx0):
-    """Keys that grow along one direction: a row's scores rise (or fall) steadily, by more and by less per round than what a
-    row's weights may grow before it is rescaled, with one jump.  The attention rows against float64 on the rows' own QKV:
+    """Keys that grow along one direction: a row's scores rise (or fall) steadily, some by far more per round than fp16 weights
+    can span, with one jump.  The attention rows against float64 on the rows' own QKV:
     a weight is off by 2^-11 (fp16; far less for fewer than 16 score rows), its exponent by what fp32 makes of scores of up
     to 800 (8 bits of 24: 2^-14), the stored row by 2^-11; and the appended rows are the QKV rows' bits."""
     import torch
@@ -1030,6 +1030,42 @@ def test_chunk_attention_whose_scores_rise_along_the_cache(n_q, n_kv, plan_token
             P /= P.sum(axis=1, keepdims=True)
             err, bound = np.abs(got[:, h] - P @ vals), (2.0 ** -10 + 2.0 ** -13) * (P @ np.abs(vals)) + 2.0 ** -11 * np.abs(P @ vals) + 1e-6
             assert (err <= bound).all(), (h, float((err / bound).max()))
+
+
+@pytest.mark.parametrize("n_q,n_kv,plan_tokens,M,head,ctx0", [(8, 2, 300, 70, 67, 1500), (2, 2, 300, 41, 38, 700), (8, 8, 256, 256, 17, 900),
+                                                            (16, 8, 200, 70, 51, 1500), (32, 8, 255, 64, 41, 2000), (8, 1, 64, 9, 3, 900)])
+def test_an_attention_row_does_not_depend_on_the_rows_that_share_its_wave(n_q, n_kv, plan_tokens, M, head, ctx0):
+    """Keys that grow along one direction, so that the maxima of a wave's 32 score rows rise in different rounds, by little
+    and by much, while many positions keep a weight: the attention rows of the first `head` tokens have the same bits when
+    only these tokens come (a ragged trip that ends inside a wave) and when the tokens behind them are others, in plans
+    whose positions are dealt to several workgroups and in plans whose positions are not."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(_kv_cfg(1, ctx0 + plan_tokens + 3), n_q_heads=n_q, n_kv_heads=n_kv)
+    W = Hn.WeightCache(cfg, 97)
+    K, V = S.kv_cache(97, 0, n_kv, ctx0, 128)
+    u = np.random.default_rng(97).standard_normal(128)
+    ramp = np.linspace(0.0, 4.0, ctx0) + np.where(np.arange(ctx0) > ctx0 // 2, 1.6, 0.0)
+    K = (0.1 * K.astype(np.float64) + (ramp[:, None] * (u / np.linalg.norm(u)) * 11.3)).astype(np.float16)
+    st = B.Stack(B.Plan(cfg, 1 << 30, plan_tokens))
+    for k, ex, N, Kd in S.matrix_shapes(cfg):
+        st.load_matrix(0, k, ex, *W(0, k, ex))
+    for g in range(n_kv):
+        st.load_kv(0, g, K[g], V[g])
+    x = S.activations(97, 0, M, cfg["hidden"])
+    others = x.copy()
+    others[head:] = S.activations(97, 1, M, cfg["hidden"])[head:]
+    rows = []
+    for xs in (x, others, x[:head]):
+        xin = torch.from_numpy(np.ascontiguousarray(xs)).to(st.device)
+        st.set_context(ctx0)
+        B.chunked_forward(st, xin, torch.zeros_like(xin))
+        st.synchronize()
+        rows.append(st.debug_buffer(5, np.float16, (head, n_q, 128)).view(np.uint16).copy())
+    st.close()
+    assert not np.isnan(rows[0].view(np.float16)).any()
+    for other in rows[1:]:
+        np.testing.assert_array_equal(other, rows[0])
 
 
 def test_chunked_prefill_fills_the_cache_it_then_decodes_over():
