@@ -24,15 +24,20 @@ int32_t ps_pack_matrix(const uint16_t *scales, const uint8_t *codes, uint32_t ro
                        uint8_t *out);
 
 /* ps_stack_set_decode_mode(st, PS_DECODE_MODE_OWN_RINV): mode 0, except that in a forward of 2 tokens
- * or more the RMS factor of a hidden-state row always comes from a launch of its own; in modes 0 and
- * 1 the epilogue of an O or down matrix that one launch covers whole and that is summed from
- * split-K planes leaves the factor itself, and so do, in larger plans, the sums of squares that O and
- * down leave (same bits: the test of that claim is what this mode is for). */
+ * or more (but for the matrices of the few-token kernel, which work them out themselves) the RMS factor
+ * of a hidden-state row always comes from a launch of its own.  In modes 0 and 1, where an O or down
+ * matrix is summed from split-K planes and one launch covers it whole, that sum leaves four sums of
+ * squares per row, which the matrix behind it adds up (MoE layers and plans with a CPU share: the
+ * finished factor); the plane sum of a QKV whose factors nobody has left works them out itself; and
+ * in plans of more than 64 tokens O and down leave sums of squares per 128 columns (same bits in every
+ * case: the test of that claim is what this mode is for). */
 #define PS_DECODE_MODE_OWN_RINV 2
 
 /* Time one kernel kind in isolation (measurement aid): every resident op of kind `kernel`
  * (PS_K_*) of a dense stack is launched back to back, `reps` passes after one warm-up pass,
- * between two events on the compute stream; *avg_launch_ms = elapsed / launches.  The
+ * between two events on the compute stream; *avg_launch_ms = elapsed / launches, where launches counts the ops
+ * of a pass that launch anything.  PS_K_RINV: the launch of PS_DECODE_MODE_OWN_RINV, whatever the mode; ops whose
+ * matrix is a few-token kernel launch nothing (0 launches of 0 ms if there are no others).  The
  * activations are whatever the workspace holds, the outputs go to the workspace.  Blocks. */
 int32_t ps_stack_time_kernel(ps_stack *st, uint32_t kernel, uint32_t reps, double *avg_launch_ms,
                              uint32_t *launches);

@@ -96,6 +96,7 @@ struct ps_stack {
     float *ssq_buf = nullptr;
     const float *ssq_use = nullptr;           // set by a PS_K_RINV op: what the matrices behind it take their RMS factors from
     const void *own_factors = nullptr;        // set by a PS_K_RINV op: rows whose factors the plane sum behind them works out itself
+    uint32_t idle_ops = 0;                    // PS_K_RINV ops issued so far that had nothing to launch
     uint32_t routed_layer = kNotRouted;       // MoE layer whose routing rode in an earlier launch of this forward
     static constexpr uint32_t kNotRouted = 0xFFFFFFFFu;
     std::vector<hipEvent_t> prof_ev;          // 2 per op of the last profiled forward
@@ -364,6 +365,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             st->ssq_use = st->ssq_of == rows ? st->ssq_buf : nullptr;
             st->ssq_of = nullptr;
             st->own_factors = nullptr;
+            ++st->idle_ops;
             if (st->ssq_use) return PS_OK;
             // the few-token kernels of QKV (factors of kind 0) and of a dense gate/up (kind 1) compute their own
             if (op.info.shard0 == 0 && few_token_gemv(p, g.qkv)) return PS_OK;
@@ -372,6 +374,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // nobody has left the factors QKV wants, and its planes are summed by a launch of its own: that one works them out
             // (a launch fewer; each of a token's workgroups reads the row again, which 64 tokens do not notice)
             if (op.info.shard0 == 0 && g.has_attn && gemm_sb_per_part(g.qkv, MP) && !st->own_rinv_launch) { st->own_factors = rows; return PS_OK; }
+            --st->idle_ops;
             if (factor_runs) { PS_HIP(launch_rinv_runs(rows, M, H, m.rms_eps, rinv, cs)); return PS_OK; }
             const bool ride = riding && op.info.shard0 == 1;
             PS_HIP(launch_rinv(rows, M, H, m.rms_eps, rinv, ride ? riding : nullptr, cs));
@@ -1677,21 +1680,27 @@ int32_t ps_stack_time_kernel(ps_stack *st, uint32_t kernel, uint32_t reps, doubl
     hipEvent_t e0, e1;
     PS_HIP(hipEventCreate(&e0));
     PS_HIP(hipEventCreate(&e1));
-    uint32_t n = 0;
+    uint32_t n = 0, ops = 0;
     int32_t rc = PS_OK;
+    // factors that a matrix's own launches work out or add up in a forward come from a launch here: it is what is timed
+    const bool own_rinv_launch = st->own_rinv_launch;
+    if (kernel == PS_K_RINV) st->own_rinv_launch = true;
     for (uint32_t r = 0; r <= reps && rc == PS_OK; ++r) {   // pass 0 warms up
         if (r == 1) { if (hipEventRecord(e0, st->compute) != hipSuccess) rc = PS_E_HIP; n = 0; }
         for (const ps::Op &op : st->dense_sched.ops) {
             if (op.info.type != PS_OP_KERNEL || op.info.kernel != kernel || op.info.slot >= 0) continue;
-            st->rinv_of = nullptr;   // timed in isolation: every launch is issued
+            st->rinv_of = nullptr;   // timed in isolation: nobody has left any factors
             st->ssq_of = nullptr;
             st->ssq_use = nullptr;
             st->own_factors = nullptr;
+            const uint32_t idle = st->idle_ops;
             rc = issue_kernel(st, st->dense_sched, op, xin, xout);
             if (rc) break;
-            ++n;
+            ++ops;
+            n += st->idle_ops == idle;
         }
     }
+    st->own_rinv_launch = own_rinv_launch;
     st->rinv_of = nullptr;
     float ms = 0;
     if (rc == PS_OK && (hipEventRecord(e1, st->compute) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
@@ -1702,8 +1711,8 @@ int32_t ps_stack_time_kernel(ps_stack *st, uint32_t kernel, uint32_t reps, doubl
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
-    if (n == 0) { ps::set_error("no resident op of kernel kind %u", kernel); return PS_E_ARG; }
-    *avg_launch_ms = (double)ms / n;
+    if (ops == 0) { ps::set_error("no resident op of kernel kind %u", kernel); return PS_E_ARG; }
+    *avg_launch_ms = n ? (double)ms / n : 0.0;
     *launches = n / reps;
     return PS_OK;
 }

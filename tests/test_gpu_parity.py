@@ -402,6 +402,28 @@ def test_sums_of_squares_left_by_o_and_down_match_a_launch_of_their_own(hidden, 
         np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("M,hidden,per_layer", [(64, 512, 2), (3, 512, 2), (3, 1024, 0), (300, 512, 2)])
+def test_the_factor_launch_timed_alone_is_one_launch_per_counted_op(M, hidden, per_layer):
+    """Whatever forwards work out elsewhere (QKV's plane sum, sums of squares left by O and down), the factor launch timed
+    alone is issued for every op that it counts: the same count, and a time near that of mode 2, where it always is (an op
+    that is counted and not issued would halve it).  Ops of the few-token kernel's matrices launch nothing."""
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(Hn.small_dense_cfg(2), hidden=hidden, n_q_heads=hidden // 128, ffn_inter=2 * hidden)
+    W = Hn.WeightCache(cfg, 17)
+    st = B.Stack(B.Plan(cfg, 1 << 30, M))
+    for layer in range(cfg["n_layers"]):
+        for kind, expert, N, K in S.matrix_shapes(cfg):
+            st.load_matrix(layer, kind, expert, *W(layer, kind, expert))
+    times = {0: [], 2: []}
+    for mode in (2, 0, 2, 0, 2, 0):
+        st.set_decode_mode(mode)
+        ms, n = st.time_kernel(B.PS_K_RINV, 400)
+        assert n == per_layer * cfg["n_layers"]
+        times[mode].append(ms)
+    st.close()
+    assert min(times[0]) >= 0.75 * min(times[2]), times
+
+
 @pytest.mark.parametrize("M,hidden", [(1, 512), (4, 1024), (16, 512)])
 def test_graph_replay_matches_eager_on_every_replay(M, hidden):
     """HIP-graph decode mode (one token; batched-decode steps of a few tokens, in the few-token kernel and in
