@@ -176,7 +176,7 @@ typedef struct ps_plan_summary_t {
 typedef struct ps_stats {
     uint64_t resident_bytes_step; /* weight bytes read in place in the last forward */
     uint64_t streamed_bytes_step; /* weight bytes copied H2D in the last forward    */
-    uint32_t n_copies, n_kernels;
+    uint32_t n_copies, n_kernels; /* copies and kernel ops issued, ops that share a launch counted as one */
     /* the rest is valid only after a forward with profiling on, once complete   */
     double copy_ms;     /* sum of copy durations on the copy stream              */
     double compute_ms;  /* sum of kernel durations on the compute stream         */

@@ -855,7 +855,7 @@ int32_t run_schedule(ps_stack *st, const ps_schedule &sc, const __half *x_in, __
                 const int32_t rc = issue_kernel(st, sc, both, x_in, x_out);
                 if (rc) return rc;
                 ss.resident_bytes_step += both.info.bytes;
-                ss.n_kernels += 2;
+                ss.n_kernels++;
             }
             if (sc.ops[i + 3].info.flags & PS_OPF_RECORD_FREE) PS_HIP(hipEventRecord(st->ev_free[sc.ops[i + 3].info.slot], st->compute));
             i += 3;

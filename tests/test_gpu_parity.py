@@ -195,6 +195,47 @@ def test_one_token_routing_rides_in_o_and_experts_share_a_launch(E, top_k, n_kv,
     _check(cfg, 79, 1, _budgets(cfg, 1, [1.0, 0.8, 0.5, 0.3]), logits=lg)
 
 
+@pytest.mark.parametrize("E,top_k,n_kv,H", [(8, 2, 1, 256), (64, 8, 2, 1024), (130, 7, 4, 384), (256, 16, 1, 256), (264, 4, 1, 256)])
+def test_resident_and_filled_experts_of_a_layer_do_share_a_launch(E, top_k, n_kv, H):
+    """The op list says which layers have resident experts and experts of a single slot fill: in those, and only those, a
+    one-token forward issues one launch of gate/up and one of down instead of two each.  Profiling, which times every op,
+    keeps them apart; both give the same bits."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(Hn.small_moe_cfg(2), n_experts=E, top_k=top_k, n_kv_heads=n_kv, hidden=H)
+    W = Hn.WeightCache(cfg, 79)
+    x = S.activations(79, 0, 1, H)
+    shared = 0
+    for budget in _budgets(cfg, 1, [0.8, 0.5, 0.3]):
+        plan = B.Plan(cfg, budget, 1)
+        st = B.Stack(plan)
+        for layer in range(cfg["n_layers"]):
+            for kind, expert, N, K in S.matrix_shapes(cfg):
+                st.load_matrix(layer, kind, expert, *W(layer, kind, expert))
+        xin = torch.from_numpy(x).to(st.device)
+        for seed in range(4):
+            lg = S.router_logits(seed, 0, cfg["n_layers"], 1, E)
+            ops = plan.schedule(lg).ops()
+            both = 0
+            for layer in range(cfg["n_layers"]):
+                slots = [o.slot >= 0 for o in ops if o.type == B.PS_OP_KERNEL and o.layer == layer and
+                         o.kernel in (B.PS_K_EXPERT_GATE_UP, B.PS_K_EXPERT_DOWN)]
+                both += slots == [False, False, True, True]
+            outs, kernels = {}, {}
+            for prof in (0, 1):
+                st.set_profiling(prof)
+                y = torch.empty_like(xin)
+                st.forward(xin, y, lg)
+                st.synchronize()
+                outs[prof], kernels[prof] = y.cpu().numpy().view(np.uint16), st.stats().n_kernels
+            np.testing.assert_array_equal(outs[0], outs[1])
+            assert kernels[1] - kernels[0] == 2 * both, (budget, seed)
+            shared += both
+        st.close()
+        plan.close()
+    assert shared > 0
+
+
 @pytest.mark.parametrize("busiest", [16, 17, 33, 48, 49, 65, 96, 97, 129])
 def test_expert_gemm_tile_by_the_busiest_experts_tokens(busiest):
     """Grouped expert launches take the smallest token tile (16, 32, 48, 64, 96, else 128) that holds the busiest
