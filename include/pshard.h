@@ -186,7 +186,7 @@ typedef struct ps_stats {
     uint64_t cpu_bytes_step; /* weight bytes read by the CPU back-end in the last forward           */
     double cpu_ms;      /* host time inside the CPU kernel in the last forward (always valid)       */
     double cpu_wait_ms; /* host time waiting for activations to arrive from the GPU (always valid)  */
-    uint32_t graph_replay; /* 1 if the last forward was one HIP-graph launch (decode mode 1), else 0  */
+    uint32_t graph_replay; /* 1 if the last forward was one HIP-graph launch (decode modes 1, 3), else 0 */
     uint32_t reserved;
 } ps_stats;
 
@@ -526,13 +526,15 @@ int32_t ps_stack_forward_chunked(ps_stack *st, const void *x_in, void *x_out, ui
                                  void *last_logits_dev, uint32_t *trips);
 /* Decode execution mode.  0 (default): one launch per shard.  1: applies when the plan is dense with
  * every shard (KV-cache shards included) resident and no CPU share, for one token or, without a KV
- * cache, for a batched-decode step of up to 64 tokens, and a replay pays: at least 64 launches a step, or less than
- * 4 MB of weights a launch (otherwise mode 0 runs, which is then the faster): the launch-per-shard
- * kernel sequence is captured once per (x_in, x_out, logits, valid rows) into a HIP graph (kernel
+ * cache, for a batched-decode step of up to 64 tokens, and a replay pays: at least 32 kernel launches a step, or more
+ * than one for every 0.75 MB of weights and cache that a launch reads (otherwise mode 0 runs, which is then the
+ * faster; ps_stats.graph_replay tells): the launch-per-shard kernel sequence is captured once per (x_in, x_out, logits, valid rows) into a HIP graph (kernel
  * nodes only) and replayed; with a KV cache the context length then travels in a
  * device word set before each replay, and the attention launch covers every chunk the cache can
  * hold (workgroups past the context leave at once).  Order and arithmetic are unchanged
- * (Algorithm 1's RunInTopologicalOrder); both modes give bit-identical results.  (A third value
+ * (Algorithm 1's RunInTopologicalOrder); both modes give bit-identical results.  3: replays wherever
+ * mode 1 applies, also where that is the slower (by 4 to 8 us a step): for a host that has better to do
+ * than to issue launches, 2.7 us each against 15 to 70 us a replay.  (The value 2
  * exists for tests only, see pshard_test.h.)  Not to be called while a forward is in flight. */
 int32_t ps_stack_set_decode_mode(ps_stack *st, int32_t mode);
 /* How streamed shards cross PCIe (Section 3: the copy of the next shard runs beside the compute of

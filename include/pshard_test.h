@@ -25,7 +25,7 @@ int32_t ps_pack_matrix(const uint16_t *scales, const uint8_t *codes, uint32_t ro
 
 /* ps_stack_set_decode_mode(st, PS_DECODE_MODE_OWN_RINV): mode 0, except that in a forward of 2 tokens
  * or more (but for the matrices of the few-token kernel, which work them out themselves) the RMS factor
- * of a hidden-state row always comes from a launch of its own.  In modes 0 and 1, where an O or down
+ * of a hidden-state row always comes from a launch of its own.  In the other modes, where an O or down
  * matrix is summed from split-K planes and one launch covers it whole, that sum leaves four sums of
  * squares per row, which the matrix behind it adds up (MoE layers and plans with a CPU share: the
  * finished factor); the plane sum of a QKV whose factors nobody has left works them out itself; and

@@ -574,7 +574,8 @@ class Stack:
         _check(lib().ps_stack_set_copy_mode(self.h, int(gather)))
 
     def set_decode_mode(self, mode):
-        """0: launch per shard, 1: HIP-graph replay where it pays (same bits), 2: mode 0 with every RMS factor from a launch of its own (see pshard_test.h)."""
+        """0: launch per shard, 1: HIP-graph replay where it pays (same bits), 2: mode 0 with every RMS factor from a launch of its own (see pshard_test.h),
+        3: HIP-graph replay wherever it is possible (same bits)."""
         with self.torch.cuda.device(self.device):
             _check(lib().ps_stack_set_decode_mode(self.h, int(mode)))
 

@@ -96,7 +96,8 @@ struct ps_stack {
     float *ssq_buf = nullptr;
     const float *ssq_use = nullptr;           // set by a PS_K_RINV op: what the matrices behind it take their RMS factors from
     const void *own_factors = nullptr;        // set by a PS_K_RINV op: rows whose factors the plane sum behind them works out itself
-    uint32_t idle_ops = 0;                    // PS_K_RINV ops issued so far that had nothing to launch
+    uint32_t launches = 0;                    // kernels issue_kernel has launched so far, or counted
+    bool count_only = false;                  // issue_kernel counts its launches and makes none (count_launches)
     uint32_t routed_layer = kNotRouted;       // MoE layer whose routing rode in an earlier launch of this forward
     static constexpr uint32_t kNotRouted = 0xFFFFFFFFu;
     std::vector<hipEvent_t> prof_ev;          // 2 per op of the last profiled forward
@@ -225,6 +226,18 @@ bool dense_gemv_args(const ps_stack *st, const Op &op, const __half *x_in, __hal
     return true;
 }
 
+// forgets what earlier launches have left for later ones of the same forward
+void reset_left(ps_stack *st) {
+    st->rinv_of = nullptr;
+    st->ssq_of = nullptr;
+    st->ssq_use = nullptr;
+    st->own_factors = nullptr;
+    st->routed_layer = ps_stack::kNotRouted;
+}
+
+// a launch of issue_kernel: counted, and made unless it is only to be counted
+#define PS_LAUNCH(call) do { ++st->launches; if (!st->count_only) PS_HIP(call); } while (0)
+
 int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __half *x_in, __half *x_out) {
     const ps_plan &p = st->plan;
     const ModelGeom &g = p.g;
@@ -270,7 +283,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         GemvArgs a = gemv_base(g.head);
         a.top_k = 1; a.W = wptr(op); a.nunits = s.ntiles; a.x = x_out + (size_t)st->head_row0 * H;
         a.out = st->logits; a.out_row0 = s.tile0 * 16;
-        PS_HIP(launch_gemv(GEMV_PLAIN, gemv_ksplit(g.head.ngroups, g.head.ntiles), a, 0, nullptr, cs));
+        PS_LAUNCH(launch_gemv(GEMV_PLAIN, gemv_ksplit(g.head.ngroups, g.head.ntiles), a, 0, nullptr, cs));
         return PS_OK;
     }
     // MoE: the layer's routing rides in the launch in front of the experts that leaves the RMS factors of their input
@@ -284,7 +297,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         dense_gemv_args(st, op, x_in, x_out, &a, &mode, &ks);
         // a MoE layer's routing rides in O's first launch
         const bool ride = riding && op.info.kernel == PS_K_O && st->routed_layer != l;
-        PS_HIP(launch_gemv(mode, ks, a, 0, ride ? riding : nullptr, cs));
+        PS_LAUNCH(launch_gemv(mode, ks, a, 0, ride ? riding : nullptr, cs));
         if (ride) st->routed_layer = l;
         return PS_OK;
     }
@@ -294,7 +307,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         int mode;
         uint32_t ks;
         dense_gemv_args(st, op, x_in, x_out, &a, &mode, &ks);
-        PS_HIP(launch_gemv_mt(mode, ks, a, M, cs));
+        PS_LAUNCH(launch_gemv_mt(mode, ks, a, M, cs));
         return PS_OK;
     }
     // Many tokens, dense: O and down leave the sums of squares of the rows they store, per 128 columns, and the matrices
@@ -319,7 +332,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                 // (the slabs' launches together cover every column: the CPU takes parts of plans of up to 64 tokens only)
                 st->ssq_of = mg.ntiles * 16 == H ? a.out : nullptr;
             }
-            PS_HIP(launch_gemm(mode, a, 0, MP, cs));
+            PS_LAUNCH(launch_gemm(mode, a, 0, MP, cs));
             return PS_OK;
         }
         GemmArgs pa = a;
@@ -327,13 +340,13 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         const uint32_t ncols = a.ntiles * 16;
         pa.out_f32 = partial; pa.out = nullptr; pa.out_stride = ncols; pa.out_row0 = 0;
         pa.sb_per_part = per; pa.part_stride = MP * ncols;
-        PS_HIP(launch_gemm(GEMM_F32, pa, 0, MP, cs));
+        PS_LAUNCH(launch_gemm(GEMM_F32, pa, 0, MP, cs));
         const bool whole_rows = mode == GEMM_RESID && ncols == H && a.out_row0 == 0 && a.out_stride == H && !st->own_rinv_launch;
         if (whole_rows && !g.moe && p.cpu_bytes == 0) {
             // four workgroups a token, whose sums of squares the dense matrices behind them add up as launch_rinv would (the
             // experts' launches and the CPU's share read finished factors: below).  Four layers of 64 tokens at H = 4096, two
             // steps: 634 -> 617 us
-            PS_HIP(launch_splitk_epilogue_resid_quarters(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out, dead, cs));
+            PS_LAUNCH(launch_splitk_epilogue_resid_quarters(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out, dead, cs));
             st->ssq_buf = dead;
             st->ssq_of = a.out;
             return PS_OK;
@@ -341,18 +354,18 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         if (whole_rows) {
             // the launch covers whole rows of the hidden state: its epilogue also leaves their RMS
             // factors (the bits rinv_kernel gives), and the PS_K_RINV op that follows is skipped
-            PS_HIP(launch_splitk_epilogue_resid_rinv(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out,
+            PS_LAUNCH(launch_splitk_epilogue_resid_rinv(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out,
                                                      m.rms_eps, rinv, riding, cs));
             if (riding) st->routed_layer = l;
             st->rinv_of = a.out;
             return PS_OK;
         }
         if (mode == GEMM_PLAIN && st->own_factors == a.x) {
-            PS_HIP(launch_splitk_epilogue_norm(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, ncols, a.x, H, m.rms_eps, a.out, a.out_stride,
+            PS_LAUNCH(launch_splitk_epilogue_norm(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, ncols, a.x, H, m.rms_eps, a.out, a.out_stride,
                                                a.out_row0, cs));
             return PS_OK;
         }
-        PS_HIP(launch_splitk_epilogue(mode, partial, (mg.nsb + per - 1) / per, pa.part_stride, M, ncols, rinv,
+        PS_LAUNCH(launch_splitk_epilogue(mode, partial, (mg.nsb + per - 1) / per, pa.part_stride, M, ncols, rinv,
                                       RowQuarters{mode == GEMM_RESID ? nullptr : st->ssq_use, M, H, m.rms_eps}, a.res,
                                       a.out, a.out_stride, a.out_row0, cs));
         return PS_OK;
@@ -365,7 +378,6 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             st->ssq_use = st->ssq_of == rows ? st->ssq_buf : nullptr;
             st->ssq_of = nullptr;
             st->own_factors = nullptr;
-            ++st->idle_ops;
             if (st->ssq_use) return PS_OK;
             // the few-token kernels of QKV (factors of kind 0) and of a dense gate/up (kind 1) compute their own
             if (op.info.shard0 == 0 && few_token_gemv(p, g.qkv)) return PS_OK;
@@ -374,10 +386,9 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // nobody has left the factors QKV wants, and its planes are summed by a launch of its own: that one works them out
             // (a launch fewer; each of a token's workgroups reads the row again, which 64 tokens do not notice)
             if (op.info.shard0 == 0 && g.has_attn && gemm_sb_per_part(g.qkv, MP) && !st->own_rinv_launch) { st->own_factors = rows; return PS_OK; }
-            --st->idle_ops;
-            if (factor_runs) { PS_HIP(launch_rinv_runs(rows, M, H, m.rms_eps, rinv, cs)); return PS_OK; }
+            if (factor_runs) { PS_LAUNCH(launch_rinv_runs(rows, M, H, m.rms_eps, rinv, cs)); return PS_OK; }
             const bool ride = riding && op.info.shard0 == 1;
-            PS_HIP(launch_rinv(rows, M, H, m.rms_eps, rinv, ride ? riding : nullptr, cs));
+            PS_LAUNCH(launch_rinv(rows, M, H, m.rms_eps, rinv, ride ? riding : nullptr, cs));
             if (ride) st->routed_layer = l;
             return PS_OK;
         }
@@ -437,7 +448,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                 attn_chunk_deal(c.ctx, MP, c.group, m.n_kv_heads, &c.nsplit, &c.rounds_per_split);
                 // the last rows of a chunk, or a chunk of a few (a longer plan's stay as they are whatever comes with them)
                 c.few = MP < kAttnOnePassTokens && M * c.group < 16;
-                PS_HIP(launch_attn_chunk(c, cs));
+                PS_LAUNCH(launch_attn_chunk(c, cs));
                 return PS_OK;
             }
             AttnArgs a{};
@@ -447,7 +458,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             a.chunk_cap = (m.kv_context + kAttnChunk - 1) / kAttnChunk;
             a.q = qkv; a.part = reinterpret_cast<float *>(WS + p.ws.apart);
             a.ctx_dev = st->use_graph ? reinterpret_cast<const uint32_t *>(WS + p.ws.ctx) : nullptr;
-            PS_HIP(launch_attn_decode(a, cs));
+            PS_LAUNCH(launch_attn_decode(a, cs));
             return PS_OK;
         }
         case PS_K_ATTN_COMBINE:
@@ -456,11 +467,11 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                 uint32_t nsplit, per;
                 attn_chunk_deal(st->ctx, MP, m.n_q_heads / m.n_kv_heads, m.n_kv_heads, &nsplit, &per);
                 if (nsplit > 1)    // every token's records merged, and the chunk's rows appended (one split: the attention did both)
-                    PS_HIP(launch_attn_combine_chunk(reinterpret_cast<const float *>(WS + p.ws.apart), nsplit, st->ctx, m.kv_context, qkv, g.qkv_w,
+                    PS_LAUNCH(launch_attn_combine_chunk(reinterpret_cast<const float *>(WS + p.ws.apart), nsplit, st->ctx, m.kv_context, qkv, g.qkv_w,
                                                      m.n_q_heads, m.n_kv_heads, M, home, reinterpret_cast<__half *>(WS + p.ws.attn), g.attn_w, cs));
                 return PS_OK;
             }
-            PS_HIP(launch_attn_combine(reinterpret_cast<const float *>(WS + p.ws.apart),
+            PS_LAUNCH(launch_attn_combine(reinterpret_cast<const float *>(WS + p.ws.apart),
                                        (m.kv_context + kAttnChunk - 1) / kAttnChunk, st->ctx,
                                        st->use_graph ? reinterpret_cast<const uint32_t *>(WS + p.ws.ctx) : nullptr, m.kv_context, qkv,
                                        m.n_q_heads, m.n_kv_heads,
@@ -468,7 +479,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                                        reinterpret_cast<__half *>(WS + p.ws.attn), cs));
             return PS_OK;
         case PS_K_ROUTE:
-            if (st->routed_layer != l) PS_HIP(launch_route(ra, cs));
+            if (st->routed_layer != l) PS_LAUNCH(launch_route(ra, cs));
             return PS_OK;
         case PS_K_EXPERT_GATE_UP:
         case PS_K_EXPERT_DOWN: {
@@ -485,13 +496,13 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                 if (gu) { a.nunits = mg.ntiles / 2; a.x = hbuf; a.x_stride = H; a.out = sbuf; a.out_stride = g.ffn_i; }
                 else { a.nunits = mg.ntiles; a.x = sbuf; a.x_stride = g.ffn_i; a.out_f32 = y; a.out_stride = H; }
                 const uint32_t units = gu ? mg.ntiles / 2 : mg.ntiles;
-                PS_HIP(launch_gemv(gu ? GEMV_GATE_UP : GEMV_F32, gemv_ksplit(mg.ngroups, units * m.top_k), a, op.ntasks, nullptr, cs));
+                PS_LAUNCH(launch_gemv(gu ? GEMV_GATE_UP : GEMV_F32, gemv_ksplit(mg.ngroups, units * m.top_k), a, op.ntasks, nullptr, cs));
             } else {
                 GemmArgs a = gemm_base(mg);
                 a.tasks = tasks; a.pairs = pairs; a.ntiles = mg.ntiles;
                 if (gu) { a.x = hbuf; a.x_stride = H; a.out = sbuf; a.out_stride = g.ffn_i; }
                 else { a.x = sbuf; a.x_stride = g.ffn_i; a.out_f32 = y; a.out_stride = H; }
-                PS_HIP(launch_gemm(gu ? GEMM_GATE_UP : GEMM_F32, a, op.ntasks, max_tok, cs));
+                PS_LAUNCH(launch_gemm(gu ? GEMM_GATE_UP : GEMM_F32, a, op.ntasks, max_tok, cs));
             }
             return PS_OK;
         }
@@ -500,7 +511,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // form computes its own) or the output head
             const bool next = l + 1 < m.n_layers ? g.has_attn && !few_token_gemv(p, g.qkv) : st->head_rows > 1;
             float *left = MP > 1 && next && !st->own_rinv_launch ? rinv : nullptr;
-            PS_HIP(launch_combine(hbuf, reinterpret_cast<const float *>(WS + p.ws.y), reinterpret_cast<const float *>(WS + p.ws.rw), M, H,
+            PS_LAUNCH(launch_combine(hbuf, reinterpret_cast<const float *>(WS + p.ws.y), reinterpret_cast<const float *>(WS + p.ws.rw), M, H,
                                   m.top_k, resid ? 1 : 0, xout, m.rms_eps, left, cs));
             if (left) st->rinv_of = xout;
             return PS_OK;
@@ -509,6 +520,8 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
     set_error("unknown kernel id %u", op.info.kernel);
     return PS_E_STATE;
 }
+
+#undef PS_LAUNCH
 
 double now_ms() {
     return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now().time_since_epoch()).count();
@@ -660,19 +673,59 @@ static bool graph_eligible(const ps_plan &p) {
     return !p.g.moe && p.n_slots == 0 && p.cpu_bytes == 0 && (p.M == 1 || (p.M <= 64 && !p.g.kv));
 }
 
-// Whether replaying an eligible plan's step beats issuing its launches one by one.  A replay costs the stream 4 to 11 us at its
-// two ends, whatever it holds (kernels inside one, and direct launches, follow each other without a gap), and saves a tenth
-// of a microsecond a launch and the host's 3.  Measured, us a step, replayed / direct, 8B-shaped layers: one token, 1 layer
-// 43.2 / 38.7, 4: 149.8 / 147.5, 8: 291.4 / 290.2, 16 (64 launches): 574.4 / 576.6, 32: 1138 / 1149; 4 tokens, 2 layers 93.8 /
-// 89.6, 8: 344 / 341; 64 tokens, 2 layers 168 / 161, 16: 1240 / 1231; 16000 cached positions, 2 layers 126 / 117, 4000, 16
-// layers 803 / 805.  So: from 64 launches on.  With less than 4 MB a launch the host is what a direct step waits for
-// (two layers of width 512: 39 us, all of it the host's, against 48 with 33 of the host's): there the mode keeps what it is
-// for, a host with time to spare.
-bool replay_pays(const ps_schedule &sc) {
+// The kernels a forward without logits launches one by one, and the weight and cache bytes they read (the dense schedule)
+int32_t count_launches(ps_stack *st, uint64_t *launches, uint64_t *bytes) {
+    const ps_plan &p = st->plan;
+    // stand-ins for the caller's rows: nothing is read or written
+    const __half *xin = reinterpret_cast<const __half *>(st->ws_base + p.ws.x0);
+    __half *xout = reinterpret_cast<__half *>(st->ws_base + p.ws.x1);
+    const uint32_t before = st->launches;
+    reset_left(st);
+    *bytes = 0;
+    st->count_only = true;
+    int32_t rc = PS_OK;
+    for (const Op &op : st->dense_sched.ops) {
+        if (op.info.type != PS_OP_KERNEL || op.info.layer == p.g.m.n_layers) continue;   // (the head's layer)
+        if (op.info.kernel != PS_K_RINV) st->rinv_of = nullptr;
+        if ((rc = issue_kernel(st, st->dense_sched, op, xin, xout)) != PS_OK) break;
+        *bytes += op.info.bytes;
+    }
+    st->count_only = false;
+    *launches = st->launches - before;
+    st->launches = before;
+    reset_left(st);
+    return rc;
+}
+
+// Whether replaying an eligible plan's step beats issuing its launches one by one.  A replay costs the stream 4 to 6 us at its two
+// ends, 8 with a KV cache (the launch that writes the context), and saves about 0.2 us a launch.  One by one, a launch
+// costs the host 2.7 us: nothing where steps are queued ahead, but a loop that waits for every step (a decode loop does, for
+// its token) then waits for the host as well, unless the kernels are much longer than that.  Replay less direct, us a step,
+// queued / waited for (the stream's 12 to 15 us per wait included):
+//   layers         4 launches    8          16         32         64        MB a launch
+//   4096 wide    +4.3 / +5.3  +3.6 / +1.7  +2.2 / +2.6  -0.8 / -0.6  -5.8 / -11.8   31
+//   3072                      +3.9 / +1.4               -0.1 / -7.2  -5.6 / -38     14
+//   2048         +5.4 / +9.6  +4.5 / +2.6  +2.9 / -7.3  -0.1 / -3.5  -7.1 / -52      6.7
+//   1024         +5.4 / +5.6               +2.7 / -14.5 -0.6 / -18   -8.0 / -67      1.6
+//   4096, 4000 positions: 12 launches +7.4 / +4.6, 24 +5.5 / +1.6, 48 +1.5 / -2.7, 96 -4.4 / -8.0;
+//   4096, 64 tokens: 7 launches +4.7 / +4.9, 14 +4.6 / +3.5, 28 +5.0 / +2.0, 56 +4.9 / +3.3, 112 -1.8 / +3.5.
+// So one by one below 32 launches, and there only as many as one for every 0.75 MB a launch reads: what the replay's ends
+// would cost does not grow with the launches, what the host loses does, the more the shorter they are.
+bool replay_pays(uint64_t launches, uint64_t bytes) { return launches >= 32 || launches * launches * 750000 >= bytes; }
+
+// Whether this stack's forwards are replayed from a graph in its decode mode: mode 3 wherever the plan allows it, mode 1 where
+// that is the faster
+int32_t pick_replay(ps_stack *st) {
+    st->use_graph = false;
+    if ((st->decode_mode != 1 && st->decode_mode != 3) || !graph_eligible(st->plan) || !st->have_dense_sched) return PS_OK;
     uint64_t launches = 0, bytes = 0;
-    for (const Op &op : sc.ops)
-        if (op.info.type == PS_OP_KERNEL) { ++launches; bytes += op.info.bytes; }
-    return launches >= 64 || bytes < launches * (4ull << 20);
+    if (st->decode_mode == 1) {
+        const int32_t rc = count_launches(st, &launches, &bytes);
+        if (rc) return rc;
+        if (!replay_pays(launches, bytes)) return PS_OK;
+    }
+    st->use_graph = true;
+    return PS_OK;
 }
 
 bool has_copies(const ps_schedule &sc) {
@@ -720,11 +773,7 @@ int32_t run_schedule(ps_stack *st, const ps_schedule &sc, const __half *x_in, __
         st->prof_is_copy.assign(sc.ops.size(), 0);
     }
     st->prof_valid = false;
-    st->rinv_of = nullptr;
-    st->ssq_of = nullptr;
-    st->ssq_use = nullptr;
-    st->own_factors = nullptr;
-    st->routed_layer = ps_stack::kNotRouted;
+    reset_left(st);
     ps_stats &ss = st->stats;
     ss = ps_stats{};
     // graph mode with a KV cache: the context length travels in device memory, where the attention
@@ -967,7 +1016,7 @@ int32_t bind_plan(ps_stack *st) {
             st->dense_descs_cap = st->dense_sched.ops.size();
         }
     }
-    st->use_graph = st->decode_mode == 1 && graph_eligible(p) && st->have_dense_sched && replay_pays(st->dense_sched);
+    if (const int32_t rc = pick_replay(st)) return rc;
     if (p.g.kv) {
         // home of every kv head's cache: where its rows live between steps (arena or pinned pool)
         const auto &m = p.g.m;
@@ -1598,13 +1647,10 @@ int32_t ps_stack_forward_chunked(ps_stack *st, const void *x_in, void *x_out, ui
 
 int32_t ps_stack_set_decode_mode(ps_stack *st, int32_t mode) {
     if (!st) { ps::set_error("NULL argument"); return PS_E_ARG; }
-    if (mode < 0 || mode > 2) { ps::set_error("decode mode must be 0, 1 or 2"); return PS_E_ARG; }
-    const ps_plan &p = st->plan;
-    // eligible: dense, one token, every shard resident (nothing to wait for but the previous kernel)
+    if (mode < 0 || mode > 3) { ps::set_error("decode mode must be 0, 1, 2 or 3"); return PS_E_ARG; }
     st->decode_mode = mode;
-    st->use_graph = mode == 1 && graph_eligible(p) && st->have_dense_sched && replay_pays(st->dense_sched);
     st->own_rinv_launch = mode == 2;
-    return PS_OK;
+    return pick_replay(st);
 }
 
 int32_t ps_stack_set_copy_mode(ps_stack *st, int32_t gather) {
@@ -1689,19 +1735,16 @@ int32_t ps_stack_time_kernel(ps_stack *st, uint32_t kernel, uint32_t reps, doubl
         if (r == 1) { if (hipEventRecord(e0, st->compute) != hipSuccess) rc = PS_E_HIP; n = 0; }
         for (const ps::Op &op : st->dense_sched.ops) {
             if (op.info.type != PS_OP_KERNEL || op.info.kernel != kernel || op.info.slot >= 0) continue;
-            st->rinv_of = nullptr;   // timed in isolation: nobody has left any factors
-            st->ssq_of = nullptr;
-            st->ssq_use = nullptr;
-            st->own_factors = nullptr;
-            const uint32_t idle = st->idle_ops;
+            reset_left(st);   // timed in isolation: nobody has left any factors
+            const uint32_t before = st->launches;
             rc = issue_kernel(st, st->dense_sched, op, xin, xout);
             if (rc) break;
             ++ops;
-            n += st->idle_ops == idle;
+            n += st->launches != before;
         }
     }
     st->own_rinv_launch = own_rinv_launch;
-    st->rinv_of = nullptr;
+    reset_left(st);
     float ms = 0;
     if (rc == PS_OK && (hipEventRecord(e1, st->compute) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                         hipEventElapsedTime(&ms, e0, e1) != hipSuccess)) {

@@ -502,6 +502,67 @@ def test_graph_replay_matches_eager_on_every_replay(M, hidden):
     st.close()
 
 
+@pytest.mark.parametrize("M,layers,hidden,inter,context,vocab,replays", [
+    (1, 1, 1024, 8192, 0, 0, False),        # 4 launches of 3.9 MB
+    (1, 1, 2048, 4096, 0, 0, False),        # 4 of 4.9
+    (3, 2, 2048, 8192, 0, 0, False),        # 8 (few-token kernels) of 8.4
+    (16, 1, 2048, 14336, 0, 0, False),      # 7 (three plane sums, the factors in QKV's) of 7.8
+    (1, 1, 1024, 16384, 200, 0, False),     # 6 of 5
+    (1, 4, 1024, 4096, 0, 0, True),         # 16 of 2.2: too many for their size
+    (16, 4, 1024, 8192, 0, 0, True),        # 28 of 2.2
+    (1, 8, 512, 1408, 0, 0, True),          # 32
+    (1, 1, 512, 1408, 0, 100352, True),     # 4 tiny ones; the head is not counted, asked for or not
+    (1, 1, 512, 1408, 300, 0, True)])
+def test_mode_1_replays_where_the_rule_says_and_mode_3_always(M, layers, hidden, inter, context, vocab, replays):
+    """Few launches of long kernels are issued one by one in mode 1, everything else is replayed; mode 3 replays both. The
+    bits are mode 0's in each."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(Hn.small_dense_cfg(layers), hidden=hidden, n_q_heads=hidden // 128, n_kv_heads=2, ffn_inter=inter)
+    if context:
+        cfg["kv_context"] = context + 8
+    if vocab:
+        cfg["vocab"] = vocab
+    g = np.random.default_rng(61)
+    quant = {}
+
+    def matrix(N, K):
+        if (N, K) not in quant:
+            quant[N, K] = ((g.random((N, K // 32)) * 0.1 / np.sqrt(K)).astype(np.float16), g.integers(0, 16, (N, K), dtype=np.uint8))
+        return quant[N, K]
+
+    st = B.Stack(B.Plan(cfg, 4 << 30, M))
+    for layer in range(layers):
+        for kind, ex, N, K in S.matrix_shapes(cfg):
+            st.load_matrix(layer, kind, ex, *matrix(N, K))
+        if context:
+            K, V = S.kv_cache(61, layer, 2, context, 128)
+            for h in range(2):
+                st.load_kv(layer, h, K[h], V[h])
+    logits = None
+    if vocab:
+        st.load_matrix(layers, B.PS_MAT_OUT, None, *matrix(vocab, hidden))
+        logits = torch.zeros(vocab, dtype=torch.float16, device=st.device)
+    x = torch.from_numpy(S.activations(61, 0, M, hidden)).to(st.device)
+    outs = {}
+    for mode in (0, 1, 3, 1):
+        st.set_decode_mode(mode)
+        for rep in range(3):
+            if context:
+                st.set_context(context)
+            if vocab:
+                st.set_logits_out(logits, 0, 1)
+            y = torch.zeros_like(x)
+            torch.cuda.synchronize()
+            st.forward(x, y)
+            st.synchronize()
+            assert st.stats().graph_replay == {0: 0, 1: int(replays), 3: 1}[mode]
+            out = np.concatenate([y.cpu().numpy().ravel()] + ([logits.cpu().numpy()] if vocab else [])).view(np.uint16)
+            np.testing.assert_array_equal(out, outs.setdefault(0, out))
+    st.close()
+    assert np.isfinite(outs[0].view(np.float16)).all() and outs[0].any()
+
+
 @pytest.mark.parametrize("kind", ["dense", "moe"])
 def test_chunked_prefill_through_the_tier_table(kind):
     """Tier table + PickTier + chunked prefill (Section 3, inference phase): a prompt of n tokens runs
