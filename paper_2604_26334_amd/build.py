@@ -2,6 +2,7 @@
 
 Besides compiling, the build CHECKS what the hand-placed waits of the MFMA GEMM rely on, from the
 compiler's own output for kernels.hip, and fails if it does not hold:
+  - the kernels that must not be placed beside a gather copy use LDS (NEEDS_LDS);
   - no kernel of the matmul / attention families uses scratch memory or spills a register (a spill
     reload is a vector-memory operation and would be counted by `s_waitcnt vmcnt(n)` like a prefetch);
   - in every gemm_w4_kernel, a vmcnt(0) stands between the opening prefetches and the first barrier; every later stretch
@@ -32,6 +33,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-ffp-c
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC] + os.environ.get("PS_EXTRA_FLAGS", "").split()
 CHECKED = "kernels.hip"      # the source whose kernels are checked
+# kept off the CUs a gather copy holds (the GEMM, the few-token GEMV and the chunk attention by LDS given at launch, which
+# the remarks do not show)
+NEEDS_LDS = ("gemv_w4_kernel", "attn_decode_kernel", "splitk_epilogue_resid_rinv_kernel",
+             "splitk_epilogue_resid_quarters_kernel", "splitk_epilogue_norm_kernel")
 NO_SCRATCH = ("gemm_w4_kernel", "gemv_w4_kernel", "gemv_mt_kernel", "attn_decode_kernel", "attn_combine_kernel", "attn_chunk_kernel", "attn_combine_chunk_kernel")
 
 
@@ -66,7 +71,7 @@ def _isa(src):
 
 def check_resource_usage(remarks):
     """The compiler's per-kernel resource remarks: matmul and attention kernels use no scratch, and the
-    gather copy kernel holds a CU's whole LDS (what keeps matmul workgroups off the CUs it reads PCIe from)."""
+    gather copy kernel holds a CU's whole LDS (what keeps matmul workgroups off the CUs it reads PCIe from: they need some)."""
     name, bad, seen, gather_lds = None, [], 0, None
     for ln in remarks.splitlines():
         m = re.search(r"remark: Function Name: (\S+)", ln)
@@ -77,13 +82,15 @@ def check_resource_usage(remarks):
         m = re.search(r"remark:\s+LDS Size \[bytes/block\]: (\d+)", ln)
         if m and name and "h2d_gather_kernel" in name:
             gather_lds = int(m.group(1))
+        if m and name and any(k in name for k in NEEDS_LDS) and int(m.group(1)) == 0:
+            bad.append("%s: no LDS, so it could be placed beside a gather copy" % name)
         m = re.search(r"remark:\s+(ScratchSize \[bytes/lane\]|SGPRs Spill|VGPRs Spill): (\d+)", ln)
         if m and name and any(k in name for k in NO_SCRATCH) and int(m.group(2)) != 0:
             bad.append("%s: %s = %s" % (name, m.group(1), m.group(2)))
     if seen == 0:
         raise RuntimeError("build check: no resource-usage remarks for the matmul kernels (compiler flag ignored?)")
     if bad:
-        raise RuntimeError("build check: scratch / spills in kernels that must have none:\n  " + "\n  ".join(bad))
+        raise RuntimeError("build check: scratch / spills in kernels that must have none, or no LDS in one that must have some:\n  " + "\n  ".join(bad))
     if gather_lds != 160 * 1024:
         raise RuntimeError("build check: h2d_gather_kernel allocates %s B of LDS, not the CU's 163840" % gather_lds)
 

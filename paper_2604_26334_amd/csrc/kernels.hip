@@ -2242,8 +2242,8 @@ constexpr uint32_t kGatherWgs = 16;
 constexpr uint32_t kLdsPerCu = 160 * 1024;   // gfx950
 __global__ __launch_bounds__(256) void h2d_gather_kernel(const CopyDesc *descs, uint32_t n) {
     __shared__ CopyDesc sd[kGatherDescs];
-    // The rest of the CU's LDS is claimed and left unused: no workgroup that needs LDS (every
-    // matmul and attention kernel does) can then be placed on this CU, where its loads would
+    // The rest of the CU's LDS is claimed and left unused: no workgroup that needs LDS (every matmul and
+    // attention kernel and the plane sums of O, down and a first layer's QKV do) can then be placed on this CU, where its loads would
     // queue behind half a megabyte of PCIe reads on the CU's one vector-memory path (a one-token
     // matmul beside a gather: 45 us without the claim, 25 us with it, 13 us alone).
     __shared__ uint8_t rest[kLdsPerCu - sizeof(CopyDesc) * kGatherDescs];
@@ -2517,10 +2517,15 @@ hipError_t launch_splitk_epilogue_resid_rinv(const float *partial, uint32_t part
 // kernel's wave w, two per lane and round with every load requested before the first is used, and leaves its sum of squares
 // for the readers to add up.  Bound by latency: a workgroup per token pulls 144 KB through each of 64 CUs in two rounds of
 // loads that wait for each other, this form 36 KB through each of 256 in one; 64 tokens of 4096 columns from eight planes
-// 4.8 -> 3.95 us (of which about 2.5 are a launch's own).
+// 4.3 -> 4.0 us in the kernel trace, 5 tokens 4.1 -> 3.4, 2 tokens of 2048 columns 3.4 -> 3.0, 2 of 512 2.7 -> 2.5 (about 2.5
+// are a launch's own), so the form serves 2 tokens and up; four steps of two layers of 64 tokens 635 -> 613 us.
 // ------------------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void splitk_epilogue_resid_quarters_kernel(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M,
                                                                             uint32_t H, const __half *res, __half *out, float *quarters) {
+    // claimed and left unused: a workgroup that needs LDS is not placed on a CU whose LDS a gather copy holds, where its
+    // loads would queue behind the reads over PCIe (beside a gather 31 us without the claim, 18 with it, 4 alone)
+    __shared__ uint32_t claim[64];
+    asm volatile("" ::"v"(&claim[threadIdx.x]));
     const uint32_t w = blockIdx.x, m = blockIdx.y, nq = H / 8;
     const float *prow = partial + (size_t)m * H;
     float ss = 0.f;

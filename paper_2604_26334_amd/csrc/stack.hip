@@ -344,8 +344,8 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         const bool whole_rows = mode == GEMM_RESID && ncols == H && a.out_row0 == 0 && a.out_stride == H && !st->own_rinv_launch;
         if (whole_rows && !g.moe && p.cpu_bytes == 0) {
             // four workgroups a token, whose sums of squares the dense matrices behind them add up as launch_rinv would (the
-            // experts' launches and the CPU's share read finished factors: below).  Four layers of 64 tokens at H = 4096, two
-            // steps: 634 -> 617 us
+            // experts' launches and the CPU's share read finished factors: below).  Four steps of two layers of 64 tokens at
+            // H = 4096: 635 -> 613 us
             PS_LAUNCH(launch_splitk_epilogue_resid_quarters(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out, dead, cs));
             st->ssq_buf = dead;
             st->ssq_of = a.out;

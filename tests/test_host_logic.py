@@ -883,6 +883,10 @@ def test_build_check_of_the_gemm_wait_counts(tmp_path):
     for lds in (3072, 65536):       # the gather kernel no longer holds its CU's whole LDS
         with pytest.raises(RuntimeError):
             Bd.check_resource_usage(clean + gather % lds)
+    beside = "remark: Function Name: _ZN2ps37splitk_epilogue_resid_quarters_kernelEPKf\nremark:     LDS Size [bytes/block]: %d [-R]\n"
+    Bd.check_resource_usage(clean + gather % 163840 + beside % 256)
+    with pytest.raises(RuntimeError, match="beside a gather"):       # it could be placed on a CU that reads PCIe
+        Bd.check_resource_usage(clean + gather % 163840 + beside % 0)
     with pytest.raises(RuntimeError):
         Bd.check_resource_usage(clean)
 
