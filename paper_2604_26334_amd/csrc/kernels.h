@@ -136,7 +136,7 @@ struct AttnArgs {
 // bytes apart, K rows [cap][128] then V rows) and, causally, the chunk's own K / V rows, read in place from the
 // tokens' QKV rows (k_own / v_own = kv head 0 of token 0, own_stride elements between tokens).  One launch per run of
 // cache shards.  nsplit == 1: finished rows out[t][q_head * 128 ..], and the tokens' K / V rows appended at positions
-// ctx .. ctx + ntok - 1 of home[kv head] (address of its K row 0); > 1: records
+// ctx .. ctx + ntok - 1 of home[kv head] (address of its K row 0; no home: not appended); > 1: records
 // part[((t * n_q + q_head) * nsplit + split) * 130] (maximum, weight sum, 128 sums) for launch_attn_combine_chunk.
 // nsplit and rounds_per_split come from attn_chunk_deal.  few: the weights in fp32's precision (fewer than 16 score rows).
 struct AttnChunkArgs {

@@ -1106,7 +1106,7 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
         }
     };
     if (rd0 < rd1) stage(rd0, 0);
-    if constexpr (!SPLIT) {
+    if (!SPLIT && a.home) {
         // The chunk's K and V rows go to the cache's home, positions ctx and up, which no row block reads: every block moves
         // the tokens whose first row it holds (as a launch of its own 5 us a layer, here inside the wait for the first round)
         const uint32_t t0 = (row0 + G - 1) / G, t1 = min(a.ntok, (row0 + 64 + G - 1) / G);
@@ -1335,8 +1335,8 @@ hipError_t launch_attn_chunk(const AttnChunkArgs &a, hipStream_t st) {
     if (a.group == 0 || a.group > 16 || !a.k_own || !a.v_own || a.nsplit == 0) return hipErrorInvalidValue;
     if (a.few && a.ntok * a.group >= 16) return hipErrorInvalidValue;
     const uint32_t rounds = (a.ctx + kAttnRound - 1) / kAttnRound + (a.ntok + kAttnRound - 1) / kAttnRound;
-    if ((uint64_t)a.nsplit * a.rounds_per_split < rounds || (a.nsplit > 1 ? !a.part : !a.out || !a.home)) return hipErrorInvalidValue;
-    if ((uint64_t)a.ctx + a.ntok > a.cap) return hipErrorInvalidValue;
+    if ((uint64_t)a.nsplit * a.rounds_per_split < rounds || (a.nsplit > 1 ? !a.part : !a.out)) return hipErrorInvalidValue;
+    if (a.home ? (uint64_t)a.ctx + a.ntok > a.cap : a.ctx > a.cap) return hipErrorInvalidValue;
     // 32-bit buffer offsets
     if (((uint64_t)a.ctx + kAttnRound) * 256u > 0x7FFFFFFFull || ((uint64_t)a.ntok + kAttnRound) * a.own_stride * 2u > 0x7FFFFFFFull) return hipErrorInvalidValue;
     dim3 grid(a.nheads, (a.ntok * a.group + 63) / 64, a.nsplit);

@@ -97,6 +97,7 @@ struct ps_stack {
     const float *ssq_use = nullptr;           // set by a PS_K_RINV op: what the matrices behind it take their RMS factors from
     const void *own_factors = nullptr;        // set by a PS_K_RINV op: rows whose factors the plane sum behind them works out itself
     uint32_t launches = 0;                    // kernels issue_kernel has launched so far, or counted
+    bool timing = false;                      // kernels are timed on whatever the workspace holds: the cache stays as it is
     bool count_only = false;                  // issue_kernel counts its launches and makes none (count_launches)
     uint32_t routed_layer = kNotRouted;       // MoE layer whose routing rode in an earlier launch of this forward
     static constexpr uint32_t kNotRouted = 0xFFFFFFFFu;
@@ -444,7 +445,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
                 c.k_own = qkv + (size_t)m.n_q_heads * m.head_dim; c.v_own = qkv + (size_t)(m.n_q_heads + m.n_kv_heads) * m.head_dim;
                 c.own_stride = g.qkv_w; c.out = reinterpret_cast<__half *>(WS + p.ws.attn); c.out_stride = g.attn_w;
                 c.part = reinterpret_cast<float *>(WS + p.ws.apart);
-                c.home = reinterpret_cast<const uint64_t *>(WS + p.ws.kvhome) + (size_t)l * m.n_kv_heads;
+                c.home = st->timing ? nullptr : reinterpret_cast<const uint64_t *>(WS + p.ws.kvhome) + (size_t)l * m.n_kv_heads;
                 attn_chunk_deal(c.ctx, MP, c.group, m.n_kv_heads, &c.nsplit, &c.rounds_per_split);
                 // the last rows of a chunk, or a chunk of a few (a longer plan's stay as they are whatever comes with them)
                 c.few = MP < kAttnOnePassTokens && M * c.group < 16;
@@ -1731,6 +1732,7 @@ int32_t ps_stack_time_kernel(ps_stack *st, uint32_t kernel, uint32_t reps, doubl
     // factors that a matrix's own launches work out or add up in a forward come from a launch here: it is what is timed
     const bool own_rinv_launch = st->own_rinv_launch;
     if (kernel == PS_K_RINV) st->own_rinv_launch = true;
+    st->timing = true;
     for (uint32_t r = 0; r <= reps && rc == PS_OK; ++r) {   // pass 0 warms up
         if (r == 1) { if (hipEventRecord(e0, st->compute) != hipSuccess) rc = PS_E_HIP; n = 0; }
         for (const ps::Op &op : st->dense_sched.ops) {
@@ -1744,6 +1746,7 @@ int32_t ps_stack_time_kernel(ps_stack *st, uint32_t kernel, uint32_t reps, doubl
         }
     }
     st->own_rinv_launch = own_rinv_launch;
+    st->timing = false;
     reset_left(st);
     float ms = 0;
     if (rc == PS_OK && (hipEventRecord(e1, st->compute) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||

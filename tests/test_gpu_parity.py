@@ -465,6 +465,39 @@ def test_the_factor_launch_timed_alone_is_one_launch_per_counted_op(M, hidden, p
     assert min(times[0]) >= 0.75 * min(times[2]), times
 
 
+@pytest.mark.parametrize("M", [256, 40])
+def test_attention_timed_alone_leaves_the_cache_as_it_is(M):
+    """The chunk attention timed alone, in plans where it also appends the chunk's rows and where a merge does: it runs at any
+    context the cache holds, also where M more rows would not fit, and not a byte of the cache changes."""
+    from paper_2604_26334_amd import binding as B
+    cap = 600
+    cfg = _kv_cfg(1, cap)
+    W = Hn.WeightCache(cfg, 19)
+    K, V = S.kv_cache(19, 0, cfg["n_kv_heads"], cap, 128)
+    plan = B.Plan(cfg, 1 << 30, M)
+    st = B.Stack(plan)
+    for kind, expert, N, Kd in S.matrix_shapes(cfg):
+        st.load_matrix(0, kind, expert, *W(0, kind, expert))
+    for g in range(cfg["n_kv_heads"]):
+        st.load_kv(0, g, K[g], V[g])
+    homes = [s for s in plan.shards() if s.kind == B.PS_SHARD_KV]
+    assert homes and all(s.resident == 1 for s in homes)
+
+    def cache():
+        st.synchronize()
+        return [st.arena[s.offset:s.offset + 2 * cap * 256].cpu().numpy().copy() for s in homes]
+
+    before = cache()
+    for ctx in (300, cap - 1):
+        st.set_context(ctx)
+        ms, n = st.time_kernel(B.PS_K_ATTN, 5)
+        assert n == 1 and ms > 0
+        for a, b in zip(before, cache()):
+            np.testing.assert_array_equal(a, b)
+    st.close()
+    plan.close()
+
+
 @pytest.mark.parametrize("M,hidden", [(1, 512), (4, 1024), (16, 512)])
 def test_graph_replay_matches_eager_on_every_replay(M, hidden):
     """HIP-graph decode mode (one token; batched-decode steps of a few tokens, in the few-token kernel and in
