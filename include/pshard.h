@@ -176,7 +176,7 @@ typedef struct ps_plan_summary_t {
 typedef struct ps_stats {
     uint64_t resident_bytes_step; /* weight bytes read in place in the last forward */
     uint64_t streamed_bytes_step; /* weight bytes copied H2D in the last forward    */
-    uint32_t n_copies, n_kernels; /* copies and kernel ops issued, ops that share a launch counted as one */
+    uint32_t n_copies, n_kernels; /* copies; kernel ops that launched anything, ops that share a launch counted as one */
     /* the rest is valid only after a forward with profiling on, once complete   */
     double copy_ms;     /* sum of copy durations on the copy stream              */
     double compute_ms;  /* sum of kernel durations on the compute stream         */
@@ -510,8 +510,9 @@ int32_t ps_stack_forward_noalloc(ps_stack *st, const void *x_in, void *x_out);
 /* Chunked prefill (Section 3, inference phase: the picked tier's size is the chunk size): n_tokens
  * rows go through the plan's schedule in ceil(n_tokens / T) trips of T = the plan's token count.  A
  * last chunk shorter than T runs the same schedule with the same launch shapes over its rows only
- * (a row's result does not depend on how many rows share its trip; rows past the end are neither
- * read nor written), so each trip costs at most what the tier's estimate prices.
+ * (a row's result does not depend on how many rows share its trip, but for the attention of a trip of
+ * fewer than 16 score rows, tokens times query heads per kv head, in a plan below 256 tokens, which
+ * keeps more bits; rows past the end are neither read nor written), so each trip costs at most what the tier's estimate prices.
  *  x_in, x_out: device fp16 [n_tokens][hidden].  router_logits / router_logits_dev: as for
  *  ps_stack_forward with [n_layers][n_tokens][n_experts].  last_logits_dev: NULL, or device fp16
  *  [vocab], 16-byte aligned: the output head runs on the last trip only, for the prompt's last token

@@ -70,8 +70,9 @@ struct ps_stack {
     void *tables_host[2] = {nullptr, nullptr};   // pinned: logits | tasks | pairs | copy descriptors of one forward (MoE)
     uint64_t tables_bytes = 0;
     int32_t decode_mode = 0;                  // as set by ps_stack_set_decode_mode (re-evaluated when a tier is installed)
+    struct Replay { hipGraphExec_t exec; uint32_t kernels; };
     bool use_graph = false;                   // all-resident decode step replayed from a HIP graph
-    std::map<std::tuple<const void *, void *, void *, uint32_t>, hipGraphExec_t> graphs;   // per (x_in, x_out, logits, valid rows and head rows)
+    std::map<std::tuple<const void *, void *, void *, uint32_t>, Replay> graphs;   // per (x_in, x_out, logits, valid rows and head rows)
     // CPU back-end (plans with shards left in system memory): worker threads, pinned host copies of
     // the activations it reads (FFN input, SwiGLU output, final hidden state) and of what it writes
     std::unique_ptr<ps::CpuPool> pool;
@@ -792,16 +793,19 @@ int32_t run_schedule(ps_stack *st, const ps_schedule &sc, const __half *x_in, __
                 // forward is asynchronous: the latest replays may still be running, and an executable
                 // graph must not be destroyed while it is in flight
                 PS_HIP(hipStreamSynchronize(st->compute));
-                for (auto &g : st->graphs) (void)hipGraphExecDestroy(g.second);
+                for (auto &g : st->graphs) (void)hipGraphExecDestroy(g.second.exec);
                 st->graphs.clear();
             }
             hipGraph_t graph = nullptr;
             PS_HIP(hipStreamBeginCapture(st->compute, hipStreamCaptureModeThreadLocal));
             int32_t rc = PS_OK;
+            uint32_t kernels = 0;
             for (const Op &op : sc.ops) {
                 if (skip_head_op(st, op)) continue;
+                const uint32_t before = st->launches;
                 rc = issue_kernel(st, sc, op, x_in, x_out);
                 if (rc) break;
+                kernels += st->launches != before;
             }
             hipError_t e = hipStreamEndCapture(st->compute, &graph);
             if (rc) { if (graph) (void)hipGraphDestroy(graph); return rc; }
@@ -810,12 +814,13 @@ int32_t run_schedule(ps_stack *st, const ps_schedule &sc, const __half *x_in, __
             e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
             (void)hipGraphDestroy(graph);
             if (e != hipSuccess) { ps::set_error("hipGraphInstantiate failed: %s", hipGetErrorString(e)); return PS_E_HIP; }
-            it = st->graphs.emplace(key, exec).first;
+            it = st->graphs.emplace(key, ps_stack::Replay{exec, kernels}).first;
         }
-        PS_HIP(hipGraphLaunch(it->second, st->compute));
+        PS_HIP(hipGraphLaunch(it->second.exec, st->compute));
         ss.graph_replay = 1;
+        ss.n_kernels = it->second.kernels;
         for (const Op &op : sc.ops)
-            if (!skip_head_op(st, op)) { ss.resident_bytes_step += op.info.bytes; ss.n_kernels++; }
+            if (!skip_head_op(st, op)) ss.resident_bytes_step += op.info.bytes;
         return PS_OK;
     }
     uint32_t filled_inline = ps_stack::kNotRouted;   // layer whose slot fill went out on the compute stream
@@ -914,6 +919,7 @@ int32_t run_schedule(ps_stack *st, const ps_schedule &sc, const __half *x_in, __
             if (prof) PS_HIP(hipEventRecord(st->prof_ev[2 * i], st->compute));
             // RMS factors left by a residual epilogue are good only for the PS_K_RINV op right behind it
             if (!(o.type == PS_OP_KERNEL && o.kernel == PS_K_RINV)) st->rinv_of = nullptr;
+            const uint32_t before = st->launches;
             int32_t rc = o.type == PS_OP_FETCH ? issue_fetch(st, op, x_in, x_out)
                          : o.type == PS_OP_CPU ? issue_cpu(st, sc, op, x_out) : issue_kernel(st, sc, op, x_in, x_out);
             if (rc) return rc;
@@ -922,7 +928,7 @@ int32_t run_schedule(ps_stack *st, const ps_schedule &sc, const __half *x_in, __
             if ((o.flags & PS_OPF_RECORD_ROUTER) && copies) PS_HIP(hipEventRecord(st->ev_router[o.layer], st->compute));
             if (o.type == PS_OP_KERNEL) {
                 if (o.slot < 0) ss.resident_bytes_step += o.bytes;
-                ss.n_kernels++;
+                ss.n_kernels += st->launches != before;
             }
         }
     }
@@ -1261,7 +1267,7 @@ int32_t ps_stack_set_tier(ps_stack *st, uint32_t tier, uint64_t *uploaded_bytes)
     PS_HIP(hipStreamSynchronize(st->copy));
     PS_HIP(hipStreamSynchronize(st->compute));
     if (tier == st->active_tier) return PS_OK;
-    for (auto &g : st->graphs) (void)hipGraphExecDestroy(g.second);
+    for (auto &g : st->graphs) (void)hipGraphExecDestroy(g.second.exec);
     st->graphs.clear();
     // KV caches are state, not copies of something on the host: a cache shard whose home changes
     // with the tier (pinned in one, streamed in the other) moves with its rows, through its host home
@@ -1798,7 +1804,7 @@ void ps_stack_destroy(ps_stack *st) {
     if (st->ev_step) (void)hipEventDestroy(st->ev_step);
     for (int b = 0; b < 2; ++b) if (st->ev_upload[b]) (void)hipEventDestroy(st->ev_upload[b]);
     for (auto e : st->prof_ev) (void)hipEventDestroy(e);
-    for (auto &g : st->graphs) (void)hipGraphExecDestroy(g.second);
+    for (auto &g : st->graphs) (void)hipGraphExecDestroy(g.second.exec);
     delete st;
 }
 

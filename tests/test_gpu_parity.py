@@ -195,6 +195,27 @@ def test_one_token_routing_rides_in_o_and_experts_share_a_launch(E, top_k, n_kv,
     _check(cfg, 79, 1, _budgets(cfg, 1, [1.0, 0.8, 0.5, 0.3]), logits=lg)
 
 
+@pytest.mark.parametrize("E,M,ops", [(256, 1, 5), (264, 1, 6), (256, 6, 5), (264, 6, 6)])
+def test_routing_has_a_launch_of_its_own_only_above_256_experts(E, M, ops):
+    """Every weight resident: a layer is QKV, O, the experts' two launches and the combine, with the routing in O's launch (one
+    token) or in O's plane sum, and one op more where it has its own launch.  Several tokens: the first layer's factors ride in
+    QKV's plane sum and the others in the launches in front of them."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(Hn.small_moe_cfg(2), n_experts=E, top_k=4)
+    W = Hn.WeightCache(cfg, 83)
+    st = B.Stack(B.Plan(cfg, 1 << 30, M))
+    for layer in range(cfg["n_layers"]):
+        for kind, expert, N, K in S.matrix_shapes(cfg):
+            st.load_matrix(layer, kind, expert, *W(layer, kind, expert))
+    x = torch.from_numpy(S.activations(83, 0, M, cfg["hidden"])).to(st.device)
+    st.forward(x, torch.empty_like(x), S.router_logits(83, 0, cfg["n_layers"], M, E))
+    st.synchronize()
+    n = st.stats().n_kernels
+    st.close()
+    assert n == ops * cfg["n_layers"]
+
+
 @pytest.mark.parametrize("E,top_k,n_kv,H", [(8, 2, 1, 256), (64, 8, 2, 1024), (130, 7, 4, 384), (256, 16, 1, 256), (264, 4, 1, 256)])
 def test_resident_and_filled_experts_of_a_layer_do_share_a_launch(E, top_k, n_kv, H):
     """The op list says which layers have resident experts and experts of a single slot fill: in those, and only those, a
