@@ -37,7 +37,8 @@ int32_t ps_pack_matrix(const uint16_t *scales, const uint8_t *codes, uint32_t ro
  * (PS_K_*) of a dense stack is launched back to back, `reps` passes after one warm-up pass,
  * between two events on the compute stream; *avg_launch_ms = elapsed / launches, where launches counts the ops
  * of a pass that launch anything.  PS_K_RINV: the launch of PS_DECODE_MODE_OWN_RINV, whatever the mode; ops whose
- * matrix is a few-token kernel launch nothing (0 launches of 0 ms if there are no others).  The
+ * matrix is a few-token kernel launch nothing (0 launches of 0 ms if there are no others).  PS_K_QKV: with the plane sum of
+ * a layer whose factors lie ready, not the first layer's.  PS_K_ATTN: appends nothing to the cache.  The
  * activations are whatever the workspace holds, the outputs go to the workspace.  Blocks. */
 int32_t ps_stack_time_kernel(ps_stack *st, uint32_t kernel, uint32_t reps, double *avg_launch_ms,
                              uint32_t *launches);
