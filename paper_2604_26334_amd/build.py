@@ -37,7 +37,7 @@ CHECKED = "kernels.hip"      # the source whose kernels are checked
 # the remarks do not show)
 NEEDS_LDS = ("gemv_w4_kernel", "attn_decode_kernel", "splitk_epilogue_resid_rinv_kernel",
              "splitk_epilogue_resid_quarters_kernel", "splitk_epilogue_norm_kernel")
-NO_SCRATCH = ("gemm_w4_kernel", "gemv_w4_kernel", "gemv_mt_kernel", "attn_decode_kernel", "attn_combine_kernel", "attn_chunk_kernel", "attn_combine_chunk_kernel")
+NO_SCRATCH = ("gemm_w4_kernel", "gemm_kslice_kernel", "gemv_w4_kernel", "gemv_mt_kernel", "attn_decode_kernel", "attn_combine_kernel", "attn_chunk_kernel", "attn_combine_chunk_kernel")
 
 
 def _run(cmd):
@@ -159,7 +159,7 @@ def check_gemm_isa(path):
         raise RuntimeError("build check: no gemm_w4_kernel in " + path)
     bad = []
     for mangled, body in funcs:
-        m = re.match(r"_ZN2ps14gemm_w4_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)(?:ELi(\d+))?EEE", mangled)
+        m = re.match(r"_ZN2ps14gemm_w4_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)(?:ELi(\d+))?(?:ELb[01])?EEE", mangled)
         if not m:
             bad.append(mangled + ": unexpected template arguments")
             continue

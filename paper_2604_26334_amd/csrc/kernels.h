@@ -48,7 +48,7 @@ struct GemmArgs {
     uint32_t sb_per_part;  // split-K: super-blocks per blockIdx.z part (0 = whole K in one part)
     uint32_t part_stride;  // split-K: elements between the fp32 partial planes
     // Sums of squares instead of a buffer of RMS factors (plans of more than 64 tokens): RESID leaves, per token and
-    // run of 128 output columns, the sum of squares of what it stored in ssq_out[run * M + token]; PLAIN and
+    // 64 output columns (half a run of 128), the sum of squares of what it stored in ssq_out[half run * M + token]; PLAIN and
     // GATE_UP with ssq_in add a token's nsb runs (K columns), in pairs, and take their RMS factors from them
     float *ssq_out;
     const float *ssq_in;

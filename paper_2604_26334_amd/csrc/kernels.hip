@@ -2,7 +2,8 @@
 // the decoder sub-layers with their fused RMSNorm / SwiGLU / residual steps, MoE routing and
 // the expert combine, and attention over the KV cache.  Weight layout: see pack.cpp.  wave64 only.
 //   matmuls by token count:  1 -> gemv_w4_kernel,  2..4 -> gemv_mt_kernel (whole scale groups),
-//                            otherwise gemm_w4_kernel (+ splitk_epilogue* when K is split)
+//                            otherwise gemm_w4_kernel (+ splitk_epilogue* when K is split), or gemm_kslice_kernel
+//                            (narrow matrices, more than 64 tokens)
 //   attention:  one query token -> attn_decode_kernel + attn_combine_kernel,
 //               a chunk of query tokens -> attn_chunk_kernel, one walk over the cache and the chunk's own
 //               rows; for a short chunk the walk is dealt out to several workgroups, whose records
@@ -1612,10 +1613,35 @@ constexpr size_t gemm_lds_bytes(int MT, int AT, int NW, int KS = 1) {
     return (size_t)KS * MT * 256 * (gemm_depth(MT, NW, KS) + 1) + (size_t)NW * 2 * AT * 1024;
 }
 
+// RMS factor of row tok of a launch's input: from the buffer of factors, or from the row's sums of squares (nsb runs of 128
+// columns, each in two halves)
+__device__ __forceinline__ float row_rinv(const GemmArgs &a, uint32_t tok, uint32_t ntok) {
+    if (!a.ssq_in) return a.rinv[tok];
+    if (a.quarters) return factor_of_quarters(RowQuarters{a.ssq_in, ntok, a.quarters, a.eps}, tok);
+    double s = 0.;
+    for (uint32_t g = 0; g < a.nsb; g += 16) {   // (the buffer goes on for 64 nsb floats per token)
+        const float *sq = a.ssq_in + (size_t)(2 * g) * ntok + tok;
+        float v[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = sq[(size_t)(2 * e) * ntok] + sq[(size_t)(2 * e + 1) * ntok];
+        s += sum_of_runs(v, a.nsb - g);
+    }
+    return rsqrtf((float)s / (float)(a.nsb * 128) + a.eps);
+}
+
+// Super-blocks of K slice w of eight: four to each half of K, as even as they go, the longer ones first
+struct KSlice { uint32_t begin, end; };
+__device__ __forceinline__ KSlice k_slice(uint32_t nsb, uint32_t w) {
+    const uint32_t half = nsb / 2, base = half / 4, more = half % 4, q = w & 3;
+    const uint32_t begin = (w >> 2) * half + q * base + min(q, more);
+    return {begin, begin + base + (q < more ? 1u : 0u)};
+}
+
 // KS: K parts inside the workgroup.  With 2, waves 0 .. NW / 2 - 1 multiply the first half of the super-blocks and
 // the others, on the same rows and tokens, the second half, each half with activation stages of its own; the
-// second half's accumulators then pass through LDS and are added to the first's.
-template <int MODE, int AT, int MT, bool GROUPED, int NW = 4, int KS = 1>
+// second half's accumulators then pass through LDS and are added to the first's.  SLICED: each part adds its four
+// slices of K up one by one, as gemm_kslice_kernel does.
+template <int MODE, int AT, int MT, bool GROUPED, int NW = 4, int KS = 1, bool SLICED = false>
 __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmArgs a) {
     extern __shared__ uint4 lds[];                 // KS x (gemm_depth + 1) stages of MT x 16 chunks, then 2 AT KB of scales per wave
     constexpr int NMT = MT / 16;
@@ -1787,6 +1813,14 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
         sb_begin = kpart * (a.nsb / 2);
         sb_end = sb_begin + a.nsb / 2;
     }
+    f4_t total[SLICED ? AT : 1][SLICED ? NMT : 1];      // of the K part's slices that are done
+    if constexpr (SLICED) {
+#pragma unroll
+        for (int t = 0; t < AT; ++t)
+#pragma unroll
+            for (int n = 0; n < NMT; ++n) total[t][n] = f4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    uint32_t slice = kpart * 4, slice_end = SLICED ? k_slice(a.nsb, slice).end : 0;
     prefetch(sb_begin, 0, sb_begin, wr[0], std::true_type{});
 #pragma unroll
     for (int d = 1; d < DEPTH; ++d) prefetch(min(sb_begin + d, sb_end - 1), d, sb_begin + d, wr[d], std::false_type{});
@@ -1800,20 +1834,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     constexpr bool FACTORS = !GROUPED && (MODE == GEMM_PLAIN || MODE == GEMM_GATE_UP), FACTORS_LATE = MT > 224;
     static_assert(!FACTORS || MT <= NW * 64, "one token per thread");
     float my_rinv = 0.f;
-    auto factor_of = [&](uint32_t t) {
-        const uint32_t tok = min(m0 + t, ntok - 1);
-        if (!a.ssq_in) { my_rinv = a.rinv[tok]; return; }
-        if (a.quarters) { my_rinv = factor_of_quarters(RowQuarters{a.ssq_in, ntok, a.quarters, a.eps}, tok); return; }
-        double s = 0.;
-        for (uint32_t g = 0; g < a.nsb; g += 16) {   // (the buffer goes on for 64 nsb floats per token)
-            const float *sq = a.ssq_in + (size_t)g * ntok + tok;
-            float v[16];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) v[e] = sq[(size_t)e * ntok];
-            s += sum_of_runs(v, a.nsb - g);
-        }
-        my_rinv = rsqrtf((float)s / (float)(a.nsb * 128) + a.eps);
-    };
+    auto factor_of = [&](uint32_t t) { my_rinv = row_rinv(a, min(m0 + t, ntok - 1), ntok); };
     if constexpr (FACTORS && !FACTORS_LATE) {
         if (threadIdx.x < MT) factor_of(threadIdx.x);
     }
@@ -1945,6 +1966,18 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
         // returned (lgkmcnt).
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(tail ? 0 : kInFlight) : "memory");
         __builtin_amdgcn_s_barrier();
+        if constexpr (SLICED) {
+            if (sb + 1 == slice_end && sb + 1 < sb_end) {
+#pragma unroll
+                for (int t = 0; t < AT; ++t)
+#pragma unroll
+                    for (int n = 0; n < NMT; ++n) {
+                        total[t][n] += acc[t][n];
+                        acc[t][n] = f4_t{0.f, 0.f, 0.f, 0.f};
+                    }
+                slice_end = k_slice(a.nsb, ++slice).end;
+            }
+        }
     };
     // whole turns of the ring, then the remaining steps (no exit from inside a turn: the ring is back
     // in phase at the loop's back edge, so no register set is live across it in another slot)
@@ -1963,6 +1996,12 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
         if (sb + 2 < sb_end) step(sb + 2, std::integral_constant<int, 2>{}, std::true_type{});
     }
 
+    if constexpr (SLICED) {
+#pragma unroll
+        for (int t = 0; t < AT; ++t)
+#pragma unroll
+            for (int n = 0; n < NMT; ++n) acc[t][n] = total[t][n] + acc[t][n];
+    }
     // (the lane, the thread and the wave's tiles are taken from scratch: nothing of them need live through the ring)
     uint32_t elane = 0;
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -2130,24 +2169,301 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
             const uint32_t run = etid / MT, tk = etid % MT, wrun = blockIdx.x * (NWR / 4) + run;
             if (run < NWR / 4 && m0 + tk < ntok && wrun * 8 < a.ntiles) {
                 const float *r4 = side + run * 4 * MT + tk;
-                a.ssq_out[(size_t)(a.out_row0 / 128 + wrun) * ntok + m0 + tk] = (r4[0] + r4[MT]) + (r4[2 * MT] + r4[3 * MT]);
+                float *half = a.ssq_out + (size_t)(a.out_row0 / 64 + wrun * 2) * ntok + m0 + tk;
+                half[0] = r4[0] + r4[MT];
+                half[ntok] = r4[2 * MT] + r4[3 * MT];
             }
         }
     }
 }
 
-template <int MODE, int AT, int MT, bool GROUPED, int NW, int KS>
+// ------------------------------------------------------------------------------------
+// GEMM of a narrow matrix with K in eight slices, one to a wave (O, down and small QKV of plans above 64 tokens).
+//
+// Such a matrix has to be cut into small tiles to give every CU one, and what a small tile of gemm_w4_kernel pays for is
+// not its MFMAs: 128 rows x 48 tokens dequantise every weight seven times for 300 tokens and read each operand from LDS for
+// two products only.  Here a workgroup of eight waves has 64 rows and 16 NMT tokens, and each wave multiplies ALL of them over
+// its own eighth of K: a weight is dequantised once per 80 tokens instead of 48, an operand read serves four
+// products, and no wave ever waits for another before the sums meet at the end: a wave's activations go through a ring of
+// LDS slots of its own (one slot: a token tile's super-block), filled a whole super-block ahead, and all waits are counts.
+// What bounds it: the fills.  2.2 MB a CU for 300 tokens x 14336, of which loads alone take 47 us (L2 to LDS runs at 68 to 100
+// KB a microsecond and CU), everything but the loads 40, together 52; a round of workgroups has about 8 us of its own (launch,
+// first loads, the exchange), so two rounds lose to the two-K-part tiles.  4096 columns, us, against those: O (K = 4096) 72 tokens 16.3 ->
+// 11.6, 128: 16.6 -> 12.4, 192: 17.0 -> 13.6, 256: 18.8 -> 16.3, 300: 20.3 -> 19.2; down (K = 14336) 45.3 -> 29.5, 45.5 -> 31.5, 46 -> 38,
+// 50.5 -> 44.8, 55.6 -> 51.7; 2048 columns, 512 tokens, K = 5632: 22.9 -> 20.8.
+// Tried without gain: 128 rows with the slices in pairs on waves that share their fills (512 tokens 66 -> 75 us).
+// ------------------------------------------------------------------------------------
+constexpr int kSliceRows = 4;     // row-tiles of a workgroup
+constexpr int kSliceWaves = 8;    // K slices
+constexpr size_t kslice_ring_bytes(int NMT) { return (size_t)kSliceWaves * NMT * 4096; }
+constexpr size_t kslice_sum_floats(int NMT) { return (size_t)kSliceWaves * kSliceRows * (NMT < 4 ? NMT : 4) * 256; }
+constexpr size_t kslice_sum_bytes(int NMT) { return (kslice_sum_floats(NMT) + NMT * 2 * 16) * sizeof(float); }
+constexpr size_t kslice_lds_bytes(int NMT) { return kslice_ring_bytes(NMT) > kslice_sum_bytes(NMT) ? kslice_ring_bytes(NMT) : kslice_sum_bytes(NMT); }
+
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// A lane's four sums of a row-tile (columns tile * 16 + rg * 4 ..) for token tok, with the mode's epilogue; RESID: sq gets
+// the sum of squares of what is stored
+template <int MODE>
+__device__ __forceinline__ void finish_rows(const GemmArgs &a, f4_t v, uint32_t tok, uint32_t tile, uint32_t rg, float rinv, uint2 res, float &sq) {
+    if (tok >= a.M || tile >= a.ntiles) return;
+    if (MODE == GEMM_PLAIN) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] *= rinv;
+    } else if (a.res) {
+        const float2 r01 = __half22float2(__builtin_bit_cast(__half2, res.x)), r23 = __half22float2(__builtin_bit_cast(__half2, res.y));
+        v[0] += r01.x; v[1] += r01.y; v[2] += r23.x; v[3] += r23.y;
+    }
+    __half2 *dst = reinterpret_cast<__half2 *>(a.out + (size_t)tok * a.out_stride + a.out_row0 + tile * 16 + rg * 4);
+    const __half2 h01 = __floats2half2_rn(v[0], v[1]), h23 = __floats2half2_rn(v[2], v[3]);
+    dst[0] = h01;
+    dst[1] = h23;
+    if (MODE == GEMM_RESID) {
+        const float2 f01 = __half22float2(h01), f23 = __half22float2(h23);
+        sq = fmaf(f01.x, f01.x, sq); sq = fmaf(f01.y, f01.y, sq);
+        sq = fmaf(f23.x, f23.x, sq); sq = fmaf(f23.y, f23.y, sq);
+    }
+}
+
+template <int MODE, int NMT>
+__device__ __forceinline__ void kslice_finish(const GemmArgs &a, const f4_t (&acc)[kSliceRows][NMT], uint4 *lds) {
+    constexpr int RT = kSliceRows;
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), m0 = blockIdx.y * (NMT * 16), M = a.M;
+    // The slices meet, four token tiles at a time: every wave's sums go into LDS, then a wave adds up the eight of two
+    // row-tiles of one token tile, a half of K after the other and each in order.  What is added to the rows is requested first.
+    const uint32_t j = lane & 15, rg = lane >> 4, pair = wave >> 2, who = wave & 3;
+    constexpr int NU = (NMT + 3) / 4;      // token tiles a wave finishes: who, who + 4, ..
+    uint2 res[NU][2];
+    if constexpr (MODE == GEMM_RESID) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const uint32_t tok = min(m0 + (who + u * 4) * 16 + j, M - 1);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const uint32_t tile = min(blockIdx.x * RT + pair * 2 + e, a.ntiles - 1);
+                res[u][e] = a.res ? *reinterpret_cast<const uint2 *>(a.res + (size_t)tok * a.out_stride + a.out_row0 + tile * 16 + rg * 4) : uint2{0u, 0u};
+            }
+        }
+    }
+    float *const side = reinterpret_cast<float *>(lds) + kslice_sum_floats(NMT);
+    f4_t *const sums = reinterpret_cast<f4_t *>(lds) + lane;      // [wave][token tile of the four][row-tile][lane]
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        constexpr int NB = NMT < 4 ? NMT : 4;
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            if (u * 4 + n >= NMT) break;
+#pragma unroll
+            for (int t = 0; t < RT; ++t) sums[((wave * NB + n) * RT + t) * 64] = acc[t][u * 4 + n];
+        }
+        if constexpr (MODE == GEMM_PLAIN) {
+            if (u == 0 && threadIdx.x < NMT * 16) side[threadIdx.x] = row_rinv(a, min(m0 + threadIdx.x, M - 1), M);
+        }
+        __syncthreads();
+        const uint32_t n = who + u * 4, tok = m0 + n * 16 + j;
+        if (n >= NMT) continue;
+        float sq[2] = {0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const uint32_t tile = blockIdx.x * RT + pair * 2 + e;
+            f4_t half[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f4_t *const s4 = sums + ((h * 4 * NB + who) * RT + pair * 2 + e) * 64;
+                half[h] = ((s4[0] + s4[NB * RT * 64]) + s4[2 * NB * RT * 64]) + s4[3 * NB * RT * 64];
+            }
+            finish_rows<MODE>(a, half[0] + half[1], tok, tile, rg, MODE == GEMM_PLAIN ? side[n * 16 + j] : 0.f, res[u][e], sq[e]);
+        }
+        if (MODE == GEMM_RESID && a.ssq_out) {
+            const float own = rows4_meet<false>(sq[0] + sq[1]);
+            if (rg == 0) side[(n * 2 + pair) * 16 + j] = own;
+        }
+    }
+    if (MODE == GEMM_RESID && a.ssq_out) {       // 64 columns: half a run
+        __syncthreads();
+        const uint32_t n = threadIdx.x >> 4, jj = threadIdx.x & 15, tok = m0 + threadIdx.x;
+        if (threadIdx.x < NMT * 16 && tok < M && blockIdx.x * RT < a.ntiles)
+            a.ssq_out[(size_t)(a.out_row0 / 64 + blockIdx.x) * M + tok] = side[n * 32 + jj] + side[n * 32 + 16 + jj];
+    }
+}
+
+template <int MODE, int NMT>
+__global__ __launch_bounds__(kSliceWaves * 64, 1) void gemm_kslice_kernel(GemmArgs a) {
+    extern __shared__ uint4 lds[];
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int RT = kSliceRows;
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t i = lane & 15, c = lane >> 4;
+    const uint32_t m0 = blockIdx.y * (NMT * 16);
+    const KSlice slice = k_slice(a.nsb, wave);
+    const uint32_t sb0 = slice.begin, nsb = slice.end - slice.begin;      // (at least two super-blocks: gemm_k_slices)
+
+    f4_t acc[RT][NMT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int n = 0; n < NMT; ++n) acc[t][n] = f4_t{0.f, 0.f, 0.f, 0.f};
+
+    const uint32_t row_b = a.x_stride * (uint32_t)sizeof(__half);
+    // (rows past the last are out of the buffer's range: zeros, never stored)
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(a.x), 0, (int)(a.M * row_b), 0x00020000), wbuf = make_rsrc(a.W);
+    // round r of a fill covers tokens 4 r .. 4 r + 3 of the tile: lane l puts chunk u0 ^ r of token 4 r + (l >> 4) into
+    // column l & 15 of that token's row (the layout of gemm_w4_kernel's stages)
+    const uint32_t u0 = lds_col((lane & 15) ^ (lane >> 4));
+    uint32_t xoff[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) xoff[r] = (r * 4 + (lane >> 4)) * row_b + (u0 ^ r) * 16u;
+    unsigned char *const ring = reinterpret_cast<unsigned char *>(lds) + wave * (NMT * 4096);
+    uint32_t wbase[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        const uint32_t tile = blockIdx.x * RT + t;
+        wbase[t] = (tile < a.ntiles ? tile : 0) * a.tile_u4 * 16u;      // (tiles past the slab read tile 0: discarded)
+    }
+    auto column = [&](uint32_t sb) -> uint32_t {   // where super-block sb of the slice (clamped to the last) starts, in bytes
+        const uint32_t s = sb0 + min(sb, nsb - 1);
+        return __builtin_amdgcn_readfirstlane(gather_col(s * 128, a.x_off, a.x_group) * (uint32_t)sizeof(__half) + m0 * row_b);
+    };
+    auto fill = [&](uint32_t col, int n) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) load_to_lds16(xbuf, (lds_void *)(ring + n * 4096 + r * 1024), xoff[r], col + n * 16 * row_b);
+    };
+    uint4 wq[RT], sc[RT];      // a super-block's codes; a scale group's scales
+    auto load_w = [&](uint32_t sb) {
+        const uint32_t sa = sb0 + sb, o = (sa >> 3) * (9 * 1024) + (sa & 7) * 1024;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) wq[t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wbuf, lane * 16, wbase[t] + o, kAuxNt));
+    };
+    auto load_sc = [&](uint32_t sb) {
+        const uint32_t g = (sb0 + sb) >> 3, o = g * (9 * 1024) + min(8u, a.nsb - g * 8u) * 1024;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) sc[t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wbuf, lane * 16, wbase[t] + o, kAuxNt));
+    };
+    // prefetched weights and scales become visible to the compiler only here: nothing derived from them is made (and waited for) earlier
+    auto arrive = [&]() {
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+            asm volatile("" : "+v"(wq[t].x), "+v"(wq[t].y), "+v"(wq[t].z), "+v"(wq[t].w), "+v"(sc[t].x), "+v"(sc[t].y), "+v"(sc[t].z), "+v"(sc[t].w));
+    };
+    h8_t A[4][RT];
+    h2_t dd[RT];
+    auto scales = [&](uint32_t sb) {
+        const uint32_t sn = (sb0 + sb) & 7, sel = sn & 1 ? 0x03020302u : 0x01000100u;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const uint32_t lo = sn & 2 ? sc[t].y : sc[t].x, hi = sn & 2 ? sc[t].w : sc[t].z;
+            dd[t] = as_h2(__builtin_amdgcn_perm(0, sn & 4 ? hi : lo, sel));
+        }
+    };
+    auto dequant = [&](int kk) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const uint32_t q = kk == 0 ? wq[t].x : kk == 1 ? wq[t].y : kk == 2 ? wq[t].z : wq[t].w;
+            h2_t w[4];
+            dequant8(q, w);
+            w[0] *= dd[t]; w[1] *= dd[t]; w[2] *= dd[t]; w[3] *= dd[t];
+            A[kk][t] = h8_t{w[0].x, w[0].y, w[1].x, w[1].y, w[2].x, w[2].y, w[3].x, w[3].y};
+        }
+    };
+    const uint32_t lane_at = (i * 16 + (c ^ i)) * 16u;
+    h8_t Bc[4], Bn[4];
+    auto read_b = [&](h8_t (&B)[4], int n) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) B[kk] = __builtin_bit_cast(h8_t, *reinterpret_cast<const uint4 *>(ring + n * 4096 + (lane_at ^ (kk * 64u))));
+    };
+    // One super-block, token tile by token tile.  REM: super-blocks behind it in the slice, 2 meaning two or more.
+    auto step = [&](uint32_t sb, auto REM) {
+        constexpr int rem = decltype(REM)::value;
+        const uint32_t next = column(sb + 1);
+        auto tile = [&](auto N) {
+            constexpr int n = decltype(N)::value;
+            constexpr bool turn = n == NMT - 1;
+            // the tile's operands have arrived in registers: its slot takes the next super-block's
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if constexpr (rem >= 1) fill(next, n);
+            __builtin_amdgcn_sched_barrier(0);
+            // Issued behind the next tile's fill: the fills of the other slots and, where that fill is of this super-block, the
+            // weights of the next (loads return in order; scales on their way make the wait a little stricter)
+            if constexpr (!turn) {
+                wait_vm<(rem >= 1 ? (NMT - 1) * 4 + RT : (NMT - 2 - n) * 4)>();
+                read_b(Bn, n + 1);
+            } else if constexpr (rem >= 1) {
+                wait_vm<(NMT - 1) * 4>();
+                read_b(Bn, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // the next super-block's A operands are made beside the last tile's products, whose operands they replace
+            if constexpr (turn && rem >= 1) { arrive(); scales(sb + 1); }
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+#pragma unroll
+                for (int t = 0; t < RT; ++t) acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[kk][t], Bc[kk], acc[t][n], 0, 0, 0);
+                if constexpr (turn && rem >= 1) dequant(kk);
+            }
+            if constexpr (turn && rem == 2) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (((sb0 + sb + 2) & 7) == 0) load_sc(sb + 2);
+                load_w(sb + 2);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) Bc[kk] = Bn[kk];
+        };
+        tile(std::integral_constant<int, 0>{});
+        tile(std::integral_constant<int, 1>{});
+        if constexpr (NMT > 2) tile(std::integral_constant<int, 2>{});
+        if constexpr (NMT > 3) tile(std::integral_constant<int, 3>{});
+        if constexpr (NMT > 4) tile(std::integral_constant<int, 4>{});
+        static_assert(NMT >= 2 && NMT <= 5, "token tiles of a workgroup");
+    };
+    load_sc(0);
+    load_w(0);
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t col0 = column(0);
+#pragma unroll
+    for (int n = 0; n < NMT; ++n) fill(col0, n);
+    arrive();
+    scales(0);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) dequant(kk);
+    __builtin_amdgcn_sched_barrier(0);
+    if (((sb0 + 1) & 7) == 0) load_sc(1);
+    load_w(1);
+    wait_vm<0>();
+    read_b(Bc, 0);
+    uint32_t sb = 0;
+    for (; sb + 2 < nsb; ++sb) step(sb, std::integral_constant<int, 2>{});
+    step(sb, std::integral_constant<int, 1>{});
+    step(sb + 1, std::integral_constant<int, 0>{});
+    kslice_finish<MODE, NMT>(a, acc, lds);
+#endif
+}
+
+template <int MODE, int NMT>
+static hipError_t launch_gemm_kslice(const GemmArgs &a, hipStream_t st) {
+    void (*const kernel)(GemmArgs) = gemm_kslice_kernel<MODE, NMT>;
+    constexpr size_t ldsb = kslice_lds_bytes(NMT);
+    static_assert(ldsb <= 160 * 1024, "LDS of a CU");
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsb);
+    if (attr != hipSuccess) return attr;
+    const dim3 grid((a.ntiles + kSliceRows - 1) / kSliceRows, (a.M + NMT * 16 - 1) / (NMT * 16));
+    hipLaunchKernelGGL(kernel, grid, dim3(kSliceWaves * 64), ldsb, st, a);
+    return hipGetLastError();
+}
+
+template <int MODE, int AT, int MT, bool GROUPED, int NW, int KS, bool SLICED = false>
 static hipError_t launch_gemm_k(const GemmArgs &a, uint32_t ntok, uint32_t gz, hipStream_t st) {
     constexpr size_t ldsb = gemm_lds_bytes(MT, AT, NW, KS);
     static_assert(ldsb <= 160 * 1024, "LDS of a CU");
     if (ldsb > 64 * 1024) {
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_w4_kernel<MODE, AT, MT, GROUPED, NW, KS>),
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_w4_kernel<MODE, AT, MT, GROUPED, NW, KS, SLICED>),
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsb);
         if (attr != hipSuccess) return attr;
     }
     constexpr uint32_t rows = NW / KS * AT;   // row-tiles of a workgroup
     dim3 grid((a.ntiles + rows - 1) / rows, (ntok + MT - 1) / MT, gz);
-    hipLaunchKernelGGL((gemm_w4_kernel<MODE, AT, MT, GROUPED, NW, KS>), grid, dim3(NW * 64), ldsb, st, a);
+    hipLaunchKernelGGL((gemm_w4_kernel<MODE, AT, MT, GROUPED, NW, KS, SLICED>), grid, dim3(NW * 64), ldsb, st, a);
     return hipGetLastError();
 }
 
@@ -2186,6 +2502,16 @@ static uint32_t gemm_pick_tile(const GemmArgs &a, uint32_t widest) {
         if (cost < best_cost) { best_cost = cost; best = mt; }
     }
     return best;
+}
+
+// K in eight slices: for matrices of at least 16 super-blocks whose plan goes in one round of 64-token tiles of 128 rows.  Which of the
+// kernels walks them goes by the rows that are there: gemm_kslice_kernel where its 64-row tiles of up to 80 tokens
+// go in one round (a second round costs it more than it gains: 512 tokens of 4096 columns, O 24 -> 31 us, down 66 -> 87), else the two K
+// parts, which then keep the slices' sums apart (SLICED) so that a row's bits do not depend on its company.  That costs them
+// up to 1.2 us a launch (512 tokens: O 24.0 -> 25.2, down 65.8 -> 66.7), against 4 and 15 us gained at 128 tokens; plans that need larger
+// tiles stay with plain K parts.  QKV of 6144 rows, 72 tokens: 16.2 -> 12.9 us, 128: 17.1 -> 15.9, from 160 on as before.
+static bool gemm_k_slices(const GemmArgs &a, uint32_t plan_tokens) {
+    return a.nsb % 2 == 0 && a.nsb >= 16 && (a.total_tiles + 7) / 8 * ((plan_tokens + 63) / 64) <= 256;
 }
 
 template <int MODE>
@@ -2227,10 +2553,22 @@ static hipError_t launch_gemm_m(const GemmArgs &a, uint32_t ntasks, uint32_t max
         if (a.M <= 48) return launch_gemm_k<MODE, 2, 48, false, 4, 1>(a, a.M, parts, st);
         return launch_gemm_k<MODE, 2, 64, false, 4, 1>(a, a.M, parts, st);
     }
-    if constexpr (MODE == GEMM_F32) return hipErrorInvalidValue;   // partial planes: at most 64 tokens
-    else {
+    if constexpr (MODE == GEMM_F32 || MODE == GEMM_GATE_UP) { if (MODE == GEMM_F32) return hipErrorInvalidValue; }   // partial planes: at most 64 tokens
+    if constexpr (MODE != GEMM_F32) {
         // Plans of more than 64 tokens.  The tile goes by the rows that are there (a.M) and never changes a bit of the
         // result; the K parts do, so they go by the whole matrix and the plan's token count.
+        if constexpr (MODE != GEMM_GATE_UP) {
+            if (gemm_k_slices(a, max_tok)) {
+                const uint32_t groups = (a.ntiles + kSliceRows - 1) / kSliceRows;
+                auto one_round = [&](uint32_t mt) { return groups * ((a.M + mt - 1) / mt) <= 256; };
+                if (one_round(32)) return launch_gemm_kslice<MODE, 2>(a, st);
+                if (one_round(48)) return launch_gemm_kslice<MODE, 3>(a, st);
+                if (one_round(64)) return launch_gemm_kslice<MODE, 4>(a, st);
+                if (one_round(80)) return launch_gemm_kslice<MODE, 5>(a, st);
+                if ((a.ntiles + 7) / 8 * ((a.M + 47) / 48) <= 256) return launch_gemm_k<MODE, 2, 48, false, 8, 2, true>(a, a.M, 1, st);
+                return launch_gemm_k<MODE, 2, 64, false, 8, 2, true>(a, a.M, 1, st);
+            }
+        }
         if (gemm_two_k_parts(a, max_tok)) {
             // the smallest tile that still leaves at most one workgroup per CU (there is one: the rule saw to it).  What each
             // tile is worth where it is the one, against the next larger: O / down, us: 200 tokens 32: 19.1 / 52 against

@@ -803,6 +803,43 @@ def test_gemm_tiles_of_every_width_give_the_same_rows(H, I, plan_tokens, counts)
     st.close()
 
 
+@pytest.mark.parametrize("H,n_q,n_kv,I,plan_tokens,counts", [
+    (4096, 0, 0, 2048, 512, (512, 385, 384, 321, 320, 257, 256, 193, 192, 129, 128, 65, 17, 1)),
+    (2048, 16, 4, 2304, 640, (640, 200, 33)), (2176, 17, 1, 2560, 300, (300, 161, 16)), (3072, 24, 24, 2816, 384, (384, 250, 100)),
+    (1024, 20, 5, 6144, 130, (130, 81, 5))])
+def test_matrices_in_eight_k_slices_give_the_same_rows(H, n_q, n_kv, I, plan_tokens, counts):
+    """Narrow matrices of 16 and more super-blocks in plans above 64 tokens: K in eight slices, on eight waves in tiles of
+    32 to 80 tokens, or walked one after the other by two K parts where the rows are too many for one round of those tiles.
+    The full trip against the oracle, every shorter one with the same bits (edges of every tile; slices of 2 and of 2 or 3
+    super-blocks; with attention QKV and the gathered input of O as well), and the same bits again where every RMS
+    factor has a launch of its own."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = dict(S.cfg_ffn_block(), hidden=H, ffn_inter=I)
+    if n_q:
+        cfg.update(n_layers=2, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, no_attn=False, no_residual=False)
+    W = Hn.WeightCache(cfg, 71)
+    x = S.activations(71, 0, plan_tokens, H)
+    st = B.Stack(B.Plan(cfg, 1 << 30, plan_tokens))
+    for layer in range(cfg["n_layers"]):
+        for k, ex, N, K in S.matrix_shapes(cfg):
+            st.load_matrix(layer, k, ex, *W(layer, k, ex))
+    xin = torch.from_numpy(x).to(st.device)
+    full = None
+    for mode, n in [(0, n) for n in counts] + [(2, counts[0]), (2, counts[-1])]:
+        st.set_decode_mode(mode)
+        xout = torch.full_like(xin, 7.0)
+        B.chunked_forward(st, xin[:n], xout[:n])
+        st.synchronize()
+        got = xout.cpu().numpy()
+        assert (got[n:] == 7.0).all()                # rows past the trip are not written
+        if full is None:
+            full = got
+            assert Hn.rel_err(got, O.stack_forward(x, cfg, W, mirror=True)) <= TOL
+        np.testing.assert_array_equal(got[:n].view(np.uint16), full[:n].view(np.uint16))
+    st.close()
+
+
 @pytest.mark.parametrize("H,attn,I,tokens", [(256, True, 512, 65), (768, True, 1280, 300), (2304, True, 768, 129),
                                              (4352, False, 256, 200), (256, False, 7168, 1024), (640, True, 768, 100)])
 def test_rms_factors_from_the_sums_of_squares_of_o_and_down(H, attn, I, tokens):
