@@ -164,7 +164,11 @@ def check_gemm_isa(path):
             bad.append(mangled + ": unexpected template arguments")
             continue
         at, mt, nw, ks = int(m.group(2)), int(m.group(3)), int(m.group(5)), int(m.group(6) or 1)
-        lpi, nfill, in_flight = gemm_wait_counts(mt, nw, at, ks)
+        # an expert's workgroups may take one of the two tiles below the launch's: three rings in one kernel
+        less = {32: 16, 48: 32, 64: 48, 96: 64, 128: 96} if m.group(4) == "1" else {}
+        tiles = [t for t in (mt, less.get(mt), less.get(less.get(mt))) if t]
+        counts = [gemm_wait_counts(t, nw, at, ks) for t in tiles]
+        found = set()
         segs, cur = [], []
         for ln in body.splitlines():
             f = ln.split()
@@ -197,19 +201,25 @@ def check_gemm_isa(path):
             steps += 1
             if not waits:
                 bad.append(mangled + ": ring step without a vmcnt wait")
-            elif waits[-1] != 0:
-                if waits[-1] != in_flight:
-                    bad.append("%s: counted wait vmcnt(%d), expected %d" % (mangled, waits[-1], in_flight))
+            elif waits[-1] == 0:       # the opening prefetches of a further tile
+                if 0 not in s[max(k for k, x in enumerate(s) if isinstance(x, str) and x == "lds") + 1:]:
+                    bad.append(mangled + ": LDS fills that no vmcnt(0) and no counted wait stands behind")
+            else:
                 # every prefetch: the activation fills, then one code load per tile; one prefetch in eight
                 # starts with a scale fill per tile (a branch: the text holds it either way)
                 nl = sum(1 for x in loads if x == "lds")
-                if nl not in (nfill, nfill + at) or loads[:nl] != ["lds"] * nl or len(loads) != nl + at:
-                    bad.append("%s: a counted ring step issues %s, expected (%d +) %d LDS fills then %d weight loads" % (
-                        mangled, loads, at, nfill, at))
+                fits = [t for t, (lpi, nfill, in_flight) in zip(tiles, counts) if waits[-1] == in_flight and nl in (nfill, nfill + at)]
+                found.update(fits)
+                if not fits or loads[:nl] != ["lds"] * nl or len(loads) != nl + at:
+                    bad.append("%s: a counted ring step issues %s and waits for vmcnt(%d), expected (%d +) LDS fills then %d weight loads and a wait by %s" % (
+                        mangled, loads, waits[-1], at, at, counts))
                 if any(not x.startswith("buffer_load") for x in loads if x != "lds"):
                     bad.append(mangled + ": a ring step touches vector memory with something other than its prefetch")
         if steps == 0:
             bad.append(mangled + ": no ring step recognised")
+        missing = [t for t, c in zip(tiles, counts) if c[2] and t not in found]
+        if missing:
+            bad.append("%s: no counted ring step of the tiles %s" % (mangled, missing))
         if ks == 2:
             over = lds_writes_behind_fills(body)
             if over:

@@ -1641,9 +1641,8 @@ __device__ __forceinline__ KSlice k_slice(uint32_t nsb, uint32_t w) {
 // the others, on the same rows and tokens, the second half, each half with activation stages of its own; the
 // second half's accumulators then pass through LDS and are added to the first's.  SLICED: each part adds its four
 // slices of K up one by one, as gemm_kslice_kernel does.
-template <int MODE, int AT, int MT, bool GROUPED, int NW = 4, int KS = 1, bool SLICED = false>
-__global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmArgs a) {
-    extern __shared__ uint4 lds[];                 // KS x (gemm_depth + 1) stages of MT x 16 chunks, then 2 AT KB of scales per wave
+template <int MODE, int AT, int MT, bool GROUPED, int NW, int KS, bool SLICED>
+__device__ __forceinline__ void gemm_w4_body(const GemmArgs &a, uint4 *lds) {   // lds: KS x (gemm_depth + 1) stages of MT x 16 chunks, then 2 AT KB of scales per wave
     constexpr int NMT = MT / 16;
     constexpr int NWR = NW / KS;                   // waves of one K part: each owns AT row-tiles
     constexpr int NFILL = MT / (4 * NWR);          // 16-byte chunks each thread moves per stage
@@ -2177,6 +2176,27 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
     }
 }
 
+// The next smaller tiles that an expert's workgroups may take (0: none)
+constexpr int gemm_lesser(int MT) { return MT == 32 ? 16 : MT == 48 ? 32 : MT == 64 ? 48 : MT == 96 ? 64 : MT == 128 ? 96 : 0; }
+
+// Grouped: the launch's tile holds the busiest expert's tokens; the workgroups of an expert with fewer take the smallest of it
+// and the two tiles below that holds theirs, since every column of a tile costs its fills, operand reads and MFMAs
+// whether a token stands behind it or not.  128 experts of 1536 + 2048 rows, us: 4 tokens each on average and 13 at most (32-token
+// tiles for all before) gate/up 54 -> 41, down 35 -> 28; 32 on average and 47 at most 64 -> 62, 48 -> 43.5.
+template <int MODE, int AT, int MT, bool GROUPED, int NW = 4, int KS = 1, bool SLICED = false>
+__global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmArgs a) {
+    extern __shared__ uint4 lds[];
+    if constexpr (GROUPED && gemm_lesser(MT)) {
+        constexpr int less = gemm_lesser(MT), least = gemm_lesser(less);
+        const uint32_t ntok = a.tasks[blockIdx.z].npairs;
+        if constexpr (least) {
+            if (ntok <= least) { gemm_w4_body<MODE, AT, least, GROUPED, NW, KS, SLICED>(a, lds); return; }
+        }
+        if (ntok <= less) { gemm_w4_body<MODE, AT, less, GROUPED, NW, KS, SLICED>(a, lds); return; }
+    }
+    gemm_w4_body<MODE, AT, MT, GROUPED, NW, KS, SLICED>(a, lds);
+}
+
 // ------------------------------------------------------------------------------------
 // GEMM of a narrow matrix with K in eight slices, one to a wave (O, down and small QKV of plans above 64 tokens).
 //
@@ -2517,12 +2537,11 @@ static bool gemm_k_slices(const GemmArgs &a, uint32_t plan_tokens) {
 template <int MODE>
 static hipError_t launch_gemm_m(const GemmArgs &a, uint32_t ntasks, uint32_t max_tok, hipStream_t st) {
     if (ntasks) {
-        // grouped: one expert per blockIdx.z; the smallest tile that holds the busiest expert's tokens, since every
-        // column of a tile is multiplied whether a token stands behind it or not (128 experts of 1536 + 2048 rows,
-        // 4 tokens each on average: gate/up 41 us in 16-token tiles, 45 in 32, 52 in 48, 65 in 64, 83 in 96, 95 in
-        // 128), while a second tile for a few busy experts costs 14 to 16 us for the workgroups that find nothing to
-        // do (24 tokens on average, 40 at most: 32-token tiles 63 us, 48-token tiles 56).  512 tokens through a
-        // layer, 48- instead of 64-token tiles: gate/up 69 -> 57 us, down 45 -> 40.
+        // grouped: one expert per blockIdx.z; the smallest tile that holds the busiest expert's tokens (128 experts of 1536 +
+        // 2048 rows, 4 tokens each on average: gate/up 41 us with every expert in 16-token tiles, 45 in 32, 52 in 48, 65 in 64,
+        // 83 in 96, 95 in 128; the kernel lets the others take smaller ones), since a second tile for a few busy experts
+        // costs 14 to 16 us for the workgroups that find nothing to do (24 tokens on average, 40 at most: 32-token tiles 63 us,
+        // 48-token tiles 56).  512 tokens through a layer, 48- instead of 64-token tiles: gate/up 69 -> 57 us, down 45 -> 40.
         if constexpr (MODE == GEMM_GATE_UP || MODE == GEMM_F32) {
             if (max_tok <= 16) return launch_gemm_k<MODE, 2, 16, true, 4, 1>(a, max_tok, ntasks, st);
             if (max_tok <= 32) return launch_gemm_k<MODE, 2, 32, true, 4, 1>(a, max_tok, ntasks, st);

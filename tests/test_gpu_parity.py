@@ -270,6 +270,25 @@ def test_expert_gemm_tile_by_the_busiest_experts_tokens(busiest):
     _check(cfg, 71, M, _budgets(cfg, M, [1.0, 0.5]), logits=lg)
 
 
+@pytest.mark.parametrize("busiest,others", [(20, (16, 17, 1)), (48, (32, 33, 17)), (64, (48, 49, 33)), (96, (64, 65, 49)), (130, (96, 97, 65))])
+def test_experts_of_a_launch_take_tiles_of_their_own(busiest, others):
+    """A grouped launch's tile holds the busiest expert's tokens (two tiles of 128 for 130); an expert with fewer takes the
+    smallest of it and the two tiles below it that holds its own: at the edges of each."""
+    cfg = dict(Hn.small_moe_cfg(1), n_experts=8, top_k=2)
+    M = max(busiest, sum(others)) + 3
+    first = np.where(np.arange(M) < busiest, 0, 4 + np.arange(M) % 2)       # expert 0: `busiest` tokens
+    second = 6 + np.arange(M) % 2
+    at = 0
+    for e, n in enumerate(others):
+        second[at:at + n] = 1 + e
+        at += n
+    lg = np.random.default_rng(busiest).uniform(-1.0, 1.0, (1, M, 8)).astype(np.float32)
+    lg[0, np.arange(M), first] += 21.0
+    lg[0, np.arange(M), second] += 20.0
+    assert sorted(np.bincount(np.concatenate([first, second]), minlength=8))[-1] == max(busiest, *others)
+    _check(cfg, 73, M, _budgets(cfg, M, [1.0]), logits=lg)
+
+
 @pytest.mark.parametrize("device_logits", [False, True])
 def test_only_the_routing_tables_in_use_are_uploaded(device_logits):
     """A trip of 40 tokens, then one of a single token through the same plan: the single token's two tasks replace the first
