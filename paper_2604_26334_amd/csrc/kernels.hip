@@ -2326,8 +2326,7 @@ __global__ __launch_bounds__(kSliceWaves * 64, 1) void gemm_kslice_kernel(GemmAr
         for (int n = 0; n < NMT; ++n) acc[t][n] = f4_t{0.f, 0.f, 0.f, 0.f};
 
     const uint32_t row_b = a.x_stride * (uint32_t)sizeof(__half);
-    // (rows past the last are out of the buffer's range: zeros, never stored)
-    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(a.x), 0, (int)(a.M * row_b), 0x00020000), wbuf = make_rsrc(a.W);
+    const __amdgpu_buffer_rsrc_t wbuf = make_rsrc(a.W);
     // round r of a fill covers tokens 4 r .. 4 r + 3 of the tile: lane l puts chunk u0 ^ r of token 4 r + (l >> 4) into
     // column l & 15 of that token's row (the layout of gemm_w4_kernel's stages)
     const uint32_t u0 = lds_col((lane & 15) ^ (lane >> 4));
@@ -2341,13 +2340,18 @@ __global__ __launch_bounds__(kSliceWaves * 64, 1) void gemm_kslice_kernel(GemmAr
         const uint32_t tile = blockIdx.x * RT + t;
         wbase[t] = (tile < a.ntiles ? tile : 0) * a.tile_u4 * 16u;      // (tiles past the slab read tile 0: discarded)
     }
-    auto column = [&](uint32_t sb) -> uint32_t {   // where super-block sb of the slice (clamped to the last) starts, in bytes
-        const uint32_t s = sb0 + min(sb, nsb - 1);
-        return __builtin_amdgcn_readfirstlane(gather_col(s * 128, a.x_off, a.x_group) * (uint32_t)sizeof(__half) + m0 * row_b);
+    // The workgroup's rows from super-block sb of the slice (clamped to the last) on, as a buffer that ends with the last row that is
+    // there: a fill's rows past it are out of its range, i.e. zeros (never stored) and no access.  What names the row is a lane
+    // offset, since a scalar offset takes no part in the range check.
+    const char *const rows = reinterpret_cast<const char *>(a.x) + (size_t)m0 * row_b;
+    const uint32_t rows_b = (a.M - m0) * row_b;
+    auto columns = [&](uint32_t sb) {
+        const uint32_t col = __builtin_amdgcn_readfirstlane(gather_col((sb0 + min(sb, nsb - 1)) * 128, a.x_off, a.x_group) * (uint32_t)sizeof(__half));
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(rows + col), 0, (int)(rows_b - col), 0x00020000);
     };
-    auto fill = [&](uint32_t col, int n) {
+    auto fill = [&](__amdgpu_buffer_rsrc_t cols, int n) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) load_to_lds16(xbuf, (lds_void *)(ring + n * 4096 + r * 1024), xoff[r], col + n * 16 * row_b);
+        for (int r = 0; r < 4; ++r) load_to_lds16(cols, (lds_void *)(ring + n * 4096 + r * 1024), xoff[r] + n * 16 * row_b, 0);
     };
     uint4 wq[RT], sc[RT];      // a super-block's codes; a scale group's scales
     auto load_w = [&](uint32_t sb) {
@@ -2395,7 +2399,7 @@ __global__ __launch_bounds__(kSliceWaves * 64, 1) void gemm_kslice_kernel(GemmAr
     // One super-block, token tile by token tile.  REM: super-blocks behind it in the slice, 2 meaning two or more.
     auto step = [&](uint32_t sb, auto REM) {
         constexpr int rem = decltype(REM)::value;
-        const uint32_t next = column(sb + 1);
+        const __amdgpu_buffer_rsrc_t next = columns(sb + 1);
         auto tile = [&](auto N) {
             constexpr int n = decltype(N)::value;
             constexpr bool turn = n == NMT - 1;
@@ -2440,9 +2444,9 @@ __global__ __launch_bounds__(kSliceWaves * 64, 1) void gemm_kslice_kernel(GemmAr
     load_sc(0);
     load_w(0);
     __builtin_amdgcn_sched_barrier(0);
-    const uint32_t col0 = column(0);
+    const __amdgpu_buffer_rsrc_t first = columns(0);
 #pragma unroll
-    for (int n = 0; n < NMT; ++n) fill(col0, n);
+    for (int n = 0; n < NMT; ++n) fill(first, n);
     arrive();
     scales(0);
 #pragma unroll
