@@ -300,8 +300,8 @@ constexpr int kMaxGroups = 16;   // K <= 16384
 template <int NW>
 struct GemvLds {
     uint4 x[NW][128];
-    float red[(NW / 2) * kMaxGroups][2][16];   // K split >= 2: at most NW / 2 units per workgroup
-    float red_ss[(NW / 2) * kMaxGroups];
+    float red[(NW > 1 ? NW / 2 : 1) * kMaxGroups][2][16];   // K split >= 2: at most NW / 2 units per workgroup
+    float red_ss[(NW > 1 ? NW / 2 : 1) * kMaxGroups];
     float corr[NW][32];   // per wave: code-offset corrections of the current scale group
 };
 
@@ -469,6 +469,12 @@ __global__ __launch_bounds__(NW * 64, 4) void gemv_w4_kernel(GemvArgs a, uint32_
     gemv_item<MODE, NW, DBUF, FULLG>(a, W, x, out, out_f32, blockIdx.x, ks, lds);
 }
 
+// Few units of one or two waves: a workgroup each, so that every unit's weights come through a CU of their own instead of
+// four units' through one (K = 1024, 176 gate/up units 4.3 -> 3.9 us; K = 512, QKV 64 units 3.3 -> 2.9, O 32 3.0 -> 2.75, gate/up 88
+// 3.7 -> 3.2; K = 2048, O 128 units 4.1 -> 3.8).  Beyond one unit per CU the larger workgroups are faster (K = 2048, 352 gate/up
+// units 5.3 -> 6.2).
+static bool gemv_unit_per_cu(uint32_t nunits, uint32_t ks, uint32_t ntasks) { return ks <= 2 && !ntasks && nunits <= 256; }
+
 template <int MODE, bool FULLG, bool ROUTE = false>
 static hipError_t launch_gemv_f(const GemvArgs &a, uint32_t ks, uint32_t ntasks, const RouteArgs &ra, hipStream_t st) {
     // waves per workgroup: at least the K split; two units per workgroup (8 waves) when that still
@@ -477,8 +483,14 @@ static hipError_t launch_gemv_f(const GemvArgs &a, uint32_t ks, uint32_t ntasks,
     // unit per workgroup).  The result does not depend on the shape.
     uint32_t nw = ks > 8 ? 16 : ks > 4 ? 8 : 4;
     if (ks == 4 && (a.nunits + 1) / 2 >= 192) nw = 8;   // (with one wave per unit, ks < 4, the larger workgroup measured slower)
+    if (!ROUTE && gemv_unit_per_cu(a.nunits, ks, ntasks)) nw = ks;
     const uint32_t units = nw / ks;
     dim3 grid((a.nunits + units - 1) / units + (ROUTE ? 1 : 0), ntasks ? ntasks : 1);
+    if constexpr (!ROUTE) {
+        if (nw == 1) hipLaunchKernelGGL((gemv_w4_kernel<MODE, 1, FULLG>), grid, dim3(64), 0, st, a, ks, ra);
+        if (nw == 2) hipLaunchKernelGGL((gemv_w4_kernel<MODE, 2, FULLG>), grid, dim3(128), 0, st, a, ks, ra);
+        if (nw <= 2) return hipGetLastError();
+    }
     if (nw == 16) hipLaunchKernelGGL((gemv_w4_kernel<MODE, 16, FULLG, ROUTE>), grid, dim3(1024), 0, st, a, ks, ra);
     else if (nw == 8) hipLaunchKernelGGL((gemv_w4_kernel<MODE, 8, FULLG, ROUTE>), grid, dim3(512), 0, st, a, ks, ra);
     else hipLaunchKernelGGL((gemv_w4_kernel<MODE, 4, FULLG, ROUTE>), grid, dim3(256), 0, st, a, ks, ra);
@@ -673,6 +685,7 @@ static hipError_t launch_gemv_mt_t(const GemvArgs &a, uint32_t ks, uint32_t ntok
     const uint32_t wpu = ks;
     uint32_t nw = wpu > 8 ? 16 : wpu > 4 ? 8 : 4;
     if (wpu == 4 && (a.nunits + 1) / 2 >= 192) nw = 8;
+    if (gemv_unit_per_cu(a.nunits, ks, 0)) nw = ks;
     const uint32_t units = nw / wpu;
     const size_t lds = gemv_mt_lds_bytes(nw, units, a.ngroups, NT);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
@@ -685,7 +698,9 @@ static hipError_t launch_gemv_mt_t(const GemvArgs &a, uint32_t ks, uint32_t ntok
     if (attr8 != hipSuccess) return attr8;
     if (nw == 16) hipLaunchKernelGGL((gemv_mt_kernel<MODE, 16>), grid, dim3(1024), lds, st, a, ks, ntok);
     else if (nw == 8) hipLaunchKernelGGL((gemv_mt_kernel<MODE, 8>), grid, dim3(512), lds, st, a, ks, ntok);
-    else hipLaunchKernelGGL((gemv_mt_kernel<MODE, 4>), grid, dim3(256), lds, st, a, ks, ntok);
+    else if (nw == 4) hipLaunchKernelGGL((gemv_mt_kernel<MODE, 4>), grid, dim3(256), lds, st, a, ks, ntok);
+    else if (nw == 2) hipLaunchKernelGGL((gemv_mt_kernel<MODE, 2>), grid, dim3(128), lds, st, a, ks, ntok);
+    else hipLaunchKernelGGL((gemv_mt_kernel<MODE, 1>), grid, dim3(64), lds, st, a, ks, ntok);
     return hipGetLastError();
 }
 

@@ -123,6 +123,16 @@ def test_few_token_decode_kernel(M, ffn):
     _check(cfg, 11, M, _budgets(cfg, M, [1.0, 0.6, 0.35]))
 
 
+@pytest.mark.parametrize("hidden,n_q,n_kv,ffn", [(1024, 24, 4, 4096), (1024, 28, 4, 4224), (2048, 16, 8, 2048), (512, 1, 1, 128)])
+@pytest.mark.parametrize("M", [1, 3])
+def test_units_of_one_or_two_waves_with_a_workgroup_each(hidden, n_q, n_kv, ffn, M):
+    """Matrices of one or two scale groups: up to 256 units (row tiles, pairs of them for gate/up) go one to a workgroup, more
+    several to one.  256 units of QKV and of gate/up, 288 and 264, K of two groups, a handful; the slabs of a streamed placement
+    have fewer and the same bits."""
+    cfg = dict(Hn.small_dense_cfg(1), hidden=hidden, n_q_heads=n_q, n_kv_heads=n_kv, ffn_inter=ffn)
+    _check(cfg, 29, M, _budgets(cfg, M, [1.0, 0.5]))
+
+
 def test_few_token_kernel_in_chunked_trips():
     """Seven tokens through a four-token plan: a full trip and a short last one (three valid rows of four) in the
     few-token kernel, eager and replayed from a graph; every row against the oracle, and a row's bits do not
