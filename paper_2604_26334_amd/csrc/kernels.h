@@ -31,6 +31,14 @@ struct GemvArgs {
     const int32_t *pairs;
 };
 
+// Two runs of 16-byte units from pinned host memory to the device, at the same places: units 0 .. first16 - 1, and n16 - first16 more
+// from unit first16 + skip16 on
+struct UploadArgs {
+    const uint4 *src;
+    uint4 *dst;
+    uint32_t first16, skip16, n16;   // n16 0: nothing
+};
+
 // M tokens on the matrix cores.  Same modes; rinv comes from a buffer.
 struct GemmArgs {
     const uint4 *W;
@@ -56,7 +64,12 @@ struct GemmArgs {
     float eps;
     const DeviceTask *tasks;
     const int32_t *pairs;
+    // An upload that rides in the launch (ungrouped PLAIN and F32, at most kUploadUnits): kUploadWgs workgroups behind the columns that
+    // the grid has without them
+    UploadArgs up;
+    uint32_t columns;     // set by the launch
 };
+constexpr uint32_t kUploadWgs = 8, kUploadUnits = kUploadWgs * 256;     // one unit a thread
 // RMS factors of M rows as what the four waves of launch_rinv would add up: sq[w * M + row], H columns (sq null: no such sums)
 struct RowQuarters {
     const float *sq;
@@ -73,8 +86,9 @@ struct CopyDesc {
 // PCIe itself, which avoids the per-call cost of many small hipMemcpyAsync
 hipError_t launch_h2d_gather(const CopyDesc *descs, uint32_t n, hipStream_t st);
 // small blocks of pinned host memory -> device, at the same places: bytes 0 .. first - 1 and second_at .. second_at + second - 1
-// (everything a multiple of 16)
-hipError_t launch_upload_tables(const void *src, void *dst, uint64_t first, uint64_t second_at, uint64_t second, hipStream_t st);
+// (everything a multiple of 16; false where it is not), and the launch that does it on its own
+bool make_upload(const void *src, void *dst, uint64_t first, uint64_t second_at, uint64_t second, UploadArgs *up);
+hipError_t launch_upload_tables(const UploadArgs &up, hipStream_t st);
 
 // MoE routing of M tokens: the top_k largest fp32 logits (ties to the lower index, in descending order) and the
 // softmax over them.  As a launch of its own, or riding in the launch that produces the layer's RMS factors or,
@@ -104,7 +118,8 @@ hipError_t launch_route(const RouteArgs &ra, hipStream_t st);
 bool route_rides(const RouteArgs &ra);
 // the factors in the order of the GEMM's sums of squares (see GemmArgs), with their bits
 hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, hipStream_t st);
-hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, const RouteArgs *route, hipStream_t st);
+// (up: an upload that rides in the launch, not together with route)
+hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, const RouteArgs *route, const UploadArgs &up, hipStream_t st);
 // residual epilogue over whole rows of the hidden state (ncols == out_stride == H, first column 0,
 // at most 8 planes) that also writes the RMS factor of each row it stores, bit-identical to
 // launch_splitk_epilogue(GEMM_RESID, ...) followed by launch_rinv(out, ...)

@@ -767,12 +767,21 @@ __device__ __forceinline__ float row_factor(const __half *x, uint32_t H, float e
     return rsqrtf((((part[0] + part[1]) + part[2]) + part[3]) / (float)H + eps);
 }
 
+// one unit of an upload
+__device__ __forceinline__ void upload_unit(const UploadArgs &up, uint32_t unit) {
+    if (unit >= up.n16) return;
+    const uint32_t idx = unit < up.first16 ? unit : unit + up.skip16;
+    reinterpret_cast<u4_t *>(up.dst)[idx] = __builtin_nontemporal_load(reinterpret_cast<const u4_t *>(up.src) + idx);
+}
+
 // NR > 0: the workgroups behind the first M route four tokens each (the MoE routing of a layer depends on nothing the
 // layer computes here, and as a launch of its own it costs 4 to 5 us).
 template <int NR>
-__global__ __launch_bounds__(256) void rinv_kernel(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, RouteArgs ra) {
+__global__ __launch_bounds__(256) void rinv_kernel(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, RouteArgs ra, UploadArgs up) {
     if constexpr (NR > 0) {
         if (blockIdx.x >= M) { route_tokens<NR>(ra, blockIdx.x - M); return; }
+    } else {
+        if (blockIdx.x >= M) { upload_unit(up, (blockIdx.x - M) * 256 + threadIdx.x); return; }
     }
     __shared__ float part[4];
     const uint32_t m = blockIdx.x;
@@ -833,11 +842,12 @@ hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, float eps, 
     return hipGetLastError();
 }
 
-hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, const RouteArgs *route, hipStream_t st) {
-    if (!route) hipLaunchKernelGGL(rinv_kernel<0>, dim3(M), dim3(256), 0, st, x, M, H, eps, rinv, RouteArgs{});
+hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, const RouteArgs *route, const UploadArgs &up, hipStream_t st) {
+    if (route && up.n16) return hipErrorInvalidValue;
+    if (!route) hipLaunchKernelGGL(rinv_kernel<0>, dim3(M + (up.n16 + 255) / 256), dim3(256), 0, st, x, M, H, eps, rinv, RouteArgs{}, up);
     else if (!route_rides(*route)) return hipErrorInvalidValue;
-    else if (route->E <= 128) hipLaunchKernelGGL(rinv_kernel<2>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, x, M, H, eps, rinv, *route);
-    else hipLaunchKernelGGL(rinv_kernel<4>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, x, M, H, eps, rinv, *route);
+    else if (route->E <= 128) hipLaunchKernelGGL(rinv_kernel<2>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, x, M, H, eps, rinv, *route, up);
+    else hipLaunchKernelGGL(rinv_kernel<4>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, x, M, H, eps, rinv, *route, up);
     return hipGetLastError();
 }
 
@@ -2201,6 +2211,12 @@ constexpr int gemm_lesser(int MT) { return MT == 32 ? 16 : MT == 48 ? 32 : MT ==
 template <int MODE, int AT, int MT, bool GROUPED, int NW = 4, int KS = 1, bool SLICED = false>
 __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmArgs a) {
     extern __shared__ uint4 lds[];
+    if constexpr (!GROUPED && (MODE == GEMM_PLAIN || MODE == GEMM_F32)) {
+        if (a.up.n16 && blockIdx.x >= a.columns) {
+            if (blockIdx.y == 0 && blockIdx.z == 0) upload_unit(a.up, (blockIdx.x - a.columns) * (NW * 64) + threadIdx.x);
+            return;
+        }
+    }
     if constexpr (GROUPED && gemm_lesser(MT)) {
         constexpr int less = gemm_lesser(MT), least = gemm_lesser(less);
         const uint32_t ntok = a.tasks[blockIdx.z].npairs;
@@ -2327,6 +2343,12 @@ template <int MODE, int NMT>
 __global__ __launch_bounds__(kSliceWaves * 64, 1) void gemm_kslice_kernel(GemmArgs a) {
     extern __shared__ uint4 lds[];
 #if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (MODE == GEMM_PLAIN) {
+        if (a.up.n16 && blockIdx.x >= a.columns) {
+            if (blockIdx.y == 0) upload_unit(a.up, (blockIdx.x - a.columns) * (kSliceWaves * 64) + threadIdx.x);
+            return;
+        }
+    }
     constexpr int RT = kSliceRows;
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t i = lane & 15, c = lane >> 4;
@@ -2480,19 +2502,20 @@ __global__ __launch_bounds__(kSliceWaves * 64, 1) void gemm_kslice_kernel(GemmAr
 }
 
 template <int MODE, int NMT>
-static hipError_t launch_gemm_kslice(const GemmArgs &a, hipStream_t st) {
+static hipError_t launch_gemm_kslice(GemmArgs a, hipStream_t st) {
     void (*const kernel)(GemmArgs) = gemm_kslice_kernel<MODE, NMT>;
     constexpr size_t ldsb = kslice_lds_bytes(NMT);
     static_assert(ldsb <= 160 * 1024, "LDS of a CU");
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsb);
     if (attr != hipSuccess) return attr;
-    const dim3 grid((a.ntiles + kSliceRows - 1) / kSliceRows, (a.M + NMT * 16 - 1) / (NMT * 16));
+    a.columns = (a.ntiles + kSliceRows - 1) / kSliceRows;
+    const dim3 grid(a.columns + (a.up.n16 ? kUploadWgs : 0), (a.M + NMT * 16 - 1) / (NMT * 16));
     hipLaunchKernelGGL(kernel, grid, dim3(kSliceWaves * 64), ldsb, st, a);
     return hipGetLastError();
 }
 
 template <int MODE, int AT, int MT, bool GROUPED, int NW, int KS, bool SLICED = false>
-static hipError_t launch_gemm_k(const GemmArgs &a, uint32_t ntok, uint32_t gz, hipStream_t st) {
+static hipError_t launch_gemm_k(GemmArgs a, uint32_t ntok, uint32_t gz, hipStream_t st) {
     constexpr size_t ldsb = gemm_lds_bytes(MT, AT, NW, KS);
     static_assert(ldsb <= 160 * 1024, "LDS of a CU");
     if (ldsb > 64 * 1024) {
@@ -2501,7 +2524,8 @@ static hipError_t launch_gemm_k(const GemmArgs &a, uint32_t ntok, uint32_t gz, h
         if (attr != hipSuccess) return attr;
     }
     constexpr uint32_t rows = NW / KS * AT;   // row-tiles of a workgroup
-    dim3 grid((a.ntiles + rows - 1) / rows, (ntok + MT - 1) / MT, gz);
+    a.columns = (a.ntiles + rows - 1) / rows;
+    dim3 grid(a.columns + (a.up.n16 ? kUploadWgs : 0), (ntok + MT - 1) / MT, gz);
     hipLaunchKernelGGL((gemm_w4_kernel<MODE, AT, MT, GROUPED, NW, KS, SLICED>), grid, dim3(NW * 64), ldsb, st, a);
     return hipGetLastError();
 }
@@ -2640,6 +2664,7 @@ static hipError_t launch_gemm_m(const GemmArgs &a, uint32_t ntasks, uint32_t max
 }
 
 hipError_t launch_gemm(int mode, const GemmArgs &a, uint32_t ntasks, uint32_t max_tok, hipStream_t st) {
+    if (a.up.n16 && (ntasks || a.up.n16 > kUploadUnits || (mode != GEMM_PLAIN && mode != GEMM_F32))) return hipErrorInvalidValue;
     // the kernel addresses weights and activations as a uniform base plus 32-bit byte offsets
     if ((uint64_t)a.ntiles * a.tile_u4 * 16u > 0xFFFFFFFFull || (uint64_t)a.M * (a.top_k ? a.top_k : 1u) * a.x_stride * 2u > 0xFFFFFFFFull)
         return hipErrorInvalidValue;
@@ -2705,23 +2730,26 @@ hipError_t launch_h2d_gather(const CopyDesc *descs, uint32_t n, hipStream_t st) 
 // ------------------------------------------------------------------------------------
 // A forward's routing tables, pinned host memory -> workspace, in 16-byte units.  Tens of KB: the time is one round
 // trip over PCIe (3 to 4 us for up to 30 KB, 8 us for 282 KB), and a kernel in the stream needs no hand-over to a copy
-// engine and back (a 16-token step of two MoE layers 186 us by hipMemcpyAsync, 177 us this way).
+// engine and back (a 16-token step of two MoE layers 186 us by hipMemcpyAsync, 177 us this way).  Nothing reads them before
+// the first layer's routing, so they ride, on workgroups of their own, in a launch in front of it: up to 32 KB
+// in the first QKV GEMM (two 16-token steps of two layers 334 -> 327 us), any number in the launch of its RMS factors where there is one
+// (512 tokens: 3.3 us for the factors and 8.3 for the upload before, 9.5 together; in the GEMM's eight workgroups those 282 KB take 13 us longer than the GEMM).  This launch is for the rest.
 // ------------------------------------------------------------------------------------
 // Two runs in one launch: the tables' areas have room for every expert, and what is not in use stays where it is.
-__global__ __launch_bounds__(256) void upload_tables_kernel(const u4_t *src, u4_t *dst, uint32_t first16, uint32_t skip16, uint32_t n16) {
-    uint32_t idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= n16) return;
-    if (idx >= first16) idx += skip16;
-    dst[idx] = __builtin_nontemporal_load(src + idx);
+__global__ __launch_bounds__(256) void upload_tables_kernel(UploadArgs up) {
+    upload_unit(up, blockIdx.x * 256 + threadIdx.x);
 }
 
-hipError_t launch_upload_tables(const void *src, void *dst, uint64_t first, uint64_t second_at, uint64_t second, hipStream_t st) {
-    if (first + second == 0) return hipSuccess;
+bool make_upload(const void *src, void *dst, uint64_t first, uint64_t second_at, uint64_t second, UploadArgs *up) {
     if ((uintptr_t)src % 16 || (uintptr_t)dst % 16 || first % 16 || second_at % 16 || second % 16 || second_at < first || (second_at + second) / 16 > 0x7FFFFFFFull)
-        return hipErrorInvalidValue;
-    const uint32_t n16 = (uint32_t)((first + second) / 16);
-    hipLaunchKernelGGL(upload_tables_kernel, dim3((n16 + 255) / 256), dim3(256), 0, st, static_cast<const u4_t *>(src), static_cast<u4_t *>(dst),
-                       (uint32_t)(first / 16), (uint32_t)((second_at - first) / 16), n16);
+        return false;
+    *up = {static_cast<const uint4 *>(src), static_cast<uint4 *>(dst), (uint32_t)(first / 16), (uint32_t)((second_at - first) / 16), (uint32_t)((first + second) / 16)};
+    return true;
+}
+
+hipError_t launch_upload_tables(const UploadArgs &up, hipStream_t st) {
+    if (up.n16 == 0) return hipSuccess;
+    hipLaunchKernelGGL(upload_tables_kernel, dim3((up.n16 + 255) / 256), dim3(256), 0, st, up);
     return hipGetLastError();
 }
 

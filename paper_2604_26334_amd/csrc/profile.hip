@@ -66,9 +66,9 @@ extern "C" int32_t ps_profile_measure(void *scratch_dev, uint64_t scratch_bytes,
     out->h2d_gbps = 8.0 * (double)kHead / (ms * 1e-3) / 1e9;
 
     // fixed launch cost: a trivial kernel, many launches
-    PS_HIP(launch_rinv(x, 4, 4096, 1e-6f, rinv, nullptr, cs));
+    PS_HIP(launch_rinv(x, 4, 4096, 1e-6f, rinv, nullptr, UploadArgs{}, cs));
     PS_HIP(hipEventRecord(e0, cs));
-    for (int i = 0; i < 50; ++i) PS_HIP(launch_rinv(x, 4, 4096, 1e-6f, rinv, nullptr, cs));
+    for (int i = 0; i < 50; ++i) PS_HIP(launch_rinv(x, 4, 4096, 1e-6f, rinv, nullptr, UploadArgs{}, cs));
     PS_HIP(hipEventRecord(e1, cs));
     PS_HIP(hipEventSynchronize(e1));
     PS_HIP(hipEventElapsedTime(&ms, e0, e1));
@@ -101,7 +101,7 @@ extern "C" int32_t ps_profile_measure(void *scratch_dev, uint64_t scratch_bytes,
         a.W = reinterpret_cast<const uint4 *>(wts); a.ntiles = mg.ntiles; a.total_tiles = mg.ntiles; a.tile_u4 = (uint32_t)(mg.tile_bytes / 16);
         a.nsb = mg.nsb; a.M = T; a.x = x; a.x_stride = 4096; a.x_group = 1; a.rinv = rinv; a.out = y;
         a.out_stride = 8192; a.top_k = 1;
-        PS_HIP(launch_rinv(x, T, 4096, 1e-6f, rinv, nullptr, cs));
+        PS_HIP(launch_rinv(x, T, 4096, 1e-6f, rinv, nullptr, UploadArgs{}, cs));
         // the executor runs two to kGemvMtTokens tokens in the few-token form of the decode kernel
         const bool few = T <= (uint32_t)kGemvMtTokens && mg.nsb % 8 == 0;
         GemvArgs fa{};
@@ -278,7 +278,7 @@ extern "C" int32_t ps_profile_db_measure(ps_profile_db *db, const ps_model_desc 
             a.ntiles = mg.ntiles; a.total_tiles = mg.ntiles; a.tile_u4 = (uint32_t)(mg.tile_bytes / 16);
             a.nsb = mg.nsb; a.M = T; a.x = x; a.x_stride = mt.K; a.x_group = 1; a.rinv = rinv; a.out = y;
             a.out_stride = mt.rows; a.top_k = 1;
-            PS_HIP(launch_rinv(x, T, mt.K, 1e-6f, rinv, nullptr, cs));
+            PS_HIP(launch_rinv(x, T, mt.K, 1e-6f, rinv, nullptr, UploadArgs{}, cs));
             // (two to kGemvMtTokens tokens: the few-token form of the decode kernel, as in the executor)
             const bool few = T <= (uint32_t)kGemvMtTokens && mg.nsb % 8 == 0;
             GemvArgs fa{};

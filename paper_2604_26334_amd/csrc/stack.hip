@@ -95,6 +95,7 @@ struct ps_stack {
     const void *rinv_of = nullptr;            // rows whose RMS factors the last residual epilogue or combine left in the workspace
     const void *ssq_of = nullptr;             // rows whose sums of squares the last residual GEMM left in ssq_buf
     float *ssq_buf = nullptr;
+    ps::UploadArgs upload{};                      // a forward's routing tables that no launch has taken along yet
     const float *ssq_use = nullptr;           // set by a PS_K_RINV op: what the matrices behind it take their RMS factors from
     const void *own_factors = nullptr;        // set by a PS_K_RINV op: rows whose factors the plane sum behind them works out itself
     uint32_t launches = 0;                    // kernels issue_kernel has launched so far, or counted
@@ -279,6 +280,15 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         return a;
     };
 
+    // The routing tables are on their way in front of everything but the first layer's RMS factors and QKV, whose launches take them
+    // along: that of the factors whatever there is, that of a GEMM what it has threads for
+    const bool factors_take = op.info.kernel == PS_K_RINV && op.info.shard0 == 0 && g.has_attn;
+    const bool qkv_takes = op.info.kernel == PS_K_QKV && MP > 1 && !few_token_gemv(p, g.qkv) && st->upload.n16 <= kUploadUnits;
+    if (st->upload.n16 && !factors_take && !qkv_takes) {
+        PS_HIP(launch_upload_tables(st->upload, cs));
+        st->upload.n16 = 0;
+    }
+    auto take_upload = [&] { const UploadArgs up = st->upload; st->upload.n16 = 0; return up; };
     if (op.info.kernel == PS_K_OUT && st->head_rows == 1) {
         // logits of one token: fused RMSNorm + GEMV over its row of the final hidden state
         const Shard &s = p.shards[op.info.shard0];
@@ -321,6 +331,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
     auto run_gemm = [&](int mode, GemmArgs a, const MatGeom &mg) -> int32_t {
         const uint32_t per = gemm_sb_per_part(mg, MP);
         a.eps = m.rms_eps;
+        if (qkv_takes) a.up = take_upload();
         // sums of squares go into an activation buffer that is dead until the next op but one has read them:
         // behind O the rows that down will write, behind down those that were this layer's input (without
         // attention that input is still down's residual, and the buffer of the attention half's output is free)
@@ -390,7 +401,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             if (op.info.shard0 == 0 && g.has_attn && gemm_sb_per_part(g.qkv, MP) && !st->own_rinv_launch) { st->own_factors = rows; return PS_OK; }
             if (factor_runs) { PS_LAUNCH(launch_rinv_runs(rows, M, H, m.rms_eps, rinv, cs)); return PS_OK; }
             const bool ride = riding && op.info.shard0 == 1;
-            PS_LAUNCH(launch_rinv(rows, M, H, m.rms_eps, rinv, ride ? riding : nullptr, cs));
+            PS_LAUNCH(launch_rinv(rows, M, H, m.rms_eps, rinv, ride ? riding : nullptr, factors_take ? take_upload() : UploadArgs{}, cs));
             if (ride) st->routed_layer = l;
             return PS_OK;
         }
@@ -1559,9 +1570,12 @@ static int32_t forward_impl(ps_stack *st, const void *x_in, void *x_out, const f
     }
     // (whole 16-byte units; the tables' areas are padded to 256 bytes, in the staging buffer as in the workspace.  Of the
     // task and pair areas only what is in use: they have room for min(experts, pairs) tasks a layer)
-    PS_HIP(launch_upload_tables(th + from, st->ws_base + p.ws.logits + from, tasks_at + sc.tasks.size() * sizeof(ps::DeviceTask) - from,
-                                pairs_at - from, ps::align_up(sc.pairs.size() * 4, 16), st->compute));
+    if (!make_upload(th + from, st->ws_base + p.ws.logits + from, tasks_at + sc.tasks.size() * sizeof(ps::DeviceTask) - from,
+                     pairs_at - from, ps::align_up(sc.pairs.size() * 4, 16), &st->upload)) {
+        ps::set_error("internal: routing tables are not whole 16-byte units"); return PS_E_STATE;
+    }
     rc = run_schedule(st, sc, static_cast<const __half *>(x_in), static_cast<__half *>(x_out));
+    st->upload = ps::UploadArgs{};      // (issued with the schedule's first kernels, or given up with it)
     // the buffer is free again once the uploads (compute stream) and the gathers (copy stream) are done
     if (has_copies(sc)) {
         PS_HIP(hipStreamWaitEvent(st->compute, st->ev_ready[0], 0));

@@ -299,6 +299,21 @@ def test_experts_of_a_launch_take_tiles_of_their_own(busiest, others):
     _check(cfg, 73, M, _budgets(cfg, M, [1.0]), logits=lg)
 
 
+@pytest.mark.parametrize("E,M,hidden", [(8, 2, 384), (64, 5, 256), (64, 64, 512), (248, 64, 256), (16, 65, 256), (256, 100, 256)])
+def test_routing_tables_ride_in_a_launch_in_front_of_the_routing(E, M, hidden):
+    """The upload of a forward's routing tables rides in the first layer's QKV GEMM (2 to 64 tokens, up to 2048 units of
+    16 bytes; 64 experts and 64 tokens are 2048 of logits alone and more with the tasks), in the launch of its RMS factors (above 64 tokens, any
+    number) or is a launch of its own.  The next forward's tables, other logits, go the same way."""
+    cfg = dict(Hn.small_moe_cfg(2), hidden=hidden, n_experts=E)
+    W = Hn.WeightCache(cfg, 83)
+    xs = [S.activations(83, t, M, hidden) for t in range(3)]
+    lgs = [S.router_logits(83, t, 2, M, E) for t in range(3)]
+    for frac in (1.0, 0.6):
+        ys, _ = Hn.run_gpu(cfg, W, _budgets(cfg, M, [frac])[0], xs, logits=lgs)
+        for x, lg, y in zip(xs, lgs, ys):
+            assert Hn.rel_err(y, O.stack_forward(x, cfg, W, logits=lg, mirror=True)) <= TOL
+
+
 @pytest.mark.parametrize("device_logits", [False, True])
 def test_only_the_routing_tables_in_use_are_uploaded(device_logits):
     """A trip of 40 tokens, then one of a single token through the same plan: the single token's two tasks replace the first
