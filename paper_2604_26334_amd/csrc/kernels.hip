@@ -1038,10 +1038,10 @@ __global__ __launch_bounds__(kAttnWaves * 64, 16 / kAttnWaves) void attn_decode_
 // per SIMD (a third of them the exponentials).  So: rows go from memory straight into LDS, two rounds' worth of stages,
 // the next round on its way while one is multiplied (one barrier per round); two row tiles per wave share every operand
 // read; two waves per SIMD.  What the scores cost is kept to the least: a tile of 16 rows is rescaled (32 multiplications)
-// only in rounds that raise one of its maxima, a round's place in memory goes into the fills' scalar base, and the stage is a
-// compile-time number.  A row's weights are always taken relative to its own running maximum: a rule by which rows wait
-// until some row of the wave has risen by 2^8 is faster (512 tokens 62.5 us against 70), but then a row's fp16 weights, and so
-// its bits, depend on the rows beside it; decided row by row it is 62.5 as well, with other roundings than these.  Rows of one (kv
+// only in rounds in which one of its rows rises by more than 2^8 above the maximum its weights are relative to, a round's place in
+// memory goes into the fills' scalar base, and the stage is a compile-time number.  Each row decides by its own scores (512 tokens 64.8
+// -> 59 us, 64 tokens 15.3 -> 15.0, against a rescaling in every round that raises a maximum): a rule by which the rows of a wave wait for
+// each other is no faster, and a row's fp16 weights, and so its bits, then depend on the rows beside it.  Rows of one (kv
 // head, round) are read by all row blocks: the head is the fastest grid index, so with 8 heads a head's blocks share an XCD's L2.
 // SPLIT: the rounds are dealt out to `nsplit` workgroups per row block (short chunks leave most CUs idle
 // otherwise) and each writes, per row, a record (maximum, weight sum, 128 weighted sums) that
@@ -1054,11 +1054,12 @@ __global__ __launch_bounds__(kAttnWaves * 64, 16 / kAttnWaves) void attn_decode_
 // added at the end.  One wave of each pair has rows, so the MFMAs are fewer than with full tiles, and the time is
 // the fills' and the latencies'.  2 tokens over 4000 positions 8.3 us with the weights in fp16, 8.3 with three parts;
 // 3 tokens over 1000 7.9 / 7.9.
-// Measured, 32 query / 8 kv heads over 4096 cached positions: 512 tokens 73.3 -> 70.0 us by the last three of these, and the
-// launch that appended the rows, 5 us, is gone; 16000 positions 226 -> 212; 64 tokens over 4000 17.5 -> 17.3.  A round takes
-// more than its largest part (row fills alone 45 us, the rest without them 49, both with the 62.5 us rule above), and these did
-// not change that: every operand requested in front of the next round's fills, the next round's scores worked out beside this
-// one's weights (+4 us), steps of 64 positions with three on their way (+6, twice the LDS reads).
+// Measured, 32 query / 8 kv heads over 4096 cached positions: 512 tokens 59 us, over 15000 170; 64 tokens over 4000 15.0 (the launch that
+// appended the rows, 5 us, is part of it).  A round takes more than its largest part (row fills alone 45 us, the rest without
+// them 49), and these did not change that: every operand requested in front of the next round's fills, the next round's scores
+// worked out beside this one's weights (+4 us), steps of 64 positions with three on their way (+6, twice the LDS reads), and four
+// waves of 64 rows each, one per SIMD, with rows of their own and no barrier (fills alone 27 us, the rest 56, both 83: a lone wave
+// waits out every fill instruction's issue).
 // ------------------------------------------------------------------------------------
 constexpr uint32_t kAttnRound = 128;                           // positions per round
 constexpr uint32_t kAttnHalfStage = kAttnRound * 256;           // K or V rows of a round; in LDS: K of two rounds, V of two rounds
@@ -1157,8 +1158,11 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
         for (int kk = 0; kk < 4; ++kk) q[t][kk] = __builtin_bit_cast(h8_t, *reinterpret_cast<const uint4 *>(qr + kk * 32));
     }
     // weights are 2^(c2 s - c2 m) of the raw scores s = q.k: 1 / sqrt(128) and log2(e) in one factor
-    const float c2 = 0.08838834764831845f * 1.4426950408889634f;
+    constexpr float c2 = 0.08838834764831845f * 1.4426950408889634f;
     constexpr float up = FEW ? 32768.f : 1.f;  // weights are held as `up` times what they are
+    // how far a row's scores may rise above the maximum its weights are relative to: 2^8 in its weights, which fp16 holds as exactly
+    // as those below 1 (few rows: not at all, their factor leaves no room)
+    constexpr float slack = FEW ? 0.f : 8.f / c2;
     float m_run[NT], l_run[NT];                // l_run: this lane's positions only
 #pragma unroll
     for (int t = 0; t < NT; ++t) { m_run[t] = -INFINITY; l_run[t] = 0.f; }
@@ -1224,12 +1228,14 @@ __global__ __launch_bounds__(512, 2) void attn_chunk_kernel(AttnChunkArgs a) {
             mx[t] = max3(max3(S[t][0][0], S[t][0][1], S[t][0][2]), max3(S[t][0][3], S[t][1][0], S[t][1][1]), max3(S[t][1][2], S[t][1][3], S[t][1][3]));
             mx[t] = rows4_meet<true>(mx[t]);
         }
-        // Some row of the tile has a new maximum: rescale (the others by 1, so what a row becomes does not depend on its
-        // neighbours).  A row that has seen nothing holds zeros, and the difference of two -inf is not a number.
+        // A row whose weights would pass 2^8 is rescaled to its new maximum, the tile's others by 1: each row by its own scores
+        // alone, so what it becomes does not depend on its neighbours.  A row that has seen nothing holds zeros, and the
+        // difference of two -inf is not a number.
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            if (__any(mx[t] > m_run[t])) {
-                mx[t] = fmaxf(m_run[t], mx[t]);
+            const bool raise = mx[t] > m_run[t] + slack;
+            if (__any(raise)) {
+                mx[t] = raise ? mx[t] : m_run[t];
                 const float resc = m_run[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run[t] - mx[t]) * c2);
                 m_run[t] = mx[t];
                 l_run[t] *= resc;
