@@ -64,6 +64,7 @@ struct GemmArgs {
     float eps;
     const DeviceTask *tasks;
     const int32_t *pairs;
+    uint32_t slices;      // RESID, plans of up to 64 tokens: K in eight slices (o_in_slices)
     // An upload that rides in the launch (ungrouped PLAIN and F32, at most kUploadUnits): kUploadWgs workgroups behind the columns that
     // the grid has without them
     UploadArgs up;

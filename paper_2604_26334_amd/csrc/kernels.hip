@@ -2602,6 +2602,12 @@ static hipError_t launch_gemm_m(const GemmArgs &a, uint32_t ntasks, uint32_t max
         return hipErrorInvalidValue;   // experts: gate/up and the fp32 rows of down
     }
     const uint32_t parts = a.sb_per_part ? (a.nsb + a.sb_per_part - 1) / a.sb_per_part : 1;
+    if constexpr (MODE == GEMM_RESID) {
+        if (max_tok <= 64 && a.slices) {
+            if (a.nsb % 2 || a.nsb < 16 || (a.ntiles + kSliceRows - 1) / kSliceRows * ((a.M + 31) / 32) > 256) return hipErrorInvalidValue;
+            return launch_gemm_kslice<MODE, 2>(a, st);
+        }
+    }
     if (max_tok <= 64) {
         // batched decode: the smallest tile that holds the rows that are there (the tile never changes a bit of the
         // result).  A matrix that goes in one part has its two halves of K on eight waves: gate/up of the 8B shapes, 224

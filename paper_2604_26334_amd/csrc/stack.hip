@@ -96,6 +96,7 @@ struct ps_stack {
     const void *ssq_of = nullptr;             // rows whose sums of squares the last residual GEMM left in ssq_buf
     float *ssq_buf = nullptr;
     ps::UploadArgs upload{};                      // a forward's routing tables that no launch has taken along yet
+    bool ssq_quarters = false;                // four sums a row (launch_splitk_epilogue_resid_quarters) instead of one per 64 columns
     const float *ssq_use = nullptr;           // set by a PS_K_RINV op: what the matrices behind it take their RMS factors from
     const void *own_factors = nullptr;        // set by a PS_K_RINV op: rows whose factors the plane sum behind them works out itself
     uint32_t launches = 0;                    // kernels issue_kernel has launched so far, or counted
@@ -172,6 +173,17 @@ const MatGeom &geom_of(const ModelGeom &g, uint32_t mat) {
 // kernel when the matrix's K is a multiple of 1024 (whole scale groups); it computes its own RMS factors
 static bool few_token_gemv(const ps_plan &p, const MatGeom &mg) {
     return p.M >= 2 && p.M <= (uint32_t)kGemvMtTokens && mg.ntiles && mg.nsb % 8 == 0;
+}
+
+// O of a dense plan of 49 to 64 tokens in eight slices of K instead of planes and a plane sum, where gate/up behind it goes in
+// one launch (which adds the sums of squares up; plane sums and the CPU's share read finished factors or four sums a row).
+// K = 4096, 64 tokens: 13.4 -> 11.0 us, 48: 11.4 -> 10.8; at 33 tokens (10.2 against 10.7), at 16 (8.3 against 11.5) and for longer rows
+// (K = 14336, 64 tokens: 19.5 against 29) the planes are faster.  Plans over a cache are fed in trips whose last is short, where
+// the planes' 32-token tiles win more than this does in the others (three trips of 64, 64 and 22 tokens 546 us in planes, 548.5 in slices).
+static bool o_in_slices(const ps_plan &p) {
+    const ModelGeom &g = p.g;
+    return g.has_attn && !g.moe && !g.kv && p.cpu_bytes == 0 && p.M > 48 && p.M <= 64 && g.m.hidden % 256 == 0 && g.o.nsb % 2 == 0 && g.o.nsb >= 16 && g.o.nsb <= 32 &&
+           (g.o.ntiles + 3) / 4 * 2 <= 256 && !gemm_sb_per_part(g.gate_up, p.M);
 }
 
 // GEMV launch description of a dense matmul op (QKV, O, GATE_UP, DOWN) of one or a few tokens
@@ -328,8 +340,10 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
     const bool factor_runs = MP > 64 && !g.moe && H % 256 == 0, sums_of_squares = factor_runs && !st->own_rinv_launch;
     // batched decode (2..64 tokens) of a narrow matrix: split K over blockIdx.z into fp32 partial
     // planes, then one epilogue kernel sums them in order and applies the mode's epilogue
+    const bool o_slices = o_in_slices(p);
     auto run_gemm = [&](int mode, GemmArgs a, const MatGeom &mg) -> int32_t {
-        const uint32_t per = gemm_sb_per_part(mg, MP);
+        a.slices = o_slices && &mg == &g.o;
+        const uint32_t per = a.slices ? 0u : gemm_sb_per_part(mg, MP);
         a.eps = m.rms_eps;
         if (qkv_takes) a.up = take_upload();
         // sums of squares go into an activation buffer that is dead until the next op but one has read them:
@@ -338,10 +352,11 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         float *const x0 = reinterpret_cast<float *>(WS + p.ws.x0), *const x1 = reinterpret_cast<float *>(WS + p.ws.x1);
         float *const dead = &mg == &g.o ? (l & 1 ? x1 : x0) : g.has_attn ? (l & 1 ? x0 : x1) : reinterpret_cast<float *>(WS + p.ws.h);
         if (!per) {
-            if (mode != GEMM_RESID) { a.ssq_in = st->ssq_use; a.quarters = MP > 64 ? 0u : H; }
-            else if (sums_of_squares) {
+            if (mode != GEMM_RESID) { a.ssq_in = st->ssq_use; a.quarters = st->ssq_quarters ? H : 0u; }
+            else if (sums_of_squares || (a.slices && !st->own_rinv_launch)) {
                 a.ssq_out = dead;
                 st->ssq_buf = a.ssq_out;
+                st->ssq_quarters = false;
                 // (the slabs' launches together cover every column: the CPU takes parts of plans of up to 64 tokens only)
                 st->ssq_of = mg.ntiles * 16 == H ? a.out : nullptr;
             }
@@ -361,6 +376,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // H = 4096: 635 -> 613 us
             PS_LAUNCH(launch_splitk_epilogue_resid_quarters(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out, dead, cs));
             st->ssq_buf = dead;
+            st->ssq_quarters = true;
             st->ssq_of = a.out;
             return PS_OK;
         }
@@ -399,7 +415,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // nobody has left the factors QKV wants, and its planes are summed by a launch of its own: that one works them out
             // (a launch fewer; each of a token's workgroups reads the row again, which 64 tokens do not notice)
             if (op.info.shard0 == 0 && g.has_attn && gemm_sb_per_part(g.qkv, MP) && !st->own_rinv_launch) { st->own_factors = rows; return PS_OK; }
-            if (factor_runs) { PS_LAUNCH(launch_rinv_runs(rows, M, H, m.rms_eps, rinv, cs)); return PS_OK; }
+            if (factor_runs || (o_slices && op.info.shard0 == 1)) { PS_LAUNCH(launch_rinv_runs(rows, M, H, m.rms_eps, rinv, cs)); return PS_OK; }
             const bool ride = riding && op.info.shard0 == 1;
             PS_LAUNCH(launch_rinv(rows, M, H, m.rms_eps, rinv, ride ? riding : nullptr, factors_take ? take_upload() : UploadArgs{}, cs));
             if (ride) st->routed_layer = l;
