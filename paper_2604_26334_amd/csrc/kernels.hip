@@ -1859,7 +1859,7 @@ __device__ __forceinline__ void gemm_w4_body(const GemmArgs &a, uint4 *lds) {   
     // at 2048 tokens, where the matrix kernels run at the card's power limit, no difference.  Runs of all tokens lie side by side; a token's runs in one row, 16 bytes of 64 rows
     // to a request, cost the 256-token tiles 7 us a launch and were slower there than the launch they replace.)
     // the RMS factor of token m0 + thread, from the buffer of factors or from the token's sums of squares (nsb of them: one
-    // per 128 columns of K): requested behind the opening prefetches, whose wait covers it, or, where the accumulators leave
+    // per 128 columns of K, in halves): requested behind the opening prefetches, whose wait covers it, or, where the accumulators leave
     // it no register, after the walk
     constexpr bool FACTORS = !GROUPED && (MODE == GEMM_PLAIN || MODE == GEMM_GATE_UP), FACTORS_LATE = MT > 224;
     static_assert(!FACTORS || MT <= NW * 64, "one token per thread");

@@ -334,7 +334,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         PS_LAUNCH(launch_gemv_mt(mode, ks, a, M, cs));
         return PS_OK;
     }
-    // Many tokens, dense: O and down leave the sums of squares of the rows they store, per 128 columns, and the matrices
+    // Many tokens, dense: O and down leave the sums of squares of the rows they store, per 64 columns, and the matrices
     // behind them take their RMS factors from those (slabs of these matrices are cut at 256 rows); factors that need a
     // launch of their own (the first layer's) are then summed in the same order
     const bool factor_runs = MP > 64 && !g.moe && H % 256 == 0, sums_of_squares = factor_runs && !st->own_rinv_launch;
