@@ -29,7 +29,7 @@ int32_t ps_pack_matrix(const uint16_t *scales, const uint8_t *codes, uint32_t ro
  * matrix is summed from split-K planes and one launch covers it whole, that sum leaves four sums of
  * squares per row, which the matrix behind it adds up (MoE layers and plans with a CPU share: the
  * finished factor); the plane sum of a QKV whose factors nobody has left works them out itself; and
- * in plans of more than 64 tokens O and down (of 49 to 64, O) leave sums of squares per 64 columns (same bits in every
+ * in plans of more than 64 tokens O and down (of 49 to 64, O) leave sums of squares per run of columns (same bits in every
  * case: the test of that claim is what this mode is for). */
 #define PS_DECODE_MODE_OWN_RINV 2
 

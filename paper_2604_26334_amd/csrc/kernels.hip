@@ -798,9 +798,9 @@ __device__ __forceinline__ float sum_of_runs(const float *v, uint32_t n) {
 }
 
 // The same factor with the sum taken the way the GEMM's residual epilogue and the matrices behind it take it (ssq_out /
-// ssq_in of GemmArgs), bit for bit: runs of 128 columns, in each the four 32-column shares of a wave, in each share the
-// four lanes of a token (4 columns of either row-tile).  H a multiple of 128.
-__global__ __launch_bounds__(256) void rinv_runs_kernel(const __half *x, uint32_t H, float eps, float *rinv) {
+// ssq_in of GemmArgs), bit for bit: runs of 128 columns (or of 64), in each the four (two) 32-column shares of a wave, in each share
+// the four lanes of a token (4 columns of either row-tile).  H a multiple of 128.
+__global__ __launch_bounds__(256) void rinv_runs_kernel(const __half *x, uint32_t H, uint32_t halves, float eps, float *rinv) {
     __shared__ float share[kMaxGroups * 8 * 4];      // K <= 16384: 128 runs
     const uint32_t m = blockIdx.x, runs = H / 128, w = (threadIdx.x >> 2) & 3, rg = threadIdx.x & 3;
     const __half *row = x + (size_t)m * H;
@@ -822,23 +822,26 @@ __global__ __launch_bounds__(256) void rinv_runs_kernel(const __half *x, uint32_
     }
     __syncthreads();
     float mine = 0.f;      // run threadIdx.x
-    if (threadIdx.x < runs) {
+    if (halves) {
+        if (threadIdx.x < runs * 2) mine = share[threadIdx.x * 2] + share[threadIdx.x * 2 + 1];
+    } else if (threadIdx.x < runs) {
         const float *r4 = share + threadIdx.x * 4;
         mine = (r4[0] + r4[1]) + (r4[2] + r4[3]);
     }
     __syncthreads();
-    if (threadIdx.x < kMaxGroups * 8) share[threadIdx.x] = mine;
+    share[threadIdx.x] = mine;
     __syncthreads();
     if (threadIdx.x == 0) {
+        const uint32_t n = halves ? runs * 2 : runs;
         double s = 0.;
-        for (uint32_t g = 0; g < runs; g += 16) s += sum_of_runs(share + g, runs - g);
+        for (uint32_t g = 0; g < n; g += 16) s += sum_of_runs(share + g, n - g);
         rinv[m] = rsqrtf((float)s / (float)H + eps);
     }
 }
 
-hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, hipStream_t st) {
-    if (H % 128 || H > kMaxGroups * 1024) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(rinv_runs_kernel, dim3(M), dim3(256), 0, st, x, H, eps, rinv);
+hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, uint32_t run, float eps, float *rinv, hipStream_t st) {
+    if (H % 128 || H > kMaxGroups * 1024 || (run != 128 && run != 64)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(rinv_runs_kernel, dim3(M), dim3(256), 0, st, x, H, (uint32_t)(run == 64), eps, rinv);
     return hipGetLastError();
 }
 
@@ -1644,18 +1647,27 @@ constexpr size_t gemm_lds_bytes(int MT, int AT, int NW, int KS = 1) {
     return (size_t)KS * MT * 256 * (gemm_depth(MT, NW, KS) + 1) + (size_t)NW * 2 * AT * 1024;
 }
 
-// RMS factor of row tok of a launch's input: from the buffer of factors, or from the row's sums of squares (nsb runs of 128
-// columns, each in two halves)
+// Where a row's sum of squares over a run of columns stands: four runs of a row side by side, so a reader of many rows takes four
+// of each by one request of whole lines
+__device__ __forceinline__ size_t ssq_at(uint32_t run, uint32_t tok, uint32_t ntok) { return ((size_t)(run >> 2) * ntok + tok) * 4 + (run & 3); }
+
+// RMS factor of row tok of a launch's input: from the buffer of factors, or from the row's sums of squares, 16 runs at a time.
+// Every workgroup reads all runs of its tokens, so their number and the requests they take are what it costs.  One 8B-shaped layer, us
+// a forward: 130 tokens of a 1024-token plan (32 runs) 146 with four or one run to a request, 151 with 64 half runs, one to a
+// request; 512 tokens of a 512-token plan (64 runs) 241.5 with four, 243.5 with one.
 __device__ __forceinline__ float row_rinv(const GemmArgs &a, uint32_t tok, uint32_t ntok) {
     if (!a.ssq_in) return a.rinv[tok];
     if (a.quarters) return factor_of_quarters(RowQuarters{a.ssq_in, ntok, a.quarters, a.eps}, tok);
     double s = 0.;
-    for (uint32_t g = 0; g < a.nsb; g += 16) {   // (the buffer goes on for 64 nsb floats per token)
-        const float *sq = a.ssq_in + (size_t)(2 * g) * ntok + tok;
+    for (uint32_t g = 0; g < a.ssq_runs; g += 16) {   // (the buffer goes on for 64 nsb floats per token)
+        const float4 *sq = reinterpret_cast<const float4 *>(a.ssq_in) + (size_t)(g / 4) * ntok + tok;
         float v[16];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = sq[(size_t)(2 * e) * ntok] + sq[(size_t)(2 * e + 1) * ntok];
-        s += sum_of_runs(v, a.nsb - g);
+        for (int e = 0; e < 4; ++e) {
+            const float4 q = sq[(size_t)e * ntok];
+            v[4 * e] = q.x; v[4 * e + 1] = q.y; v[4 * e + 2] = q.z; v[4 * e + 3] = q.w;
+        }
+        s += sum_of_runs(v, a.ssq_runs - g);
     }
     return rsqrtf((float)s / (float)(a.nsb * 128) + a.eps);
 }
@@ -1856,10 +1868,10 @@ __device__ __forceinline__ void gemm_w4_body(const GemmArgs &a, uint4 *lds) {   
     for (int d = 1; d < DEPTH; ++d) prefetch(min(sb_begin + d, sb_end - 1), d, sb_begin + d, wr[d], std::false_type{});
     // (A launch of its own for the factors is 4 to 6 us and two dependent-launch gaps for a pass over data the matrix in
     // front had in registers: two layers of 300 tokens at H = 4096 351 -> 339 us, two trips of 512 tokens 1222 -> 1203 us;
-    // at 2048 tokens, where the matrix kernels run at the card's power limit, no difference.  Runs of all tokens lie side by side; a token's runs in one row, 16 bytes of 64 rows
-    // to a request, cost the 256-token tiles 7 us a launch and were slower there than the launch they replace.)
-    // the RMS factor of token m0 + thread, from the buffer of factors or from the token's sums of squares (nsb of them: one
-    // per 128 columns of K, in halves): requested behind the opening prefetches, whose wait covers it, or, where the accumulators leave
+    // at 2048 tokens, where the matrix kernels run at the card's power limit, no difference.  All of a token's runs in one row,
+    // 16 bytes of 64 rows to a request, cost the 256-token tiles 7 us a launch and were slower there than the launch they replace.)
+    // the RMS factor of token m0 + thread, from the buffer of factors or from the token's sums of squares (one per 128
+    // columns of K or per 64): requested behind the opening prefetches, whose wait covers it, or, where the accumulators leave
     // it no register, after the walk
     constexpr bool FACTORS = !GROUPED && (MODE == GEMM_PLAIN || MODE == GEMM_GATE_UP), FACTORS_LATE = MT > 224;
     static_assert(!FACTORS || MT <= NW * 64, "one token per thread");
@@ -2199,9 +2211,13 @@ __device__ __forceinline__ void gemm_w4_body(const GemmArgs &a, uint4 *lds) {   
             const uint32_t run = etid / MT, tk = etid % MT, wrun = blockIdx.x * (NWR / 4) + run;
             if (run < NWR / 4 && m0 + tk < ntok && wrun * 8 < a.ntiles) {
                 const float *r4 = side + run * 4 * MT + tk;
-                float *half = a.ssq_out + (size_t)(a.out_row0 / 64 + wrun * 2) * ntok + m0 + tk;
-                half[0] = r4[0] + r4[MT];
-                half[ntok] = r4[2 * MT] + r4[3 * MT];
+                if constexpr (SLICED) {
+                    float *const halves = a.ssq_out + ssq_at(a.out_row0 / 64 + wrun * 2, m0 + tk, ntok);
+                    halves[0] = r4[0] + r4[MT];
+                    halves[1] = r4[2 * MT] + r4[3 * MT];
+                } else {
+                    a.ssq_out[ssq_at(a.out_row0 / 128 + wrun, m0 + tk, ntok)] = (r4[0] + r4[MT]) + (r4[2 * MT] + r4[3 * MT]);
+                }
             }
         }
     }
@@ -2337,11 +2353,11 @@ __device__ __forceinline__ void kslice_finish(const GemmArgs &a, const f4_t (&ac
             if (rg == 0) side[(n * 2 + pair) * 16 + j] = own;
         }
     }
-    if (MODE == GEMM_RESID && a.ssq_out) {       // 64 columns: half a run
+    if (MODE == GEMM_RESID && a.ssq_out) {       // the workgroup's 64 columns are a run
         __syncthreads();
         const uint32_t n = threadIdx.x >> 4, jj = threadIdx.x & 15, tok = m0 + threadIdx.x;
         if (threadIdx.x < NMT * 16 && tok < M && blockIdx.x * RT < a.ntiles)
-            a.ssq_out[(size_t)(a.out_row0 / 64 + blockIdx.x) * M + tok] = side[n * 32 + jj] + side[n * 32 + 16 + jj];
+            a.ssq_out[ssq_at(a.out_row0 / 64 + blockIdx.x, tok, M)] = side[n * 32 + jj] + side[n * 32 + 16 + jj];
     }
 }
 
@@ -2579,8 +2595,8 @@ static uint32_t gemm_pick_tile(const GemmArgs &a, uint32_t widest) {
 // parts, which then keep the slices' sums apart (SLICED) so that a row's bits do not depend on its company.  That costs them
 // up to 1.2 us a launch (512 tokens: O 24.0 -> 25.2, down 65.8 -> 66.7), against 4 and 15 us gained at 128 tokens; plans that need larger
 // tiles stay with plain K parts.  QKV of 6144 rows, 72 tokens: 16.2 -> 12.9 us, 128: 17.1 -> 15.9, from 160 on as before.
-static bool gemm_k_slices(const GemmArgs &a, uint32_t plan_tokens) {
-    return a.nsb % 2 == 0 && a.nsb >= 16 && (a.total_tiles + 7) / 8 * ((plan_tokens + 63) / 64) <= 256;
+bool gemm_k_slices(uint32_t nsb, uint32_t total_tiles, uint32_t plan_tokens) {
+    return plan_tokens > 64 && nsb % 2 == 0 && nsb >= 16 && (total_tiles + 7) / 8 * ((plan_tokens + 63) / 64) <= 256;
 }
 
 template <int MODE>
@@ -2632,7 +2648,7 @@ static hipError_t launch_gemm_m(const GemmArgs &a, uint32_t ntasks, uint32_t max
         // Plans of more than 64 tokens.  The tile goes by the rows that are there (a.M) and never changes a bit of the
         // result; the K parts do, so they go by the whole matrix and the plan's token count.
         if constexpr (MODE != GEMM_GATE_UP) {
-            if (gemm_k_slices(a, max_tok)) {
+            if (gemm_k_slices(a.nsb, a.total_tiles, max_tok)) {
                 const uint32_t groups = (a.ntiles + kSliceRows - 1) / kSliceRows;
                 auto one_round = [&](uint32_t mt) { return groups * ((a.M + mt - 1) / mt) <= 256; };
                 if (one_round(32)) return launch_gemm_kslice<MODE, 2>(a, st);

@@ -96,7 +96,7 @@ struct ps_stack {
     const void *ssq_of = nullptr;             // rows whose sums of squares the last residual GEMM left in ssq_buf
     float *ssq_buf = nullptr;
     ps::UploadArgs upload{};                      // a forward's routing tables that no launch has taken along yet
-    bool ssq_quarters = false;                // four sums a row (launch_splitk_epilogue_resid_quarters) instead of one per 64 columns
+    uint32_t ssq_runs = 0;                    // sums of squares a row there; 0: four (launch_splitk_epilogue_resid_quarters)
     const float *ssq_use = nullptr;           // set by a PS_K_RINV op: what the matrices behind it take their RMS factors from
     const void *own_factors = nullptr;        // set by a PS_K_RINV op: rows whose factors the plane sum behind them works out itself
     uint32_t launches = 0;                    // kernels issue_kernel has launched so far, or counted
@@ -334,13 +334,14 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         PS_LAUNCH(launch_gemv_mt(mode, ks, a, M, cs));
         return PS_OK;
     }
-    // Many tokens, dense: O and down leave the sums of squares of the rows they store, per 64 columns, and the matrices
+    // Many tokens, dense: O and down leave the sums of squares of the rows they store, per run of columns, and the matrices
     // behind them take their RMS factors from those (slabs of these matrices are cut at 256 rows); factors that need a
     // launch of their own (the first layer's) are then summed in the same order
     const bool factor_runs = MP > 64 && !g.moe && H % 256 == 0, sums_of_squares = factor_runs && !st->own_rinv_launch;
     // batched decode (2..64 tokens) of a narrow matrix: split K over blockIdx.z into fp32 partial
     // planes, then one epilogue kernel sums them in order and applies the mode's epilogue
     const bool o_slices = o_in_slices(p);
+    auto run_columns = [&](const MatGeom &mg) { return gemm_k_slices(mg.nsb, mg.ntiles, MP) || (o_slices && &mg == &g.o) ? 64u : 128u; };
     auto run_gemm = [&](int mode, GemmArgs a, const MatGeom &mg) -> int32_t {
         a.slices = o_slices && &mg == &g.o;
         const uint32_t per = a.slices ? 0u : gemm_sb_per_part(mg, MP);
@@ -352,11 +353,11 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         float *const x0 = reinterpret_cast<float *>(WS + p.ws.x0), *const x1 = reinterpret_cast<float *>(WS + p.ws.x1);
         float *const dead = &mg == &g.o ? (l & 1 ? x1 : x0) : g.has_attn ? (l & 1 ? x0 : x1) : reinterpret_cast<float *>(WS + p.ws.h);
         if (!per) {
-            if (mode != GEMM_RESID) { a.ssq_in = st->ssq_use; a.quarters = st->ssq_quarters ? H : 0u; }
+            if (mode != GEMM_RESID) { a.ssq_in = st->ssq_use; a.ssq_runs = st->ssq_runs; a.quarters = st->ssq_runs ? 0u : H; }
             else if (sums_of_squares || (a.slices && !st->own_rinv_launch)) {
                 a.ssq_out = dead;
                 st->ssq_buf = a.ssq_out;
-                st->ssq_quarters = false;
+                st->ssq_runs = H / run_columns(mg);
                 // (the slabs' launches together cover every column: the CPU takes parts of plans of up to 64 tokens only)
                 st->ssq_of = mg.ntiles * 16 == H ? a.out : nullptr;
             }
@@ -376,7 +377,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // H = 4096: 635 -> 613 us
             PS_LAUNCH(launch_splitk_epilogue_resid_quarters(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out, dead, cs));
             st->ssq_buf = dead;
-            st->ssq_quarters = true;
+            st->ssq_runs = 0;
             st->ssq_of = a.out;
             return PS_OK;
         }
@@ -415,7 +416,10 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // nobody has left the factors QKV wants, and its planes are summed by a launch of its own: that one works them out
             // (a launch fewer; each of a token's workgroups reads the row again, which 64 tokens do not notice)
             if (op.info.shard0 == 0 && g.has_attn && gemm_sb_per_part(g.qkv, MP) && !st->own_rinv_launch) { st->own_factors = rows; return PS_OK; }
-            if (factor_runs || (o_slices && op.info.shard0 == 1)) { PS_LAUNCH(launch_rinv_runs(rows, M, H, m.rms_eps, rinv, cs)); return PS_OK; }
+            if (factor_runs || (o_slices && op.info.shard0 == 1)) {      // (the rows are O's, or down's of the layer before)
+                PS_LAUNCH(launch_rinv_runs(rows, M, H, run_columns(g.has_attn && op.info.shard0 == 1 ? g.o : g.down), m.rms_eps, rinv, cs));
+                return PS_OK;
+            }
             const bool ride = riding && op.info.shard0 == 1;
             PS_LAUNCH(launch_rinv(rows, M, H, m.rms_eps, rinv, ride ? riding : nullptr, factors_take ? take_upload() : UploadArgs{}, cs));
             if (ride) st->routed_layer = l;
