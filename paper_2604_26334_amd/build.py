@@ -37,7 +37,7 @@ CHECKED = "kernels.hip"      # the source whose kernels are checked
 # the remarks do not show)
 NEEDS_LDS = ("gemv_w4_kernel", "attn_decode_kernel", "splitk_epilogue_resid_rinv_kernel",
              "splitk_epilogue_resid_quarters_kernel", "splitk_epilogue_norm_kernel")
-NO_SCRATCH = ("gemm_w4_kernel", "gemm_kslice_kernel", "gemv_w4_kernel", "gemv_mt_kernel", "attn_decode_kernel", "attn_combine_kernel", "attn_chunk_kernel", "attn_combine_chunk_kernel")
+NO_SCRATCH = ("gemm_w4_kernel", "gemm_w4_upload_kernel", "gemm_kslice_kernel", "gemv_w4_kernel", "gemv_mt_kernel", "attn_decode_kernel", "attn_combine_kernel", "attn_chunk_kernel", "attn_combine_chunk_kernel")
 
 
 def _run(cmd):
@@ -154,18 +154,19 @@ def lds_writes_behind_fills(body):
 def check_gemm_isa(path):
     """The invariant behind the GEMM's hand-counted waits, read off the generated code."""
     txt = open(path).read()
-    funcs = re.findall(r"^(_ZN2ps14gemm_w4_kernel\w+):[^\n]*\n(.*?)\n\.Lfunc_end", txt, flags=re.S | re.M)
+    funcs = re.findall(r"^(_ZN2ps(?:14gemm_w4_kernel|21gemm_w4_upload_kernel)\w+):[^\n]*\n(.*?)\n\.Lfunc_end", txt, flags=re.S | re.M)
     if not funcs:
         raise RuntimeError("build check: no gemm_w4_kernel in " + path)
     bad = []
     for mangled, body in funcs:
-        m = re.match(r"_ZN2ps14gemm_w4_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)(?:ELi(\d+))?(?:ELb[01])?EEE", mangled)
-        if not m:
+        m = re.match(r"_ZN2ps14gemm_w4_kernelILi\d+ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)ELi(\d+)ELb[01]EEE", mangled)
+        up = re.match(r"_ZN2ps21gemm_w4_upload_kernelILi(\d+)EEE", mangled)
+        if not m and not up:
             bad.append(mangled + ": unexpected template arguments")
             continue
-        at, mt, nw, ks = int(m.group(2)), int(m.group(3)), int(m.group(5)), int(m.group(6) or 1)
+        at, mt, nw, ks = (int(m.group(k)) for k in (1, 2, 4, 5)) if m else (2, int(up.group(1)), 4, 1)
         # an expert's workgroups may take one of the two tiles below the launch's: three rings in one kernel
-        less = {32: 16, 48: 32, 64: 48, 96: 64, 128: 96} if m.group(4) == "1" else {}
+        less = {32: 16, 48: 32, 64: 48, 96: 64, 128: 96} if m and m.group(3) == "1" else {}
         tiles = [t for t in (mt, less.get(mt), less.get(less.get(mt))) if t]
         counts = [gemm_wait_counts(t, nw, at, ks) for t in tiles]
         found = set()

@@ -66,10 +66,6 @@ struct GemmArgs {
     const DeviceTask *tasks;
     const int32_t *pairs;
     uint32_t slices;      // RESID, plans of up to 64 tokens: K in eight slices (o_in_slices)
-    // An upload that rides in the launch (ungrouped PLAIN and F32, at most kUploadUnits): kUploadWgs workgroups behind the columns that
-    // the grid has without them
-    UploadArgs up;
-    uint32_t columns;     // set by the launch
 };
 constexpr uint32_t kUploadWgs = 8, kUploadUnits = kUploadWgs * 256;     // one unit a thread
 // RMS factors of M rows as what the four waves of launch_rinv would add up: sq[w * M + row], H columns (sq null: no such sums)
@@ -104,6 +100,8 @@ struct RouteArgs {
 uint32_t gemv_ksplit(uint32_t ngroups, uint32_t total_units);
 hipError_t launch_gemv(int mode, uint32_t ksplit, const GemvArgs &a, uint32_t ntasks, const RouteArgs *route, hipStream_t st);
 hipError_t launch_gemm(int mode, const GemmArgs &a, uint32_t ntasks, uint32_t max_tok, hipStream_t st);
+// the same for partial planes (F32, ungrouped) with an upload of at most kUploadUnits riding in it, on kUploadWgs workgroups of its own
+hipError_t launch_gemm_upload(const GemmArgs &a, uint32_t max_tok, const UploadArgs &up, hipStream_t st);
 // Two to kGemvMtTokens tokens of a dense sub-layer whose K is a multiple of 1024 (rows of x x_stride
 // elements apart, rows of out and res out_stride apart): the one-token kernel's launch shape with the dot
 // products on the matrix cores; PLAIN, RESID and GATE_UP, the RMS factors computed from the activations

@@ -775,12 +775,12 @@ __device__ __forceinline__ void upload_unit(const UploadArgs &up, uint32_t unit)
 }
 
 // NR > 0: the workgroups behind the first M route four tokens each (the MoE routing of a layer depends on nothing the
-// layer computes here, and as a launch of its own it costs 4 to 5 us).
+// layer computes here, and as a launch of its own it costs 4 to 5 us).  NR < 0: they take an upload.
 template <int NR>
 __global__ __launch_bounds__(256) void rinv_kernel(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, RouteArgs ra, UploadArgs up) {
     if constexpr (NR > 0) {
         if (blockIdx.x >= M) { route_tokens<NR>(ra, blockIdx.x - M); return; }
-    } else {
+    } else if constexpr (NR < 0) {
         if (blockIdx.x >= M) { upload_unit(up, (blockIdx.x - M) * 256 + threadIdx.x); return; }
     }
     __shared__ float part[4];
@@ -847,7 +847,8 @@ hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, uint32_t ru
 
 hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, const RouteArgs *route, const UploadArgs &up, hipStream_t st) {
     if (route && up.n16) return hipErrorInvalidValue;
-    if (!route) hipLaunchKernelGGL(rinv_kernel<0>, dim3(M + (up.n16 + 255) / 256), dim3(256), 0, st, x, M, H, eps, rinv, RouteArgs{}, up);
+    if (up.n16) hipLaunchKernelGGL(rinv_kernel<-1>, dim3(M + (up.n16 + 255) / 256), dim3(256), 0, st, x, M, H, eps, rinv, RouteArgs{}, up);
+    else if (!route) hipLaunchKernelGGL(rinv_kernel<0>, dim3(M), dim3(256), 0, st, x, M, H, eps, rinv, RouteArgs{}, up);
     else if (!route_rides(*route)) return hipErrorInvalidValue;
     else if (route->E <= 128) hipLaunchKernelGGL(rinv_kernel<2>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, x, M, H, eps, rinv, *route, up);
     else hipLaunchKernelGGL(rinv_kernel<4>, dim3(M + (route->M + 3) / 4), dim3(256), 0, st, x, M, H, eps, rinv, *route, up);
@@ -2233,12 +2234,6 @@ constexpr int gemm_lesser(int MT) { return MT == 32 ? 16 : MT == 48 ? 32 : MT ==
 template <int MODE, int AT, int MT, bool GROUPED, int NW = 4, int KS = 1, bool SLICED = false>
 __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmArgs a) {
     extern __shared__ uint4 lds[];
-    if constexpr (!GROUPED && (MODE == GEMM_PLAIN || MODE == GEMM_F32)) {
-        if (a.up.n16 && blockIdx.x >= a.columns) {
-            if (blockIdx.y == 0 && blockIdx.z == 0) upload_unit(a.up, (blockIdx.x - a.columns) * (NW * 64) + threadIdx.x);
-            return;
-        }
-    }
     if constexpr (GROUPED && gemm_lesser(MT)) {
         constexpr int less = gemm_lesser(MT), least = gemm_lesser(less);
         const uint32_t ntok = a.tasks[blockIdx.z].npairs;
@@ -2248,6 +2243,18 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 2) void gemm_w4_kernel(GemmA
         if (ntok <= less) { gemm_w4_body<MODE, AT, less, GROUPED, NW, KS, SLICED>(a, lds); return; }
     }
     gemm_w4_body<MODE, AT, MT, GROUPED, NW, KS, SLICED>(a, lds);
+}
+
+// Partial planes of up to 64 tokens with an upload behind the grid's columns: a kernel of its own, since the question whether
+// there is an upload costs every launch that asks it 0.4 us (four steps of two 2048-wide layers, 6 tokens: 345 -> 354 us, 48: 404 -> 414).
+template <int MT>
+__global__ __launch_bounds__(256, 2) void gemm_w4_upload_kernel(GemmArgs a, UploadArgs up, uint32_t columns) {
+    extern __shared__ uint4 lds[];
+    if (blockIdx.x >= columns) {
+        if (blockIdx.y == 0 && blockIdx.z == 0) upload_unit(up, (blockIdx.x - columns) * 256 + threadIdx.x);
+        return;
+    }
+    gemm_w4_body<GEMM_F32, 2, MT, false, 4, 1, false>(a, lds);
 }
 
 // ------------------------------------------------------------------------------------
@@ -2365,12 +2372,6 @@ template <int MODE, int NMT>
 __global__ __launch_bounds__(kSliceWaves * 64, 1) void gemm_kslice_kernel(GemmArgs a) {
     extern __shared__ uint4 lds[];
 #if defined(__HIP_DEVICE_COMPILE__)
-    if constexpr (MODE == GEMM_PLAIN) {
-        if (a.up.n16 && blockIdx.x >= a.columns) {
-            if (blockIdx.y == 0) upload_unit(a.up, (blockIdx.x - a.columns) * (kSliceWaves * 64) + threadIdx.x);
-            return;
-        }
-    }
     constexpr int RT = kSliceRows;
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t i = lane & 15, c = lane >> 4;
@@ -2524,20 +2525,19 @@ __global__ __launch_bounds__(kSliceWaves * 64, 1) void gemm_kslice_kernel(GemmAr
 }
 
 template <int MODE, int NMT>
-static hipError_t launch_gemm_kslice(GemmArgs a, hipStream_t st) {
+static hipError_t launch_gemm_kslice(const GemmArgs &a, hipStream_t st) {
     void (*const kernel)(GemmArgs) = gemm_kslice_kernel<MODE, NMT>;
     constexpr size_t ldsb = kslice_lds_bytes(NMT);
     static_assert(ldsb <= 160 * 1024, "LDS of a CU");
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsb);
     if (attr != hipSuccess) return attr;
-    a.columns = (a.ntiles + kSliceRows - 1) / kSliceRows;
-    const dim3 grid(a.columns + (a.up.n16 ? kUploadWgs : 0), (a.M + NMT * 16 - 1) / (NMT * 16));
+    const dim3 grid((a.ntiles + kSliceRows - 1) / kSliceRows, (a.M + NMT * 16 - 1) / (NMT * 16));
     hipLaunchKernelGGL(kernel, grid, dim3(kSliceWaves * 64), ldsb, st, a);
     return hipGetLastError();
 }
 
 template <int MODE, int AT, int MT, bool GROUPED, int NW, int KS, bool SLICED = false>
-static hipError_t launch_gemm_k(GemmArgs a, uint32_t ntok, uint32_t gz, hipStream_t st) {
+static hipError_t launch_gemm_k(const GemmArgs &a, uint32_t ntok, uint32_t gz, hipStream_t st) {
     constexpr size_t ldsb = gemm_lds_bytes(MT, AT, NW, KS);
     static_assert(ldsb <= 160 * 1024, "LDS of a CU");
     if (ldsb > 64 * 1024) {
@@ -2546,8 +2546,7 @@ static hipError_t launch_gemm_k(GemmArgs a, uint32_t ntok, uint32_t gz, hipStrea
         if (attr != hipSuccess) return attr;
     }
     constexpr uint32_t rows = NW / KS * AT;   // row-tiles of a workgroup
-    a.columns = (a.ntiles + rows - 1) / rows;
-    dim3 grid(a.columns + (a.up.n16 ? kUploadWgs : 0), (ntok + MT - 1) / MT, gz);
+    dim3 grid((a.ntiles + rows - 1) / rows, (ntok + MT - 1) / MT, gz);
     hipLaunchKernelGGL((gemm_w4_kernel<MODE, AT, MT, GROUPED, NW, KS, SLICED>), grid, dim3(NW * 64), ldsb, st, a);
     return hipGetLastError();
 }
@@ -2643,8 +2642,8 @@ static hipError_t launch_gemm_m(const GemmArgs &a, uint32_t ntasks, uint32_t max
         if (a.M <= 48) return launch_gemm_k<MODE, 2, 48, false, 4, 1>(a, a.M, parts, st);
         return launch_gemm_k<MODE, 2, 64, false, 4, 1>(a, a.M, parts, st);
     }
-    if constexpr (MODE == GEMM_F32 || MODE == GEMM_GATE_UP) { if (MODE == GEMM_F32) return hipErrorInvalidValue; }   // partial planes: at most 64 tokens
-    if constexpr (MODE != GEMM_F32) {
+    if constexpr (MODE == GEMM_F32) return hipErrorInvalidValue;   // partial planes: at most 64 tokens
+    else {
         // Plans of more than 64 tokens.  The tile goes by the rows that are there (a.M) and never changes a bit of the
         // result; the K parts do, so they go by the whole matrix and the plan's token count.
         if constexpr (MODE != GEMM_GATE_UP) {
@@ -2691,11 +2690,30 @@ static hipError_t launch_gemm_m(const GemmArgs &a, uint32_t ntasks, uint32_t max
     }
 }
 
+template <int MT>
+static hipError_t launch_gemm_upload_t(const GemmArgs &a, const UploadArgs &up, hipStream_t st) {
+    constexpr size_t ldsb = gemm_lds_bytes(MT, 2, 4);
+    static_assert(ldsb <= 64 * 1024, "LDS without an attribute");
+    const uint32_t columns = (a.ntiles + 7) / 8, parts = a.sb_per_part ? (a.nsb + a.sb_per_part - 1) / a.sb_per_part : 1;
+    hipLaunchKernelGGL(gemm_w4_upload_kernel<MT>, dim3(columns + kUploadWgs, (a.M + MT - 1) / MT, parts), dim3(256), ldsb, st, a, up, columns);
+    return hipGetLastError();
+}
+
+// the kernel addresses weights and activations as a uniform base plus 32-bit byte offsets
+static bool gemm_in_reach(const GemmArgs &a) {
+    return (uint64_t)a.ntiles * a.tile_u4 * 16u <= 0xFFFFFFFFull && (uint64_t)a.M * (a.top_k ? a.top_k : 1u) * a.x_stride * 2u <= 0xFFFFFFFFull;
+}
+
+hipError_t launch_gemm_upload(const GemmArgs &a, uint32_t max_tok, const UploadArgs &up, hipStream_t st) {
+    if (up.n16 > kUploadUnits || max_tok > 64 || !gemm_in_reach(a)) return hipErrorInvalidValue;
+    if (a.M <= 16) return launch_gemm_upload_t<16>(a, up, st);
+    if (a.M <= 32) return launch_gemm_upload_t<32>(a, up, st);
+    if (a.M <= 48) return launch_gemm_upload_t<48>(a, up, st);
+    return launch_gemm_upload_t<64>(a, up, st);
+}
+
 hipError_t launch_gemm(int mode, const GemmArgs &a, uint32_t ntasks, uint32_t max_tok, hipStream_t st) {
-    if (a.up.n16 && (ntasks || a.up.n16 > kUploadUnits || (mode != GEMM_PLAIN && mode != GEMM_F32))) return hipErrorInvalidValue;
-    // the kernel addresses weights and activations as a uniform base plus 32-bit byte offsets
-    if ((uint64_t)a.ntiles * a.tile_u4 * 16u > 0xFFFFFFFFull || (uint64_t)a.M * (a.top_k ? a.top_k : 1u) * a.x_stride * 2u > 0xFFFFFFFFull)
-        return hipErrorInvalidValue;
+    if (!gemm_in_reach(a)) return hipErrorInvalidValue;
     switch (mode) {
         case GEMM_PLAIN: return launch_gemm_m<GEMM_PLAIN>(a, ntasks, max_tok, st);
         case GEMM_RESID: return launch_gemm_m<GEMM_RESID>(a, ntasks, max_tok, st);
@@ -2760,7 +2778,7 @@ hipError_t launch_h2d_gather(const CopyDesc *descs, uint32_t n, hipStream_t st) 
 // trip over PCIe (3 to 4 us for up to 30 KB, 8 us for 282 KB), and a kernel in the stream needs no hand-over to a copy
 // engine and back (a 16-token step of two MoE layers 186 us by hipMemcpyAsync, 177 us this way).  Nothing reads them before
 // the first layer's routing, so they ride, on workgroups of their own, in a launch in front of it: up to 32 KB
-// in the first QKV GEMM (two 16-token steps of two layers 334 -> 327 us), any number in the launch of its RMS factors where there is one
+// in the first QKV GEMM where that leaves planes (two 16-token steps of two layers 334 -> 327 us), any number in the launch of its RMS factors where there is one
 // (512 tokens: 3.3 us for the factors and 8.3 for the upload before, 9.5 together; in the GEMM's eight workgroups those 282 KB take 13 us longer than the GEMM).  This launch is for the rest.
 // ------------------------------------------------------------------------------------
 // Two runs in one launch: the tables' areas have room for every expert, and what is not in use stays where it is.

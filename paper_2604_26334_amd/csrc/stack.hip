@@ -293,9 +293,9 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
     };
 
     // The routing tables are on their way in front of everything but the first layer's RMS factors and QKV, whose launches take them
-    // along: that of the factors whatever there is, that of a GEMM what it has threads for
+    // along: that of the factors whatever there is, that of a QKV in planes (whose factors have no launch) what it has threads for
     const bool factors_take = op.info.kernel == PS_K_RINV && op.info.shard0 == 0 && g.has_attn;
-    const bool qkv_takes = op.info.kernel == PS_K_QKV && MP > 1 && !few_token_gemv(p, g.qkv) && st->upload.n16 <= kUploadUnits;
+    const bool qkv_takes = st->upload.n16 && st->upload.n16 <= kUploadUnits && op.info.kernel == PS_K_QKV && !few_token_gemv(p, g.qkv) && gemm_sb_per_part(g.qkv, MP);
     if (st->upload.n16 && !factors_take && !qkv_takes) {
         PS_HIP(launch_upload_tables(st->upload, cs));
         st->upload.n16 = 0;
@@ -346,7 +346,6 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         a.slices = o_slices && &mg == &g.o;
         const uint32_t per = a.slices ? 0u : gemm_sb_per_part(mg, MP);
         a.eps = m.rms_eps;
-        if (qkv_takes) a.up = take_upload();
         // sums of squares go into an activation buffer that is dead until the next op but one has read them:
         // behind O the rows that down will write, behind down those that were this layer's input (without
         // attention that input is still down's residual, and the buffer of the attention half's output is free)
@@ -369,7 +368,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
         const uint32_t ncols = a.ntiles * 16;
         pa.out_f32 = partial; pa.out = nullptr; pa.out_stride = ncols; pa.out_row0 = 0;
         pa.sb_per_part = per; pa.part_stride = MP * ncols;
-        PS_LAUNCH(launch_gemm(GEMM_F32, pa, 0, MP, cs));
+        PS_LAUNCH(qkv_takes ? launch_gemm_upload(pa, MP, take_upload(), cs) : launch_gemm(GEMM_F32, pa, 0, MP, cs));
         const bool whole_rows = mode == GEMM_RESID && ncols == H && a.out_row0 == 0 && a.out_stride == H && !st->own_rinv_launch;
         if (whole_rows && !g.moe && p.cpu_bytes == 0) {
             // four workgroups a token, whose sums of squares the dense matrices behind them add up as launch_rinv would (the

@@ -299,10 +299,10 @@ def test_experts_of_a_launch_take_tiles_of_their_own(busiest, others):
     _check(cfg, 73, M, _budgets(cfg, M, [1.0]), logits=lg)
 
 
-@pytest.mark.parametrize("E,M,hidden", [(8, 2, 384), (64, 5, 256), (64, 64, 512), (248, 64, 256), (16, 65, 256), (256, 100, 256)])
+@pytest.mark.parametrize("E,M,hidden", [(8, 2, 384), (64, 5, 256), (64, 64, 512), (16, 20, 512), (16, 40, 512), (16, 60, 512), (248, 64, 256), (16, 65, 256), (256, 100, 256)])
 def test_routing_tables_ride_in_a_launch_in_front_of_the_routing(E, M, hidden):
     """The upload of a forward's routing tables rides in the first layer's QKV GEMM (2 to 64 tokens, up to 2048 units of
-    16 bytes; 64 experts and 64 tokens are 2048 of logits alone and more with the tasks), in the launch of its RMS factors (above 64 tokens, any
+    16 bytes, in each token tile; 64 experts and 64 tokens are 2048 of logits alone and more with the tasks), in the launch of its RMS factors (above 64 tokens, any
     number) or is a launch of its own.  The next forward's tables, other logits, go the same way."""
     cfg = dict(Hn.small_moe_cfg(2), hidden=hidden, n_experts=E)
     W = Hn.WeightCache(cfg, 83)
