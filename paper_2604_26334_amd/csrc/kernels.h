@@ -129,9 +129,10 @@ hipError_t launch_splitk_epilogue_resid_rinv(const float *partial, uint32_t part
                                              uint32_t H, const __half *res, __half *out, float eps, float *rinv,
                                              const RouteArgs *route, hipStream_t st);
 // the same stores over four times the workgroups, with the sums of squares the factors come from instead of the factors
-// (quarters[w * M + row]; whoever wants a factor adds a row's four): their bits once added up
+// (quarters[w * M + row]; whoever wants a factor adds a row's four): their bits once added up.  slices: eight planes are the slices of a
+// matrix with K in slices, stores and sums of squares (per 64 columns) have the bits of the GEMM's in one launch; H a multiple of 256
 hipError_t launch_splitk_epilogue_resid_quarters(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M, uint32_t H,
-                                                 const __half *res, __half *out, float *quarters, hipStream_t st);
+                                                 const __half *res, __half *out, float *quarters, bool slices, hipStream_t st);
 // Decode attention over a KV cache, one new token.  A cache shard of one kv head is K rows
 // [cap][128] followed by V rows [cap][128], fp16; `nheads` shards lie head_stride bytes apart from
 // kv (kv heads head0 .. head0 + nheads - 1).  Each workgroup covers one kv head x one chunk of 256

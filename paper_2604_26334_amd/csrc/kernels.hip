@@ -789,6 +789,16 @@ __global__ __launch_bounds__(256) void rinv_kernel(const __half *x, uint32_t M, 
     if (threadIdx.x == 0) rinv[m] = f;
 }
 
+// Where a row's sum of squares over a run of columns stands: four runs of a row side by side, so a reader of many rows takes four
+// of each by one request of whole lines
+__device__ __forceinline__ size_t ssq_at(uint32_t run, uint32_t tok, uint32_t ntok) { return ((size_t)(run >> 2) * ntok + tok) * 4 + (run & 3); }
+
+// v of another lane of the row
+template <int CTRL>
+__device__ __forceinline__ float dpp_of(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
+
 // up to 16 runs' sums of squares, in pairs (runs from n on count as zeros)
 __device__ __forceinline__ float sum_of_runs(const float *v, uint32_t n) {
     auto four = [&](uint32_t k) {
@@ -816,8 +826,8 @@ __global__ __launch_bounds__(256) void rinv_runs_kernel(const __half *x, uint32_
             part[t] = fmaf((float)a23.x, (float)a23.x, part[t]); part[t] = fmaf((float)a23.y, (float)a23.y, part[t]);
         }
         float sq = part[0] + part[1];
-        sq += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sq), 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
-        sq += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sq), 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
+        sq += dpp_of<0xB1>(sq);   // quad_perm 1,0,3,2
+        sq += dpp_of<0x4E>(sq);   // quad_perm 2,3,0,1
         if (rg == 0) share[run * 4 + w] = sq;
     }
     __syncthreads();
@@ -1647,10 +1657,6 @@ constexpr int gemm_depth(int MT, int NW = 4, int KS = 1) { return NW / KS == 8 ?
 constexpr size_t gemm_lds_bytes(int MT, int AT, int NW, int KS = 1) {
     return (size_t)KS * MT * 256 * (gemm_depth(MT, NW, KS) + 1) + (size_t)NW * 2 * AT * 1024;
 }
-
-// Where a row's sum of squares over a run of columns stands: four runs of a row side by side, so a reader of many rows takes four
-// of each by one request of whole lines
-__device__ __forceinline__ size_t ssq_at(uint32_t run, uint32_t tok, uint32_t ntok) { return ((size_t)(run >> 2) * ntok + tok) * 4 + (run & 3); }
 
 // RMS factor of row tok of a launch's input: from the buffer of factors, or from the row's sums of squares, 16 runs at a time.
 // Every workgroup reads all runs of its tokens, so their number and the requests they take are what it costs.  One 8B-shaped layer, us
@@ -3013,7 +3019,10 @@ hipError_t launch_splitk_epilogue_resid_rinv(const float *partial, uint32_t part
 // loads that wait for each other, this form 36 KB through each of 256 in one; 64 tokens of 4096 columns from eight planes
 // 4.3 -> 4.0 us in the kernel trace, 5 tokens 4.1 -> 3.4, 2 tokens of 2048 columns 3.4 -> 3.0, 2 of 512 2.7 -> 2.5 (about 2.5
 // are a launch's own), so the form serves 2 tokens and up; four steps of two layers of 64 tokens 635 -> 613 us.
+// SLICES: the planes are the eight K slices of a matrix that gemm_kslice_kernel finishes in one launch for more rows: the same
+// sums in the same order, half of K after half, and the same sums of squares per 64 columns, which are eight lanes' here.
 // ------------------------------------------------------------------------------------
+template <bool SLICES>
 __global__ __launch_bounds__(64) void splitk_epilogue_resid_quarters_kernel(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M,
                                                                             uint32_t H, const __half *res, __half *out, float *quarters) {
     // claimed and left unused: a workgroup that needs LDS is not placed on a CU whose LDS a gather copy holds, where its
@@ -3040,7 +3049,7 @@ __global__ __launch_bounds__(64) void splitk_epilogue_resid_quarters_kernel(cons
 #pragma unroll
         for (uint32_t u = 0; u < 2; ++u) {
             if (q0 + u * 256 >= nq) break;
-            float r[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            float r[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, first[8];     // first: of the first half of K
 #pragma unroll
             for (uint32_t p = 0; p < 8; ++p) {
                 const bool on = p < parts;   // adding +0 leaves a sum that started at +0 unchanged
@@ -3048,6 +3057,14 @@ __global__ __launch_bounds__(64) void splitk_epilogue_resid_quarters_kernel(cons
                 r[2] += on ? a[u][p][0].z : 0.f; r[3] += on ? a[u][p][0].w : 0.f;
                 r[4] += on ? a[u][p][1].x : 0.f; r[5] += on ? a[u][p][1].y : 0.f;
                 r[6] += on ? a[u][p][1].z : 0.f; r[7] += on ? a[u][p][1].w : 0.f;
+                if (SLICES && p == 3) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) { first[e] = r[e]; r[e] = 0.f; }
+                }
+            }
+            if (SLICES) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) r[e] = first[e] + r[e];
             }
             if (res) {
 #pragma unroll
@@ -3062,18 +3079,40 @@ __global__ __launch_bounds__(64) void splitk_epilogue_resid_quarters_kernel(cons
             }
             const uint4 o = uint4{d[0], d[1], d[2], d[3]};
             *reinterpret_cast<uint4 *>(out + (size_t)m * H + (q0 + u * 256) * 8) = o;
-            ss += sumsq8(o);
+            if constexpr (SLICES) {
+                // as four columns each of two row-tiles are added up there: lane and lane ^ 2 hold the same columns of either tile,
+                // lane ^ 1 the tile's other half, the mirrored lane the run's other two tiles
+                const h2_t h[4] = {as_h2(d[0]), as_h2(d[1]), as_h2(d[2]), as_h2(d[3])};
+                float sq[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    float part = 0.f;
+                    part = fmaf((float)h[2 * e].x, (float)h[2 * e].x, part); part = fmaf((float)h[2 * e].y, (float)h[2 * e].y, part);
+                    part = fmaf((float)h[2 * e + 1].x, (float)h[2 * e + 1].x, part); part = fmaf((float)h[2 * e + 1].y, (float)h[2 * e + 1].y, part);
+                    sq[e] = part + dpp_of<0x4E>(part);      // quad_perm 2,3,0,1
+                }
+                float run = sq[0] + sq[1];
+                run += dpp_of<0xB1>(run);                   // quad_perm 1,0,3,2
+                run += dpp_of<0x141>(run);                  // row_half_mirror
+                const uint32_t q = q0 + u * 256;
+                if (q % 8 == 0) quarters[ssq_at(q / 8, m, M)] = run;
+            } else {
+                ss += sumsq8(o);
+            }
         }
     }
-    ss = wave_sum(ss);
-    if (threadIdx.x == 0) quarters[w * M + m] = ss;
+    if constexpr (!SLICES) {
+        ss = wave_sum(ss);
+        if (threadIdx.x == 0) quarters[w * M + m] = ss;
+    }
 }
 
 hipError_t launch_splitk_epilogue_resid_quarters(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M, uint32_t H,
-                                                 const __half *res, __half *out, float *quarters, hipStream_t st) {
+                                                 const __half *res, __half *out, float *quarters, bool slices, hipStream_t st) {
     if (M == 0) return hipSuccess;
-    if (parts == 0 || parts > 8 || H % 8 || part_stride % 4 || !partial || !out || !quarters || M > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(splitk_epilogue_resid_quarters_kernel, dim3(4, M), dim3(64), 0, st, partial, parts, part_stride, M, H, res, out, quarters);
+    if (parts == 0 || parts > 8 || H % 8 || part_stride % 4 || !partial || !out || !quarters || M > 65535 || (slices && (parts != 8 || H % 256))) return hipErrorInvalidValue;
+    if (slices) hipLaunchKernelGGL(splitk_epilogue_resid_quarters_kernel<true>, dim3(4, M), dim3(64), 0, st, partial, parts, part_stride, M, H, res, out, quarters);
+    else hipLaunchKernelGGL(splitk_epilogue_resid_quarters_kernel<false>, dim3(4, M), dim3(64), 0, st, partial, parts, part_stride, M, H, res, out, quarters);
     return hipGetLastError();
 }
 

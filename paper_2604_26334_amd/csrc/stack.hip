@@ -177,14 +177,18 @@ static bool few_token_gemv(const ps_plan &p, const MatGeom &mg) {
 
 // O of a dense plan of 49 to 64 tokens in eight slices of K instead of planes and a plane sum, where gate/up behind it goes in
 // one launch (which adds the sums of squares up; plane sums and the CPU's share read finished factors or four sums a row).
-// K = 4096, 64 tokens: 13.4 -> 11.0 us, 48: 11.4 -> 10.8; at 33 tokens (10.2 against 10.7), at 16 (8.3 against 11.5) and for longer rows
-// (K = 14336, 64 tokens: 19.5 against 29) the planes are faster.  Plans over a cache are fed in trips whose last is short, where
-// the planes' 32-token tiles win more than this does in the others (three trips of 64, 64 and 22 tokens 546 us in planes, 548.5 in slices).
+// K = 4096, 64 tokens: 13.4 -> 11.0 us, 48: 11.4 -> 10.8; for longer rows (K = 14336, 64 tokens: 19.5 against 29) the planes are
+// faster.  So they are for fewer rows (33 tokens: 10.2 against 10.7, 16: 8.3 against 11.5), where a trip through the plan takes
+// them: K divides into eight equal parts, so the planes are the slices, and their sum adds them in the slices' order (two layers
+// in a plan of 64, us a forward: 16 rows 116.6 in four-sum planes, 119.7 in one launch, 117.5 so; 64 + 16 rows 270.4, 270.9, 267.3; 40 and
+// 41 rows alike).  Over a cache the one launch gains nothing in full trips either (two layers, 64 rows over 4000 positions
+// 211.3 -> 212.8 us, 128 401.6 -> 402.8).
 static bool o_in_slices(const ps_plan &p) {
     const ModelGeom &g = p.g;
-    return g.has_attn && !g.moe && !g.kv && p.cpu_bytes == 0 && p.M > 48 && p.M <= 64 && g.m.hidden % 256 == 0 && g.o.nsb % 2 == 0 && g.o.nsb >= 16 && g.o.nsb <= 32 &&
-           (g.o.ntiles + 3) / 4 * 2 <= 256 && !gemm_sb_per_part(g.gate_up, p.M);
+    return g.has_attn && !g.moe && !g.kv && p.cpu_bytes == 0 && p.M > 48 && p.M <= 64 && g.m.hidden % 256 == 0 && g.o.nsb >= 16 && g.o.nsb <= 32 &&
+           gemm_sb_per_part(g.o, p.M) * 8 == g.o.nsb && (g.o.ntiles + 3) / 4 * 2 <= 256 && !gemm_sb_per_part(g.gate_up, p.M);
 }
+constexpr uint32_t kSlicePlaneRows = 40;      // up to this many rows of a trip: planes
 
 // GEMV launch description of a dense matmul op (QKV, O, GATE_UP, DOWN) of one or a few tokens
 bool dense_gemv_args(const ps_stack *st, const Op &op, const __half *x_in, __half *x_out, GemvArgs *out, int *mode,
@@ -343,7 +347,8 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
     const bool o_slices = o_in_slices(p);
     auto run_columns = [&](const MatGeom &mg) { return gemm_k_slices(mg.nsb, mg.ntiles, MP) || (o_slices && &mg == &g.o) ? 64u : 128u; };
     auto run_gemm = [&](int mode, GemmArgs a, const MatGeom &mg) -> int32_t {
-        a.slices = o_slices && &mg == &g.o;
+        const bool in_slices = o_slices && &mg == &g.o;
+        a.slices = in_slices && (M > kSlicePlaneRows || a.ntiles * 16 != H || st->own_rinv_launch);
         const uint32_t per = a.slices ? 0u : gemm_sb_per_part(mg, MP);
         a.eps = m.rms_eps;
         // sums of squares go into an activation buffer that is dead until the next op but one has read them:
@@ -374,9 +379,9 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // four workgroups a token, whose sums of squares the dense matrices behind them add up as launch_rinv would (the
             // experts' launches and the CPU's share read finished factors: below).  Four steps of two layers of 64 tokens at
             // H = 4096: 635 -> 613 us
-            PS_LAUNCH(launch_splitk_epilogue_resid_quarters(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out, dead, cs));
+            PS_LAUNCH(launch_splitk_epilogue_resid_quarters(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out, dead, in_slices, cs));
             st->ssq_buf = dead;
-            st->ssq_runs = 0;
+            st->ssq_runs = in_slices ? H / 64 : 0;
             st->ssq_of = a.out;
             return PS_OK;
         }
@@ -711,7 +716,8 @@ int32_t count_launches(ps_stack *st, uint64_t *launches, uint64_t *bytes) {
     // stand-ins for the caller's rows: nothing is read or written
     const __half *xin = reinterpret_cast<const __half *>(st->ws_base + p.ws.x0);
     __half *xout = reinterpret_cast<__half *>(st->ws_base + p.ws.x1);
-    const uint32_t before = st->launches;
+    const uint32_t before = st->launches, n_valid = st->n_valid;
+    st->n_valid = p.M;
     reset_left(st);
     *bytes = 0;
     st->count_only = true;
@@ -723,6 +729,7 @@ int32_t count_launches(ps_stack *st, uint64_t *launches, uint64_t *bytes) {
         *bytes += op.info.bytes;
     }
     st->count_only = false;
+    st->n_valid = n_valid;
     *launches = st->launches - before;
     st->launches = before;
     reset_left(st);

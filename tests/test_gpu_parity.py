@@ -850,14 +850,15 @@ def test_gemm_tiles_of_every_width_give_the_same_rows(H, I, plan_tokens, counts)
 @pytest.mark.parametrize("H,n_q,n_kv,I,plan_tokens,counts", [
     (4096, 0, 0, 2048, 512, (512, 385, 384, 321, 320, 257, 256, 193, 192, 129, 128, 65, 17, 1)),
     (2048, 16, 4, 2304, 640, (640, 200, 33)), (2176, 17, 1, 2560, 300, (300, 161, 16)), (3072, 24, 24, 2816, 384, (384, 250, 100)),
-    (1024, 20, 5, 6144, 130, (130, 81, 5)), (2048, 16, 4, 2176, 300, (300, 90, 7)), (1024, 9, 3, 2304, 200, (200, 65, 16)), (2048, 16, 4, 14336, 64, (64, 33, 32, 17, 1)), (2048, 16, 8, 14336, 49, (49, 16))])
+    (1024, 20, 5, 6144, 130, (130, 81, 5)), (2048, 16, 4, 2176, 300, (300, 90, 7)), (1024, 9, 3, 2304, 200, (200, 65, 16)), (2048, 16, 4, 14336, 64, (64, 41, 40, 33, 32, 17, 1)),
+    (2048, 24, 8, 14336, 60, (60, 41, 40, 9)), (2048, 16, 8, 14336, 49, (49, 16))])
 def test_matrices_in_eight_k_slices_give_the_same_rows(H, n_q, n_kv, I, plan_tokens, counts):
     """Narrow matrices of 16 and more super-blocks in plans above 64 tokens: K in eight slices, on eight waves in tiles of
     32 to 80 tokens, or walked one after the other by two K parts where the rows are too many for one round of those tiles.
     The full trip against the oracle, every shorter one with the same bits (edges of every tile; slices of 2 and of 2 or 3
     super-blocks; with attention QKV and the gathered input of O as well; O without down and down without O, whose sums of squares are
-    per 128 columns then), and the same bits again where every RMS factor has a launch of its own.  The last two: O alone in a plan of 49 to 64 tokens, in front of a gate/up of one launch (2048
-    wide: with these weights and 14336 columns the oracle's own rows of a 4096-wide layer leave fp16's range)."""
+    per 128 columns then), and the same bits again where every RMS factor has a launch of its own.  The last three: O alone in a plan of 49 to 64 tokens, in front of a gate/up
+    of one launch, by planes that are the slices for up to 40 rows (2048 wide: with these weights and 14336 columns the oracle's own rows of a 4096-wide layer leave fp16's range)."""
     import torch
     from paper_2604_26334_amd import binding as B
     cfg = dict(S.cfg_ffn_block(), hidden=H, ffn_inter=I)
