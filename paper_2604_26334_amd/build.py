@@ -8,10 +8,13 @@ compiler's own output for kernels.hip, and fails if it does not hold:
   - in every gemm_w4_kernel, a vmcnt(0) stands between the opening prefetches and the first barrier; every later stretch
     between two barriers that ends in a counted wait vmcnt(n > 0) issues exactly the loads of one
     prefetch, LDS fills first, and n is the count the kernel's ring depth implies; nothing else
-    touches vector memory inside the ring (a grouped kernel holds the rings of up to three tiles: each is there, each step is one of theirs);
+    touches vector memory inside the ring (a grouped kernel holds the rings of up to three tiles: each is there, told by its opening
+    prefetches, and its steps are checked against its own counts);
   - in every gemm_w4_kernel of two K parts, on every path to a write into LDS (the exchange of the parts' sums, which
     lies over the ring's stages), a vmcnt(0) and then a barrier stand behind the last LDS fill: no wave's fill can
-    land on another wave's sums.
+    land on another wave's sums;
+  - in every gemm_kslice_kernel, on every path: a wave reads a ring slot only once the slot's fill has landed, refills it only
+    once those reads have returned, and meets the first barrier with every fill landed and read.
 """
 import os
 import re
@@ -106,20 +109,26 @@ def gemm_wait_counts(mt, nw, at=2, ks=1):
     return lpi, nfill, land * lpi + (at if early else 0)
 
 
-def lds_writes_behind_fills(body):
-    """LDS writes of a kernel's text that some path reaches while a fill (a load straight into LDS) may still be in flight
-    in this or another wave.  Per path: a fill leaves 2, vmcnt(0) turns 2 into 1 (this wave's have landed), a barrier
-    turns 1 into 0 (everyone's have: all waves run the same steps).  A counted wait changes nothing."""
+def blocks_of(body):
+    """(labels in order, instructions of each) of a kernel's text."""
     blocks, order, cur = {"": []}, [""], ""
     for ln in body.splitlines():
         ln = ln.split(";")[0].strip()
-        m = re.match(r"(\.\w+):$", ln)
+        m = re.match(r"(\.LBB\w+):", ln)
         if m:
             cur = m.group(1)
             blocks[cur] = []
             order.append(cur)
         elif ln and not ln.startswith("."):
             blocks[cur].append(ln)
+    return order, blocks
+
+
+def lds_writes_behind_fills(body):
+    """LDS writes of a kernel's text that some path reaches while a fill (a load straight into LDS) may still be in flight
+    in this or another wave.  Per path: a fill leaves 2, vmcnt(0) turns 2 into 1 (this wave's have landed), a barrier
+    turns 1 into 0 (everyone's have: all waves run the same steps).  A counted wait changes nothing."""
+    order, blocks = blocks_of(body)
     bad, seen, todo = [], {}, [("", 0)]
     while todo:
         name, state = todo.pop()
@@ -151,6 +160,79 @@ def lds_writes_behind_fills(body):
     return sorted(set(bad))
 
 
+def kslice_ring_faults(body, nmt):
+    """The first thing that some path of gemm_kslice_kernel's text up to its first barrier does against the ring of `nmt` slots
+    that each wave keeps (none: empty): four fills to a slot and four reads from it, slot after slot; a read before the slot's fill has landed (loads return in the
+    order of their issue, vmcnt counts those still out), a fill before the reads of what was there have returned, a fill that
+    is out or unread at the barrier.  Where a path goes round the loop, only where the ring stands and what is out counts."""
+    order, blocks = blocks_of(body)
+    cap, seen = 4 * nmt, set()
+    todo = [("", (), 0, 0, False)]    # label, loads out (slot or -1 each), fills issued (mod the ring), fills not read yet, reads out
+    while todo:
+        at = todo.pop()
+        if at in seen:
+            continue
+        seen.add(at)
+        if len(seen) > 10000:
+            return ["more paths than such a walk has"]
+        name, out, nf, unread, reads = at
+        ended = False
+        for ln in blocks[name]:
+            ins = ln.split()[0]
+            if ins.startswith("buffer_load") and re.search(r"\blds\b", ln):
+                if reads:
+                    return ["a fill while reads are out"]
+                if unread >= cap:
+                    return ["a fill of a slot that was not read"]
+                out, nf, unread = out + (nf // 4,), (nf + 1) % cap, unread + 1
+            elif re.match(r"(buffer_|global_|flat_|scratch_)", ins):
+                out += (-1,)
+            elif ins == "s_waitcnt":
+                m = re.search(r"vmcnt\((\d+)\)", ln)
+                if m:
+                    out = out[max(0, len(out) - int(m.group(1))):]
+                if "lgkmcnt(0)" in ln:
+                    reads = False
+            elif ins.startswith("ds_"):
+                if ins != "ds_read_b128" or unread <= 0:
+                    return [ins + " where an operand of a filled slot is read"]
+                elif (nf - unread) % cap // 4 in out:
+                    return ["a read of a slot whose fill may be out"]
+                unread, reads = unread - 1, True
+            elif ins == "s_barrier":
+                if unread or any(x >= 0 for x in out):
+                    return ["a barrier with fills out or unread"]
+                ended = True
+                break
+            elif ins.startswith("s_cbranch"):
+                todo.append((ln.split()[-1], out, nf, unread, reads))
+            elif ins == "s_branch":
+                todo.append((ln.split()[-1], out, nf, unread, reads))
+                ended = True
+                break
+            elif ins == "s_endpgm":
+                return ["an end before the slices meet"]
+            if len(out) > 64:
+                return ["more loads out than vmcnt counts"]
+        if not ended:
+            if order.index(name) + 1 == len(order):
+                return ["no barrier"]
+            todo.append((order[order.index(name) + 1], out, nf, unread, reads))
+    return []
+
+
+def check_kslice_isa(path):
+    """The invariant behind gemm_kslice_kernel's hand-counted waits, read off the generated code."""
+    txt = open(path).read()
+    funcs = re.findall(r"^(_ZN2ps18gemm_kslice_kernelILi\d+ELi(\d+)E\w+):[^\n]*\n(.*?)\n\.Lfunc_end", txt, flags=re.S | re.M)
+    if not funcs:
+        raise RuntimeError("build check: no gemm_kslice_kernel in " + path)
+    bad = [(mangled, kslice_ring_faults(body, int(nmt))) for mangled, nmt, body in funcs]
+    if any(faults for _, faults in bad):
+        raise RuntimeError("build check: rings of K slices:\n  " + "\n  ".join("%s: %s" % (m, ", ".join(f)) for m, f in bad if f))
+    return len(funcs)
+
+
 def check_gemm_isa(path):
     """The invariant behind the GEMM's hand-counted waits, read off the generated code."""
     txt = open(path).read()
@@ -159,17 +241,19 @@ def check_gemm_isa(path):
         raise RuntimeError("build check: no gemm_w4_kernel in " + path)
     bad = []
     for mangled, body in funcs:
-        m = re.match(r"_ZN2ps14gemm_w4_kernelILi\d+ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)ELi(\d+)ELb[01]EEE", mangled)
+        m = re.match(r"_ZN2ps14gemm_w4_kernelILi\d+ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)(?:ELi(\d+))?(?:ELb[01])?EEE", mangled)
         up = re.match(r"_ZN2ps21gemm_w4_upload_kernelILi(\d+)EEE", mangled)
         if not m and not up:
             bad.append(mangled + ": unexpected template arguments")
             continue
-        at, mt, nw, ks = (int(m.group(k)) for k in (1, 2, 4, 5)) if m else (2, int(up.group(1)), 4, 1)
+        at, mt, nw, ks = (int(m.group(k) or 1) for k in (1, 2, 4, 5)) if m else (2, int(up.group(1)), 4, 1)
         # an expert's workgroups may take one of the two tiles below the launch's: three rings in one kernel
         less = {32: 16, 48: 32, 64: 48, 96: 64, 128: 96} if m and m.group(3) == "1" else {}
         tiles = [t for t in (mt, less.get(mt), less.get(less.get(mt))) if t]
-        counts = [gemm_wait_counts(t, nw, at, ks) for t in tiles]
-        found = set()
+        counts = {t: gemm_wait_counts(t, nw, at, ks) for t in tiles}
+        # by its opening prefetches: two with the first's scales (the rings of four waves with counted waits)
+        openings = {2 * counts[t][1] + at: t for t in tiles if len(tiles) > 1 and counts[t][2]}
+        tile, found = (None if len(tiles) > 1 else mt), set()
         segs, cur = [], []
         for ln in body.splitlines():
             f = ln.split()
@@ -194,11 +278,19 @@ def check_gemm_isa(path):
         if 0 not in segs[0][last_load + 1:]:
             bad.append(mangled + ": no vmcnt(0) between the opening prefetches and the first barrier")
         steps = 0
-        for s in segs[1:-1]:
+        for k, s in enumerate(segs[:-1]):
             loads = [x for x in s if isinstance(x, str)]
             waits = [x for x in s if isinstance(x, int)]
             if "lds" not in loads:
                 continue       # not a ring step
+            opening = loads[loads.index("lds"):]
+            if len(tiles) > 1 and waits and waits[-1] == 0 and len(opening) - opening.count("lds") == 2 * at:
+                tile = openings.get(opening.count("lds"))
+                if tile in found or tile is None:
+                    bad.append("%s: opening prefetches of %s" % (mangled, opening))
+                found.add(tile)
+            if k == 0:
+                continue
             steps += 1
             if not waits:
                 bad.append(mangled + ": ring step without a vmcnt wait")
@@ -208,17 +300,16 @@ def check_gemm_isa(path):
             else:
                 # every prefetch: the activation fills, then one code load per tile; one prefetch in eight
                 # starts with a scale fill per tile (a branch: the text holds it either way)
-                nl = sum(1 for x in loads if x == "lds")
-                fits = [t for t, (lpi, nfill, in_flight) in zip(tiles, counts) if waits[-1] == in_flight and nl in (nfill, nfill + at)]
-                found.update(fits)
-                if not fits or loads[:nl] != ["lds"] * nl or len(loads) != nl + at:
-                    bad.append("%s: a counted ring step issues %s and waits for vmcnt(%d), expected (%d +) LDS fills then %d weight loads and a wait by %s" % (
-                        mangled, loads, waits[-1], at, at, counts))
+                nl = loads.count("lds")
+                lpi, nfill, in_flight = counts.get(tile, (0, 0, 0))
+                if waits[-1] != in_flight or nl not in (nfill, nfill + at) or loads[:nl] != ["lds"] * nl or len(loads) != nl + at:
+                    bad.append("%s: a counted ring step of the %s-token ring issues %s and waits for vmcnt(%d), expected %d (+ %d) LDS fills, %d weight loads and vmcnt(%d)" % (
+                        mangled, tile, loads, waits[-1], nfill, at, at, in_flight))
                 if any(not x.startswith("buffer_load") for x in loads if x != "lds"):
                     bad.append(mangled + ": a ring step touches vector memory with something other than its prefetch")
         if steps == 0:
             bad.append(mangled + ": no ring step recognised")
-        missing = [t for t, c in zip(tiles, counts) if c[2] and t not in found] if len(tiles) > 1 else []
+        missing = [t for t in tiles if counts[t][2] and t not in found] if len(tiles) > 1 else []
         if missing:
             bad.append("%s: no counted ring step of the tiles %s" % (mangled, missing))
         if ks == 2:
@@ -235,7 +326,7 @@ def build():
     with ThreadPoolExecutor(max_workers=6) as ex:
         isa = ex.submit(_isa, CHECKED)
         objs = list(ex.map(_compile, SOURCES))
-        n = check_gemm_isa(isa.result())
+        n = check_gemm_isa(isa.result()) + check_kslice_isa(isa.result())
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

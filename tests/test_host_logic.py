@@ -918,3 +918,75 @@ def test_build_check_of_the_exchange_between_two_k_parts(tmp_path, behind, ok):
     else:
         with pytest.raises(RuntimeError, match="possibly in flight"):
             Bd.check_gemm_isa(str(p))
+
+
+def _grouped_isa(step16_wait=3, open32=6, omit=False):
+    """Text of a grouped kernel of 48-token tiles: rings of 48, 32 and 16 tokens, each with two opening prefetches."""
+    lds, w4 = "\tbuffer_load_dwordx4 v1, s[4:7], 0 offen lds\n", "\tbuffer_load_dwordx4 v[2:5], v1, s[4:7], 0 offen\n"
+    body = ""
+    for fills, opening, wait in ((3, 8, 5), (2, open32, 4), (1, 4, step16_wait)):
+        if omit and fills == 2:
+            continue
+        body += lds * (opening - fills) + w4 * 2 + lds * fills + w4 * 2 + "\ts_waitcnt vmcnt(0)\n\ts_barrier\n"
+        body += (lds * (fills + 2) + w4 * 2 + "\ts_waitcnt vmcnt(%d) lgkmcnt(0)\n\ts_barrier\n" % wait) * 2
+        body += "\tglobal_store_dword v[8:9], v7, off\n"
+    return "_ZN2ps14gemm_w4_kernelILi2ELi2ELi48ELb1ELi4ELi1ELb0EEEvNS_8GemmArgsE: ; @x\n" + body + "\ts_endpgm\n.Lfunc_end0:\n"
+
+
+@pytest.mark.parametrize("planted,ok", [({}, True), (dict(step16_wait=5), False), (dict(step16_wait=4), False), (dict(open32=7), False), (dict(omit=True), False)])
+def test_build_check_of_each_ring_of_a_grouped_gemm(tmp_path, planted, ok):
+    """A grouped kernel holds one ring per token tile: a step is held against its own ring's counts.  A 16-token step with
+    scales has as many fills as a 48-token one without, so with that ring's wait it would fit some tile, and still wait too little."""
+    from paper_2604_26334_amd import build as Bd
+    assert [Bd.gemm_wait_counts(t, 4) for t in (16, 32, 48)] == [(3, 1, 3), (4, 2, 4), (5, 3, 5)]
+    p = tmp_path / "k.s"
+    p.write_text(_grouped_isa(**planted))
+    if ok:
+        assert Bd.check_gemm_isa(str(p)) == 1
+    else:
+        with pytest.raises(RuntimeError):
+            Bd.check_gemm_isa(str(p))
+
+
+def _sliced_isa(nmt, change=None):
+    """Text of a walk over a ring of nmt slots: opening fills and weights, a loop over super-blocks, the last two."""
+    fill, w4 = "\tbuffer_load_dwordx4 v1, s[4:7], 0 offen lds\n", "\tbuffer_load_dwordx4 v[2:5], v1, s[4:7], 0 offen\n"
+    read, back = "\tds_read_b128 v[2:5], v1\n", "\ts_waitcnt lgkmcnt(0)\n"
+    wait = lambda n: "\ts_waitcnt vmcnt(%d)\n" % n   # noqa: E731
+    t = dict(first=wait(0), step=[(nmt - 1) * 4 + 4] * (nmt - 1), turn=(nmt - 1) * 4, last=[(nmt - 2 - n) * 4 for n in range(nmt - 1)],
+             back=back, fills=4, behind=w4 * 4, end="")
+    t.update(change or {})
+    step = "".join(t["back"] + fill * t["fills"] + wait(t["step"][n] if n < nmt - 1 else t["turn"]) + read * 4 for n in range(nmt))
+    text = (w4 * 8 + fill * (4 * nmt) + w4 * 4 + t["first"] + read * 4 + "\ts_cbranch_vccnz .LBB0_3\n.LBB0_1: ; two or more to go\n" + step +
+            "\ts_cbranch_scc1 .LBB0_2\n" + w4 * 4 + ".LBB0_2:\n" + t["behind"] + "\ts_cbranch_scc0 .LBB0_1\n.LBB0_3: ; the last but one\n" + step)
+    for n in range(nmt - 1):
+        text += back + wait(t["last"][n]) + read * 4
+    return ("_ZN2ps18gemm_kslice_kernelILi1ELi%dEEEvNS_8GemmArgsE: ; @x\n" % nmt + text + t["end"] + back +
+            "\ts_barrier\n\tds_write_b128 v1, v[2:5]\n\ts_barrier\n\ts_endpgm\n.Lfunc_end0:\n")
+
+
+@pytest.mark.parametrize("nmt", [2, 3, 4, 5])
+@pytest.mark.parametrize("planted,fault", [
+    ({}, None), (dict(behind=""), "may be out"), (dict(turn=1), "may be out"), (dict(first=1), "may be out"), (dict(last=1), "may be out"), (dict(back=""), "reads are out"),
+    (dict(fills=3), "."), (dict(end="fill"), "fills out"), (dict(end="read"), "filled slot")])
+def test_build_check_of_the_rings_of_k_slices(tmp_path, nmt, planted, fault):
+    """gemm_kslice_kernel has no barrier around its rings, only counts: the build refuses text in which some path reads a slot
+    whose fill may be out (a load fewer behind it than the wait counts on, or a wait too weak), refills one before its reads are
+    back, or meets the other waves with a fill out."""
+    from paper_2604_26334_amd import build as Bd
+    change = dict(planted)
+    for key in ("turn", "first", "last"):
+        if key in change:
+            change[key] = {"turn": (nmt - 1) * 4 + 1, "first": "\ts_waitcnt vmcnt(%d)\n" % ((nmt - 1) * 4 + 5),
+                           "last": [(nmt - 2 - n) * 4 + 1 for n in range(nmt - 1)]}[key]
+    if "end" in change:
+        change["end"] = {"fill": "\ts_waitcnt lgkmcnt(0)\n\tbuffer_load_dwordx4 v1, s[4:7], 0 offen lds\n", "read": "\tds_read_b128 v[2:5], v1\n"}[change["end"]]
+    if change.get("behind") == "":      # the wait counts on weights that are not there
+        change["behind"] = "\tv_nop\n"
+    p = tmp_path / "k.s"
+    p.write_text(_sliced_isa(nmt, change))
+    if fault is None:
+        assert Bd.check_kslice_isa(str(p)) == 1
+    else:
+        with pytest.raises(RuntimeError, match=fault):
+            Bd.check_kslice_isa(str(p))
