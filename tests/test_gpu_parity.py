@@ -886,6 +886,87 @@ def test_matrices_in_eight_k_slices_give_the_same_rows(H, n_q, n_kv, I, plan_tok
     st.close()
 
 
+def _sliced_stack(cfg, W, budget, plan_tokens):
+    from paper_2604_26334_amd import binding as B
+    plan = B.Plan(cfg, budget, plan_tokens)
+    st = B.Stack(plan)
+    for layer in range(cfg["n_layers"]):
+        for k, ex, N, K in S.matrix_shapes(cfg):
+            st.load_matrix(layer, k, ex, *W(layer, k, ex))
+    return plan, st
+
+
+def _sliced_cfg(H, n_q, n_kv, I, layers):
+    cfg = dict(S.cfg_ffn_block(), hidden=H, ffn_inter=I, n_layers=layers)
+    if n_q:
+        cfg.update(n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, no_attn=False, no_residual=False)
+    return cfg
+
+
+@pytest.mark.parametrize("H,n_q,n_kv,I,layers,plan_tokens,counts,cut", [
+    (4096, 0, 0, 2048, 1, 512, (512, 321, 100), "D"), (2048, 16, 4, 2304, 2, 640, (640, 130), "QOD"), (2176, 17, 1, 2560, 2, 300, (300, 33), "QOD"),
+    (3072, 24, 24, 2816, 2, 384, (384, 250), "OD"), (2048, 16, 4, 14336, 1, 64, (64, 20), "O")])
+def test_matrices_in_k_slices_cut_into_slabs(H, n_q, n_kv, I, layers, plan_tokens, counts, cut):
+    """A streamed placement cuts these matrices into slabs, which take kernels of their own (a whole matrix two K parts, its slabs
+    tiles of eight slices; O's planes for a short trip only whole): the bits are those of the pinned placement, for full and
+    short trips, also where every RMS factor has a launch of its own.  Slabs of 256 rows and more, of any 16 at H = 2176."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = _sliced_cfg(H, n_q, n_kv, I, layers)
+    W = Hn.WeightCache(cfg, 73)
+    x = S.activations(73, 0, plan_tokens, H)
+    whole = {B.PS_SHARD_QKV: (n_q + 2 * n_kv) * 8, B.PS_SHARD_O: H // 16, B.PS_SHARD_DOWN: H // 16}
+    seen, want = set(), {}
+    for budget in _budgets(cfg, plan_tokens, [1.0, 0.5, 0.15]):
+        plan, st = _sliced_stack(cfg, W, budget, plan_tokens)
+        seen |= {s.kind for s in plan.shards() if s.kind in whole and s.ntiles < whole[s.kind]}
+        xin = torch.from_numpy(x).to(st.device)
+        for mode in (0, 2):
+            st.set_decode_mode(mode)
+            for n in counts:
+                xout = torch.full_like(xin, 7.0)
+                B.chunked_forward(st, xin[:n], xout[:n])
+                st.synchronize()
+                got = xout.cpu().numpy()
+                assert (got[n:] == 7.0).all()
+                if n not in want:
+                    want[n] = got[:n].view(np.uint16)
+                np.testing.assert_array_equal(got[:n].view(np.uint16), want[n])
+        st.close()
+        plan.close()
+    assert {dict(Q=B.PS_SHARD_QKV, O=B.PS_SHARD_O, D=B.PS_SHARD_DOWN)[c] for c in cut} <= seen
+    assert Hn.rel_err(want[counts[0]].view(np.float16), O.stack_forward(x, cfg, W, mirror=True)) <= TOL
+
+
+@pytest.mark.parametrize("H,n_q,n_kv,I,plan_tokens,counts", [(4096, 0, 0, 2048, 512, (512, 320, 67)), (2048, 16, 4, 2304, 300, (300, 41)), (2048, 16, 4, 14336, 64, (64, 23))])
+def test_infinities_and_nans_of_a_row_stay_in_it_through_the_k_slices(H, n_q, n_kv, I, plan_tokens, counts):
+    """A row with an infinity (its RMS factor is 0, and 0 times infinity no number) or a NaN comes out as NaN, also as the last row
+    of a trip, behind which a tile's fills find nothing; every other row keeps its bits."""
+    import torch
+    from paper_2604_26334_amd import binding as B
+    cfg = _sliced_cfg(H, n_q, n_kv, I, 1)
+    W = Hn.WeightCache(cfg, 79)
+    x = S.activations(79, 0, plan_tokens, H)
+    plan, st = _sliced_stack(cfg, W, 1 << 30, plan_tokens)
+    for n in counts:
+        ys = []
+        for bad in ((), (5, n - 1)):
+            xs = x[:n].copy()
+            for i, row in enumerate(bad):
+                xs[row, 1 + 130 * i] = (np.inf, np.nan)[i]
+            xin = torch.from_numpy(xs).to(st.device)
+            xout = torch.full_like(xin, 7.0)
+            B.chunked_forward(st, xin, xout)
+            st.synchronize()
+            ys.append(xout.cpu().numpy())
+        assert np.isfinite(ys[0].astype(np.float32)).all()
+        assert np.isnan(ys[1][[5, n - 1]]).all()
+        ok = np.setdiff1d(np.arange(n), [5, n - 1])
+        np.testing.assert_array_equal(ys[1][ok].view(np.uint16), ys[0][ok].view(np.uint16))
+    st.close()
+    plan.close()
+
+
 @pytest.mark.parametrize("H,attn,I,tokens", [(256, True, 512, 65), (768, True, 1280, 300), (2304, True, 768, 129),
                                              (4352, False, 256, 200), (256, False, 7168, 1024), (640, True, 768, 100)])
 def test_rms_factors_from_the_sums_of_squares_of_o_and_down(H, attn, I, tokens):
