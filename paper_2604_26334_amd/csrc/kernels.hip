@@ -3,7 +3,7 @@
 // the expert combine, and attention over the KV cache.  Weight layout: see pack.cpp.  wave64 only.
 //   matmuls by token count:  1 -> gemv_w4_kernel,  2..4 -> gemv_mt_kernel (whole scale groups),
 //                            otherwise gemm_w4_kernel (+ splitk_epilogue* when K is split), or gemm_kslice_kernel
-//                            (narrow matrices, more than 64 tokens)
+//                            (narrow matrices, more than 64 tokens; O from 49 tokens)
 //   attention:  one query token -> attn_decode_kernel + attn_combine_kernel,
 //               a chunk of query tokens -> attn_chunk_kernel, one walk over the cache and the chunk's own
 //               rows; for a short chunk the walk is dealt out to several workgroups, whose records
@@ -471,8 +471,9 @@ __global__ __launch_bounds__(NW * 64, 4) void gemv_w4_kernel(GemvArgs a, uint32_
 
 // Few units of one or two waves: a workgroup each, so that every unit's weights come through a CU of their own instead of
 // four units' through one (K = 1024, 176 gate/up units 4.3 -> 3.9 us; K = 512, QKV 64 units 3.3 -> 2.9, O 32 3.0 -> 2.75, gate/up 88
-// 3.7 -> 3.2; K = 2048, O 128 units 4.1 -> 3.8).  Beyond one unit per CU the larger workgroups are faster (K = 2048, 352 gate/up
-// units 5.3 -> 6.2).
+// 3.7 -> 3.2; K = 2048, O 128 units 4.1 -> 3.8).  Such steps are bound by the host where they are issued launch by launch, so it
+// shows where they are replayed (three layers of K = 512 and a head, two steps 160.0 -> 153.1 us).  Beyond one unit per CU the
+// larger workgroups are faster (K = 2048, 352 gate/up units 5.3 -> 6.2).
 static bool gemv_unit_per_cu(uint32_t nunits, uint32_t ks, uint32_t ntasks) { return ks <= 2 && !ntasks && nunits <= 256; }
 
 template <int MODE, bool FULLG, bool ROUTE = false>
@@ -1661,7 +1662,9 @@ constexpr size_t gemm_lds_bytes(int MT, int AT, int NW, int KS = 1) {
 // RMS factor of row tok of a launch's input: from the buffer of factors, or from the row's sums of squares, 16 runs at a time.
 // Every workgroup reads all runs of its tokens, so their number and the requests they take are what it costs.  One 8B-shaped layer, us
 // a forward: 130 tokens of a 1024-token plan (32 runs) 146 with four or one run to a request, 151 with 64 half runs, one to a
-// request; 512 tokens of a 512-token plan (64 runs) 241.5 with four, 243.5 with one.
+// request; 512 tokens of a 512-token plan (64 runs) 241.5 with four, 243.5 with one.  Tried without gain: 32 runs to a round trip;
+// whole runs where a sliced matrix is walked by two K parts, i.e. a second form of the loads (two layers, 330 tokens of a
+// 512-token plan 390 -> 388.5 us, but 200 tokens 296 -> 303).
 __device__ __forceinline__ float row_rinv(const GemmArgs &a, uint32_t tok, uint32_t ntok) {
     if (!a.ssq_in) return a.rinv[tok];
     if (a.quarters) return factor_of_quarters(RowQuarters{a.ssq_in, ntok, a.quarters, a.eps}, tok);
@@ -2264,7 +2267,8 @@ __global__ __launch_bounds__(256, 2) void gemm_w4_upload_kernel(GemmArgs a, Uplo
 }
 
 // ------------------------------------------------------------------------------------
-// GEMM of a narrow matrix with K in eight slices, one to a wave (O, down and small QKV of plans above 64 tokens).
+// GEMM of a narrow matrix with K in eight slices, one to a wave (O, down and small QKV of plans above 64 tokens, O of some
+// plans of 49 to 64).
 //
 // Such a matrix has to be cut into small tiles to give every CU one, and what a small tile of gemm_w4_kernel pays for is
 // not its MFMAs: 128 rows x 48 tokens dequantise every weight seven times for 300 tokens and read each operand from LDS for
@@ -2272,11 +2276,12 @@ __global__ __launch_bounds__(256, 2) void gemm_w4_upload_kernel(GemmArgs a, Uplo
 // its own eighth of K: a weight is dequantised once per 80 tokens instead of 48, an operand read serves four
 // products, and no wave ever waits for another before the sums meet at the end: a wave's activations go through a ring of
 // LDS slots of its own (one slot: a token tile's super-block), filled a whole super-block ahead, and all waits are counts.
-// What bounds it: the fills.  2.2 MB a CU for 300 tokens x 14336, of which loads alone take 47 us (L2 to LDS runs at 68 to 100
-// KB a microsecond and CU), everything but the loads 40, together 52; a round of workgroups has about 8 us of its own (launch,
-// first loads, the exchange), so two rounds lose to the two-K-part tiles.  4096 columns, us, against those: O (K = 4096) 72 tokens 16.3 ->
-// 11.6, 128: 16.6 -> 12.4, 192: 17.0 -> 13.6, 256: 18.8 -> 16.3, 300: 20.3 -> 19.2; down (K = 14336) 45.3 -> 29.5, 45.5 -> 31.5, 46 -> 38,
-// 50.5 -> 44.8, 55.6 -> 51.7; 2048 columns, 512 tokens, K = 5632: 22.9 -> 20.8.
+// What bounds it: the fills.  300 tokens x 14336: 80 tokens' activations, 2.3 MB, and 0.5 MB of weights a CU, of which loads alone take 47
+// us, everything but the loads 40, together 52.  Some 8 us of a round are its own (launch, first loads, the exchange), so the
+// loads run at about 72 KB a microsecond and CU, where L2 to LDS alone reaches 68 to 100 by the shape of the requests; and two
+// rounds lose to the two-K-part tiles.  4096 columns, us, against those, plans of as many tokens: O (K = 4096) 72 tokens 15.4 ->
+// 11.3, 128: 15.8 -> 11.8, 192: 16.4 -> 13.5, 256: 17.4 -> 15.4, 300: 20.0 -> 19.1; down (K = 14336) 42.5 -> 28.0, 43 -> 29.5,
+// 44.6 -> 38.0, 47.5 -> 43.9, 53.3 -> 51.6; 2048 columns, 200 tokens: O 9.9 -> 7.5, down (K = 5632) 19.4 -> 13.8, 512: 10.8 -> 10.1, 21.0 -> 20.2.
 // Tried without gain: 128 rows with the slices in pairs on waves that share their fills (512 tokens 66 -> 75 us).
 // ------------------------------------------------------------------------------------
 constexpr int kSliceRows = 4;     // row-tiles of a workgroup
@@ -2597,9 +2602,13 @@ static uint32_t gemm_pick_tile(const GemmArgs &a, uint32_t widest) {
 // K in eight slices: for matrices of at least 16 super-blocks whose plan goes in one round of 64-token tiles of 128 rows.  Which of the
 // kernels walks them goes by the rows that are there: gemm_kslice_kernel where its 64-row tiles of up to 80 tokens
 // go in one round (a second round costs it more than it gains: 512 tokens of 4096 columns, O 24 -> 31 us, down 66 -> 87), else the two K
-// parts, which then keep the slices' sums apart (SLICED) so that a row's bits do not depend on its company.  That costs them
-// up to 1.2 us a launch (512 tokens: O 24.0 -> 25.2, down 65.8 -> 66.7), against 4 and 15 us gained at 128 tokens; plans that need larger
-// tiles stay with plain K parts.  QKV of 6144 rows, 72 tokens: 16.2 -> 12.9 us, 128: 17.1 -> 15.9, from 160 on as before.
+// parts, which then keep the slices' sums apart (SLICED) so that a row's bits do not depend on its company.  That costs them up to
+// 1 us a launch (512 tokens: O 23.6 -> 24.3, down 67.8 -> 68.4; three additions of the accumulators and their zeroes, which no MFMA covers), against 4
+// and 14 us gained at 128 tokens; plans that need larger tiles stay with plain K parts.  QKV of 6144 rows, 72 tokens: 15.9 -> 13.0 us, 128:
+// 16.5 -> 15.7; 192 to 320, in two K parts, 0.8 slower.  Two layers, us a forward, against plain K parts in all plans: 4096 wide, plan of
+// 512, 200 tokens 292 -> 288, 300: 335 -> 334, 384: 379 -> 387, 512: 463 -> 468 (as one layer, 70: 128 -> 109); 2048 wide, plan of 512, 70: 129 -> 109, 200:
+// 138 -> 123, 300: 150 -> 142, 400: 156 -> 156, 512: 173 -> 172, plan of 1024, 500: 174 -> 173, 700: 193 -> 199, 1024: 255 -> 257.  So the
+// rule gives up to 2 % of the long trips of such a plan for up to 15 % of its short ones.
 bool gemm_k_slices(uint32_t nsb, uint32_t total_tiles, uint32_t plan_tokens) {
     return plan_tokens > 64 && nsb % 2 == 0 && nsb >= 16 && (total_tiles + 7) / 8 * ((plan_tokens + 63) / 64) <= 256;
 }
