@@ -56,8 +56,9 @@ struct GemmArgs {
     uint32_t sb_per_part;  // split-K: super-blocks per blockIdx.z part (0 = whole K in one part)
     uint32_t part_stride;  // split-K: elements between the fp32 partial planes
     // Sums of squares instead of a buffer of RMS factors (plans of more than 64 tokens): RESID leaves, per token and run of 128
-    // output columns (of 64 where K goes in slices: gemm_k_slices), the sum of squares of what it stored, four runs of a token side by side:
-    // ssq_out[(run / 4 * M + token) * 4 + run % 4]; PLAIN and GATE_UP with ssq_in add a token's ssq_runs runs (K columns), in pairs, and take their RMS factors from them
+    // output columns (of 64 where K goes in slices: gemm_k_slices), the sum of squares of what it stored, four runs of a token side
+    // by side: ssq_out[(run / 4 * M + token) * 4 + run % 4].  PLAIN and GATE_UP with ssq_in add a token's ssq_runs runs (nsb, or
+    // twice as many of 64 columns; K columns), in pairs, so that both give the same sum, and take their RMS factors from them
     float *ssq_out;
     const float *ssq_in;
     uint32_t ssq_runs;
@@ -118,8 +119,8 @@ hipError_t launch_route(const RouteArgs &ra, hipStream_t st);
 bool route_rides(const RouteArgs &ra);
 // a matrix in plans of more than 64 tokens: K in eight slices, and sums of squares (RESID) per 64 columns instead of 128
 bool gemm_k_slices(uint32_t nsb, uint32_t total_tiles, uint32_t plan_tokens);
-// the factors in the order of the GEMM's sums of squares (see GemmArgs; run: 128 or 64 columns), with their bits
-hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, uint32_t run, float eps, float *rinv, hipStream_t st);
+// the factors in the order of the GEMM's sums of squares (see GemmArgs), with their bits
+hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, hipStream_t st);
 // (up: an upload that rides in the launch, not together with route)
 hipError_t launch_rinv(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, const RouteArgs *route, const UploadArgs &up, hipStream_t st);
 // residual epilogue over whole rows of the hidden state (ncols == out_stride == H, first column 0,

@@ -809,9 +809,9 @@ __device__ __forceinline__ float sum_of_runs(const float *v, uint32_t n) {
 }
 
 // The same factor with the sum taken the way the GEMM's residual epilogue and the matrices behind it take it (ssq_out /
-// ssq_in of GemmArgs), bit for bit: runs of 128 columns (or of 64), in each the four (two) 32-column shares of a wave, in each share
-// the four lanes of a token (4 columns of either row-tile).  H a multiple of 128.
-__global__ __launch_bounds__(256) void rinv_runs_kernel(const __half *x, uint32_t H, uint32_t halves, float eps, float *rinv) {
+// ssq_in of GemmArgs), bit for bit: runs of 128 columns, in each the four 32-column shares of a wave, in each share the
+// four lanes of a token (4 columns of either row-tile).  H a multiple of 128.
+__global__ __launch_bounds__(256) void rinv_runs_kernel(const __half *x, uint32_t H, float eps, float *rinv) {
     __shared__ float share[kMaxGroups * 8 * 4];      // K <= 16384: 128 runs
     const uint32_t m = blockIdx.x, runs = H / 128, w = (threadIdx.x >> 2) & 3, rg = threadIdx.x & 3;
     const __half *row = x + (size_t)m * H;
@@ -833,26 +833,23 @@ __global__ __launch_bounds__(256) void rinv_runs_kernel(const __half *x, uint32_
     }
     __syncthreads();
     float mine = 0.f;      // run threadIdx.x
-    if (halves) {
-        if (threadIdx.x < runs * 2) mine = share[threadIdx.x * 2] + share[threadIdx.x * 2 + 1];
-    } else if (threadIdx.x < runs) {
+    if (threadIdx.x < runs) {
         const float *r4 = share + threadIdx.x * 4;
         mine = (r4[0] + r4[1]) + (r4[2] + r4[3]);
     }
     __syncthreads();
-    share[threadIdx.x] = mine;
+    if (threadIdx.x < kMaxGroups * 8) share[threadIdx.x] = mine;
     __syncthreads();
     if (threadIdx.x == 0) {
-        const uint32_t n = halves ? runs * 2 : runs;
         double s = 0.;
-        for (uint32_t g = 0; g < n; g += 16) s += sum_of_runs(share + g, n - g);
+        for (uint32_t g = 0; g < runs; g += 16) s += sum_of_runs(share + g, runs - g);
         rinv[m] = rsqrtf((float)s / (float)H + eps);
     }
 }
 
-hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, uint32_t run, float eps, float *rinv, hipStream_t st) {
-    if (H % 128 || H > kMaxGroups * 1024 || (run != 128 && run != 64)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(rinv_runs_kernel, dim3(M), dim3(256), 0, st, x, H, (uint32_t)(run == 64), eps, rinv);
+hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, hipStream_t st) {
+    if (H % 128 || H > kMaxGroups * 1024) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(rinv_runs_kernel, dim3(M), dim3(256), 0, st, x, H, eps, rinv);
     return hipGetLastError();
 }
 
@@ -1669,6 +1666,7 @@ __device__ __forceinline__ float row_rinv(const GemmArgs &a, uint32_t tok, uint3
     if (!a.ssq_in) return a.rinv[tok];
     if (a.quarters) return factor_of_quarters(RowQuarters{a.ssq_in, ntok, a.quarters, a.eps}, tok);
     double s = 0.;
+    float whole = 0.f;                                // of up to 16 runs of 128 columns: runs of 64 take two turns
     for (uint32_t g = 0; g < a.ssq_runs; g += 16) {   // (the buffer goes on for 64 nsb floats per token)
         const float4 *sq = reinterpret_cast<const float4 *>(a.ssq_in) + (size_t)(g / 4) * ntok + tok;
         float v[16];
@@ -1677,8 +1675,10 @@ __device__ __forceinline__ float row_rinv(const GemmArgs &a, uint32_t tok, uint3
             const float4 q = sq[(size_t)e * ntok];
             v[4 * e] = q.x; v[4 * e + 1] = q.y; v[4 * e + 2] = q.z; v[4 * e + 3] = q.w;
         }
-        s += sum_of_runs(v, a.ssq_runs - g);
+        whole += sum_of_runs(v, a.ssq_runs - g);
+        if (a.ssq_runs == a.nsb || (g & 16)) { s += whole; whole = 0.f; }
     }
+    s += whole;
     return rsqrtf((float)s / (float)(a.nsb * 128) + a.eps);
 }
 

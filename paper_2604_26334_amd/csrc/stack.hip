@@ -420,10 +420,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // nobody has left the factors QKV wants, and its planes are summed by a launch of its own: that one works them out
             // (a launch fewer; each of a token's workgroups reads the row again, which 64 tokens do not notice)
             if (op.info.shard0 == 0 && g.has_attn && gemm_sb_per_part(g.qkv, MP) && !st->own_rinv_launch) { st->own_factors = rows; return PS_OK; }
-            if (factor_runs || (o_slices && op.info.shard0 == 1)) {      // (the rows are O's, or down's of the layer before)
-                PS_LAUNCH(launch_rinv_runs(rows, M, H, run_columns(g.has_attn && op.info.shard0 == 1 ? g.o : g.down), m.rms_eps, rinv, cs));
-                return PS_OK;
-            }
+            if (factor_runs || (o_slices && op.info.shard0 == 1)) { PS_LAUNCH(launch_rinv_runs(rows, M, H, m.rms_eps, rinv, cs)); return PS_OK; }
             const bool ride = riding && op.info.shard0 == 1;
             PS_LAUNCH(launch_rinv(rows, M, H, m.rms_eps, rinv, ride ? riding : nullptr, factors_take ? take_upload() : UploadArgs{}, cs));
             if (ride) st->routed_layer = l;
