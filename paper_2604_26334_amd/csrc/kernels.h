@@ -56,7 +56,7 @@ struct GemmArgs {
     uint32_t sb_per_part;  // split-K: super-blocks per blockIdx.z part (0 = whole K in one part)
     uint32_t part_stride;  // split-K: elements between the fp32 partial planes
     // Sums of squares instead of a buffer of RMS factors (plans of more than 64 tokens): RESID leaves, per token and run of 128
-    // output columns (of 64 where K goes in slices: gemm_k_slices), the sum of squares of what it stored, four runs of a token side
+    // output columns (of 64 where a workgroup has no more: gemm_leaves_halves), the sum of squares of what it stored, four runs of a token side
     // by side: ssq_out[(run / 4 * M + token) * 4 + run % 4].  PLAIN and GATE_UP with ssq_in add a token's ssq_runs runs (nsb, or
     // twice as many of 64 columns; K columns), in pairs, so that both give the same sum, and take their RMS factors from them
     float *ssq_out;
@@ -117,8 +117,8 @@ hipError_t launch_splitk_epilogue_norm(const float *partial, uint32_t parts, uin
                                        uint32_t H, float eps, __half *out, uint32_t out_stride, uint32_t out_row0, hipStream_t st);
 hipError_t launch_route(const RouteArgs &ra, hipStream_t st);
 bool route_rides(const RouteArgs &ra);
-// a matrix in plans of more than 64 tokens: K in eight slices, and sums of squares (RESID) per 64 columns instead of 128
-bool gemm_k_slices(uint32_t nsb, uint32_t total_tiles, uint32_t plan_tokens);
+// whether the launches of a matrix in plans of more than 64 tokens leave sums of squares (RESID) per 64 columns for M rows
+bool gemm_leaves_halves(uint32_t nsb, uint32_t total_tiles, uint32_t plan_tokens, uint32_t M);
 // the factors in the order of the GEMM's sums of squares (see GemmArgs), with their bits
 hipError_t launch_rinv_runs(const __half *x, uint32_t M, uint32_t H, float eps, float *rinv, hipStream_t st);
 // (up: an upload that rides in the launch, not together with route)
@@ -131,7 +131,7 @@ hipError_t launch_splitk_epilogue_resid_rinv(const float *partial, uint32_t part
                                              const RouteArgs *route, hipStream_t st);
 // the same stores over four times the workgroups, with the sums of squares the factors come from instead of the factors
 // (quarters[w * M + row]; whoever wants a factor adds a row's four): their bits once added up.  slices: eight planes are the slices of a
-// matrix with K in slices, stores and sums of squares (per 64 columns) have the bits of the GEMM's in one launch; H a multiple of 256
+// matrix with K in slices, stores and sums of squares (per 128 columns) have the bits of the GEMM's in one launch; H a multiple of 256
 hipError_t launch_splitk_epilogue_resid_quarters(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M, uint32_t H,
                                                  const __half *res, __half *out, float *quarters, bool slices, hipStream_t st);
 // Decode attention over a KV cache, one new token.  A cache shard of one kv head is K rows

@@ -1659,9 +1659,8 @@ constexpr size_t gemm_lds_bytes(int MT, int AT, int NW, int KS = 1) {
 // RMS factor of row tok of a launch's input: from the buffer of factors, or from the row's sums of squares, 16 runs at a time.
 // Every workgroup reads all runs of its tokens, so their number and the requests they take are what it costs.  One 8B-shaped layer, us
 // a forward: 130 tokens of a 1024-token plan (32 runs) 146 with four or one run to a request, 151 with 64 half runs, one to a
-// request; 512 tokens of a 512-token plan (64 runs) 241.5 with four, 243.5 with one.  Tried without gain: 32 runs to a round trip;
-// whole runs where a sliced matrix is walked by two K parts, i.e. a second form of the loads (two layers, 330 tokens of a
-// 512-token plan 390 -> 388.5 us, but 200 tokens 296 -> 303).
+// request; 512 tokens of a 512-token plan (64 runs) 241.5 with four, 243.5 with one.  Two such layers, 330 tokens of a 512-token plan 382.5 with
+// halves, 380.4 with whole runs, 16 rows of a 64-token plan 118.5 and 117.2.  32 runs to a round trip gained nothing.
 __device__ __forceinline__ float row_rinv(const GemmArgs &a, uint32_t tok, uint32_t ntok) {
     if (!a.ssq_in) return a.rinv[tok];
     if (a.quarters) return factor_of_quarters(RowQuarters{a.ssq_in, ntok, a.quarters, a.eps}, tok);
@@ -2221,13 +2220,7 @@ __device__ __forceinline__ void gemm_w4_body(const GemmArgs &a, uint4 *lds) {   
             const uint32_t run = etid / MT, tk = etid % MT, wrun = blockIdx.x * (NWR / 4) + run;
             if (run < NWR / 4 && m0 + tk < ntok && wrun * 8 < a.ntiles) {
                 const float *r4 = side + run * 4 * MT + tk;
-                if constexpr (SLICED) {
-                    float *const halves = a.ssq_out + ssq_at(a.out_row0 / 64 + wrun * 2, m0 + tk, ntok);
-                    halves[0] = r4[0] + r4[MT];
-                    halves[1] = r4[2 * MT] + r4[3 * MT];
-                } else {
-                    a.ssq_out[ssq_at(a.out_row0 / 128 + wrun, m0 + tk, ntok)] = (r4[0] + r4[MT]) + (r4[2 * MT] + r4[3 * MT]);
-                }
+                a.ssq_out[ssq_at(a.out_row0 / 128 + wrun, m0 + tk, ntok)] = (r4[0] + r4[MT]) + (r4[2 * MT] + r4[3 * MT]);
             }
         }
     }
@@ -2606,11 +2599,16 @@ static uint32_t gemm_pick_tile(const GemmArgs &a, uint32_t widest) {
 // 1 us a launch (512 tokens: O 23.6 -> 24.3, down 67.8 -> 68.4; three additions of the accumulators and their zeroes, which no MFMA covers), against 4
 // and 14 us gained at 128 tokens; plans that need larger tiles stay with plain K parts.  QKV of 6144 rows, 72 tokens: 15.9 -> 13.0 us, 128:
 // 16.5 -> 15.7; 192 to 320, in two K parts, 0.8 slower.  Two layers, us a forward, against plain K parts in all plans: 4096 wide, plan of
-// 512, 200 tokens 292 -> 288, 300: 335 -> 334, 384: 379 -> 387, 512: 463 -> 468 (as one layer, 70: 128 -> 109); 2048 wide, plan of 512, 70: 129 -> 109, 200:
-// 138 -> 123, 300: 150 -> 142, 400: 156 -> 156, 512: 173 -> 172, plan of 1024, 500: 174 -> 173, 700: 193 -> 199, 1024: 255 -> 257.  So the
-// rule gives up to 2 % of the long trips of such a plan for up to 15 % of its short ones.
-bool gemm_k_slices(uint32_t nsb, uint32_t total_tiles, uint32_t plan_tokens) {
+// 512, 70 tokens 253 -> 217, 130: 266 -> 246, 200: 293 -> 290, 300: 340 -> 339, 384: 385 -> 390, 512: 474 -> 476; 2048 wide, plan of 512, 70: 127 ->
+// 107, 200: 139 -> 123, 400: 156 -> 156, 512: 166 -> 166, plan of 1024, 500: 165 -> 164, 700: 197 -> 201, 1024: 245 -> 247.  So the rule gives
+// up to 2 % of the long trips of such a plan for up to 15 % of its short ones.
+static bool gemm_k_slices(uint32_t nsb, uint32_t total_tiles, uint32_t plan_tokens) {
     return plan_tokens > 64 && nsb % 2 == 0 && nsb >= 16 && (total_tiles + 7) / 8 * ((plan_tokens + 63) / 64) <= 256;
+}
+// (by the whole matrix, so that all its slabs leave the same sums of squares)
+static bool gemm_slice_tiles(uint32_t total_tiles, uint32_t M) { return (total_tiles + kSliceRows - 1) / kSliceRows * ((M + 79) / 80) <= 256; }
+bool gemm_leaves_halves(uint32_t nsb, uint32_t total_tiles, uint32_t plan_tokens, uint32_t M) {
+    return gemm_k_slices(nsb, total_tiles, plan_tokens) && gemm_slice_tiles(total_tiles, M);
 }
 
 template <int MODE>
@@ -2665,10 +2663,12 @@ static hipError_t launch_gemm_m(const GemmArgs &a, uint32_t ntasks, uint32_t max
             if (gemm_k_slices(a.nsb, a.total_tiles, max_tok)) {
                 const uint32_t groups = (a.ntiles + kSliceRows - 1) / kSliceRows;
                 auto one_round = [&](uint32_t mt) { return groups * ((a.M + mt - 1) / mt) <= 256; };
-                if (one_round(32)) return launch_gemm_kslice<MODE, 2>(a, st);
-                if (one_round(48)) return launch_gemm_kslice<MODE, 3>(a, st);
-                if (one_round(64)) return launch_gemm_kslice<MODE, 4>(a, st);
-                if (one_round(80)) return launch_gemm_kslice<MODE, 5>(a, st);
+                if (gemm_slice_tiles(a.total_tiles, a.M)) {
+                    if (one_round(32)) return launch_gemm_kslice<MODE, 2>(a, st);
+                    if (one_round(48)) return launch_gemm_kslice<MODE, 3>(a, st);
+                    if (one_round(64)) return launch_gemm_kslice<MODE, 4>(a, st);
+                    return launch_gemm_kslice<MODE, 5>(a, st);
+                }
                 if ((a.ntiles + 7) / 8 * ((a.M + 47) / 48) <= 256) return launch_gemm_k<MODE, 2, 48, false, 8, 2, true>(a, a.M, 1, st);
                 return launch_gemm_k<MODE, 2, 64, false, 8, 2, true>(a, a.M, 1, st);
             }
@@ -3029,7 +3029,7 @@ hipError_t launch_splitk_epilogue_resid_rinv(const float *partial, uint32_t part
 // 4.3 -> 4.0 us in the kernel trace, 5 tokens 4.1 -> 3.4, 2 tokens of 2048 columns 3.4 -> 3.0, 2 of 512 2.7 -> 2.5 (about 2.5
 // are a launch's own), so the form serves 2 tokens and up; four steps of two layers of 64 tokens 635 -> 613 us.
 // SLICES: the planes are the eight K slices of a matrix that gemm_kslice_kernel finishes in one launch for more rows: the same
-// sums in the same order, half of K after half, and the same sums of squares per 64 columns, which are eight lanes' here.
+// sums in the same order, half of K after half, and the same sums of squares, a run of 128 columns being 16 lanes' here.
 // ------------------------------------------------------------------------------------
 template <bool SLICES>
 __global__ __launch_bounds__(64) void splitk_epilogue_resid_quarters_kernel(const float *partial, uint32_t parts, uint32_t part_stride, uint32_t M,
@@ -3090,7 +3090,8 @@ __global__ __launch_bounds__(64) void splitk_epilogue_resid_quarters_kernel(cons
             *reinterpret_cast<uint4 *>(out + (size_t)m * H + (q0 + u * 256) * 8) = o;
             if constexpr (SLICES) {
                 // as four columns each of two row-tiles are added up there: lane and lane ^ 2 hold the same columns of either tile,
-                // lane ^ 1 the tile's other half, the mirrored lane the run's other two tiles
+                // lane ^ 1 the tile's other half, the lane mirrored in its eight the other two tiles of 64 columns, the one mirrored in its
+                // row the run's other half
                 const h2_t h[4] = {as_h2(d[0]), as_h2(d[1]), as_h2(d[2]), as_h2(d[3])};
                 float sq[2];
 #pragma unroll
@@ -3103,8 +3104,9 @@ __global__ __launch_bounds__(64) void splitk_epilogue_resid_quarters_kernel(cons
                 float run = sq[0] + sq[1];
                 run += dpp_of<0xB1>(run);                   // quad_perm 1,0,3,2
                 run += dpp_of<0x141>(run);                  // row_half_mirror
+                run += dpp_of<0x140>(run);                  // row_mirror
                 const uint32_t q = q0 + u * 256;
-                if (q % 8 == 0) quarters[ssq_at(q / 8, m, M)] = run;
+                if (q % 16 == 0) quarters[ssq_at(q / 16, m, M)] = run;
             } else {
                 ss += sumsq8(o);
             }

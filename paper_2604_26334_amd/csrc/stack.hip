@@ -180,7 +180,7 @@ static bool few_token_gemv(const ps_plan &p, const MatGeom &mg) {
 // K = 4096, 64 tokens: 13.4 -> 11.0 us, 48: 11.4 -> 10.8; for longer rows (K = 14336, 64 tokens: 19.5 against 29) the planes are
 // faster.  So they are for fewer rows (33 tokens: 10.2 against 10.7, 16: 8.3 against 11.5), where a trip through the plan takes
 // them: K divides into eight equal parts, so the planes are the slices, and their sum adds them in the slices' order (two layers
-// in a plan of 64, us a forward: 16 rows 116.6 in four-sum planes, 119.7 in one launch, 117.5 so; 64 + 16 rows 270.4, 270.9, 267.3; 40 and
+// in a plan of 64, us a forward: 16 rows 116.9 in four-sum planes, 119.7 in one launch, 117.2 so; 64 + 16 rows 262, 263, 259; 40 and
 // 41 rows alike).  Over a cache the one launch gains nothing in full trips either (two layers, 64 rows over 4000 positions
 // 211.3 -> 212.8 us, 128 401.6 -> 402.8).
 static bool o_in_slices(const ps_plan &p) {
@@ -345,7 +345,6 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
     // batched decode (2..64 tokens) of a narrow matrix: split K over blockIdx.z into fp32 partial
     // planes, then one epilogue kernel sums them in order and applies the mode's epilogue
     const bool o_slices = o_in_slices(p);
-    auto run_columns = [&](const MatGeom &mg) { return gemm_k_slices(mg.nsb, mg.ntiles, MP) || (o_slices && &mg == &g.o) ? 64u : 128u; };
     auto run_gemm = [&](int mode, GemmArgs a, const MatGeom &mg) -> int32_t {
         const bool in_slices = o_slices && &mg == &g.o;
         a.slices = in_slices && (M > kSlicePlaneRows || a.ntiles * 16 != H || st->own_rinv_launch);
@@ -361,7 +360,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             else if (sums_of_squares || (a.slices && !st->own_rinv_launch)) {
                 a.ssq_out = dead;
                 st->ssq_buf = a.ssq_out;
-                st->ssq_runs = H / run_columns(mg);
+                st->ssq_runs = a.slices || gemm_leaves_halves(mg.nsb, mg.ntiles, MP, M) ? H / 64 : H / 128;
                 // (the slabs' launches together cover every column: the CPU takes parts of plans of up to 64 tokens only)
                 st->ssq_of = mg.ntiles * 16 == H ? a.out : nullptr;
             }
@@ -381,7 +380,7 @@ int32_t issue_kernel(ps_stack *st, const ps_schedule &sc, const Op &op, const __
             // H = 4096: 635 -> 613 us
             PS_LAUNCH(launch_splitk_epilogue_resid_quarters(partial, (mg.nsb + per - 1) / per, pa.part_stride, M, H, a.res, a.out, dead, in_slices, cs));
             st->ssq_buf = dead;
-            st->ssq_runs = in_slices ? H / 64 : 0;
+            st->ssq_runs = in_slices ? H / 128 : 0;
             st->ssq_of = a.out;
             return PS_OK;
         }

@@ -857,7 +857,7 @@ def test_matrices_in_eight_k_slices_give_the_same_rows(H, n_q, n_kv, I, plan_tok
     32 to 80 tokens, or walked one after the other by two K parts where the rows are too many for one round of those tiles.
     The full trip against the oracle, every shorter one with the same bits (edges of every tile; slices of 2 and of 2 or 3
     super-blocks; with attention QKV and the gathered input of O as well; O without down and down without O, whose sums of squares are
-    per 128 columns then), and the same bits again where every RMS factor has a launch of its own.  The last three: O alone in a plan of 49 to 64 tokens, in front of a gate/up
+    per 128 columns then, as are the two K parts'), and the same bits again where every RMS factor has a launch of its own.  The last three: O alone in a plan of 49 to 64 tokens, in front of a gate/up
     of one launch, by planes that are the slices for up to 40 rows (2048 wide: with these weights and 14336 columns the oracle's own rows of a 4096-wide layer leave fp16's range)."""
     import torch
     from paper_2604_26334_amd import binding as B
@@ -907,9 +907,9 @@ def _sliced_cfg(H, n_q, n_kv, I, layers):
     (4096, 0, 0, 2048, 1, 512, (512, 321, 100), "D"), (2048, 16, 4, 2304, 2, 640, (640, 130), "QOD"), (2176, 17, 1, 2560, 2, 300, (300, 33), "QOD"),
     (3072, 24, 24, 2816, 2, 384, (384, 250), "OD"), (2048, 16, 4, 14336, 1, 64, (64, 20), "O")])
 def test_matrices_in_k_slices_cut_into_slabs(H, n_q, n_kv, I, layers, plan_tokens, counts, cut):
-    """A streamed placement cuts these matrices into slabs, which take kernels of their own (a whole matrix two K parts, its slabs
-    tiles of eight slices; O's planes for a short trip only whole): the bits are those of the pinned placement, for full and
-    short trips, also where every RMS factor has a launch of its own.  Slabs of 256 rows and more, of any 16 at H = 2176."""
+    """A streamed placement cuts these matrices into slabs, in tiles of their own and, where O has planes for a short trip only whole,
+    in a kernel of their own: the bits are those of the pinned placement, for full and short trips (two K parts and eight waves'
+    slices), also where every RMS factor has a launch of its own.  Slabs of 256 rows and more, of any 16 at H = 2176."""
     import torch
     from paper_2604_26334_amd import binding as B
     cfg = _sliced_cfg(H, n_q, n_kv, I, layers)
